@@ -25,68 +25,80 @@ __device__ __forceinline__ void load8_f32(const float* p, float (&f)[8]) {
   f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
 }
 // ---- per-channel constants, worked out once per wave ------------------------------------------------
-// A thread of the elementwise kernels owns a group of 8 channels, and the 64 / CGB lanes of a wave that own the same
-// group would each repeat the 64-bit arithmetic that turns the group's exact totals into the constants of the row
-// loop.  Instead the lanes share it: lane (cgl = lane % CGB, sub = lane / CGB) takes channel sub % 8 of the group (two
-// channels, sub and sub + 4, when only four lanes share a group) and, where the sums exist in copies, the copies
-// sub / 8, sub / 8 + parts, ...; the integer words of the copies are added across those lanes, the lane works out the
-// constants of its channel(s), and they travel to the lanes that need them by lane shuffles.  No LDS.  Every lane of a
-// wave must take part (shuffles), also the lanes whose channel group does not exist.
+// A thread of the elementwise kernels owns a group of 8 channels, and the lanes of a wave that own the same group would
+// each repeat the 64-bit arithmetic that turns the group's exact totals into the constants of the row loop.  Instead the
+// lanes share it: lane (cgl = lane % CGB, sub = lane / CGB) takes channel sub % 8 of the group, works out the constants of
+// that channel, and they travel to the lanes that need them by lane shuffles.  Every lane of a wave must take part
+// (shuffles), also the lanes whose channel group does not exist.
 struct LaneShare {
-  int CGB, cgl, sub, nch, part, parts;
+  int CGB, cgl, sub;
   __device__ __forceinline__ explicit LaneShare(int cgb) : CGB(cgb) {
-    const int lane = threadIdx.x & 63, S = 64 / cgb;   // CGB divides 64
+    const int lane = threadIdx.x & 63;   // CGB is 1, 2, 4 or 8
     cgl = lane % cgb; sub = lane / cgb;
-    nch = S >= 8 ? 1 : 2;
-    part = S >= 8 ? sub / 8 : 0;
-    parts = S >= 8 ? S / 8 : 1;
   }
-  // k-th channel of the group this lane works on (k < nch)
-  __device__ __forceinline__ int channel(int k) const { return nch == 1 ? sub % 8 : sub + 4 * k; }
-  // the value lane-computed for channel i of the group, given this lane's values r[k]
-  __device__ __forceinline__ float gather(const float (&r)[2], int i) const {
-    return nch == 1 ? __shfl(r[0], cgl + CGB * i) : __shfl(i < 4 ? r[0] : r[1], cgl + CGB * (i & 3));
+  __device__ __forceinline__ int channel() const { return sub % 8; }   // of the group: what this lane works out
+  // the value lane-computed for channel i of the group, given this lane's value
+  __device__ __forceinline__ float gather(float r, int i) const { return __shfl(r, cgl + CGB * i); }
+};
+// The totals a wave's lanes need for their channels, NSUM of them: sums 0 and 1 of `a0`, then of `a1`.
+//   COPIES == 0: the arrays are single.  Every lane loads the words of its own channel, no LDS.
+//   COPIES > 0: the arrays exist in kStatReplicas copies.  Loaded by every wave of a workgroup for itself they are 768 bytes
+//   a lane, 200 MB over the 1024 workgroups of a launch and more than the tensor it works on (bn_bwd_apply over 25088 x 256
+//   took 36 us; its tensors are 38 MB).  So the workgroup shares them: thread t takes one (sum, channel) of the workgroup's W = 8 CGB
+//   channels and COPIES of its copies, adds them as integers and leaves the total in LDS, where the lanes fetch what they
+//   need after one barrier.  Steps with batch 128: ResNet-18's 64-channel half 4197 -> 3581 us; with the copies also dropped
+//   where no narrow kernel runs, 1024-channel bottleneck module 5326 -> 4605 us, MobileNet-v2 module 4328 -> 3434 us.
+// The loads come back before anything is waited for, so that a kernel can put its first rows in front of them.
+template <int COPIES, int NSUM>
+struct Totals {
+  static constexpr int N = COPIES > 0 ? COPIES : NSUM;
+  long long hi[N], lo[N], big[N];
+  __device__ __forceinline__ void load(const stat_t* a0, const stat_t* a1, int C, int CGB, int c_base, int c_lane, int rep) {
+    if (COPIES == 0) {
+#pragma unroll
+      for (int w = 0; w < NSUM; ++w) {
+        const stat_t* q = (w < 2 ? a0 : a1) + (size_t)(w & 1) * C + c_lane;
+        hi[w] = q[0]; lo[w] = q[2 * (size_t)C]; big[w] = q[4 * (size_t)C];
+      }
+    } else {
+      const int W = 8 * CGB, slot = threadIdx.x % (W * NSUM), part = threadIdx.x / (W * NSUM), parts = kStatReplicas / (COPIES > 0 ? COPIES : 1);
+      const int which = slot / W, c = c_base + slot % W;
+      const stat_t* p = (which < 2 ? a0 : a1) + (size_t)(which & 1) * C + (c < C ? c : c_base) + (size_t)(part % parts) * rep;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const stat_t* q = p + (size_t)j * parts * rep;
+        hi[j] = q[0]; lo[j] = q[2 * (size_t)C]; big[j] = q[4 * (size_t)C];
+      }
+    }
+  }
+  // COPIES > 0: every thread leaves its total; call before get(), by the whole workgroup
+  __device__ __forceinline__ void share(double* lds) {
+    if (COPIES == 0) return;
+    long long h = 0, l = 0;
+    double b = 0.0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      h += hi[j]; l += lo[j];
+      b += __builtin_bit_cast(double, big[j]);
+    }
+    lds[threadIdx.x] = stat_value(h, l, __builtin_bit_cast(long long, b));
+    __syncthreads();
+  }
+  // total `w` of channel c_local of the workgroup's channels (COPIES == 0: of this lane's channel)
+  __device__ __forceinline__ double get(const double* lds, int w, int c_local, int CGB) const {
+    if (COPIES == 0) return stat_value(hi[w < N ? w : 0], lo[w < N ? w : 0], big[w < N ? w : 0]);
+    const int W = 8 * CGB, parts = kStatReplicas / (COPIES > 0 ? COPIES : 1);
+    double v = 0.0;
+    for (int p = 0; p < parts; ++p) v += lds[(p * NSUM + w) * W + c_local];   // the copies another thread took
+    return v;
   }
 };
-// The words of one of the two sums (which = 0 / 1) of channel c in the COPIES copies this lane takes (copy part,
-// part + parts, ...; COPIES * parts = kStatReplicas, or COPIES = 1 and rep = 0 where the array is a single copy, which
-// every lane then reads).  Loads only -- nothing is added and nothing depends on `valid` (a lane without a channel is given
-// an existing one and its result is dropped) -- so that a kernel issues the loads of ALL the sums it needs back to back
-// and waits for memory once.
-template <int COPIES>
-struct RawTotal { long long hi[COPIES], lo[COPIES], big[COPIES]; };
-template <int COPIES>
-__device__ __forceinline__ void chan_load(RawTotal<COPIES>& t, const LaneShare& ls, const stat_t* stats, int C, int which, int c, int rep) {
-  const stat_t* p = stats + (size_t)which * C + c;
-#pragma unroll
-  for (int j = 0; j < COPIES; ++j) {
-    const stat_t* q = p + (size_t)(ls.part + j * ls.parts) * rep;
-    t.hi[j] = q[0];
-    t.lo[j] = q[2 * (size_t)C];
-    t.big[j] = q[4 * (size_t)C];
-  }
-}
-// The total: this lane's copies (added as integers, hence independent of the order the workgroups arrived in) as a
-// double, then -- where there are copies -- the other lanes' in a fixed order.
-template <int COPIES>
-__device__ __forceinline__ double chan_total(const RawTotal<COPIES>& t, const LaneShare& ls, int rep) {
-  long long hi = 0, lo = 0;
-  double big = 0.0;
-#pragma unroll
-  for (int j = 0; j < COPIES; ++j) {
-    hi += t.hi[j];
-    lo += t.lo[j];
-    big += __builtin_bit_cast(double, t.big[j]);
-  }
-  double v = stat_value(hi, lo, __builtin_bit_cast(long long, big));
-  if (rep > 0)
-    for (int off = 8 * ls.CGB; off < 64; off <<= 1) v += __shfl_xor(v, off);   // lanes 8 * CGB apart hold the other copies
-  return v;
-}
-// copies a lane takes for an array with (rep > 0) or without copies: the template argument of the functions above
-static int host_copies_per_lane(int CGB, int rep) {
-  const int S = 64 / CGB, parts = S >= 8 ? S / 8 : 1;   // as in LaneShare
-  return rep > 0 ? kStatReplicas / parts : 1;
+constexpr int kTotalsLds = 256;   // doubles
+// copies a thread takes (the kernels' COPIES): 256 threads cover 8 CGB channels x NSUM sums x what is left of the copies
+static int host_copies_per_thread(int CGB, int nsum, int rep) {
+  if (rep <= 0) return 0;
+  const int parts = 256 / (8 * CGB * nsum);
+  return parts >= kStatReplicas ? 1 : kStatReplicas / parts;
 }
 // Batch mean and 1 / sqrt(variance + eps) from the totals sum x and sum x^2 over M rows.  The subtraction that gives the
 // variance is done in double on the exact totals, so a mean that is large against the spread costs no digits here.
@@ -182,15 +194,13 @@ hipError_t launch_bn_stats(const bf16_t* x, stat_t* sums, int M, int C, hipStrea
 }
 
 // ---- BN apply: y = relu?( gamma*xhat + beta [+ res] [+ gamma2*xhat2 + beta2] ) ------------------------
-__device__ __forceinline__ void bn_running(const stat_t* sums, int rep, float* run_mean, float* run_var, int C, int M, float mom) {
-  const double invM = 1.0 / (double)M;
+// one running-statistics step of channel c from the totals sum x and sum x^2
+__device__ __forceinline__ void bn_running(double s1, double s2, double invM, int M, float mom, float* run_mean, float* run_var, int c) {
+  const double mean = s1 * invM;
+  const float var = (float)fmax(s2 * invM - mean * mean, 0.0);
   const float unbias = M > 1 ? (float)M / (float)(M - 1) : 1.f;
-  for (int c = threadIdx.x; c < C; c += blockDim.x) {
-    const double mean = stat_load(sums, C, 0, c, rep) * invM;
-    const float var = (float)fmax(stat_load(sums, C, 1, c, rep) * invM - mean * mean, 0.0);
-    run_mean[c] = (1.f - mom) * run_mean[c] + mom * (float)mean;
-    run_var[c] = (1.f - mom) * run_var[c] + mom * var * unbias;
-  }
+  run_mean[c] = (1.f - mom) * run_mean[c] + mom * (float)mean;
+  run_var[c] = (1.f - mom) * run_var[c] + mom * var * unbias;
 }
 
 // Elementwise kernels over [M, C] with per-channel constants: a thread keeps ONE group of 8 channels for all
@@ -204,8 +214,7 @@ static ApplyShape apply_shape(int M, int C) {
   ApplyShape r;
   const int CG = C / 8;
   // at most 8 groups (64 channels) per block: eight lanes of a wave then share a group and each works out the constants
-  // of ONE channel (LaneShare); with 16 groups a lane has two channels and the kernels of the 640-channel layers lose
-  // 2 - 3 us per launch
+  // of ONE channel (LaneShare)
   r.CGB = CG >= 8 ? 8 : (CG >= 4 ? 4 : (CG >= 2 ? 2 : 1));
   r.RL = kThreads / r.CGB;
   const int cblocks = (CG + r.CGB - 1) / r.CGB;
@@ -220,72 +229,12 @@ static ApplyShape apply_shape(int M, int C) {
   return r;
 }
 
-// scale and shift of the 8 channels from c0 on (and of the second operand's, if there is one), see LaneShare
-template <int COPIES>
-__device__ __forceinline__ void bn_apply_setup(const BnApplyArgs& a, const LaneShare& ls, int c0, float (&sc)[8], float (&sh)[8],
-                                               float (&sc2)[8], float (&sh2)[8]) {
-  const int C = a.C;
-  const double invM = 1.0 / (double)a.M;
-  const bool two = a.x2 != nullptr;
-  const stat_t* sums2 = two ? a.sums2 : a.sums;
-  const float *gamma2 = two ? a.gamma2 : a.gamma, *beta2 = two ? a.beta2 : a.beta;
-  RawTotal<COPIES> raw[2][2][2];   // [channel of this lane][x | x2][sum | sum of squares]
-  float gm[2][2], bt[2][2];
-  float r_sc[2] = {0.f, 0.f}, r_sh[2] = {0.f, 0.f}, r_sc2[2] = {0.f, 0.f}, r_sh2[2] = {0.f, 0.f};
-  auto load = [&](int k) {   // called with constants: the arrays stay in registers
-    const int c = c0 + ls.channel(k);
-    chan_load(raw[k][0][0], ls, a.sums, C, 0, c, a.rep_stride);
-    chan_load(raw[k][0][1], ls, a.sums, C, 1, c, a.rep_stride);
-    gm[k][0] = a.gamma[c];
-    bt[k][0] = a.beta[c];
-    if (two) {
-      chan_load(raw[k][1][0], ls, sums2, C, 0, c, a.rep_stride);
-      chan_load(raw[k][1][1], ls, sums2, C, 1, c, a.rep_stride);
-      gm[k][1] = gamma2[c];
-      bt[k][1] = beta2[c];
-    }
-  };
-  auto compute = [&](int k) {
-    float mean, is;
-    bn_moments(chan_total(raw[k][0][0], ls, a.rep_stride), chan_total(raw[k][0][1], ls, a.rep_stride), invM, a.eps, mean, is);
-    r_sc[k] = gm[k][0] * is;
-    r_sh[k] = bt[k][0] - mean * r_sc[k];
-    if (two) {
-      bn_moments(chan_total(raw[k][1][0], ls, a.rep_stride), chan_total(raw[k][1][1], ls, a.rep_stride), invM, a.eps, mean, is);
-      r_sc2[k] = gm[k][1] * is;
-      r_sh2[k] = bt[k][1] - mean * r_sc2[k];
-    }
-  };
-  // every load first (one wait for memory), then the arithmetic -- unless a lane has two channels in eight copies each,
-  // which would not fit the registers
-  load(0);
-  if (COPIES < 8 && ls.nch == 2) load(1);
-  compute(0);
-  if (ls.nch == 2) {
-    if (COPIES >= 8) load(1);
-    compute(1);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    sc[i] = ls.gather(r_sc, i);
-    sh[i] = ls.gather(r_sh, i);
-  }
-  if (two) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      sc2[i] = ls.gather(r_sc2, i);
-      sh2[i] = ls.gather(r_sh2, i);
-    }
-  }
-}
-
-template <int COPIES>   // copies of the sums a lane takes (copies_per_lane): a kernel each, so that each has the registers it needs
+// TWO: a second normalised operand (a.x2).  COPIES: see Totals; a kernel each, so that each has the registers it needs
+template <int COPIES, bool TWO>
 __global__ __launch_bounds__(kThreads) void bn_apply_kernel(BnApplyArgs a, int CGB, int rows_per_block) {
+  constexpr int NSUM = TWO ? 4 : 2;
+  __shared__ double totals[COPIES > 0 ? kTotalsLds : 1];
   const int C = a.C;
-  if (blockIdx.x == 0 && blockIdx.y == 0) {
-    if (a.run_mean) bn_running(a.sums, a.rep_stride, a.run_mean, a.run_var, C, a.M, a.momentum);
-    if (a.x2 && a.run_mean2) bn_running(a.sums2, a.rep_stride, a.run_mean2, a.run_var2, C, a.M, a.momentum);
-  }
   const int RL = kThreads / CGB;
   const int cg = blockIdx.x * CGB + threadIdx.x % CGB, rl = threadIdx.x / CGB;
   const int c0 = cg * 8;
@@ -303,7 +252,36 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(BnApplyArgs a, int C
   {
     const LaneShare ls(CGB);
     const bool valid = c0 < C;
-    bn_apply_setup<COPIES>(a, ls, valid ? c0 : 0, sc, sh, sc2, sh2);
+    const int c_base = blockIdx.x * CGB * 8, c = (valid ? c0 : 0) + ls.channel(), cl = ls.cgl * 8 + ls.channel();
+    Totals<COPIES, NSUM> t;
+    t.load(a.sums, TWO ? a.sums2 : a.sums, C, CGB, c_base, c, a.rep_stride);
+    const float gm = a.gamma[c], bt = a.beta[c];
+    const float gm2 = TWO ? a.gamma2[c] : 0.f, bt2 = TWO ? a.beta2[c] : 0.f;
+    t.share(totals);
+    const double invM = 1.0 / (double)a.M;
+    float mean, is;
+    // one lane per channel, of the first block of rows
+    const bool writes = valid && blockIdx.y == 0 && threadIdx.x < 64 && ls.sub < 8;
+    double s1 = t.get(totals, 0, cl, CGB), s2 = t.get(totals, 1, cl, CGB);
+    bn_moments(s1, s2, invM, a.eps, mean, is);
+    if (writes && a.run_mean) bn_running(s1, s2, invM, a.M, a.momentum, a.run_mean, a.run_var, c);
+    const float r_sc = gm * is, r_sh = bt - mean * r_sc;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      sc[i] = ls.gather(r_sc, i);
+      sh[i] = ls.gather(r_sh, i);
+    }
+    if (TWO) {
+      s1 = t.get(totals, 2, cl, CGB); s2 = t.get(totals, 3, cl, CGB);
+      bn_moments(s1, s2, invM, a.eps, mean, is);
+      if (writes && a.run_mean2) bn_running(s1, s2, invM, a.M, a.momentum, a.run_mean2, a.run_var2, c);
+      const float r_sc2 = gm2 * is, r_sh2 = bt2 - mean * r_sc2;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        sc2[i] = ls.gather(r_sc2, i);
+        sh2[i] = ls.gather(r_sh2, i);
+      }
+    }
     if (!valid) return;
   }
   auto one_row = [&](int row, const uint4& xu) {
@@ -318,7 +296,7 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(BnApplyArgs a, int C
 #pragma unroll
       for (int i = 0; i < 8; ++i) f[i] += rr[i];
     }
-    if (a.x2) {
+    if (TWO) {
       float g[8];
       unpack8(*reinterpret_cast<const uint4*>(a.x2 + o), g);
 #pragma unroll
@@ -357,12 +335,16 @@ hipError_t launch_bn_apply(const BnApplyArgs& a, hipStream_t s) {
   if (!al16(a.sums) || !al16(a.gamma) || !al16(a.beta) || (a.x2 && (!al16(a.sums2) || !al16(a.gamma2) || !al16(a.beta2))))
     return hipErrorInvalidValue;   // per-channel vectors are read 16 bytes at a time
   const ApplyShape r = apply_shape(a.M, a.C);
-  switch (host_copies_per_lane(r.CGB, a.rep_stride)) {
-    case 1: hipLaunchKernelGGL(bn_apply_kernel<1>, r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block); break;
-    case 2: hipLaunchKernelGGL(bn_apply_kernel<2>, r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block); break;
-    case 4: hipLaunchKernelGGL(bn_apply_kernel<4>, r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block); break;
-    default: hipLaunchKernelGGL(bn_apply_kernel<8>, r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block); break;
+#define FDG_LAUNCH_BN_APPLY(CP, TWO) \
+  hipLaunchKernelGGL((bn_apply_kernel<CP, TWO>), r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block)
+  switch (host_copies_per_thread(r.CGB, a.x2 ? 4 : 2, a.rep_stride)) {
+    case 0: if (a.x2) FDG_LAUNCH_BN_APPLY(0, true); else FDG_LAUNCH_BN_APPLY(0, false); break;
+    case 1: if (a.x2) FDG_LAUNCH_BN_APPLY(1, true); else FDG_LAUNCH_BN_APPLY(1, false); break;
+    case 2: if (a.x2) FDG_LAUNCH_BN_APPLY(2, true); else FDG_LAUNCH_BN_APPLY(2, false); break;
+    case 4: if (a.x2) FDG_LAUNCH_BN_APPLY(4, true); else FDG_LAUNCH_BN_APPLY(4, false); break;
+    default: if (a.x2) FDG_LAUNCH_BN_APPLY(8, true); else FDG_LAUNCH_BN_APPLY(8, false); break;
   }
+#undef FDG_LAUNCH_BN_APPLY
   return hipGetLastError();
 }
 
@@ -383,30 +365,6 @@ __device__ __forceinline__ void load_masked_dy(const void* dy, const bf16_t* mas
 // the upper end of the gate: +inf unless the activation was clamped (ReLU6)
 __device__ __forceinline__ float gate_top(float gate_hi) { return gate_hi > 0.f ? gate_hi : __builtin_inff(); }
 
-// batch mean and 1 / sqrt(variance + eps) of the 8 channels from c0 on, see LaneShare
-template <int COPIES>
-__device__ __forceinline__ void bn_moments_setup(const stat_t* sums, int rep, int C, int M, float eps, const LaneShare& ls, int c0,
-                                                 float (&mu)[8], float (&iv)[8]) {
-  const double invM = 1.0 / (double)M;
-  RawTotal<COPIES> raw[2][2];
-  float r_mu[2] = {0.f, 0.f}, r_iv[2] = {0.f, 0.f};
-  auto load = [&](int k) {   // called with constants: the arrays stay in registers
-    const int c = c0 + ls.channel(k);
-    chan_load(raw[k][0], ls, sums, C, 0, c, rep);
-    chan_load(raw[k][1], ls, sums, C, 1, c, rep);
-  };
-  auto compute = [&](int k) { bn_moments(chan_total(raw[k][0], ls, rep), chan_total(raw[k][1], ls, rep), invM, eps, r_mu[k], r_iv[k]); };
-  load(0);
-  if (ls.nch == 2) load(1);
-  compute(0);
-  if (ls.nch == 2) compute(1);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    mu[i] = ls.gather(r_mu, i);
-    iv[i] = ls.gather(r_iv, i);
-  }
-}
-
 template <bool DY_F32, int COPIES>
 __global__ __launch_bounds__(kThreads) void bn_bwd_reduce_kernel(BnBwdArgs a, int CGB, int rows_per_block) {
   extern __shared__ float smem[];  // 2 * 256 * 8 floats
@@ -421,8 +379,19 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_reduce_kernel(BnBwdArgs a, in
   for (int i = 0; i < 8; ++i) v[0][i] = v[1][i] = 0.f;
   {
     const LaneShare ls(CGB);
-    const int c0 = cvalid ? cg * 8 : 0;
-    bn_moments_setup<COPIES>(a.sums, a.rep_stride, C, a.M, a.eps, ls, c0, mu, iv);
+    double* totals = reinterpret_cast<double*>(smem);   // before the partial sums need it
+    Totals<COPIES, 2> t;
+    t.load(a.sums, a.sums, C, CGB, blockIdx.x * CGB * 8, (cvalid ? cg * 8 : 0) + ls.channel(), a.rep_stride);
+    t.share(totals);
+    const int cl = ls.cgl * 8 + ls.channel();
+    float mean, is;
+    bn_moments(t.get(totals, 0, cl, CGB), t.get(totals, 1, cl, CGB), 1.0 / (double)a.M, a.eps, mean, is);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      mu[i] = ls.gather(mean, i);
+      iv[i] = ls.gather(is, i);
+    }
+    if (COPIES > 0) __syncthreads();
   }
   if (cvalid) {
     const int row_lo = blockIdx.y * rows_per_block, row_hi = min(a.M, row_lo + rows_per_block);
@@ -448,75 +417,22 @@ hipError_t launch_bn_bwd_reduce(const BnBwdArgs& a, hipStream_t s) {
   const size_t sm = 2 * (size_t)kThreads * 8 * sizeof(float);
 #define FDG_LAUNCH_REDUCE(F32, CP) \
   hipLaunchKernelGGL((bn_bwd_reduce_kernel<F32, CP>), r.grid, dim3(kThreads), sm, s, a, r.CGB, r.rows_per_block)
-  switch (host_copies_per_lane(r.CGB, a.rep_stride)) {
+  switch (host_copies_per_thread(r.CGB, 2, a.rep_stride)) {
+    case 0: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 0); else FDG_LAUNCH_REDUCE(false, 0); break;
     case 1: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 1); else FDG_LAUNCH_REDUCE(false, 1); break;
     case 2: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 2); else FDG_LAUNCH_REDUCE(false, 2); break;
-    case 4: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 4); else FDG_LAUNCH_REDUCE(false, 4); break;
-    default: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 8); else FDG_LAUNCH_REDUCE(false, 8); break;
+    default: if (a.dy_is_f32) FDG_LAUNCH_REDUCE(true, 4); else FDG_LAUNCH_REDUCE(false, 4); break;
   }
 #undef FDG_LAUNCH_REDUCE
   return hipGetLastError();
 }
 
-// Constants of the batch-norm backward for the 8 channels from c0 on, see LaneShare.  Per channel: xhat = x*is - mean*is;
-// dx = gi*g - gi*k1 - gi*k2*xhat = gi*g + (pa*x + pb).  The lanes with `writes` store dbeta and dgamma of their channel(s).
-// The forward and the backward sums have copies (a.rep_stride == a.brep_stride > 0) or neither has.
-template <int COPIES>
-__device__ __forceinline__ void bn_bwd_setup(const BnBwdArgs& a, const LaneShare& ls, int c0, bool writes, float (&gi)[8],
-                                             float (&pa)[8], float (&pb)[8]) {
-  const int C = a.C, rep = a.rep_stride;
-  const double invMd = 1.0 / (double)a.M;
-  const float invM = (float)invMd;
-  RawTotal<COPIES> raw[2][2][2];   // [channel of this lane][forward sums | backward sums][first | second sum]
-  float gm[2];
-  float r_gi[2] = {0.f, 0.f}, r_pa[2] = {0.f, 0.f}, r_pb[2] = {0.f, 0.f};
-  auto load = [&](int k) {   // called with constants: the arrays stay in registers
-    const int c = c0 + ls.channel(k);
-    chan_load(raw[k][0][0], ls, a.sums, C, 0, c, rep);
-    chan_load(raw[k][0][1], ls, a.sums, C, 1, c, rep);
-    chan_load(raw[k][1][0], ls, a.bsums, C, 0, c, rep);
-    chan_load(raw[k][1][1], ls, a.bsums, C, 1, c, rep);
-    gm[k] = a.gamma[c];
-  };
-  auto compute = [&](int k) {
-    const int c = c0 + ls.channel(k);
-    const double s1 = chan_total(raw[k][0][0], ls, rep), s2 = chan_total(raw[k][0][1], ls, rep);
-    const double t1 = chan_total(raw[k][1][0], ls, rep), t2 = chan_total(raw[k][1][1], ls, rep);
-    float mean, is;
-    bn_moments(s1, s2, invMd, a.eps, mean, is);
-    const float b1 = (float)t1;
-    // sum g*xhat from sum g*x and sum g: the difference is taken in double on the exact totals
-    const float b2 = a.raw_sums ? is * (float)(t2 - (s1 * invMd) * t1) : (float)t2;
-    const float g = gm[k] * is;
-    const float k1 = b1 * invM, k2 = b2 * invM;
-    r_gi[k] = g;
-    r_pa[k] = -g * k2 * is;
-    r_pb[k] = -g * k1 + g * k2 * is * mean;
-    if (writes) {
-      a.dbeta[c] = b1;
-      a.dgamma[c] = b2;
-    }
-  };
-  // every load first (one wait for memory), then the arithmetic -- unless a lane has two channels in eight copies each,
-  // which would not fit the registers
-  load(0);
-  if (COPIES < 8 && ls.nch == 2) load(1);
-  compute(0);
-  if (ls.nch == 2) {
-    if (COPIES >= 8) load(1);
-    compute(1);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    gi[i] = ls.gather(r_gi, i);
-    pa[i] = ls.gather(r_pa, i);
-    pb[i] = ls.gather(r_pb, i);
-  }
-}
-
 // dx = gamma*invstd*(g - S1/M - xhat*S2/M) [+ addend];  dgamma = S2, dbeta = S1
+// With xhat = x*is - mean*is: dx = gi*g - gi*k1 - gi*k2*xhat = gi*g + (pa*x + pb), three constants per channel.
+// The forward and the backward sums have copies (a.rep_stride == a.brep_stride > 0) or neither has.
 template <bool DY_F32, int COPIES>
 __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BnBwdArgs a, int CGB, int rows_per_block) {
+  __shared__ double totals[COPIES > 0 ? kTotalsLds : 1];
   const int C = a.C;
   const int RL = kThreads / CGB;
   const int cg = blockIdx.x * CGB + threadIdx.x % CGB, rl = threadIdx.x / CGB;
@@ -544,8 +460,34 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BnBwdArgs a, int
   {
     const LaneShare ls(CGB);
     const bool valid = c0 < C;
-    const bool writes = valid && blockIdx.y == 0 && threadIdx.x < 64 && ls.part == 0;   // one lane per channel of the block
-    bn_bwd_setup<COPIES>(a, ls, valid ? c0 : 0, writes, gi, pa, pb);
+    const bool writes = valid && blockIdx.y == 0 && threadIdx.x < 64 && ls.sub < 8;   // one lane per channel of the block
+    const int c = (valid ? c0 : 0) + ls.channel(), cl = ls.cgl * 8 + ls.channel();
+    Totals<COPIES, 4> t;
+    t.load(a.sums, a.bsums, C, CGB, blockIdx.x * CGB * 8, c, a.rep_stride);
+    const float gm = a.gamma[c];
+    t.share(totals);
+    const double invMd = 1.0 / (double)a.M;
+    const float invM = (float)invMd;
+    const double s1 = t.get(totals, 0, cl, CGB), s2 = t.get(totals, 1, cl, CGB);
+    const double t1 = t.get(totals, 2, cl, CGB), t2 = t.get(totals, 3, cl, CGB);
+    float mean, is;
+    bn_moments(s1, s2, invMd, a.eps, mean, is);
+    const float b1 = (float)t1;
+    // sum g*xhat from sum g*x and sum g: the difference is taken in double on the exact totals
+    const float b2 = a.raw_sums ? is * (float)(t2 - (s1 * invMd) * t1) : (float)t2;
+    const float g = gm * is;
+    const float k1 = b1 * invM, k2 = b2 * invM;
+    const float r_pa = -g * k2 * is, r_pb = -g * k1 + g * k2 * is * mean;
+    if (writes) {
+      a.dbeta[c] = b1;
+      a.dgamma[c] = b2;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      gi[i] = ls.gather(g, i);
+      pa[i] = ls.gather(r_pa, i);
+      pb[i] = ls.gather(r_pb, i);
+    }
     if (!valid) return;
   }
   if (!rows_wanted) return;
@@ -606,7 +548,8 @@ hipError_t launch_bn_bwd_apply(const BnBwdArgs& a_in, hipStream_t s) {
   if (!a.out_f32 && !a.out_b16) r.grid.y = 1;   // only dgamma / dbeta
 #define FDG_LAUNCH_APPLY(F32, CP) \
   hipLaunchKernelGGL((bn_bwd_apply_kernel<F32, CP>), r.grid, dim3(kThreads), 0, s, a, r.CGB, r.rows_per_block)
-  switch (host_copies_per_lane(r.CGB, a.rep_stride)) {
+  switch (host_copies_per_thread(r.CGB, 4, a.rep_stride)) {
+    case 0: if (a.dy_is_f32) FDG_LAUNCH_APPLY(true, 0); else FDG_LAUNCH_APPLY(false, 0); break;
     case 1: if (a.dy_is_f32) FDG_LAUNCH_APPLY(true, 1); else FDG_LAUNCH_APPLY(false, 1); break;
     case 2: if (a.dy_is_f32) FDG_LAUNCH_APPLY(true, 2); else FDG_LAUNCH_APPLY(false, 2); break;
     case 4: if (a.dy_is_f32) FDG_LAUNCH_APPLY(true, 4); else FDG_LAUNCH_APPLY(false, 4); break;
