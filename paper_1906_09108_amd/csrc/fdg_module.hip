@@ -847,6 +847,22 @@ const BnInfo* closing_bn(const Plan& p, const SlotView& v, const LayerPlan& L, c
   return &p.bns[bn];
 }
 
+// Which of the two forms of the stream between layers (fp32, and its bf16 copy) a layer reads: what nobody reads is not
+// written.  Of ResNet-101's 1024-channel stage at batch 128 (25.7 M values) the fp32 form is 103 MB and the bf16 copy 51 MB of
+// the 410 MB that the data gradient which ends a block moved; that launch is bound by them.
+// Forward, fp32: the shortcut of a block that adds its input; the bf16 copy (operand, gate, batch-norm input) always.
+bool reads_fp32_input(const LayerPlan& L) {
+  switch (L.kind) {
+    case FDG_BASIC_POSTACT: case FDG_BASIC_PREACT: case FDG_BOTTLENECK_POSTACT: return !L.projects;
+    case FDG_INVERTED_RESIDUAL: return L.stride == 1 && L.c_in == L.c_out;
+    default: return false;
+  }
+}
+// Backward: a pre-activation block hands the bf16 gradient to its convolutions and adds the fp32 one only to an identity
+// shortcut; every other layer takes the fp32 gradient.
+bool reads_bf16_gradient(const LayerPlan& L) { return L.kind == FDG_BASIC_PREACT; }
+bool reads_fp32_gradient(const LayerPlan& L) { return !(L.kind == FDG_BASIC_PREACT && L.projects); }
+
 // The layers of the module on x (fp32 NCHW) with the weights of slot v, every intermediate the backward needs
 // written where v keeps them.  `replayed`: this forward ran before (v's snapshot and labels are in place); running
 // statistics stay as they are and y_dev may be NULL (a head then needs it as scratch for loss and logits).
@@ -857,7 +873,8 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
     FDG_TRY(launch_fill_zero(v.sums(p.bns[0]), p.stat_floats * kStatWords * sizeof(stat_t) * (p.stat_rep ? kStatReplicas : 1), s));
   // module input: fp32 NCHW -> fp32 NHWC stream + bf16 NHWC copy (kept for the backward)
   int cur = 0;
-  FDG_TRY(launch_nchw_to_nhwc(x_dev, (p.d.c_in % 8 == 0) ? m->S(cur) : nullptr, v.xin(), N, p.d.c_in, p.d.h_in * p.d.w_in,
+  const bool tracing = m->trace && !replayed;   // a trace holds every layer's fp32 output
+  FDG_TRY(launch_nchw_to_nhwc(x_dev, (p.d.c_in % 8 == 0 && reads_fp32_input(p.L[0])) ? m->S(cur) : nullptr, v.xin(), N, p.d.c_in, p.d.h_in * p.d.w_in,
                               p.Cp_in, 1.f, s));
   const bf16_t* cur_b = v.xin();
   bool stats_ready = false;   // the sums of this layer's leading BN were taken by the producer of its input
@@ -873,6 +890,8 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
   for (size_t li = 0; li < p.L.size(); ++li) {
     const LayerPlan& L = p.L[li];
     const int nxt = cur ^ 1;
+    // this layer's fp32 output: where the module's output is made from it, the layer above adds it, or a trace wants it
+    float* const S_out = (tracing || (li + 1 < p.L.size() ? reads_fp32_input(p.L[li + 1]) : y_dev != nullptr)) ? m->S(nxt) : nullptr;
     bool next_ready = false;
     bool owes = false;
     if (L.kind == FDG_STEM_CONV_BN_RELU) {
@@ -882,7 +901,7 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
       if (above_takes(li, b0, false)) {
         pend.owed = owes = true; pend.b = &b0; pend.x_raw = v.act(L.act[0]); pend.res = nullptr; pend.layer = li;
       } else {
-        FDG_TRY(bn_apply(m, v, b0, v.act(L.act[0]), nullptr, nullptr, nullptr, m->S(nxt), v.act(L.out_b), replayed, s));
+        FDG_TRY(bn_apply(m, v, b0, v.act(L.act[0]), nullptr, nullptr, nullptr, S_out, v.act(L.out_b), replayed, s));
       }
     } else if (L.kind == FDG_BASIC_POSTACT) {
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]];
@@ -911,11 +930,11 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
         const BnInfo& bp = p.bns[L.bn[2]];
         bf16_t* t_p = v.act(L.act[3]);
         FDG_TRY(mconv_forward(m, cp, cur_b, v.W(cp), nullptr, nullptr, t_p, v.sums(bp), s));
-        FDG_TRY(bn_apply(m, v, b2, t_c2, nullptr, &bp, t_p, m->S(nxt), v.act(L.out_b), replayed, s));
+        FDG_TRY(bn_apply(m, v, b2, t_c2, nullptr, &bp, t_p, S_out, v.act(L.out_b), replayed, s));
       } else if (above_takes(li, b2, true)) {
         pend.owed = owes = true; pend.b = &b2; pend.x_raw = t_c2; pend.res = m->S(cur); pend.layer = li;
       } else {
-        FDG_TRY(bn_apply(m, v, b2, t_c2, m->S(cur), nullptr, nullptr, m->S(nxt), v.act(L.out_b), replayed, s));
+        FDG_TRY(bn_apply(m, v, b2, t_c2, m->S(cur), nullptr, nullptr, S_out, v.act(L.out_b), replayed, s));
       }
     } else if (L.kind == FDG_BOTTLENECK_POSTACT) {
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]], &c3 = p.convs[L.conv[3]];
@@ -932,9 +951,9 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
         const BnInfo& bp = p.bns[L.bn[2]];
         bf16_t* t_p = v.act(L.act[3]);
         FDG_TRY(mconv_forward(m, cp, cur_b, v.W(cp), nullptr, nullptr, t_p, v.sums(bp), s));
-        FDG_TRY(bn_apply(m, v, b3, t_c3, nullptr, &bp, t_p, m->S(nxt), v.act(L.out_b), replayed, s));
+        FDG_TRY(bn_apply(m, v, b3, t_c3, nullptr, &bp, t_p, S_out, v.act(L.out_b), replayed, s));
       } else {
-        FDG_TRY(bn_apply(m, v, b3, t_c3, m->S(cur), nullptr, nullptr, m->S(nxt), v.act(L.out_b), replayed, s));
+        FDG_TRY(bn_apply(m, v, b3, t_c3, m->S(cur), nullptr, nullptr, S_out, v.act(L.out_b), replayed, s));
       }
     } else if (L.kind == FDG_STEM_POOL) {
       const ConvInfo& c0 = p.convs[L.conv[0]];
@@ -945,7 +964,7 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
       FDG_TRY(launch_im2col7(cur_b, col, N, L.Hi, L.Wi, s));
       FDG_TRY(mconv_forward(m, c0, col, v.W(c0), nullptr, nullptr, t_c, v.sums(b0), s));
       FDG_TRY(bn_apply(m, v, b0, t_c, nullptr, nullptr, nullptr, nullptr, t_a, replayed, s));
-      FDG_TRY(launch_maxpool3s2(t_a, m->S(nxt), v.act(L.out_b), N, c0.sh.Hi, c0.sh.Wi, L.c_out, s));
+      FDG_TRY(launch_maxpool3s2(t_a, S_out, v.act(L.out_b), N, c0.sh.Hi, c0.sh.Wi, L.c_out, s));
     } else if (L.kind == FDG_INVERTED_RESIDUAL) {
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]], &c3 = p.convs[L.conv[3]];
       const BnInfo &b1 = p.bns[L.bn[0]], &b2 = p.bns[L.bn[1]], &b3 = p.bns[L.bn[3]];
@@ -958,7 +977,7 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
       FDG_TRY(bn_apply(m, v, b2, t_c2, nullptr, nullptr, nullptr, nullptr, t_a2, replayed, s, /*relu6*/ 2));
       FDG_TRY(mconv_forward(m, c3, t_a2, v.W(c3), nullptr, nullptr, t_c3, v.sums(b3), s));
       const bool adds = L.stride == 1 && L.c_in == L.c_out;
-      FDG_TRY(bn_apply(m, v, b3, t_c3, adds ? m->S(cur) : nullptr, nullptr, nullptr, m->S(nxt), v.act(L.out_b), replayed, s, /*no activation*/ 0));
+      FDG_TRY(bn_apply(m, v, b3, t_c3, adds ? m->S(cur) : nullptr, nullptr, nullptr, S_out, v.act(L.out_b), replayed, s, /*no activation*/ 0));
     } else if (L.kind == FDG_BASIC_PREACT) {
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]];
       const BnInfo &b1 = p.bns[L.bn[0]], &b2 = p.bns[L.bn[1]];
@@ -977,7 +996,7 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
       stat_t* next_stats = nullptr;
       if (li + 1 < p.L.size() && (p.L[li + 1].kind == FDG_BASIC_PREACT || p.L[li + 1].kind == FDG_HEAD_PREACT))
         next_stats = v.sums(p.bns[p.L[li + 1].bn[0]]);
-      FDG_TRY(mconv_forward(m, c2, t_o2, v.W(c2), shortcut, m->S(nxt), v.act(L.out_b), next_stats, s));
+      FDG_TRY(mconv_forward(m, c2, t_o2, v.W(c2), shortcut, S_out, v.act(L.out_b), next_stats, s));
       next_ready = next_stats != nullptr;
     } else {  // heads
       const bf16_t* o = cur_b;
@@ -1138,7 +1157,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
   FDG_TRY(launch_fill_zero(m->ws + p.o_bsums, p.o_running - p.o_bsums, s));
   int cur = 0;
   if (!p.is_top)  // gradient shrinking of Eq. 15: multiply by beta before anything else
-    FDG_TRY(launch_nchw_to_nhwc(grad_out_dev, m->G(cur), m->GB(cur), N, p.out_c, p.out_h * p.out_w, p.out_c, p.d.beta, s));
+    FDG_TRY(launch_nchw_to_nhwc(grad_out_dev, m->G(cur), reads_bf16_gradient(p.L.back()) ? m->GB(cur) : nullptr, N, p.out_c, p.out_h * p.out_w, p.out_c, p.d.beta, s));
   if (m->trace && !p.is_top)
     FDG_TRY(hipMemcpyAsync(m->trace + p.tr_bwd[p.L.size()], m->G(cur), (size_t)N * p.out_h * p.out_w * p.out_c * 4,
                            hipMemcpyDeviceToDevice, s));
@@ -1151,6 +1170,11 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
     const bool need_dx = !(li == 0 && p.d.is_bottom);
     const bool fed_here = fed;
     fed = false;
+    // the gradient of this layer's input, in the forms the layer below reads (the module's grad_in is made from the fp32 one)
+    float* const G_out = (li == 0 || m->trace || reads_fp32_gradient(p.L[li - 1])) ? m->G(nxt) : nullptr;
+    bf16_t* const GB_out = (li > 0 && reads_bf16_gradient(p.L[li - 1])) ? m->GB(nxt) : nullptr;
+    // whether the incoming fp32 gradient still has to be gated by this layer's output
+    auto gate_of = [&](const bf16_t* y) { return fed_here ? nullptr : y; };
     if (L.kind == FDG_HEAD_POSTACT || L.kind == FDG_HEAD_PREACT) {
       const int J = p.d.num_classes;
       float* dp = reinterpret_cast<float*>(m->ws + p.o_dp);
@@ -1159,10 +1183,10 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       if (L.kind == FDG_HEAD_PREACT) {
         const BnInfo& b0 = p.bns[L.bn[0]];
         FDG_TRY(launch_pool_bwd(dp, m->TPB(), nullptr, N, p.head_HW, p.head_C, s));
-        FDG_TRY(bn_backward(m, v, b0, m->TPB(), true, v.act(L.act[0]), in_b, nullptr, m->G(nxt), m->GB(nxt), s));
+        FDG_TRY(bn_backward(m, v, b0, m->TPB(), true, v.act(L.act[0]), in_b, nullptr, G_out, GB_out, s));
       } else {
-        FDG_TRY(side_wait_readers(m, m->GB(nxt), s));
-        FDG_TRY(launch_pool_bwd(dp, m->G(nxt), m->GB(nxt), N, p.head_HW, p.head_C, s));
+        FDG_TRY(side_wait_readers(m, GB_out, s));
+        FDG_TRY(launch_pool_bwd(dp, G_out, GB_out, N, p.head_HW, p.head_C, s));
       }
     } else if (L.kind == FDG_STEM_CONV_BN_RELU) {
       const ConvInfo& c0 = p.convs[L.conv[0]];
@@ -1170,7 +1194,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       if (fed_here) FDG_TRY(bn_backward_fed_from_above(m, v, b0, m->G(cur), v.act(L.act[0]), m->T(0), s));
       else FDG_TRY(bn_backward(m, v, b0, m->G(cur), true, v.act(L.out_b), v.act(L.act[0]), nullptr, nullptr, m->T(0), s));
       FDG_TRY(mconv_wgrad(m, c0, in_b, m->T(0), s));
-      if (need_dx) FDG_TRY(mconv_dgrad(m, c0, m->T(0), v.Wt(c0), nullptr, nullptr, m->G(nxt), m->GB(nxt), s));
+      if (need_dx) FDG_TRY(mconv_dgrad(m, c0, m->T(0), v.Wt(c0), nullptr, nullptr, G_out, GB_out, s));
     } else if (L.kind == FDG_BASIC_POSTACT) {
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]];
       const BnInfo &b1 = p.bns[L.bn[0]], &b2 = p.bns[L.bn[1]];
@@ -1226,21 +1250,21 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       if (L.projects) {
         const ConvInfo& cp = p.convs[L.conv[2]];
         const BnInfo& bp = p.bns[L.bn[2]];
-        FDG_TRY(bn_backward(m, v, bp, m->G(cur), true, t_y, v.act(L.act[3]), nullptr, nullptr, m->T(1), s));
+        FDG_TRY(bn_backward(m, v, bp, m->G(cur), true, gate_of(t_y), v.act(L.act[3]), nullptr, nullptr, m->T(1), s));
         FDG_TRY(mconv_wgrad(m, cp, in_b, m->T(1), s));
         if (need_dx && conv_dgrad_pair_applies(c1.sh, cp.sh)) {
           // the data gradients of the 3x3 and of the projection beside it, both stride 2, in one launch
-          FDG_TRY(side_wait_readers(m, m->GB(nxt), s));
+          FDG_TRY(side_wait_readers(m, GB_out, s));
           const double bytes = 2 * (conv_out_elems(c1.sh) + conv_out_elems(cp.sh)) + 2 * (conv_w_elems(c1.sh) + conv_w_elems(cp.sh)) +
                                conv_in_elems(c1.sh) * (4 + 2);
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh) + conv_flops(cp.sh), bytes, s);
           const hipError_t e = conv_dgrad_gated_pair(c1.sh, m->T(0), v.Wt(c1), cp.sh, m->T(1), v.Wt(cp), nullptr, nullptr, nullptr,
-                                                     m->G(nxt), m->GB(nxt), s);
+                                                     G_out, GB_out, s);
           ps.label(c1.sh);
           FDG_TRY(e);
         } else if (need_dx) {
           FDG_TRY(mconv_dgrad(m, cp, m->T(1), v.Wt(cp), nullptr, nullptr, m->TPB(), nullptr, s));
-          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->TPB(), nullptr, m->G(nxt), m->GB(nxt), s));
+          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->TPB(), nullptr, G_out, GB_out, s));
         }
       } else if (need_dx) {
         // identity shortcut: the masked incoming gradient joins the branch gradient.  Where the narrow kernel runs
@@ -1251,30 +1275,30 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
         const bool feeds = bb && bb->C == c1.sh.Cip && conv_dgrad_feeds_next(c1.sh);
         if (fuse1) {
           FDG_TRY(side_wait_readers(m, m->T(2), s));
-          FDG_TRY(side_wait_readers(m, m->GB(nxt), s));
+          FDG_TRY(side_wait_readers(m, GB_out, s));
           {
             const ConvInputBnBwd bn = g32 ? bn_bwd_input(m, v, b1, gf, true, t_c1, m->T(2)) : bn_bwd_input(m, v, b1, m->T(1), false, t_c1, m->T(2));
             const double bytes = conv_out_elems(c1.sh) * (2 + 2 + 2) + 2 * conv_w_elems(c1.sh) +
                                  conv_in_elems(c1.sh) * (4 + 2 + (feeds ? 2 + 2 : 0) + 4 + 2);
             ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
-            const hipError_t e = conv_dgrad_after_bn(c1.sh, bn, v.Wt(c1), m->G(cur), t_y, feeds ? in_b : nullptr, feeds ? bnx : nullptr,
-                                                     feeds ? m->bsums(*bb) : nullptr, feeds, m->G(nxt), m->GB(nxt), s, p.stat_rep);
+            const hipError_t e = conv_dgrad_after_bn(c1.sh, bn, v.Wt(c1), m->G(cur), gate_of(t_y), feeds ? in_b : nullptr, feeds ? bnx : nullptr,
+                                                     feeds ? m->bsums(*bb) : nullptr, feeds, G_out, GB_out, s, p.stat_rep);
             ps.label(c1.sh);
             FDG_TRY(e);
           }
           fed = feeds;
           FDG_TRY(mconv_wgrad(m, c1, in_b, m->T(2), s));
         } else if (feeds) {
-          FDG_TRY(side_wait_readers(m, m->GB(nxt), s));
+          FDG_TRY(side_wait_readers(m, GB_out, s));
           const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (4 + 2 + 2 + 2 + 4 + 2);
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
-          const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), t_y, in_b, bnx,
-                                                       m->bsums(*bb), m->G(nxt), m->GB(nxt), s, p.stat_rep);
+          const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), in_b, bnx,
+                                                       m->bsums(*bb), G_out, GB_out, s, p.stat_rep);
           ps.label(c1.sh);
           FDG_TRY(e);
           fed = true;
         } else {
-          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->G(cur), t_y, m->G(nxt), m->GB(nxt), s));
+          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), G_out, GB_out, s));
         }
       }
     } else if (L.kind == FDG_BOTTLENECK_POSTACT) {
@@ -1293,11 +1317,11 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       if (L.projects) {
         const ConvInfo& cp = p.convs[L.conv[2]];
         const BnInfo& bp = p.bns[L.bn[2]];
-        FDG_TRY(bn_backward(m, v, bp, m->G(cur), true, t_y, v.act(L.act[3]), nullptr, nullptr, m->T(1), s));
+        FDG_TRY(bn_backward(m, v, bp, m->G(cur), true, gate_of(t_y), v.act(L.act[3]), nullptr, nullptr, m->T(1), s));
         FDG_TRY(mconv_wgrad(m, cp, in_b, m->T(1), s));
         if (need_dx) {
           FDG_TRY(mconv_dgrad(m, cp, m->T(1), v.Wt(cp), nullptr, nullptr, m->TPB(), nullptr, s));
-          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->TPB(), nullptr, m->G(nxt), m->GB(nxt), s));
+          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->TPB(), nullptr, G_out, GB_out, s));
         }
       } else if (need_dx) {
         // identity shortcut: as in the basic block, the data gradient that ends this block's backward can also gate by
@@ -1305,16 +1329,16 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
         const bf16_t* bnx = nullptr;
         const BnInfo* bb = li > 0 ? closing_bn(p, v, p.L[li - 1], &bnx) : nullptr;
         if (bb && bb->C == c1.sh.Cip && conv_dgrad_feeds_next(c1.sh)) {
-          FDG_TRY(side_wait_readers(m, m->GB(nxt), s));
+          FDG_TRY(side_wait_readers(m, GB_out, s));
           const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (4 + 2 + 2 + 2 + 4 + 2);
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
-          const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), t_y, in_b, bnx,
-                                                       m->bsums(*bb), m->G(nxt), m->GB(nxt), s, p.stat_rep);
+          const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), in_b, bnx,
+                                                       m->bsums(*bb), G_out, GB_out, s, p.stat_rep);
           ps.label(c1.sh);
           FDG_TRY(e);
           fed = true;
         } else {
-          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->G(cur), t_y, m->G(nxt), m->GB(nxt), s));
+          FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), G_out, GB_out, s));
         }
       }
     } else if (L.kind == FDG_STEM_POOL) {
@@ -1348,7 +1372,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       FDG_TRY(launch_dwconv3_dgrad(m->T(0), v.Wt(c2), nullptr, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s, gf));
       FDG_TRY(bn_backward(m, v, b1, gf, true, t_a1, t_c1, nullptr, nullptr, m->T(0), s, 6.f));
       FDG_TRY(mconv_wgrad(m, c1, in_b, m->T(0), s));
-      if (need_dx) FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, m->G(nxt), m->GB(nxt), s));
+      if (need_dx) FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, G_out, GB_out, s));
     } else {  // pre-activation block: y = conv2(o2) + shortcut
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]];
       const BnInfo &b1 = p.bns[L.bn[0]], &b2 = p.bns[L.bn[1]];
@@ -1371,16 +1395,16 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
             ps.label(c1.sh);
             FDG_TRY(e);
           }
-          FDG_TRY(bn_backward_after_gated_dgrad(m, v, b1, m->T(0), in_b, nullptr, need_dx ? m->G(nxt) : nullptr,
-                                                need_dx ? m->GB(nxt) : nullptr, s));
+          FDG_TRY(bn_backward_after_gated_dgrad(m, v, b1, m->T(0), in_b, nullptr, need_dx ? G_out : nullptr,
+                                                need_dx ? GB_out : nullptr, s));
         } else {
           FDG_TRY(mconv_dgrad(m, cp, m->GB(cur), v.Wt(cp), nullptr, nullptr, m->TPB(), nullptr, s));
           FDG_TRY(dgrad_relu_bn_backward(m, v, c1, m->T(1), v.Wt(c1), m->TPB(), b1, t_o1, in_b, m->T(0), nullptr,
-                                         need_dx ? m->G(nxt) : nullptr, need_dx ? m->GB(nxt) : nullptr, s));
+                                         need_dx ? G_out : nullptr, need_dx ? GB_out : nullptr, s));
         }
       } else {
         FDG_TRY(dgrad_relu_bn_backward(m, v, c1, m->T(1), v.Wt(c1), nullptr, b1, t_o1, in_b, m->T(0), m->G(cur),
-                                       need_dx ? m->G(nxt) : nullptr, need_dx ? m->GB(nxt) : nullptr, s));
+                                       need_dx ? G_out : nullptr, need_dx ? GB_out : nullptr, s));
       }
     }
     if (m->trace && need_dx) {

@@ -1,5 +1,6 @@
 """Layer-by-layer parity (tests/layerwise.py, bars of tests/test_gpu_layerwise.py) of small modules whose shapes sit at the
 edges of the rules that choose a kernel: partly filled channel groups, remainders of tiles, the ends of a rule's range."""
+import numpy as np
 import pytest
 
 import fdg_workloads as W
@@ -31,3 +32,36 @@ COPIES = {
 @pytest.mark.parametrize("name", sorted(COPIES))
 def test_sums_in_copies(name):
     check(name, ModuleSpec(6, 16, 23, 21, COPIES[name], delay=1, is_bottom=False, beta=0.5, name=name, **H))
+
+
+# The streams between layers are written only in the forms (fp32, bf16) that the next layer reads, a trace makes every layer
+# write its fp32 form: the same bits either way, whatever follows what
+STREAMS = {
+    "post": [Layer(W.STEM, 3, 16, 1), Layer(W.BASIC_POSTACT, 16, 32, 2), Layer(W.BASIC_PREACT, 32, 32, 1),
+             Layer(W.BASIC_PREACT, 32, 64, 2), Layer(W.BASIC_POSTACT, 64, 64, 1), Layer(W.BOTTLENECK_POSTACT, 64, 64, 1)],
+    "pre": [Layer(W.STEM, 3, 16, 1), Layer(W.BASIC_PREACT, 16, 32, 1), Layer(W.BASIC_PREACT, 32, 32, 1),
+            Layer(W.BASIC_POSTACT, 32, 32, 1), Layer(W.INVERTED_RESIDUAL, 32, 32, 1), Layer(W.INVERTED_RESIDUAL, 32, 16, 2)],
+}
+
+
+@pytest.mark.parametrize("name", sorted(STREAMS))
+@pytest.mark.parametrize("replay", [False, True])
+def test_streams_with_and_without_a_trace(name, replay):
+    import torch as t
+    from paper_1906_09108_amd import FdgModule
+    spec = ModuleSpec(4, 3, 16, 16, STREAMS[name], delay=1, is_bottom=True, beta=0.5, name=name, **H)
+    results = []
+    for traced in (False, True):
+        m = FdgModule(spec, save_mode=1 if replay else 0)
+        m.set_params(W.make_params(spec, 0, perturb_bn=True))
+        if traced:
+            m.trace_attach()
+        for it in range(3):
+            y = m.forward(t.from_numpy(W.make_input(spec, it, 0)).cuda())
+            if it >= 1:
+                m.backward_delayed(t.from_numpy(W.make_grad_out(spec, it - 1, 0)).cuda())
+                m.update(spec.lr)
+        results.append((y.cpu().numpy(), m.get_grads(), m.get_params(), m.get_bn_running()))
+        m.close()
+    for a, b in zip(*results):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
