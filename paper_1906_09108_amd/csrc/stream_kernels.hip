@@ -667,29 +667,38 @@ hipError_t launch_fc_fwd(const float* pooled, const float* W, const float* b, fl
   return hipGetLastError();
 }
 
-// single block: per-row log-sum-exp, loss, dlogits
-__global__ __launch_bounds__(kThreads) void softmax_ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                              float* __restrict__ y, float* __restrict__ dl, int N, int J) {
-  __shared__ float red[kThreads];
+// One workgroup of 1024 threads: log-sum-exp of each row, loss, dlogits.  G lanes share a row (16 for up to 16 classes, else a
+// whole wave), so that a row's classes are read in J / G coalesced steps; a thread to a row walked its classes one after the
+// other, three times: 128 rows of 200 classes took 106 us, now 31.  The loss adds the rows of a group, then the groups, in order.
+template <int G>
+__global__ __launch_bounds__(1024) void softmax_ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
+                                                          float* __restrict__ y, float* __restrict__ dl, int N, int J) {
+  constexpr int GROUPS = 1024 / G;
+  __shared__ float red[GROUPS];
+  const int g = threadIdx.x / G, t = threadIdx.x % G;
   float part = 0.f;
-  for (int n = threadIdx.x; n < N; n += kThreads) {
+  for (int n = g; n < N; n += GROUPS) {
     const float* l = logits + (size_t)n * J;
-    float mx = l[0];
-    for (int j = 1; j < J; ++j) mx = fmaxf(mx, l[j]);
+    float mx = l[t < J ? t : 0];
+    for (int j = t + G; j < J; j += G) mx = fmaxf(mx, l[j]);
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, G));
     float z = 0.f;
-    for (int j = 0; j < J; ++j) z += expf(l[j] - mx);
+    for (int j = t; j < J; j += G) z += expf(l[j] - mx);
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) z += __shfl_xor(z, off, G);
     const float lse = mx + logf(z);
     const int lab = min(max(labels[n], 0), J - 1);
     part += lse - l[lab];
-    for (int j = 0; j < J; ++j) {
-      const float sm = expf(l[j] - lse);
+    for (int j = t; j < J; j += G) {
+      const float v = l[j], sm = expf(v - lse);
       dl[(size_t)n * J + j] = (sm - (j == lab ? 1.f : 0.f)) / (float)N;
-      y[1 + (size_t)n * J + j] = l[j];
+      y[1 + (size_t)n * J + j] = v;
     }
   }
-  red[threadIdx.x] = part;
+  if (t == 0) red[g] = part;
   __syncthreads();
-  for (int off = kThreads / 2; off > 0; off >>= 1) {
+  for (int off = GROUPS / 2; off > 0; off >>= 1) {
     if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
     __syncthreads();
   }
@@ -697,7 +706,8 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(const float* __res
 }
 hipError_t launch_softmax_ce(const float* logits, const int32_t* labels, float* y, float* dl, int N, int J,
                              hipStream_t s) {
-  hipLaunchKernelGGL(softmax_ce_kernel, dim3(1), dim3(kThreads), 0, s, logits, labels, y, dl, N, J);
+  if (J <= 16) hipLaunchKernelGGL(softmax_ce_kernel<16>, dim3(1), dim3(1024), 0, s, logits, labels, y, dl, N, J);
+  else hipLaunchKernelGGL(softmax_ce_kernel<64>, dim3(1), dim3(1024), 0, s, logits, labels, y, dl, N, J);
   return hipGetLastError();
 }
 
@@ -715,7 +725,18 @@ __global__ __launch_bounds__(256) void fc_bwd_kernel(const float* __restrict__ p
     if (idx < N * C) {
       const int n = idx / C, c = idx % C;
       float s = 0.f;
-      for (int j = 0; j < J; ++j) s += dl[(size_t)n * J + j] * W[(size_t)j * C + c];
+      for (int j0 = 0; j0 < J; j0 += 16) {   // the loads of 16 classes before their sums: 200 classes 41 -> 18 us
+        float d[16], w[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const int j = min(j0 + k, J - 1);
+          d[k] = dl[(size_t)n * J + j];
+          w[k] = W[(size_t)j * C + c];
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          if (j0 + k < J) s += d[k] * w[k];
+      }
       dp[idx] = s;
     }
     return;

@@ -5,6 +5,7 @@ import pytest
 
 import fdg_workloads as W
 from fdg_workloads import Layer, ModuleSpec
+from tests import test_gpu_kernels as TK
 from tests import test_gpu_layerwise as LT
 
 pytestmark = pytest.mark.gpu
@@ -65,3 +66,16 @@ def test_streams_with_and_without_a_trace(name, replay):
         m.close()
     for a, b in zip(*results):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+# A thread makes 2 x 2 cells of a depthwise convolution and walks segments of 8 cells for its weight gradient: odd heights and
+# widths, single rows and columns, one cell more and less than a segment, a partly filled block of 8 channel groups
+@pytest.mark.parametrize("case", [(2, 1, 17, 72, 1), (3, 17, 1, 8, 2), (2, 8, 8, 64, 1), (2, 15, 16, 72, 2), (5, 7, 15, 136, 1), (1, 2, 2, 8, 2)])
+def test_depthwise_edges(case):
+    TK.test_depthwise_convolution_kernels(case)
+
+
+# Classes on 16 lanes or a wave to a row, and 16 classes to a step of the gradient: at, below and above those counts
+@pytest.mark.parametrize("case", [(70, 2, 2, 24, 15), (3, 1, 1, 8, 16), (65, 2, 2, 16, 17), (17, 1, 2, 40, 65), (5, 1, 1, 8, 1)])
+def test_head_edges(case):
+    TK.test_head_kernels_one_by_one(case)
