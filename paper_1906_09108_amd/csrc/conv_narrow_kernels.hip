@@ -14,6 +14,8 @@
 #include "conv_common.h"
 #include <stdio.h>
 #include <stdlib.h>
+#include <algorithm>
+#include <type_traits>
 
 namespace fdg {
 
@@ -671,7 +673,9 @@ struct NarrowWgradLaunch {
   int rows_total;   // N * HP
   int KP;           // positions a workgroup contracts over: R * PW rounded up to 32
   int xunits, dyunits;   // 16-byte units of the two LDS regions (multiples of 256)
-  int fold_off;          // LDS byte offset of 4 KB for adding up an earlier launch's slices
+  int fold_off;          // LDS byte offset of 4 KB (64 channels: fold_rounds x 8 KB) for adding up an earlier launch's slices
+  int buffers, fold_rounds;                // 64 channels: tile buffers; rounds of 8 KB at fold_off
+  unsigned long long magic_pw, magic_hp;   // 64 channels: narrow_div by PW and HP
   float* partial;
   size_t stride;    // floats per slice
 };
@@ -699,7 +703,8 @@ template <int C, bool STEM>
 __global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(WgradArgs a, NarrowWgradLaunch L) {
   constexpr int U = C / 8, ROWB = C * 2, NCB = C / 16, WK = 4 / NCB;
   constexpr int UX = STEM ? 2 : U, ROWBX = UX * 16, NCBI = STEM ? 1 : NCB;   // x side: units, bytes, 16-channel blocks
-  constexpr bool SWZ_DY = C == 64, SWZ_X = !STEM && C == 64;
+  static_assert(STEM || C < 64, "64 -> 64 channels have a kernel of their own");
+  constexpr bool SWZ_DY = C == 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -784,7 +789,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(WgradArgs a, Nar
   for (int tile = first_tile; tile < L.tiles; tile += gridDim.x) {
     if (tile != first_tile) __syncthreads();           // every wave is done reading the previous tile
     pr0 = tile * L.R;
-    fill(a.x, L.xunits, 1, pr0 - 1, L.R + 2, 0, UXLOG, STEM ? 1 : UX, STEM ? 8 : C, SWZ_X);
+    fill(a.x, L.xunits, 1, pr0 - 1, L.R + 2, 0, UXLOG, STEM ? 1 : UX, STEM ? 8 : C, false);
     fill(a.dy, L.dyunits, 0, pr0, L.R, L.xunits, ULOG, U, C, SWZ_DY);
     const bool folds = tile == first_tile && (int)blockIdx.x < fold_blocks;
     if (folds) fold_red[tid] = fold_load(blockIdx.x);
@@ -814,8 +819,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(WgradArgs a, Nar
           const int idx = pp + shift[t0 + t];
 #pragma unroll
           for (int j = 0; j < NCBI; ++j) {
-            const int bslot = SWZ_X ? (j ^ (idx & 2)) : j;
-            narrow_read_tr8(rb[t][j], (unsigned)(idx * ROWBX + bslot * 32 + (i16 & 3) * 8), 16 * ROWBX);
+            narrow_read_tr8(rb[t][j], (unsigned)(idx * ROWBX + j * 32 + (i16 & 3) * 8), 16 * ROWBX);
           }
         }
         narrow_frags_landed();
@@ -866,6 +870,235 @@ __global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(WgradArgs a, Nar
   }
 }
 
+// 64 -> 64 channels.  The result is 147 KB a slice and a 32-position step of one wave needs 37 operand fragments where each
+// wave holds one block of 16 output channels: read by four waves, those reads, the wait for each batch of them and the wait
+// for each tile took far longer than the matrix instructions.  Here
+//   * eight waves, two per SIMD: wave (wc, wi, wk) holds 32 output x 32 input channels of all nine taps and takes every second
+//     step, 20 fragments for 36 instructions; a batch of 3 fragments is read during the instructions of the batch before it
+//     (ds reads return in order, so "at most the younger batch outstanding" is a counted wait);
+//   * two tile buffers: the next tile loads while the present one is contracted;
+//   * no more workgroups than give each about kWgrad64Positions positions, because each writes (and a later launch reads) a slice.
+// The halves wk are added through LDS, either wave of a pair finishing a part of the taps.
+// 128 x 64 x 64: 303 -> 98 us; 128 x 8 x 8: 18.8 -> 11 us.
+constexpr int kWgrad64Positions = 192;
+constexpr int kWgrad64Exchange = 4 * 9 * 4 * 1024;   // bytes: four pairs of waves, nine taps, four blocks
+template <int YOUNGER>
+__device__ __forceinline__ void narrow_frags_landed_but() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(YOUNGER) : "memory"); }
+__device__ __forceinline__ void narrow_read_tr64(NarrowFrag& f, unsigned addr) {   // rows of 128 bytes
+  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.lo) : "v"(addr));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:2048" : "=v"(f.hi) : "v"(addr));
+}
+
+__global__ __launch_bounds__(512) void conv_wgrad_narrow64_kernel(WgradArgs a, NarrowWgradLaunch L) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // at LDS address 0: no static LDS in this kernel
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave & 1, wi = (wave >> 1) & 1, wk = wave >> 2;
+  const int W = a.Wi, H = a.Hi, PW = L.PW, HP = L.HP;
+  const char* zero = reinterpret_cast<const char*>(g_narrow_zero);
+  const unsigned buf_bytes = (unsigned)(L.xunits + L.dyunits) * 16u;
+
+  // Positions as in the kernel above: idx 0 of the x region is one position before padded row pr0 - 1, of the dy region the first
+  // of padded row pr0.  The 32-byte slot of a position is XORed with bits 1 and 2 of idx, so that the eight positions a half
+  // wave reads cover all banks.  Unit `pos` of a buffer (the dy region follows the x region) is decoded into what does not change
+  // from tile to tile: its padded row relative to the region's first as q1 images and r1 rows, and the pixel that gives.
+  const int u16 = ((lane & 7) ^ ((((lane >> 3) & 2) << 1) | ((lane >> 4) & 2))) * 16;   // idx & 7 == (pos >> 3) & 7 in both regions
+  const int total_units = L.xunits + L.dyunits, pixels = a.N * H * W;
+  struct Pos { int off, r1; };                       // r1 < 0: padding whatever the tile
+  auto decode = [&](int base) {
+    const bool is_x = base < L.xunits;
+    const int xp = ((base + lane - (is_x ? 0 : L.xunits)) >> 3) - (is_x ? 1 : 0);
+    const int lr = xp >= 0 ? narrow_div(xp, L.magic_pw) : 0, c = xp - lr * PW;
+    const int q1 = narrow_div(lr, L.magic_hp), r1 = lr - q1 * HP;
+    Pos p;
+    p.r1 = xp >= 0 && lr < (is_x ? L.R + 2 : L.R) && c >= 1 && c <= W ? r1 : -(1 << 24);
+    p.off = (q1 * H + r1) * W + c - 1;
+    return p;
+  };
+  constexpr int KEPT = 10;                           // rounds of 512 units decoded once: all of them with two buffers
+  Pos kept[KEPT];
+#pragma unroll
+  for (int k = 0; k < KEPT; ++k) kept[k] = decode(k * 512 + wave * 64);
+  auto fill_tile = [&](int tile, int buf) {
+    const int pr0 = tile * L.R;
+    // the regions' first padded rows (pr0 - 1 >= -1) as image and row, and the pixel number of their column 1
+    const int nx = pr0 >= 1 ? (pr0 - 1) / HP : -1, hx = pr0 - 1 - nx * HP, nd = pr0 / HP, hd = pr0 - nd * HP;
+    const int px = (nx * H + hx - 1) * W, pd = (nd * H + hd - 1) * W;
+    auto one = [&](const Pos& p, int base) {
+      const bool is_x = base < L.xunits;             // uniform: regions are whole rounds of a wave
+      const char* src = reinterpret_cast<const char*>(is_x ? a.x : a.dy);
+      int hr = (is_x ? hx : hd) + p.r1, pix = (is_x ? px : pd) + p.off;
+      const bool wraps = hr >= HP;                   // into the next image, whose two padding rows hold no pixels
+      hr -= wraps ? HP : 0;
+      pix -= wraps ? 2 * W : 0;
+      const bool ok = (unsigned)(hr - 1) < (unsigned)H && (unsigned)pix < (unsigned)pixels;
+      const char* g = src + (size_t)(unsigned)pix * 128 + u16;
+      narrow_dma16(ok ? g : zero, smem + (size_t)buf * buf_bytes + (size_t)base * 16);
+    };
+#pragma unroll
+    for (int k = 0; k < KEPT; ++k) {
+      const int base = k * 512 + wave * 64;
+      if (base < total_units) one(kept[k], base);
+    }
+    for (int base = KEPT * 512 + wave * 64; base < total_units; base += 512) one(decode(base), base);
+  };
+
+  f32x4 acc[9][2][2];   // [tap][output block][input block]
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[t][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // LDS addresses of this lane's fragments in step 0 of buffer 0: a step moves every position by 32 and so leaves the swizzle
+  // alone; the second block of a pair is 32 bytes away under it
+  const int g = lane >> 4, i16 = lane & 15;
+  const int pp0 = 4 * g + (i16 >> 2);
+  const unsigned in_row = (unsigned)(i16 & 3) * 8u;
+  const unsigned aaddr = (unsigned)L.xunits * 16u + (unsigned)(pp0 * 128 + ((2 * wc) ^ (pp0 & 2) ^ ((pp0 >> 2) & 1)) * 32) + in_row;
+  unsigned xaddr[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    const int dh = (a.tap[t] & 0xff) - 8, dw = ((a.tap[t] >> 8) & 0xff) - 8;
+    const int idx = pp0 + 1 + (1 + dh) * PW + dw;
+    xaddr[t] = (unsigned)(idx * 128 + ((2 * wi) ^ (idx & 2) ^ ((idx >> 2) & 1)) * 32) + in_row;
+  }
+
+  // An earlier launch's slices, behind this launch's first loads: up to four rounds at once, in each of which either half of the
+  // workgroup takes a block of 16 float4 of that result; 16 thread groups take every 16th slice each, added in order.
+  float4* fold_red = reinterpret_cast<float4*>(smem + L.fold_off);
+  const int fold_blocks = a.prev_slices > 0 ? (a.prev_n4 + 15) / 16 : 0;
+
+  const int first_tile = narrow_xcd_consecutive(blockIdx.x, gridDim.x);
+  const int steps = L.KP / 32;
+  if (first_tile < L.tiles) fill_tile(first_tile, 0);
+  for (int r0 = blockIdx.x; 2 * r0 < fold_blocks; r0 += L.fold_rounds * gridDim.x) {   // the same for every thread
+    const int fgrp = (tid >> 4) & 15, fhalf = tid >> 8;
+    float4 sum[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) sum[f] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = fgrp; k0 < a.prev_slices; k0 += 64) {
+      float4 v[4][4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int i = (2 * (r0 + f * (int)gridDim.x) + fhalf) * 16 + (tid & 15), k = k0 + 16 * j;
+          v[f][j] = f < L.fold_rounds && i < a.prev_n4 && k < a.prev_slices
+                        ? reinterpret_cast<const float4*>(a.prev_partial)[(size_t)k * a.prev_stride4 + i]
+                        : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { sum[f].x += v[f][j].x; sum[f].y += v[f][j].y; sum[f].z += v[f][j].z; sum[f].w += v[f][j].w; }
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+      if (f < L.fold_rounds) fold_red[f * 512 + tid] = sum[f];
+    __syncthreads();
+    const int f = tid >> 5, half = (tid >> 4) & 1;
+    const int i = (2 * (r0 + f * (int)gridDim.x) + half) * 16 + (tid & 15);
+    if (f < L.fold_rounds && i < a.prev_n4) {
+      float4* dst = reinterpret_cast<float4*>(a.prev_dw) + i;
+      float4 t = a.prev_overwrite ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
+      for (int k = 0; k < 16; ++k) {
+        const float4 p = fold_red[f * 512 + half * 256 + k * 16 + (tid & 15)];
+        t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+      }
+      *dst = t;
+    }
+    __syncthreads();
+  }
+  int cur = 0;
+  for (int tile = first_tile; tile < L.tiles; tile += gridDim.x) {
+    if (L.buffers == 1 && tile != first_tile) {
+      __syncthreads();
+      fill_tile(tile, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();   // this tile has landed; every wave is done with the other buffer
+    if (L.buffers == 2 && tile + (int)gridDim.x < L.tiles) fill_tile(tile + gridDim.x, cur ^ 1);
+    const unsigned b0 = (unsigned)cur * buf_bytes;
+    NarrowFrag fa[2], rb[2][3];
+    // batch q of a step: input block q / 3 (q >= 3: the second), taps 3 (q % 3) .. + 2
+    auto read_a = [&](unsigned at) {
+      narrow_read_tr64(fa[0], at + aaddr);
+      narrow_read_tr64(fa[1], at + (aaddr ^ 32u));
+    };
+    auto read_b = [&](unsigned at, auto Q) {
+      constexpr int q = decltype(Q)::value;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) narrow_read_tr64(rb[q & 1][k], at + (xaddr[3 * (q % 3) + k] ^ (q >= 3 ? 32u : 0u)));
+    };
+    for (int st = wk; st < steps; st += 2) {
+      const unsigned at = b0 + (unsigned)st * 4096u;
+      // nothing is left in flight from one step to the next: the compiler takes the output of such a read as written at
+      // once and may copy what a loop carries
+      read_a(at);
+      read_b(at, std::integral_constant<int, 0>{});
+      bf16x8 A[2];
+      auto batch = [&](auto Q) {
+        constexpr int q = decltype(Q)::value;
+        if constexpr (q < 5) {
+          read_b(at, std::integral_constant<int, q + 1>{});
+          narrow_frags_landed_but<6>();
+        } else {
+          narrow_frags_landed();
+        }
+        if constexpr (q == 0) { A[0] = narrow_join(fa[0]); A[1] = narrow_join(fa[1]); }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const bf16x8 B = narrow_join(rb[q & 1][k]);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) acc[3 * (q % 3) + k][i][q / 3] = mfma16(A[i], B, acc[3 * (q % 3) + k][i][q / 3]);
+        }
+      };
+      batch(std::integral_constant<int, 0>{});
+      batch(std::integral_constant<int, 1>{});
+      batch(std::integral_constant<int, 2>{});
+      batch(std::integral_constant<int, 3>{});
+      batch(std::integral_constant<int, 4>{});
+      batch(std::integral_constant<int, 5>{});
+    }
+    if (L.buffers == 2) cur ^= 1;
+  }
+
+  // ---- the halves of the contraction: wk = 1 parks taps 0 .. 4, wk = 0 taps 5 .. 8, and each adds what it finds to the others ----
+  __syncthreads();
+  float4* park = reinterpret_cast<float4*>(smem) + (size_t)(wave & 3) * 36 * 64 + lane;
+  auto park_taps = [&](auto LO, auto HI) {
+#pragma unroll
+    for (int t = decltype(LO)::value; t < decltype(HI)::value; ++t)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const f32x4 v = acc[t][b >> 1][b & 1];
+        park[(t * 4 + b) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+      }
+  };
+  float* out = L.partial + (size_t)blockIdx.x * L.stride;
+  auto store_taps = [&](auto LO, auto HI) {
+#pragma unroll
+    for (int t = decltype(LO)::value; t < decltype(HI)::value; ++t)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const float4 p = park[(t * 4 + b) * 64];
+        const f32x4 v = acc[t][b >> 1][b & 1];
+        const float sum[4] = {v[0] + p.x, v[1] + p.y, v[2] + p.z, v[3] + p.w};
+        const int ci = wi * 32 + (b & 1) * 16 + i16;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) out[((size_t)(wc * 32 + (b >> 1) * 16 + 4 * g + k) * 9 + t) * 64 + ci] = sum[k];
+      }
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 5> I5;
+  typedef std::integral_constant<int, 9> I9;
+  if (wk) park_taps(I0{}, I5{}); else park_taps(I5{}, I9{});
+  __syncthreads();
+  if (wk) store_taps(I5{}, I9{}); else store_taps(I0{}, I5{});
+}
+
 // dw (+)= sum of the slices: a block owns 16 float4 of the result, 16 thread groups take every 16th slice each
 __global__ __launch_bounds__(256) void wgrad_slices_reduce_kernel(float4* __restrict__ dw, const float4* __restrict__ partial,
                                                                   int n4, int slices, size_t stride4, int overwrite) {
@@ -891,7 +1124,7 @@ __global__ __launch_bounds__(256) void wgrad_slices_reduce_kernel(float4* __rest
   }
 }
 
-struct NarrowWgradPlan { NarrowWgradLaunch L; int blocks; size_t lds; };
+struct NarrowWgradPlan { NarrowWgradLaunch L; int blocks; size_t lds; bool wide; };
 
 // tile height: about one tile per compute unit, within 96 KB of LDS; at most 256 workgroups (and slices)
 static bool wgrad_narrow_is_stem(const WgradArgs& a) { return a.Cx == 8 && a.Ci <= 8 && a.Co != a.Cx; }
@@ -902,6 +1135,31 @@ bool plan_wgrad_narrow(const WgradArgs& a, NarrowWgradPlan& P) {
   const int PW = a.Wi + 2, HP = a.Hi + 2;
   const long long rows_total = (long long)a.N * HP;
   if (rows_total * PW >= (1ll << 30)) return false;
+  P.wide = C == 64 && !wgrad_narrow_is_stem(a);
+  if (P.wide) {   // conv_wgrad_narrow64_kernel: two buffers, tiles of at least kWgrad64Positions positions where they fit
+    long long want = std::max((rows_total + 255) / 256, (long long)(kWgrad64Positions + PW - 1) / PW);
+    int R = (int)std::min(want, rows_total);
+    for (;; --R) {
+      const int KP = (R * PW + 31) / 32 * 32, xpos = KP + 2 * PW + 2;
+      const int xunits = (xpos * 8 + 63) / 64 * 64, dyunits = KP * 8;
+      const size_t one = (size_t)(xunits + dyunits) * 16;
+      // images too wide for two buffers of one row go through one; wider than that is another kernel's
+      P.L.buffers = 2 * one <= 152 * 1024 ? 2 : 1;
+      if (P.L.buffers == 1 && R > 1) continue;
+      const size_t both = P.L.buffers * one;
+      if (both > 152 * 1024 || HP > (1 << 19)) return false;
+      P.L.R = R; P.L.PW = PW; P.L.HP = HP; P.L.rows_total = (int)rows_total; P.L.KP = KP;
+      P.L.xunits = xunits; P.L.dyunits = dyunits;
+      P.L.magic_pw = ((1ull << 40) + PW - 1) / PW;
+      P.L.magic_hp = ((1ull << 40) + HP - 1) / HP;
+      P.L.tiles = (int)((rows_total + R - 1) / R);
+      P.blocks = P.L.tiles < 256 ? P.L.tiles : 256;
+      P.L.fold_off = (int)both;
+      P.L.fold_rounds = (int)std::min<size_t>(4, (160 * 1024 - both) / 8192);
+      P.lds = std::max((size_t)P.L.fold_off + 8192 * P.L.fold_rounds, (size_t)kWgrad64Exchange);
+      return true;
+    }
+  }
   int R = (int)((rows_total + 255) / 256);
   if (R < 1) R = 1;
   for (;; --R) {
@@ -1013,6 +1271,19 @@ static hipError_t run_wgrad_narrow(const WgradArgs& a, const NarrowWgradPlan& P,
   return hipGetLastError();
 }
 
+static hipError_t run_wgrad_narrow64(const WgradArgs& a, const NarrowWgradPlan& P, hipStream_t s) {
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_narrow64_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  note_kernel("conv_wgrad_narrow_kernel<64>");
+  hipLaunchKernelGGL(conv_wgrad_narrow64_kernel, dim3(P.blocks), dim3(512), P.lds, s, a, P.L);
+  return hipGetLastError();
+}
+
 hipError_t launch_conv_wgrad_narrow(const WgradArgs& a, hipStream_t s) {
   NarrowWgradPlan P;
   if (!conv_wgrad_narrow_applies(a) || !plan_wgrad_narrow(a, P)) return hipErrorInvalidValue;
@@ -1026,7 +1297,7 @@ hipError_t launch_conv_wgrad_narrow(const WgradArgs& a, hipStream_t s) {
   if (wgrad_narrow_is_stem(a))
     e = a.Co == 16 ? run_wgrad_narrow<16, true>(a, P, s) : (a.Co == 32 ? run_wgrad_narrow<32, true>(a, P, s) : run_wgrad_narrow<64, true>(a, P, s));
   else
-    e = a.Co == 16 ? run_wgrad_narrow<16, false>(a, P, s) : (a.Co == 32 ? run_wgrad_narrow<32, false>(a, P, s) : run_wgrad_narrow<64, false>(a, P, s));
+    e = a.Co == 16 ? run_wgrad_narrow<16, false>(a, P, s) : (a.Co == 32 ? run_wgrad_narrow<32, false>(a, P, s) : run_wgrad_narrow64(a, P, s));
   if (e != hipSuccess || a.defer_reduce) return e;
   return launch_wgrad_slices_reduce(a.dw, a.scratch, (int)(n / 4), P.blocks, n / 4, a.overwrite, s);
 }

@@ -79,3 +79,19 @@ def test_depthwise_edges(case):
 @pytest.mark.parametrize("case", [(70, 2, 2, 24, 15), (3, 1, 1, 8, 16), (65, 2, 2, 16, 17), (17, 1, 2, 40, 65), (5, 1, 1, 8, 1)])
 def test_head_edges(case):
     TK.test_head_kernels_one_by_one(case)
+
+
+# 64 -> 64 channel weight gradients: one tile per workgroup and one row, several tiles with a ragged last one (two buffers), an
+# image too wide for two buffers.  The kernel alone, to the bound of 32-bit sums: through a whole block a pre-activation that
+# two orders of a sum put on either side of zero moves a gradient of so few pixels by more than the kernel's own error.
+@pytest.mark.parametrize("case", [(3, 1, 7, 64, 64, 3, 1), (4, 9, 21, 64, 64, 3, 1), (23, 47, 50, 64, 64, 3, 1), (2, 3, 170, 64, 64, 3, 1)])
+def test_weight_gradient_of_64_channels(case):
+    TK.test_conv_wgrad(case)
+
+
+# The slices of one weight gradient are added up by the next, of the same and of another width
+@pytest.mark.parametrize("name", ["64 64", "32 64", "64 32"])
+def test_slices_of_an_earlier_weight_gradient(name):
+    first, second = (int(c) for c in name.split())
+    layers = [Layer(W.BASIC_POSTACT, first, first, 1), Layer(W.BASIC_POSTACT, first, second, 1), Layer(W.BASIC_POSTACT, second, second, 1)]
+    check(f"slices {name}", ModuleSpec(8, first, 21, 19, layers, delay=1, is_bottom=False, beta=0.5, name=f"slices {name}", **H))
