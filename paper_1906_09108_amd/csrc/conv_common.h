@@ -344,7 +344,7 @@ __device__ __forceinline__ void combine_and_store32(const GatherConvArgs& a, f32
     }
   __syncthreads();
   const int wave = wave_m * 2 + wk;
-  store_rows32<FN, BN, 10, 32, 4, F32S>(a, keep, m_tile + wave_m * 64 + wk * 32, c_tile, lane, smem + (size_t)wave * out_stage_bytes(BN),
+  store_rows32<FN, BN, BN == 96 ? 6 : 10, 32, 4, F32S>(a, keep, m_tile + wave_m * 64 + wk * 32, c_tile, lane, smem + (size_t)wave * out_stage_bytes(BN),
                        smem + (size_t)4 * out_stage_bytes(BN));
 }
 
@@ -391,6 +391,10 @@ __device__ __forceinline__ void combine8_and_store32(const GatherConvArgs& a, f3
 bool conv_gather_wide_applies(const GatherConvArgs& a);
 bool conv_gather_pair_applies(const GatherConvArgs& a);   // the two-workgroup form of the wide gather kernel runs it
 hipError_t launch_conv_gather_wide(const GatherConvArgs& a, hipStream_t s);
+// 1x1 layers on the same kernel that the wide form does not take: long contractions into 40 .. 96 channels, 72 .. 120 channels
+// into at least 128 (conv_wide_kernels.hip).  No gate, no bnx.
+bool conv_gather_thin_applies(const GatherConvArgs& a);
+hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s);
 // The wide-channel weight gradient: output and input channels multiples of 160, output width dividing 64.
 bool conv_wgrad_wide_applies(const WgradArgs& a);
 hipError_t launch_conv_wgrad_wide(const WgradArgs& a, hipStream_t s);

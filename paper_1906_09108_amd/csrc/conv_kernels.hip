@@ -175,6 +175,7 @@ hipError_t launch_conv_gather(const GatherConvArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   if (conv_gather_wide_applies(a)) return launch_conv_gather_wide(a, s);
   if (conv_narrow_applies(a)) return launch_conv_narrow(a, s);
+  if (conv_gather_thin_applies(a)) return launch_conv_gather_thin(a, s);
   if (a.gate || a.bnx) return hipErrorInvalidValue;   // the generic kernel is not asked for them (conv_dgrad_gates)
   if (a.Co <= 16) return run_gather<256, 16, 4, 1>(a, s);
   if (a.Co <= 32) return run_gather<256, 32, 4, 1>(a, s);
@@ -360,7 +361,11 @@ static void wgrad_plan(const WgradArgs& a, int& splits, int& chunks_per_split, i
   const int co_tiles = (a.Co + BM - 1) / BM, ci_tiles = (a.Ci + BN - 1) / BN;
   const int total_chunks = (Mtot + BK - 1) / BK;
   const int base = co_tiles * ci_tiles * a.ntaps;
-  splits = (1024 + base - 1) / base;
+  // 1x1 layers of the 128 x 128 form take one round of workgroups, two to a compute unit (64 KB of LDS): each part is written and
+  // read back (128 x 64 x 64, 64 -> 128, stride 2: 38 -> 27 us).  With nine taps the parts are a smaller share and shorter
+  // workgroups balance better (3x3 of that layer: 110 us, 126 with one round).
+  const int target = BN == 128 && a.ntaps == 1 ? 512 : 1024;
+  splits = (target + base - 1) / base;
   if (splits > total_chunks) splits = total_chunks;
   if (splits < 1) splits = 1;
   chunks_per_split = (total_chunks + splits - 1) / splits;

@@ -1230,6 +1230,44 @@ static hipError_t run_wide(const GatherConvArgs& a, hipStream_t s) {
   return a.Ci % 64 == 0 ? run_wide_k<BN, STAGES, false>(a, s) : run_wide_k<BN, STAGES, true>(a, s);
 }
 
+// 1x1 layers of inverted residual blocks.  The generic kernel holds one 32-channel chunk ahead and ends in 8-byte stores, so a
+// contraction over 384 channels was twelve waits for memory in a row; here whole 64-channel chunks arrive by direct loads, two
+// or three ahead, and the output leaves in rows.  128 x 16 x 16: 384 -> 64 28.5 -> 14.5 us,
+// 576 -> 96 55 -> 20, 96 -> 576 62 -> 43.
+bool conv_gather_thin_applies(const GatherConvArgs& a) {
+  if (a.nclass > 1 || a.ntaps != 1 || a.gate || a.bnx || a.stats_f32 || a.w_rows != a.Co || a.Kw % 8 != 0) return false;
+  if (a.Hi >= 32768 || a.Wi >= 32768 || (long long)a.N * a.OH * a.OW >= (1ll << 30)) return false;
+  const long long tiles = ((long long)a.N * a.OH * a.OW + 127) / 128;
+  if (a.Co >= 128) return a.Ci % 8 == 0 && a.Ci > 64 && a.Ci < 128 && tiles * ((a.Co + 127) / 128) >= 300;
+  return a.Ci % 64 == 0 && a.Ci >= 128 && a.Co >= 40 && a.Co <= 96 && tiles >= 128;   // fewer tiles: the generic kernel's 64-channel ones
+}
+
+template <int BN, int STAGES, bool KTAIL>
+static hipError_t run_thin(const GatherConvArgs& a, hipStream_t s) {
+  constexpr size_t lds = gather_dma_lds_bytes(BN, STAGES);
+  static_assert(lds <= 160 * 1024, "LDS of one compute unit");
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  static char name[64];
+  if (!name[0]) snprintf(name, sizeof(name), "conv_gather_dma_pair_kernel<%d, %d>", BN, STAGES);
+  note_kernel(name);
+  const int m_tiles = (a.N * a.OH * a.OW + 127) / 128, n_tiles = (a.Co + BN - 1) / BN;
+  hipLaunchKernelGGL((conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, false>), dim3(m_tiles * n_tiles), dim3(256), lds, s, a, m_tiles, n_tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s) {
+  if (!conv_gather_thin_applies(a) || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
+  if (a.Co >= 128) return run_thin<128, 2, true>(a, s);   // two workgroups to a compute unit: most of the time is output
+  if (a.Co <= 64) return run_thin<64, 3, false>(a, s);
+  return run_thin<96, 4, false>(a, s);
+}
+
 hipError_t launch_conv_gather_wide(const GatherConvArgs& a, hipStream_t s) {
   if (a.w_rows != a.Co) return hipErrorInvalidValue;   // weight rows past the last one are clamped, not zero
   if (a.nclass > 1) {   // the caller has checked conv_gather_wide_applies on the common fields

@@ -95,3 +95,16 @@ def test_slices_of_an_earlier_weight_gradient(name):
     first, second = (int(c) for c in name.split())
     layers = [Layer(W.BASIC_POSTACT, first, first, 1), Layer(W.BASIC_POSTACT, first, second, 1), Layer(W.BASIC_POSTACT, second, second, 1)]
     check(f"slices {name}", ModuleSpec(8, first, 21, 19, layers, delay=1, is_bottom=False, beta=0.5, name=f"slices {name}", **H))
+
+
+# 1x1 layers of few output channels behind a long contraction and of 72 .. 120 input channels: both ends of the ranges, a ragged
+# last tile of pixels, channel counts that fill no tile, stride 2
+THIN = [(9, 43, 43, 128, 40, 1, 1), (9, 43, 43, 192, 64, 1, 1), (9, 43, 43, 128, 72, 1, 1), (8, 46, 46, 384, 96, 1, 1), (33, 23, 23, 72, 152, 1, 1),
+        (21, 31, 31, 120, 264, 1, 1), (9, 85, 85, 128, 64, 1, 2), (9, 43, 43, 64, 128, 1, 1)]
+
+
+@pytest.mark.parametrize("case", THIN)
+def test_thin_1x1_layers(case):
+    TK.test_conv_fwd(case)
+    TK.test_conv_dgrad(case)
+    TK.test_conv_wgrad(case)
