@@ -129,10 +129,11 @@ __global__ __launch_bounds__(256) void maxpool3s2_bwd_kernel(const bf16_t* __res
 // Memory sets the floor (each tensor moved once), but a thread that made one output cell spent its time on the vector ALU:
 // four 64-bit divisions, and nine taps each unpacked for one use.  Here a thread makes 2 x 2 output cells of 8 channels from a
 // patch of (S + 3)^2 cells whose loads are all issued first; a cell is unpacked once for up to four outputs, the filter once
-// for the thread, and the image index comes from the block index.  128 x 16 x 16 x 384, stride 1: forward 25.8 -> 18.4 us
-// (50 MB, 2.7 TB/s), data gradient 39.7 -> 22.5 us.
+// for the thread, and the image index comes from the block index.  128 x 16 x 16 x 384, stride 1: forward 26.5 -> 17.3 us
+// (50 MB, 2.9 TB/s), data gradient 40.5 -> 17.4 us.
 // FLIP: the data gradient at unit stride, dx[h, w] = sum of dy[h + 1 - r, w + 1 - q] * w[r][q]: the same patch, its cells taken
-// from the last to the first.  Sums run over (r, q) in order either way.
+// from the last to the first.  Sums run over (r, q) in order either way.  A cell outside the image is left out, not multiplied as
+// a zero: an infinite weight or cell reaches the outputs it reaches in the definition and no others.
 template <int S, bool FLIP>
 __global__ __launch_bounds__(256) void dwconv3_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wt,
                                                       bf16_t* __restrict__ y, float* __restrict__ y_f32, int H, int W, int C, int Ho,
@@ -170,6 +171,8 @@ __global__ __launch_bounds__(256) void dwconv3_kernel(const bf16_t* __restrict__
 #pragma unroll
     for (int qq = 0; qq < P; ++qq) {
       const int pr = FLIP ? P - 1 - rr : rr, pq = FLIP ? P - 1 - qq : qq;
+      const int h = h0 + pr, w = w0 + pq;
+      if (h < 0 || h >= H || w < 0 || w >= W) continue;
       float f[8];
       unpack(raw[pr][pq], f);
 #pragma unroll
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(256) void dwconv3_kernel(const bf16_t* __restrict__
 
 // Data gradient at stride 2: dx[h, w] = sum over taps with h + 1 - r = 2 ho, w + 1 - q = 2 wo of dy[ho, wo] * w[r][q].  A thread
 // makes the cells (2a, 2b) .. (2a + 1, 2b + 1), which together take each of the nine taps once, from dy[a .. a + 1][b .. b + 1].
-// 128 x 32 x 32 x 192 from 16 x 16: 52.4 -> 21.9 us (63 MB, 2.9 TB/s).
+// 128 x 32 x 32 x 192 from 16 x 16: 52.2 -> 13.9 us (63 MB, 4.5 TB/s).
 __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ wt,
                                                              bf16_t* __restrict__ dx, float* __restrict__ dx_f32, int H, int W, int C,
                                                              int Ho, int Wo, int blocks_per_image) {
@@ -223,17 +226,23 @@ __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __res
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[a][b][j] = 0.f;
+  float k[9][8];
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int t = 0; t < 9; ++t) unpack(*reinterpret_cast<const uint4*>(wt + (size_t)t * C + cg * 8), k[t]);
+  // dy cell by dy cell, the last first: every sum then runs over (r, q) in order.  r = 1 reaches the even row from dy row a, r = 0
+  // and 2 the odd row from dy rows a + 1 and a; columns alike.  A cell outside dy is left out, not multiplied as a zero.
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      float k[8];
-      unpack(*reinterpret_cast<const uint4*>(wt + (size_t)(r * 3 + q) * C + cg * 8), k);
-      // r = 1 reaches the even row from dy row a, r = 0 and 2 the odd row from dy rows a + 1 and a; columns alike
-      const int a = r == 1 ? 0 : 1, b = q == 1 ? 0 : 1, ga = r == 0 ? 1 : 0, gb = q == 0 ? 1 : 0;
+  for (int cell = 3; cell >= 0; --cell) {
+    const int ga = cell >> 1, gb = cell & 1;
+    if (hb + ga >= Ho || wb + gb >= Wo) continue;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[a][b][j] += g[ga][gb][j] * k[j];
+    for (int t = 0; t < 9; ++t) {
+      const int r = t / 3, q = t % 3;
+      if ((r == 0 ? 1 : 0) != ga || (q == 0 ? 1 : 0) != gb) continue;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[r == 1 ? 0 : 1][q == 1 ? 0 : 1][j] += g[ga][gb][j] * k[t][j];
     }
+  }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -251,8 +260,9 @@ __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __res
 // with the three columns of x in registers, so that a step loads and unpacks one new column (two at stride 2) and one cell of
 // dy.  The 72 sums of a lane are added over the eight lanes of a wave that share its channels by halves (lanes exchange the
 // half they do not keep: 63 shuffles instead of 216, or of 9 rounds through LDS), over the four waves through LDS, and go to
-// part[by][tap][c]; second pass: dw[c][tap] = sum over chunks.  All orders are fixed.
-// 128 x 16 x 16 x 384, stride 1: 44.3 + 33.0 (second pass) -> 25.1 + 5.3 us.
+// part[by][tap][c]; second pass: dw[c][tap] = sum over chunks.  All orders are fixed.  Products with cells outside the image or
+// past the end of a row are left out, not added as zeros (an infinity on the other side would make them NaN).
+// 128 x 16 x 16 x 384, stride 1, both passes: 67.0 -> 17.1 us (50 MB); 128 x 32 x 32 x 192, stride 2: 69.1 -> 17.8 us.
 constexpr int kDwSegment = 8;
 template <int S>
 __global__ __launch_bounds__(256) void dwconv3_wgrad_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
@@ -282,32 +292,53 @@ __global__ __launch_bounds__(256) void dwconv3_wgrad_kernel(const bf16_t* __rest
         return v;
       };
       float f[3][3][8];   // [column][row]
+      uint4 first_columns[3 - S][3];
 #pragma unroll
       for (int q = 0; q < 3 - S; ++q)
 #pragma unroll
-        for (int r = 0; r < 3; ++r) unpack(cell(r, w_lo * S - 1 + q), f[q][r]);
+        for (int r = 0; r < 3; ++r) first_columns[q][r] = cell(r, w_lo * S - 1 + q);
+      // the loads of AHEAD steps before their sums: across the branches below the compiler moves none.  At unit stride a second
+      // step ahead costs the third wave of a SIMD (128 x 16 x 16 x 384: 17.1 -> 22.7 us)
+      constexpr int AHEAD = S;
+      uint4 gv[AHEAD], nv[AHEAD][S][3];
 #pragma unroll
       for (int i = 0; i < kDwSegment; ++i) {
-        const int wo = w_lo + i;
-        uint4 gv = make_uint4(0u, 0u, 0u, 0u);
-        if (wo < Wo) gv = *reinterpret_cast<const uint4*>(out + (size_t)i * C);
-        uint4 nv[S][3];
+        const int wo = w_lo + i, slot = i % AHEAD;
+        if (slot == 0) {
+          if (wo >= Wo) break;
 #pragma unroll
-        for (int q = 0; q < S; ++q)
+          for (int k = 0; k < AHEAD; ++k) {
+            gv[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (wo + k < Wo) gv[k] = *reinterpret_cast<const uint4*>(out + (size_t)(i + k) * C);
 #pragma unroll
-          for (int r = 0; r < 3; ++r) nv[q][r] = cell(r, wo * S + 2 - S + q);
+            for (int q = 0; q < S; ++q)
+#pragma unroll
+              for (int r = 0; r < 3; ++r) nv[k][q][r] = cell(r, (wo + k) * S + 2 - S + q);
+          }
+        }
+        if (i == 0) {
+#pragma unroll
+          for (int q = 0; q < 3 - S; ++q)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) unpack(first_columns[q][r], f[q][r]);
+        }
         float g[8];
-        unpack(gv, g);
+        unpack(gv[slot], g);
 #pragma unroll
         for (int q = 0; q < S; ++q)
 #pragma unroll
-          for (int r = 0; r < 3; ++r) unpack(nv[q][r], f[3 - S + q][r]);
+          for (int r = 0; r < 3; ++r) unpack(nv[slot][q][r], f[3 - S + q][r]);
 #pragma unroll
-        for (int r = 0; r < 3; ++r)
+        for (int q = 0; q < 3; ++q) {
+          const int w = wo * S - 1 + q;
+          if (wo >= Wo || w < 0 || w >= W) continue;
 #pragma unroll
-          for (int q = 0; q < 3; ++q)
+          for (int r = 0; r < 3; ++r) {
+            if (h0 + r < 0 || h0 + r >= H) continue;
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc[(r * 3 + q) * 8 + j] += g[j] * f[q][r][j];
+          }
+        }
 #pragma unroll
         for (int q = 0; q < 3 - S; ++q)
 #pragma unroll

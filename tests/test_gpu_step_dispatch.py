@@ -75,6 +75,40 @@ def test_depthwise_edges(case):
     TK.test_depthwise_convolution_kernels(case)
 
 
+# A tap outside the image is left out, not multiplied by zero: an infinite weight, activation or gradient reaches the results
+# that it reaches in the definition and no others
+@pytest.mark.parametrize("where", ["weights", "activations", "gradients"])
+@pytest.mark.parametrize("case", [(2, 5, 11, 72, 1), (2, 6, 9, 16, 2), (1, 8, 8, 16, 1), (2, 7, 18, 16, 2)])
+def test_infinities_at_the_border_of_a_depthwise_convolution(case, where):
+    import torch as t
+    from paper_1906_09108_amd import kernels as K
+    n, h, w, c, s = case
+    print("depthwise infinities", case, where, flush=True)
+    ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+    rng = np.random.default_rng(17)
+    x, wgt, dy = (TK.bf16_round(rng.standard_normal(sh).astype(np.float32)) for sh in ((n, c, h, w), (c, 1, 3, 3), (n, c, ho, wo)))
+    marked = {"weights": wgt, "activations": x, "gradients": dy}[where]
+    rows, cols = (sorted({0, z // 2, z - 1}) for z in marked.shape[2:])
+    for k, (i, j) in enumerate((i, j) for i in rows for j in cols):      # a corner, an edge or the middle in channel k of image 0
+        marked[0 if where != "weights" else k, k if where != "weights" else 0, i, j] = np.inf if k % 2 else -np.inf
+    xd, dyd = TK.to_dev_nhwc_b16(x), TK.to_dev_nhwc_b16(dy)
+    wt = t.from_numpy(np.ascontiguousarray(wgt.reshape(c, 9).T)).to(t.bfloat16).cuda()
+    y, dx = (t.empty(sh, dtype=t.bfloat16, device="cuda") for sh in ((n, ho, wo, c), (n, h, w, c)))
+    dw = t.empty((c, 9), device="cuda")
+    scratch = t.empty(K.fdgk_dwconv3_wgrad_scratch_bytes(n, h, w, c, s) // 4, device="cuda")
+    K.fdgk_dwconv3_fwd(xd, wt, y, n, h, w, c, s)
+    K.fdgk_dwconv3_dgrad(dyd, wt, dx, n, h, w, c, s)
+    K.fdgk_dwconv3_wgrad(xd, dyd, dw, scratch, n, h, w, c, s)
+    with np.errstate(invalid="ignore"):
+        pairs = {"forward": (TK.nhwc_to_nchw(y), TK.K32.dwconv_fwd(x, wgt, s, 1), TK.B16_TOL),
+                 "data gradient": (TK.nhwc_to_nchw(dx), TK.K32.dwconv_bwd_data(dy, wgt, x.shape, s, 1), TK.B16_TOL),
+                 "weight gradient": (dw.cpu().numpy().reshape(c, 1, 3, 3), TK.K32.dwconv_bwd_weight(x, dy, 3, s, 1), TK.F32_TOL)}
+    for name, (got, ref, tol) in pairs.items():
+        ok = np.isfinite(ref)
+        assert np.array_equal(np.where(ok, 0, got), np.where(ok, 0, ref), equal_nan=True), name
+        assert np.isfinite(got[ok]).all() and np.abs(got[ok] - ref[ok]).max() <= tol * np.abs(ref[ok]).max(), name
+
+
 # Classes on 16 lanes or a wave to a row, and 16 classes to a step of the gradient: at, below and above those counts
 @pytest.mark.parametrize("case", [(70, 2, 2, 24, 15), (3, 1, 1, 8, 16), (65, 2, 2, 16, 17), (17, 1, 2, 40, 65), (5, 1, 1, 8, 1)])
 def test_head_edges(case):
