@@ -4,6 +4,8 @@
 // HBM-bound.  Tensors are NHWC; a thread owns 8 consecutive channels of one pixel (one 16-byte bf16 access).
 #include "fdg_internal.h"
 
+#include <algorithm>
+
 namespace fdg {
 namespace {
 
@@ -392,14 +394,12 @@ __global__ __launch_bounds__(256) void dwconv3_wgrad_reduce_kernel(const float* 
   dw[(size_t)(i % C) * 9 + i / C] = s;
 }
 
-int dw_chunks(int N, int Ho, int Wo, int C) {
-  const size_t M = (size_t)N * Ho * Wo;
-  const int cblocks = (C / 8 + 7) / 8;
-  size_t chunks = (1024 + cblocks - 1) / cblocks;
-  const size_t most = (M + 255) / 256;            // at least 256 pixels per chunk
-  if (chunks > most) chunks = most;
-  return (int)(chunks < 1 ? 1 : chunks);
-}
+// Segments of the weight gradient's rows, and the chunks they are dealt to: one segment to a lane (32 to a workgroup) up to about
+// 1024 workgroups.  With less scratch the chunks are longer: any scratch for a chunk per 256 cells does.
+size_t dw_units(int N, int Ho, int Wo) { return (size_t)N * Ho * ((Wo + kDwSegment - 1) / kDwSegment); }
+size_t dw_most_chunks(int C) { const size_t cblocks = (C / 8 + 7) / 8; return (1024 + cblocks - 1) / cblocks; }
+size_t dw_chunks(int N, int Ho, int Wo, int C) { return std::min((dw_units(N, Ho, Wo) + 31) / 32, dw_most_chunks(C)); }
+size_t dw_least_chunks(int N, int Ho, int Wo, int C) { return std::min(((size_t)N * Ho * Wo + 255) / 256, dw_most_chunks(C)); }
 
 }  // namespace
 
@@ -461,19 +461,18 @@ hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, 
 size_t dwconv3_wgrad_scratch_bytes(int N, int H, int W, int C, int stride) {
   if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || C % 8 != 0 || (stride != 1 && stride != 2)) return 0;
   const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
-  return (size_t)dw_chunks(N, Ho, Wo, C) * 9 * C * sizeof(float);
+  return dw_chunks(N, Ho, Wo, C) * 9 * C * sizeof(float);
 }
 
 hipError_t launch_dwconv3_wgrad(const bf16_t* x, const bf16_t* dy, float* dw, float* scratch, size_t scratch_bytes, int N, int H, int W,
                                 int C, int stride, hipStream_t s) {
-  const size_t need = dwconv3_wgrad_scratch_bytes(N, H, W, C, stride);
-  if (!need || !scratch || scratch_bytes < need) return hipErrorInvalidValue;
+  if (!dwconv3_wgrad_scratch_bytes(N, H, W, C, stride) || !scratch) return hipErrorInvalidValue;
   const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
-  // as many chunks as give each lane a segment, within those the scratch is sized for
-  const size_t units = (size_t)N * Ho * ((Wo + kDwSegment - 1) / kDwSegment);
+  const size_t room = scratch_bytes / ((size_t)9 * C * sizeof(float));
+  if (room < dw_least_chunks(N, Ho, Wo, C)) return hipErrorInvalidValue;
+  const size_t units = dw_units(N, Ho, Wo);
   if (units >= ((size_t)1 << 32)) return hipErrorInvalidValue;
-  const size_t most = dw_chunks(N, Ho, Wo, C), want = (units + 31) / 32;
-  int chunks = (int)(want < most ? want : most);
+  int chunks = (int)std::min(dw_chunks(N, Ho, Wo, C), room);
   const int per = (int)((units + chunks - 1) / chunks);
   chunks = (int)((units + per - 1) / per);
   const dim3 grid((C / 8 + 7) / 8, chunks);

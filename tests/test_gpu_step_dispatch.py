@@ -75,6 +75,31 @@ def test_depthwise_edges(case):
     TK.test_depthwise_convolution_kernels(case)
 
 
+# The weight gradient's chunks: a segment to a lane with the scratch it asks for, longer ones with less (a chunk per 256 cells is
+# enough, less is refused); single-pixel images, rows a cell longer than a segment, more segments than chunks
+@pytest.mark.parametrize("case", [(1024, 1, 1, 64, 1), (40, 3, 9, 72, 1), (600, 2, 2, 16, 2), (64, 33, 33, 128, 1)])
+def test_depthwise_weight_gradient_at_scratch_limits(case):
+    import torch as t
+    from paper_1906_09108_amd import kernels as K
+    n, h, w, c, s = case
+    print("depthwise scratch", case, flush=True)
+    ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+    rng = np.random.default_rng(19)
+    x, dy = (TK.bf16_round(rng.standard_normal(sh).astype(np.float32)) for sh in ((n, c, h, w), (n, c, ho, wo)))
+    xd, dyd = TK.to_dev_nhwc_b16(x), TK.to_dev_nhwc_b16(dy)
+    ref = TK.K32.dwconv_bwd_weight(x, dy, 3, s, 1)
+    segments, groups = n * ho * -(-wo // 8), -(-c // 64)
+    full, least = (min(-(-1024 // groups), k) for k in (-(-segments // 32), -(-n * ho * wo // 256)))
+    assert K.fdgk_dwconv3_wgrad_scratch_bytes(n, h, w, c, s) == full * 36 * c
+    for chunks in sorted({full, (full + least) // 2, least}):
+        scratch = t.full((chunks * 9 * c,), float("nan"), device="cuda")
+        dw = t.full((c, 9), float("nan"), device="cuda")
+        K.fdgk_dwconv3_wgrad(xd, dyd, dw, scratch, n, h, w, c, s)
+        assert TK.rel(dw.cpu().numpy().reshape(c, 1, 3, 3), ref) <= TK.F32_TOL, chunks
+    with pytest.raises(RuntimeError):
+        K.fdgk_dwconv3_wgrad(xd, dyd, dw, t.empty(least * 9 * c - 1, device="cuda"), n, h, w, c, s)
+
+
 # A tap outside the image is left out, not multiplied by zero: an infinite weight, activation or gradient reaches the results
 # that it reaches in the definition and no others
 @pytest.mark.parametrize("where", ["weights", "activations", "gradients"])
