@@ -23,8 +23,8 @@ __host__ __device__ static inline int pack_tap(int dh, int dw, int kofs) { retur
 // total is kept EXACTLY, in 64-bit fixed point: the partial s is split into hi = rint(s * 2^11) and
 // lo = rint((s - hi * 2^-11) * 2^62) (exact for 2^-39 <= |s| < 2^39; smaller partials are rounded to 2^-62) and both
 // words are added with integer atomics.  Integer addition is associative, so the total does not depend on the order in
-// which workgroups arrive: two runs on the same input give the same bits, which no fp32 atomic sum does.  Up to 4096
-// partials fit.  A partial of 2^39 (5.5e11) or more -- a network that is blowing up -- goes to a third word, a double
+// which workgroups arrive: two runs on the same input give the same bits, which no fp32 atomic sum does.  Either word of a
+// partial is at most 2^50, so kStatMaxPartials = 2^13 - 1 of them fit (a module whose batch norms take more keeps copies).  A partial of 2^39 (5.5e11) or more -- a network that is blowing up -- goes to a third word, a double
 // added with a floating-point atomic: still a sum, no longer order independent.
 // A sums array for C channels is stat_t[3][2][C] (word, which of the two sums, channel), zero before the producers run;
 // value = big + hi * 2^-11 + lo * 2^-62.
@@ -32,6 +32,7 @@ __host__ __device__ static inline int pack_tap(int dh, int dw, int kofs) { retur
 // layers), so an array may exist in kStatReplicas copies, rep_stride stat_t elements apart: workgroup b adds into copy
 // b % kStatReplicas and whoever reads the sums adds the copies (integers again).  rep_stride = 0: a single copy.
 constexpr int kStatReplicas = 8;
+constexpr int kStatMaxPartials = (1 << 13) - 1;
 typedef long long stat_t;
 constexpr int kStatWords = 3;                                   // stat_t per sum: hi, lo, big (a double)
 inline size_t stat_elems(size_t channels) { return 2 * channels * kStatWords; }   // stat_t of a sums array

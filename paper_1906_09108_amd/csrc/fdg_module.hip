@@ -326,10 +326,14 @@ bool build_plan(const fdg_module_desc* desc, int save_mode, Plan& p, fdg_status*
   p.P = p.small_off + p.small_count;
   if (p.P >= (1ull << 31) || p.warena_elems >= (1ull << 32) || p.maxE >= (1ull << 31)) { *why = FDG_ERR_UNSUPPORTED; return false; }
   for (const ConvInfo& ci : p.convs) p.emit_blocks += emit_blocks_for(ci.sh.Co, ci.sh.Cip, ci.sh.T);
-  // copies only for the narrow 3x3 kernels: the 1x1 layers that feed the next one (conv_dgrad_feeds_next holds for them too)
-  // have at most a few hundred workgroups per channel, and every reader of a sums array pays for its copies
-  for (const ConvInfo& ci : p.convs)
-    if (!ci.depthwise && ci.sh.T == 9 && conv_dgrad_feeds_next(ci.sh)) p.stat_rep = (int)(p.stat_floats * kStatWords);
+  // Copies of the sums for the narrow 3x3 kernels, whose launches are shorter than their atomics on one cache line, and where a
+  // batch norm takes more partials than one array holds: a workgroup per 128 pixels or more (in up to four parity classes) adds
+  // one.  Not for the 1x1 layers that feed the next one (conv_dgrad_feeds_next holds for them too): every reader of a sums array
+  // pays for its copies (bottleneck module of 256 channels at 56 x 56, batch 128, 3136 workgroups: 5134 us with, 4134 without).
+  bool copies = false;
+  for (const ConvInfo& ci : p.convs) copies = copies || (!ci.depthwise && ci.sh.T == 9 && conv_dgrad_feeds_next(ci.sh));
+  for (const BnInfo& b : p.bns) copies = copies || (b.M + 127) / 128 + 4 > kStatMaxPartials;
+  if (copies) p.stat_rep = (int)(p.stat_floats * kStatWords);
   const size_t stat_copies = p.stat_rep ? kStatReplicas : 1;
   // workspace layout
   size_t o = 0;

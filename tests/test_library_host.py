@@ -133,6 +133,20 @@ def test_learning_rate_schedule_of_section_5a():
 
 
 
+def test_sums_have_copies_where_one_array_does_not_hold_the_partials():
+    """An exact sum holds 2^13 - 1 partials (either word of one is at most 2^50 of a 64-bit integer) and a convolution adds one
+    per 128 pixels: a module whose batch norms see more than that keeps eight copies of its sums, one without narrow 3x3 layers
+    and with fewer pixels a single one.  Every other part of a workspace grows by the same bytes per image here."""
+    def ws(n):
+        return binding.fdg_module_workspace_bytes(ModuleSpec(n, 512, 64, 64, [Layer(W.BOTTLENECK_POSTACT, 512, 512, 1)] * 2, delay=1))
+    assert (255 * 64 * 64) // 128 + 4 <= 2 ** 13 - 1 < (256 * 64 * 64) // 128 + 4
+    image = ws(255) - ws(254)
+    assert image > 0 and ws(254) - ws(253) == image and ws(257) - ws(256) == image
+    channels = 2 * (128 + 128 + 512)                       # of the module's batch norms
+    one = 2 * channels * 3 * 8                          # two sums of three 64-bit words
+    assert ws(256) - ws(255) - image == 7 * one * (1 + 2)      # the backward's array and one in each of two slots
+
+
 def test_build_refuses_scratch_in_kernels_with_hand_counted_waits():
     """The build reads the compiler's resource-usage remarks and fails when a kernel whose vmcnt waits are counted by hand
     uses scratch memory beyond what is listed for it (a spill or a table moved to memory inside the counted loop adds loads
