@@ -208,13 +208,15 @@ __device__ __forceinline__ void transpose8x8(const uint4 (&r)[8], uint4 (&o)[8])
 
 struct WgradLaunch {
   int chunks_per_split;
+  int second_sum;        // 1x1 form: chunks of a split after which its second sum begins
   int ci_tiles;
   float* partial;        // when set: pixel split z, contraction part wk store their block at partial + (z * WK + wk) * split_stride
   size_t split_stride;   // (plain stores: a second kernel adds the parts in a fixed order); else fp32 atomics into dw
 };
 
-template <int BM, int BN, int WM, int WN, int WK>
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(WgradArgs a, WgradLaunch L) {
+// TWO: a split is summed in two halves, added at its end (see wgrad_plan)
+template <int BM, int BN, int WM, int WN, int WK, bool TWO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_wgrad_kernel(WgradArgs a, WgradLaunch L) {
   static_assert(WM * WN * WK == 4, "four waves");
   constexpr int KSTEPS = WK == 1 ? 2 : 1;
   constexpr int BK = 32 * WK * KSTEPS;
@@ -251,15 +253,9 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgradArgs a, WgradLaunc
   const int chan = (isA ? co0 : ci0) + cg * 8;
   const bool chan_ok = isA ? chan < a.Co : (isB && chan < a.Cx);
 
-  f32x4 acc[FA][FB];
-#pragma unroll
-  for (int i = 0; i < FA; ++i)
-#pragma unroll
-    for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
   uint4 r[8];
   const uint4 zero4 = make_uint4(0, 0, 0, 0);
-  auto load_global = [&](int chunk) {
+  auto load_global = [&](int chunk) __attribute__((always_inline)) {
     const int mb = chunk * BK + pg * 8;
     if (isA) {
 #pragma unroll
@@ -290,7 +286,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgradArgs a, WgradLaunc
       }
     }
   };
-  auto store_lds = [&](int buf) {
+  auto store_lds = [&](int buf) __attribute__((always_inline)) {
     if (!(isA || isB)) return;
     uint4 o[8];
     transpose8x8(r, o);
@@ -304,33 +300,50 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgradArgs a, WgradLaunc
     store_lds(0);
   }
   __syncthreads();
-  for (int ch = chunk_lo; ch < chunk_hi; ++ch) {
-    const int buf = (ch - chunk_lo) & 1;
-    const bool more = ch + 1 < chunk_hi;
-    if (more) load_global(ch + 1);
+  auto contract = [&](int lo, int hi, f32x4 (&acc)[FA][FB]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      const int unit = (WK == 1 ? ks : wk) * 4 + (lane >> 4);
-      bf16x8 fa[FA], fb[FB];
+    for (int i = 0; i < FA; ++i)
 #pragma unroll
-      for (int f = 0; f < FA; ++f)
-        {
+      for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ch = lo; ch < hi; ++ch) {
+      const int buf = (ch - chunk_lo) & 1;
+      const bool more = ch + 1 < chunk_hi;
+      if (more) load_global(ch + 1);
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        const int unit = (WK == 1 ? ks : wk) * 4 + (lane >> 4);
+        bf16x8 fa[FA], fb[FB];
+#pragma unroll
+        for (int f = 0; f < FA; ++f) {
           const int row = wm * TM + f * 16 + (lane & 15);
           fa[f] = *reinterpret_cast<const bf16x8*>(&sA[buf][row * PITCH + (unit ^ swz(row)) * 8]);
         }
 #pragma unroll
-      for (int f = 0; f < FB; ++f)
-        {
+        for (int f = 0; f < FB; ++f) {
           const int row = wn * TN + f * 16 + (lane & 15);
           fb[f] = *reinterpret_cast<const bf16x8*>(&sB[buf][row * PITCH + (unit ^ swz(row)) * 8]);
         }
 #pragma unroll
-      for (int i = 0; i < FA; ++i)
+        for (int i = 0; i < FA; ++i)
 #pragma unroll
-        for (int j = 0; j < FB; ++j) acc[i][j] = mfma16(fa[i], fb[j], acc[i][j]);
+          for (int j = 0; j < FB; ++j) acc[i][j] = mfma16(fa[i], fb[j], acc[i][j]);
+      }
+      if (more) store_lds(buf ^ 1);
+      __syncthreads();
     }
-    if (more) store_lds(buf ^ 1);
-    __syncthreads();
+  };
+  f32x4 acc[FA][FB];
+  if constexpr (TWO) {
+    f32x4 first[FA][FB];
+    const int mid = min(chunk_hi, chunk_lo + L.second_sum);
+    contract(chunk_lo, mid, first);
+    contract(mid, chunk_hi, acc);
+#pragma unroll
+    for (int i = 0; i < FA; ++i)
+#pragma unroll
+      for (int j = 0; j < FB; ++j) acc[i][j] += first[i][j];
+  } else {
+    contract(chunk_lo, chunk_hi, acc);
   }
 
   // D[co][ci]: lane holds co = 4*(lane>>4)+v, ci = lane&15
@@ -363,7 +376,8 @@ static void wgrad_plan(const WgradArgs& a, int& splits, int& chunks_per_split, i
   const int base = co_tiles * ci_tiles * a.ntaps;
   // 1x1 layers of the 128 x 128 form take one round of workgroups, two to a compute unit (64 KB of LDS): each part is written and
   // read back (128 x 64 x 64, 64 -> 128, stride 2: 38 -> 27 us).  With nine taps the parts are a smaller share and shorter
-  // workgroups balance better (3x3 of that layer: 110 us, 126 with one round).
+  // workgroups balance better (3x3 of that layer: 110 us, 126 with one round).  A workgroup of the single round sums its pixels in
+  // two halves, so that no sum runs over more of them than with two rounds.
   const int target = BN == 128 && a.ntaps == 1 ? 512 : 1024;
   splits = (target + base - 1) / base;
   if (splits > total_chunks) splits = total_chunks;
@@ -380,6 +394,7 @@ static hipError_t run_wgrad(const WgradArgs& a, hipStream_t s) {
   int splits, parts;
   WgradLaunch L;
   wgrad_plan<BM, BN, WK>(a, splits, L.chunks_per_split, parts);
+  L.second_sum = (L.chunks_per_split + 1) / 2;
   L.ci_tiles = ci_tiles;
   const size_t elems = (size_t)a.Co * a.ntaps * a.Ci;
   // with scratch memory every part stores its block and a second kernel adds the parts in a fixed order (the result is
@@ -395,7 +410,9 @@ static hipError_t run_wgrad(const WgradArgs& a, hipStream_t s) {
   static char name[64];
   if (!name[0]) snprintf(name, sizeof(name), "conv_wgrad_kernel<%d, %d, %d, %d, %d>", BM, BN, WM, WN, WK);
   note_kernel(name);
-  hipLaunchKernelGGL((conv_wgrad_kernel<BM, BN, WM, WN, WK>), grid, dim3(256), 0, s, a, L);
+  constexpr bool CAN = BM == 128 && BN == 128;   // the form whose 1x1 layers take one round
+  if (CAN && a.ntaps == 1) hipLaunchKernelGGL((conv_wgrad_kernel<BM, BN, WM, WN, WK, CAN>), grid, dim3(256), 0, s, a, L);
+  else hipLaunchKernelGGL((conv_wgrad_kernel<BM, BN, WM, WN, WK, false>), grid, dim3(256), 0, s, a, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !stored) return e;
   return launch_wgrad_reduce(a.dw, a.scratch, elems, parts, a.overwrite, s);

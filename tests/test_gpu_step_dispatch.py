@@ -167,3 +167,24 @@ def test_thin_1x1_layers(case):
     TK.test_conv_fwd(case)
     TK.test_conv_dgrad(case)
     TK.test_conv_wgrad(case)
+
+
+# One round of workgroups means longer sums: the 1x1 weight gradient against 64 bits on long lists of pixels.  The error of fp32
+# sums grows with the pixels of one sum; with 1024 workgroups, one sum each, it is 1.42e-7, 1.53e-7 and 1.79e-7 here, with 512
+# it was 1.59e-7, 1.78e-7 and 2.10e-7.  Bounds: 4 % above the former.
+@pytest.mark.parametrize("case", [(131072, 384, 64, 1.48e-7), (134912, 448, 64, 1.59e-7), (401408, 72, 136, 1.86e-7)])
+def test_weight_gradient_of_1x1_layers_against_64_bits(case):
+    import torch as t
+    from paper_1906_09108_amd import kernels as K
+    pixels, ci, co, bound = case
+    g = t.Generator(device="cuda")
+    g.manual_seed(3)
+    x = t.randn(pixels, ci, generator=g, device="cuda").relu().bfloat16()
+    dy = t.randn(pixels, co, generator=g, device="cuda").bfloat16()
+    scratch = t.empty(K.fdgk_conv_wgrad_scratch_bytes(1, pixels, 1, ci, co, 1, 1) // 4, device="cuda")
+    dw = t.empty(co, ci, device="cuda")
+    K.fdgk_conv_wgrad(x, dy, dw, scratch, 1, pixels, 1, ci, co, 1, 1, overwrite=True)
+    ref = dy.cpu().double().T @ x.cpu().double()
+    err = float((dw.cpu().double() - ref).norm() / ref.norm())
+    print(f"1x1 weight gradient {case}: {err:.3e}", flush=True)
+    assert err <= bound
