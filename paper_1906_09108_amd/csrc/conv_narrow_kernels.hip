@@ -669,6 +669,7 @@ hipError_t run_narrow_tr_c(const GatherConvArgs& a, hipStream_t s) {
 struct NarrowWgradLaunch {
   int R;            // padded rows per tile
   int tiles;        // tiles in all; workgroup b takes tiles b, b + gridDim.x, ...
+  int workers;      // 64 channels: workgroups that take tiles and write a slice; the others only add up earlier slices
   int PW, HP;       // padded row length W + 2 and padded image height H + 2
   int rows_total;   // N * HP
   int KP;           // positions a workgroup contracts over: R * PW rounded up to 32
@@ -877,10 +878,14 @@ __global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(WgradArgs a, Nar
 //     step, 20 fragments for 36 instructions; a batch of 3 fragments is read during the instructions of the batch before it
 //     (ds reads return in order, so "at most the younger batch outstanding" is a counted wait);
 //   * two tile buffers: the next tile loads while the present one is contracted;
-//   * no more workgroups than give each about kWgrad64Positions positions, because each writes (and a later launch reads) a slice.
+//   * no more workgroups than give each about kWgrad64Positions positions, because each writes (and a later launch reads) a slice;
+//     about kWgrad64Least of them where that would be fewer.  Alone, workgroups of 192 positions / 8 of them: 2 x 8 x 8 14.4 /
+//     12.2 us, 8 x 8 x 8 14.6 / 13.4; 64 x 8 x 8 16.8 with 192 positions, 19.7 with 64;
+//   * enough workgroups to add up the earlier slices in one round, whatever the tiles.  Where that was left to the workgroups that
+//     have tiles, a step of two basic blocks at 8 x 8 took 476 us for one image and 280 for 8, now 196 and 204.
 // The halves wk are added through LDS, either wave of a pair finishing a part of the taps.
 // Alone, 128 x 64 x 64: 137.6 -> 68.2 us; with its own reduction launch, 128 x 8 x 8: 29.4 -> 21.7 us.
-constexpr int kWgrad64Positions = 192;
+constexpr int kWgrad64Positions = 192, kWgrad64Least = 8;
 constexpr int kWgrad64Exchange = 4 * 9 * 4 * 1024;   // bytes: four pairs of waves, nine taps, four blocks
 template <int YOUNGER>
 __device__ __forceinline__ void narrow_frags_landed_but() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(YOUNGER) : "memory"); }
@@ -970,9 +975,10 @@ __global__ __launch_bounds__(512) void conv_wgrad_narrow64_kernel(WgradArgs a, N
   float4* fold_red = reinterpret_cast<float4*>(smem + L.fold_off);
   const int fold_blocks = a.prev_slices > 0 ? (a.prev_n4 + 15) / 16 : 0;
 
-  const int first_tile = narrow_xcd_consecutive(blockIdx.x, gridDim.x);
+  const bool works = (int)blockIdx.x < L.workers;
+  const int first_tile = works ? narrow_xcd_consecutive(blockIdx.x, L.workers) : 0;
   const int steps = L.KP / 32;
-  if (first_tile < L.tiles) fill_tile(first_tile, 0);
+  if (works) fill_tile(first_tile, 0);
   for (int r0 = blockIdx.x; 2 * r0 < fold_blocks; r0 += L.fold_rounds * gridDim.x) {   // the same for every thread
     const int fgrp = (tid >> 4) & 15, fhalf = tid >> 8;
     float4 sum[4];
@@ -1011,15 +1017,16 @@ __global__ __launch_bounds__(512) void conv_wgrad_narrow64_kernel(WgradArgs a, N
     }
     __syncthreads();
   }
+  if (!works) return;
   int cur = 0;
-  for (int tile = first_tile; tile < L.tiles; tile += gridDim.x) {
+  for (int tile = first_tile; tile < L.tiles; tile += L.workers) {
     if (L.buffers == 1 && tile != first_tile) {
       __syncthreads();
       fill_tile(tile, 0);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();   // this tile has landed; every wave is done with the other buffer
-    if (L.buffers == 2 && tile + (int)gridDim.x < L.tiles) fill_tile(tile + gridDim.x, cur ^ 1);
+    if (L.buffers == 2 && tile + L.workers < L.tiles) fill_tile(tile + L.workers, cur ^ 1);
     const unsigned b0 = (unsigned)cur * buf_bytes;
     NarrowFrag fa[2], rb[2][3];
     // batch q of a step: input block q / 3 (q >= 3: the second), taps 3 (q % 3) .. + 2
@@ -1137,7 +1144,8 @@ bool plan_wgrad_narrow(const WgradArgs& a, NarrowWgradPlan& P) {
   if (rows_total * PW >= (1ll << 30)) return false;
   P.wide = C == 64 && !wgrad_narrow_is_stem(a);
   if (P.wide) {   // conv_wgrad_narrow64_kernel: two buffers, tiles of at least kWgrad64Positions positions where they fit
-    long long want = std::max((rows_total + 255) / 256, (long long)(kWgrad64Positions + PW - 1) / PW);
+    const long long positions = std::min<long long>(kWgrad64Positions, rows_total * PW / kWgrad64Least);
+    const long long want = std::max((rows_total + 255) / 256, std::max<long long>(1, positions / PW));
     int R = (int)std::min(want, rows_total);
     for (;; --R) {
       const int KP = (R * PW + 31) / 32 * 32, xpos = KP + 2 * PW + 2;
@@ -1280,7 +1288,11 @@ static hipError_t run_wgrad_narrow64(const WgradArgs& a, const NarrowWgradPlan& 
     configured = true;
   }
   note_kernel("conv_wgrad_narrow_kernel<64>");
-  hipLaunchKernelGGL(conv_wgrad_narrow64_kernel, dim3(P.blocks), dim3(512), P.lds, s, a, P.L);
+  NarrowWgradLaunch L = P.L;
+  L.workers = P.blocks;
+  const int per_group = 32 * L.fold_rounds;   // float4 of an earlier result that a workgroup adds up in one round
+  const int folders = a.prev_slices > 0 ? (a.prev_n4 + per_group - 1) / per_group : 0;
+  hipLaunchKernelGGL(conv_wgrad_narrow64_kernel, dim3(std::max(L.workers, folders)), dim3(512), P.lds, s, a, L);
   return hipGetLastError();
 }
 

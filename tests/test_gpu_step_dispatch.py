@@ -148,12 +148,14 @@ def test_weight_gradient_of_64_channels(case):
     TK.test_conv_wgrad(case)
 
 
-# The slices of one weight gradient are added up by the next, of the same and of another width
+# The slices of one weight gradient are added up by the next, of the same and of another width; with a few images and, where the
+# next has fewer tiles than it takes workgroups to add them up, with one
+@pytest.mark.parametrize("n,h,w", [(8, 21, 19), (1, 12, 11)])
 @pytest.mark.parametrize("name", ["64 64", "32 64", "64 32"])
-def test_slices_of_an_earlier_weight_gradient(name):
+def test_slices_of_an_earlier_weight_gradient(name, n, h, w):
     first, second = (int(c) for c in name.split())
     layers = [Layer(W.BASIC_POSTACT, first, first, 1), Layer(W.BASIC_POSTACT, first, second, 1), Layer(W.BASIC_POSTACT, second, second, 1)]
-    check(f"slices {name}", ModuleSpec(8, first, 21, 19, layers, delay=1, is_bottom=False, beta=0.5, name=f"slices {name}", **H))
+    check(f"slices {name} n{n}", ModuleSpec(n, first, h, w, layers, delay=1, is_bottom=False, beta=0.5, name=f"slices {name}", **H))
 
 
 # 1x1 layers of few output channels behind a long contraction and of 72 .. 120 input channels: both ends of the ranges, a ragged
