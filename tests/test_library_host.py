@@ -162,3 +162,22 @@ x.hip:20:1: remark:     ScratchSize [bytes/lane]: 16 [-Rpass-analysis=kernel-res
 """
     bad = scratch_users(sample, NO_SCRATCH["conv_wide_kernels.hip"])
     assert bad == [("_ZN3fdg23conv_gather_pipe_kernelILi160ELi4ELb0EEEvNS_14GatherConvArgsEii", 64)]
+
+
+def test_the_scratch_check_sees_every_kernel_with_hand_counted_waits():
+    """Kernels that are no template and kernels in an unnamed namespace are matched too; every source that waits for a counted
+    number of outstanding loads is looked at, and a listed kernel that the remarks do not mention is reported."""
+    from paper_1906_09108_amd import build
+    sample = """x.hip:1:1: remark: Function Name: _ZN3fdg12_GLOBAL__N_126conv_wgrad_narrow64_kernelENS_9WgradArgsENS0_17NarrowWgradLaunchE [-Rpass-analysis=kernel-resource-usage]
+x.hip:1:1: remark:     ScratchSize [bytes/lane]: 8 [-Rpass-analysis=kernel-resource-usage]
+x.hip:9:1: remark: Function Name: _ZN3fdg12_GLOBAL__N_124conv_wgrad_narrow_kernelILi16ELb0EEEvNS_9WgradArgsENS0_17NarrowWgradLaunchE [-Rpass-analysis=kernel-resource-usage]
+x.hip:9:1: remark:     ScratchSize [bytes/lane]: 0 [-Rpass-analysis=kernel-resource-usage]
+"""
+    listed = build.NO_SCRATCH["conv_narrow_kernels.hip"]
+    assert build.scratch_users(sample, listed) == [("_ZN3fdg12_GLOBAL__N_126conv_wgrad_narrow64_kernelENS_9WgradArgsENS0_17NarrowWgradLaunchE", 8)]
+    assert build.unchecked(sample, listed) == [] and build.unchecked(sample, {"conv_patch_kernel": 0}) == ["conv_patch_kernel"]
+    for src in build.SOURCES:   # vmcnt / lgkmcnt with a number of its own, other than 0, or as an operand
+        text = open(os.path.join(build.CSRC, src)).read()
+        assert not re.search(r"s_waitcnt (?:vmcnt|lgkmcnt)\((?!0\))", text) or src in build.NO_SCRATCH, src
+    kernels = {n for names in build.NO_SCRATCH.values() for n in names}
+    assert {"conv_wgrad_narrow64_kernel", "conv_gather_dma_pair_kernel"} <= kernels
