@@ -41,6 +41,9 @@ extern "C" {
  *   y_f32 / y_b16 optional outputs (at least one);  stats_sums optional sums array of co channels, zero it first:
  *   first sum += sum of bf16(y[..,o]), second sum += sum of bf16(y[..,o])^2 over all pixels -- the
  *   batch-norm statistics of the tensor just written, taken in the epilogue instead of a second pass. */
+/* Name of the convolution kernel that the calling thread's last convolution call launched, as a profiler prints it ("" before
+ * the first): which of the kernels for a shape ran.  A string that is never freed. */
+const char* fdgk_last_kernel(void);
 size_t fdgk_sums_bytes(int c);
 int fdgk_sums_read(const void* sums, int c, double* host_out, void* hip_stream);
 int fdgk_conv_fwd(const void* x_b16, const void* w_b16, const float* addend_f32, float* y_f32, void* y_b16,

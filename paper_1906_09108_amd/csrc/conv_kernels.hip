@@ -409,7 +409,7 @@ static hipError_t run_wgrad(const WgradArgs& a, hipStream_t s) {
   dim3 grid(co_tiles, ci_tiles * a.ntaps, splits);
   static char name[64];
   if (!name[0]) snprintf(name, sizeof(name), "conv_wgrad_kernel<%d, %d, %d, %d, %d>", BM, BN, WM, WN, WK);
-  note_kernel(name);
+  note_kernel(BM == 128 && BN == 128 && a.ntaps == 1 ? "conv_wgrad_kernel<128, 128, two sums>" : name);
   constexpr bool CAN = BM == 128 && BN == 128;   // the form whose 1x1 layers take one round
   if (CAN && a.ntaps == 1) hipLaunchKernelGGL((conv_wgrad_kernel<BM, BN, WM, WN, WK, CAN>), grid, dim3(256), 0, s, a, L);
   else hipLaunchKernelGGL((conv_wgrad_kernel<BM, BN, WM, WN, WK, false>), grid, dim3(256), 0, s, a, L);

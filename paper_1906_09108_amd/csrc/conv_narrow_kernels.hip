@@ -1287,7 +1287,7 @@ static hipError_t run_wgrad_narrow64(const WgradArgs& a, const NarrowWgradPlan& 
     if (e != hipSuccess) return e;
     configured = true;
   }
-  note_kernel("conv_wgrad_narrow_kernel<64>");
+  note_kernel("conv_wgrad_narrow64_kernel");
   NarrowWgradLaunch L = P.L;
   L.workers = P.blocks;
   const int per_group = 32 * L.fold_rounds;   // float4 of an earlier result that a workgroup adds up in one round

@@ -170,6 +170,8 @@ int fdgk_conv_wgrad(const void* x_b16, const void* dy_b16, float* dw_f32, float*
                          scratch_bytes, overwrite != 0, st(hip_stream));
 }
 
+const char* fdgk_last_kernel(void) { return last_kernel(); }
+
 size_t fdgk_sums_bytes(int c) { return c > 0 ? stat_elems((size_t)c) * sizeof(stat_t) : 0; }
 
 int fdgk_sums_read(const void* sums, int c, double* host_out, void* hip_stream) {

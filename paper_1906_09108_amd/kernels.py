@@ -10,7 +10,7 @@ KERNEL_EXPORTS = ["fdgk_conv_fwd", "fdgk_conv_fwd_bn_applies", "fdgk_conv_fwd_bn
                   "fdgk_bn_bwd", "fdgk_sgd", "fdgk_bn_bwd_static", "fdgk_bn_bwd_static_max_c", "fdgk_sums_bytes", "fdgk_sums_read",
                   "fdgk_avgpool", "fdgk_fc_fwd", "fdgk_softmax_ce", "fdgk_fc_bwd", "fdgk_pool_bwd", "fdgk_nchw_to_nhwc", "fdgk_nhwc_to_nchw",
                   "fdgk_im2col7", "fdgk_maxpool3s2", "fdgk_maxpool3s2_bwd", "fdgk_dwconv3_fwd", "fdgk_dwconv3_dgrad",
-                  "fdgk_dwconv3_wgrad_scratch_bytes", "fdgk_dwconv3_wgrad"]
+                  "fdgk_dwconv3_wgrad_scratch_bytes", "fdgk_dwconv3_wgrad", "fdgk_last_kernel"]
 _ready = False
 
 
@@ -55,12 +55,14 @@ def _lib():
         lib.fdgk_dwconv3_dgrad.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_wgrad_scratch_bytes.argtypes = [i, i, i, i, i]
         lib.fdgk_dwconv3_wgrad.argtypes = [vp, vp, vp, vp, sz, i, i, i, i, i, vp]
+        lib.fdgk_last_kernel.argtypes = []
         for n in KERNEL_EXPORTS:
             if getattr(lib, n).argtypes is None:   # a pointer passed without a declared type would be cut to 32 bits
                 raise RuntimeError(f"{n}: argument types not declared")
             getattr(lib, n).restype = i
         lib.fdgk_conv_wgrad_scratch_bytes.restype = sz
         lib.fdgk_sums_bytes.restype = sz
+        lib.fdgk_last_kernel.restype = ctypes.c_char_p
         lib.fdgk_dwconv3_wgrad_scratch_bytes.restype = sz
         _ready = True
     return lib
@@ -69,6 +71,10 @@ def _lib():
 def _ok(rc: int, name: str) -> None:
     if rc != 0:
         raise RuntimeError(f"{name} failed with hipError_t {rc}")
+
+
+def fdgk_last_kernel() -> str:
+    return _lib().fdgk_last_kernel().decode()
 
 
 def fdgk_sums_bytes(c: int) -> int:

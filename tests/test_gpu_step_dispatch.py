@@ -145,7 +145,9 @@ def test_head_edges(case):
 # two orders of a sum put on either side of zero moves a gradient of so few pixels by more than the kernel's own error.
 @pytest.mark.parametrize("case", [(3, 1, 7, 64, 64, 3, 1), (4, 9, 21, 64, 64, 3, 1), (23, 47, 50, 64, 64, 3, 1), (2, 3, 170, 64, 64, 3, 1)])
 def test_weight_gradient_of_64_channels(case):
+    from paper_1906_09108_amd import kernels as K
     TK.test_conv_wgrad(case)
+    assert K.fdgk_last_kernel() == "conv_wgrad_narrow64_kernel"
 
 
 # The slices of one weight gradient are added up by the next, of the same and of another width; with a few images and, where the
@@ -189,4 +191,5 @@ def test_weight_gradient_of_1x1_layers_against_64_bits(case):
     ref = dy.cpu().double().T @ x.cpu().double()
     err = float((dw.cpu().double() - ref).norm() / ref.norm())
     print(f"1x1 weight gradient {case}: {err:.3e}", flush=True)
+    assert K.fdgk_last_kernel() == "conv_wgrad_kernel<128, 128, two sums>"
     assert err <= bound
