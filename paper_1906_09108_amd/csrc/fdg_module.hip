@@ -751,7 +751,7 @@ hipError_t bn_backward(const fdg_module* m, const SlotView& v, const BnInfo& b, 
   a.rep_stride = a.brep_stride = m->p.stat_rep;
   if (hipError_t e = side_wait_readers(m, out_b16, s); e != hipSuccess) return e;
   // the reduce pass reads dy, gate and x; the apply pass reads them again and writes dx
-  const double rd = (dy_f32 ? 4 : 2) + 2 + 2;
+  const double rd = (dy_f32 ? 4 : 2) + (mask ? 2 : 0) + 2;
   ProfScope ps(m, PC_BN_BWD, 0, (double)b.M * b.C * (rd + ((out_f32 || out_b16) ? rd : 0) + (addend ? 4 : 0) +
                                                      (out_f32 ? 4 : 0) + (out_b16 ? 2 : 0)), s);
   hipError_t e = launch_bn_bwd_reduce(a, s);
@@ -1179,6 +1179,8 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
     bf16_t* const GB_out = (li > 0 && reads_bf16_gradient(p.L[li - 1])) ? m->GB(nxt) : nullptr;
     // whether the incoming fp32 gradient still has to be gated by this layer's output
     auto gate_of = [&](const bf16_t* y) { return fed_here ? nullptr : y; };
+    // bytes an element of this layer's input gradient takes to write, and its shortcut (fp32, gated by y) to read
+    const double write_bytes = (G_out ? 4 : 0) + (GB_out ? 2 : 0), shortcut_bytes = fed_here ? 4 : 4 + 2;
     if (L.kind == FDG_HEAD_POSTACT || L.kind == FDG_HEAD_PREACT) {
       const int J = p.d.num_classes;
       float* dp = reinterpret_cast<float*>(m->ws + p.o_dp);
@@ -1222,7 +1224,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
         FDG_TRY(side_wait_readers(m, m->T(1), s));
         {
           const ConvInputBnBwd bn = bn_bwd_input(m, v, b2, m->G(cur), true, t_c2, m->T(0));
-          const double bytes = conv_out_elems(c2.sh) * (4 + 2 + 2) + 2 * conv_w_elems(c2.sh) + conv_in_elems(c2.sh) * (2 + 2 + 2);
+          const double bytes = conv_out_elems(c2.sh) * (4 + 2 + 2) + 2 * conv_w_elems(c2.sh) + conv_in_elems(c2.sh) * (2 + 2 + (g32 ? 4 : 2));
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c2.sh), bytes, s);
           const hipError_t e = conv_dgrad_after_bn(c2.sh, bn, v.Wt(c2), nullptr, nullptr, t_a1, t_c1, m->bsums(b1), g32, g32 ? gf : nullptr,
                                                    g32 ? nullptr : m->T(1), s, p.stat_rep);
@@ -1260,7 +1262,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
           // the data gradients of the 3x3 and of the projection beside it, both stride 2, in one launch
           FDG_TRY(side_wait_readers(m, GB_out, s));
           const double bytes = 2 * (conv_out_elems(c1.sh) + conv_out_elems(cp.sh)) + 2 * (conv_w_elems(c1.sh) + conv_w_elems(cp.sh)) +
-                               conv_in_elems(c1.sh) * (4 + 2);
+                               conv_in_elems(c1.sh) * write_bytes;
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh) + conv_flops(cp.sh), bytes, s);
           const hipError_t e = conv_dgrad_gated_pair(c1.sh, m->T(0), v.Wt(c1), cp.sh, m->T(1), v.Wt(cp), nullptr, nullptr, nullptr,
                                                      G_out, GB_out, s);
@@ -1282,8 +1284,8 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
           FDG_TRY(side_wait_readers(m, GB_out, s));
           {
             const ConvInputBnBwd bn = g32 ? bn_bwd_input(m, v, b1, gf, true, t_c1, m->T(2)) : bn_bwd_input(m, v, b1, m->T(1), false, t_c1, m->T(2));
-            const double bytes = conv_out_elems(c1.sh) * (2 + 2 + 2) + 2 * conv_w_elems(c1.sh) +
-                                 conv_in_elems(c1.sh) * (4 + 2 + (feeds ? 2 + 2 : 0) + 4 + 2);
+            const double bytes = conv_out_elems(c1.sh) * ((g32 ? 4 : 2) + 2 + 2) + 2 * conv_w_elems(c1.sh) +
+                                 conv_in_elems(c1.sh) * (shortcut_bytes + (feeds ? 2 + 2 : 0) + write_bytes);
             ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
             const hipError_t e = conv_dgrad_after_bn(c1.sh, bn, v.Wt(c1), m->G(cur), gate_of(t_y), feeds ? in_b : nullptr, feeds ? bnx : nullptr,
                                                      feeds ? m->bsums(*bb) : nullptr, feeds, G_out, GB_out, s, p.stat_rep);
@@ -1294,7 +1296,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
           FDG_TRY(mconv_wgrad(m, c1, in_b, m->T(2), s));
         } else if (feeds) {
           FDG_TRY(side_wait_readers(m, GB_out, s));
-          const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (4 + 2 + 2 + 2 + 4 + 2);
+          const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (shortcut_bytes + 2 + 2 + write_bytes);
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
           const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), in_b, bnx,
                                                        m->bsums(*bb), G_out, GB_out, s, p.stat_rep);
@@ -1334,7 +1336,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
         const BnInfo* bb = li > 0 ? closing_bn(p, v, p.L[li - 1], &bnx) : nullptr;
         if (bb && bb->C == c1.sh.Cip && conv_dgrad_feeds_next(c1.sh)) {
           FDG_TRY(side_wait_readers(m, GB_out, s));
-          const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (4 + 2 + 2 + 2 + 4 + 2);
+          const double bytes = 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) + conv_in_elems(c1.sh) * (shortcut_bytes + 2 + 2 + write_bytes);
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), bytes, s);
           const hipError_t e = conv_dgrad_feeding_next(c1.sh, m->T(0), v.Wt(c1), m->G(cur), gate_of(t_y), in_b, bnx,
                                                        m->bsums(*bb), G_out, GB_out, s, p.stat_rep);

@@ -193,3 +193,38 @@ def test_weight_gradient_of_1x1_layers_against_64_bits(case):
     print(f"1x1 weight gradient {case}: {err:.3e}", flush=True)
     assert K.fdgk_last_kernel() == "conv_wgrad_kernel<128, 128, two sums>"
     assert err <= bound
+
+
+# The bytes that timing records charge are those of the tensors a launch is given: a gradient that arrives gated needs no gate, the
+# forms of the stream that nobody reads are not written, a batch norm without an activation behind it reads no gate
+@pytest.mark.parametrize("name", ["basic", "projecting", "inverted"])
+def test_bytes_of_the_timing_records(name):
+    import torch as t
+    from paper_1906_09108_amd import FdgModule
+    if name == "basic":
+        spec = ModuleSpec(8, 16, 16, 16, [Layer(W.BASIC_POSTACT, 16, 16, 1)] * 2, delay=0, beta=0.5, name=name, **H)
+        e, w = 8 * 16 * 16 * 16, 2 * 16 * 9 * 16
+        # conv2 of the upper block (bf16 in; gate, batch-norm input, fp32 out); its conv1 (fp32 gradient and batch-norm input in,
+        # bf16 out; gated fp32 shortcut, gate and batch-norm input of the block below, fp32 out); the lower block's, fed from above
+        expected = {"conv_dgrad": e * ((2 + 8) + (8 + 6 + 4 + 4) + (8 + 4 + 4) + (8 + 4 + 4)) + 4 * w, "bn_bwd": e * (8 + 8 + 2)}
+    elif name == "projecting":
+        spec = ModuleSpec(2, 128, 8, 8, [Layer(W.BASIC_POSTACT, 128, 128, 2)], delay=0, beta=0.5, name=name, **H)
+        e, o, w, wp = 2 * 64 * 128, 2 * 16 * 128, 128 * 9 * 128, 128 * 128
+        # conv2 (bf16 in, gate and batch-norm input, bf16 out), then conv1 and the projection in one launch (fp32 out)
+        expected = {"conv_dgrad": 2 * o + 2 * w + o * (2 + 2 + 2) + 2 * (o + o) + 2 * (w + wp) + 4 * e}
+    else:
+        spec = ModuleSpec(2, 16, 8, 8, [Layer(W.INVERTED_RESIDUAL, 16, 16, 1)], delay=0, beta=0.5, name=name, **H)
+        m = 2 * 8 * 8
+        expected = {"bn_bwd": m * 16 * (6 + 6 + 2) + 2 * m * 96 * (8 + 8 + 2)}
+    mod = FdgModule(spec)
+    mod.set_params(W.make_params(spec, 0))
+    mod.profile_enable(True)
+    x, g = (t.from_numpy(f(spec, 0, 0)).cuda() for f in (W.make_input, W.make_grad_out))
+    mod.forward(x)
+    mod.backward_delayed(g, t.empty_like(x))
+    got = {}
+    for r in mod.profile_read():
+        got[r["name"]] = got.get(r["name"], 0) + r["bytes"]
+    mod.close()
+    for k, v in expected.items():
+        assert got[k] == v, (k, got[k], v)
