@@ -141,13 +141,17 @@ def test_head_edges(case):
 
 
 # 64 -> 64 channel weight gradients: one tile per workgroup and one row, several tiles with a ragged last one (two buffers), an
-# image too wide for two buffers.  The kernel alone, to the bound of 32-bit sums: through a whole block a pre-activation that
-# two orders of a sum put on either side of zero moves a gradient of so few pixels by more than the kernel's own error.
-@pytest.mark.parametrize("case", [(3, 1, 7, 64, 64, 3, 1), (4, 9, 21, 64, 64, 3, 1), (23, 47, 50, 64, 64, 3, 1), (2, 3, 170, 64, 64, 3, 1)])
-def test_weight_gradient_of_64_channels(case):
+# image too wide for two buffers, the same with more tiles than workgroups, the widest images the kernel takes and one column
+# more.  The kernel alone, to the bound of 32-bit sums: through a whole block a pre-activation that two orders of a sum put on
+# either side of zero moves a gradient of so few pixels by more than the kernel's own error.
+@pytest.mark.parametrize("case,narrow", [((3, 1, 7, 64, 64, 3, 1), True), ((4, 9, 21, 64, 64, 3, 1), True),
+                                         ((23, 47, 50, 64, 64, 3, 1), True), ((2, 3, 170, 64, 64, 3, 1), True),
+                                         ((2, 130, 160, 64, 64, 3, 1), True), ((1, 3, 286, 64, 64, 3, 1), True),
+                                         ((1, 3, 287, 64, 64, 3, 1), False)])
+def test_weight_gradient_of_64_channels(case, narrow):
     from paper_1906_09108_amd import kernels as K
     TK.test_conv_wgrad(case)
-    assert K.fdgk_last_kernel() == "conv_wgrad_narrow64_kernel"
+    assert (K.fdgk_last_kernel() == "conv_wgrad_narrow64_kernel") == narrow, K.fdgk_last_kernel()
 
 
 # The slices of one weight gradient are added up by the next, of the same and of another width; with a few images and, where the
@@ -160,16 +164,26 @@ def test_slices_of_an_earlier_weight_gradient(name, n, h, w):
     check(f"slices {name} n{n}", ModuleSpec(n, first, h, w, layers, delay=1, is_bottom=False, beta=0.5, name=f"slices {name}", **H))
 
 
-# 1x1 layers of few output channels behind a long contraction and of 72 .. 120 input channels: both ends of the ranges, a ragged
-# last tile of pixels, channel counts that fill no tile, stride 2
-THIN = [(9, 43, 43, 128, 40, 1, 1), (9, 43, 43, 192, 64, 1, 1), (9, 43, 43, 128, 72, 1, 1), (8, 46, 46, 384, 96, 1, 1), (33, 23, 23, 72, 152, 1, 1),
-        (21, 31, 31, 120, 264, 1, 1), (9, 85, 85, 128, 64, 1, 2), (9, 43, 43, 64, 128, 1, 1)]
+# 1x1 layers of few output channels behind a long contraction and of 72 .. 120 input channels: both ends of the ranges on either
+# side of the tiles a rule asks for, a ragged last tile of pixels, channel counts that fill no tile, stride 2.  With each the
+# kernels that forward and data gradient run.
+GENERIC64, GENERIC = "conv_gather_kernel<128, 64, 2, 2>", "conv_gather_kernel<128, 128, 2, 2>"
+PIPE, THIN64, THIN96, PAIR = "conv_gather_pipe_kernel<128, 4, false>", *(f"conv_gather_dma_pair_kernel<{k}>" for k in ("64, 3", "96, 4", "128, 2"))
+THIN = [((9, 43, 43, 128, 40, 1, 1), THIN64, GENERIC), ((9, 43, 43, 192, 64, 1, 1), THIN64, PIPE),
+        ((8, 45, 45, 128, 64, 1, 1), GENERIC64, PIPE), ((9, 43, 43, 128, 72, 1, 1), THIN96, GENERIC),
+        ((9, 43, 43, 128, 104, 1, 1), GENERIC, GENERIC), ((8, 46, 46, 384, 96, 1, 1), THIN96, PAIR),
+        ((37, 23, 23, 72, 264, 1, 1), PAIR, GENERIC), ((33, 23, 23, 72, 152, 1, 1), GENERIC, GENERIC),
+        ((21, 31, 31, 120, 264, 1, 1), PAIR, GENERIC), ((9, 85, 85, 128, 64, 1, 2), THIN64, PIPE),
+        ((9, 43, 43, 64, 128, 1, 1), PIPE, THIN64)]
 
 
-@pytest.mark.parametrize("case", THIN)
-def test_thin_1x1_layers(case):
+@pytest.mark.parametrize("case,forward,dgrad", THIN)
+def test_thin_1x1_layers(case, forward, dgrad):
+    from paper_1906_09108_amd import kernels as K
     TK.test_conv_fwd(case)
+    assert K.fdgk_last_kernel() == forward
     TK.test_conv_dgrad(case)
+    assert K.fdgk_last_kernel() == dgrad
     TK.test_conv_wgrad(case)
 
 
