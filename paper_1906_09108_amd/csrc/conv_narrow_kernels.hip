@@ -1131,7 +1131,7 @@ __global__ __launch_bounds__(256) void wgrad_slices_reduce_kernel(float4* __rest
   }
 }
 
-struct NarrowWgradPlan { NarrowWgradLaunch L; int blocks; size_t lds; bool wide; };
+struct NarrowWgradPlan { NarrowWgradLaunch L; int blocks; size_t lds; };
 
 // tile height: about one tile per compute unit, within 96 KB of LDS; at most 256 workgroups (and slices)
 static bool wgrad_narrow_is_stem(const WgradArgs& a) { return a.Cx == 8 && a.Ci <= 8 && a.Co != a.Cx; }
@@ -1142,8 +1142,7 @@ bool plan_wgrad_narrow(const WgradArgs& a, NarrowWgradPlan& P) {
   const int PW = a.Wi + 2, HP = a.Hi + 2;
   const long long rows_total = (long long)a.N * HP;
   if (rows_total * PW >= (1ll << 30)) return false;
-  P.wide = C == 64 && !wgrad_narrow_is_stem(a);
-  if (P.wide) {   // conv_wgrad_narrow64_kernel: two buffers, tiles of at least kWgrad64Positions positions where they fit
+  if (C == 64 && !wgrad_narrow_is_stem(a)) {   // conv_wgrad_narrow64_kernel: two buffers, tiles of about kWgrad64Positions positions where they fit
     const long long positions = std::min<long long>(kWgrad64Positions, rows_total * PW / kWgrad64Least);
     const long long want = std::max((rows_total + 255) / 256, std::max<long long>(1, positions / PW));
     int R = (int)std::min(want, rows_total);

@@ -54,19 +54,6 @@ __device__ __forceinline__ void stat_add(stat_t* stats, int C, int which, int c,
 __device__ __forceinline__ double stat_value(long long hi, long long lo, long long big) {
   return __builtin_bit_cast(double, big) + ((double)hi * 0x1p-11 + (double)lo * 0x1p-62);
 }
-// the total of channel c, copies added
-__device__ __forceinline__ double stat_load(const stat_t* stats, int C, int which, int c, int rep_stride) {
-  const stat_t* p = stats + (size_t)which * C + c;
-  long long hi = p[0], lo = p[2 * (size_t)C];
-  double big = __builtin_bit_cast(double, p[4 * (size_t)C]);
-  if (rep_stride > 0)
-    for (int r = 1; r < kStatReplicas; ++r) {
-      const stat_t* q = p + (size_t)r * rep_stride;
-      hi += q[0]; lo += q[2 * (size_t)C];
-      big += __builtin_bit_cast(double, q[4 * (size_t)C]);
-    }
-  return stat_value(hi, lo, __builtin_bit_cast(long long, big));
-}
 #endif
 
 struct GatherConvArgs {

@@ -342,7 +342,7 @@ hipError_t launch_bn_apply(const BnApplyArgs& a, hipStream_t s) {
     case 1: if (a.x2) FDG_LAUNCH_BN_APPLY(1, true); else FDG_LAUNCH_BN_APPLY(1, false); break;
     case 2: if (a.x2) FDG_LAUNCH_BN_APPLY(2, true); else FDG_LAUNCH_BN_APPLY(2, false); break;
     case 4: if (a.x2) FDG_LAUNCH_BN_APPLY(4, true); else FDG_LAUNCH_BN_APPLY(4, false); break;
-    default: if (a.x2) FDG_LAUNCH_BN_APPLY(8, true); else FDG_LAUNCH_BN_APPLY(8, false); break;
+    default: FDG_LAUNCH_BN_APPLY(8, true); break;   // two sums of 64 channels: four copies a thread
   }
 #undef FDG_LAUNCH_BN_APPLY
   return hipGetLastError();
