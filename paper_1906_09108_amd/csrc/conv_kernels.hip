@@ -375,7 +375,7 @@ static void wgrad_plan(const WgradArgs& a, int& splits, int& chunks_per_split, i
   const int total_chunks = (Mtot + BK - 1) / BK;
   const int base = co_tiles * ci_tiles * a.ntaps;
   // 1x1 layers of the 128 x 128 form take one round of workgroups, two to a compute unit (64 KB of LDS): each part is written and
-  // read back (128 x 64 x 64, 64 -> 128, stride 2: 38 -> 27 us).  With nine taps the parts are a smaller share and shorter
+  // read back (128 x 64 x 64, 64 -> 128, stride 2: 36 -> 25 us).  With nine taps the parts are a smaller share and shorter
   // workgroups balance better (3x3 of that layer: 110 us, 126 with one round).  A workgroup of the single round sums its pixels in
   // two halves, so that no sum runs over more of them than with two rounds.
   const int target = BN == 128 && a.ntaps == 1 ? 512 : 1024;

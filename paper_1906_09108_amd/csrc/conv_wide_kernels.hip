@@ -195,7 +195,8 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
   combine_and_store32<FN, BN, F32S>(b, acc, m0, c0, wave_m, wk, lane, smem);
 }
 
-// Within 256 registers, so that two workgroups (two waves per SIMD) fit a compute unit: the two-stage form.
+// Within 256 registers.  <128, 2> (73 KB of LDS, like <64, 3>) so fits two workgroups on a compute unit, two waves per SIMD;
+// <96, 4> holds 112 KB and one workgroup.
 // F32S: sums of the fp32 values in the output stage (GatherConvArgs::stats_f32), for a data gradient that feeds the layer below.
 template <int BN, int STAGES, bool KTAIL, bool F32S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_gather_dma_pair_kernel(
@@ -1234,12 +1235,16 @@ static hipError_t run_wide(const GatherConvArgs& a, hipStream_t s) {
 // contraction over 384 channels was twelve waits for memory in a row; here whole 64-channel chunks arrive by direct loads, two
 // or three ahead, and the output leaves in rows.  128 x 16 x 16: 384 -> 64 28.5 -> 14.5 us,
 // 576 -> 96 55 -> 20, 96 -> 576 62 -> 43.
+// The bounds on the tiles are those of the layers it was first measured on; they are no break-even.  Just above them, generic ->
+// this kernel: 16 x 32 x 32 (128 tiles) 128 -> 40 13.6 -> 9.7 us, 576 -> 96 41.7 -> 17.0; 32 x 16 x 16 (320) 96 -> 576 29.7 -> 13.3.
+// Below them the generic kernel still runs and is the slower one too: 15 x 32 x 32 128 -> 40 13.1 (9.3), 576 -> 96 44.5 (16.8);
+// 1 x 32 x 32 35.1 (14.6); 16 x 16 x 16 96 -> 576 27.1 (10.8).
 bool conv_gather_thin_applies(const GatherConvArgs& a) {
   if (a.nclass > 1 || a.ntaps != 1 || a.gate || a.bnx || a.stats_f32 || a.w_rows != a.Co || a.Kw % 8 != 0) return false;
   if (a.Hi >= 32768 || a.Wi >= 32768 || (long long)a.N * a.OH * a.OW >= (1ll << 30)) return false;
   const long long tiles = ((long long)a.N * a.OH * a.OW + 127) / 128;
   if (a.Co >= 128) return a.Ci % 8 == 0 && a.Ci > 64 && a.Ci < 128 && tiles * ((a.Co + 127) / 128) >= 300;
-  return a.Ci % 64 == 0 && a.Ci >= 128 && a.Co >= 40 && a.Co <= 96 && tiles >= 128;   // fewer tiles: the generic kernel's 64-channel ones
+  return a.Ci % 64 == 0 && a.Ci >= 128 && a.Co >= 40 && a.Co <= 96 && tiles >= 128;
 }
 
 template <int BN, int STAGES, bool KTAIL>

@@ -329,7 +329,8 @@ bool build_plan(const fdg_module_desc* desc, int save_mode, Plan& p, fdg_status*
   // Copies of the sums for the narrow 3x3 kernels, whose launches are shorter than their atomics on one cache line, and where a
   // batch norm takes more partials than one array holds: a workgroup per 128 pixels or more (in up to four parity classes) adds
   // one.  Not for the 1x1 layers that feed the next one (conv_dgrad_feeds_next holds for them too): every reader of a sums array
-  // pays for its copies (bottleneck module of 256 channels at 56 x 56, batch 128, 3136 workgroups: 5134 us with, 4134 without).
+  // pays for its copies (eight bottleneck blocks of 1024 channels at 14 x 14, batch 128: 4303 us with copies, 4226 without; two
+  // of 256 channels at 56 x 56, 3136 workgroups a launch: 4128 either way).
   bool copies = false;
   for (const ConvInfo& ci : p.convs) copies = copies || (!ci.depthwise && ci.sh.T == 9 && conv_dgrad_feeds_next(ci.sh));
   for (const BnInfo& b : p.bns) copies = copies || (b.M + 127) / 128 + 4 > kStatMaxPartials;
