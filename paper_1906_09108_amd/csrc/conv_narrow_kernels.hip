@@ -1143,8 +1143,8 @@ bool plan_wgrad_narrow(const WgradArgs& a, NarrowWgradPlan& P) {
   const long long rows_total = (long long)a.N * HP;
   if (rows_total * PW >= (1ll << 30)) return false;
   if (C == 64 && !wgrad_narrow_is_stem(a)) {   // conv_wgrad_narrow64_kernel: two buffers, tiles of about kWgrad64Positions positions where they fit
-    const long long positions = std::min<long long>(kWgrad64Positions, rows_total * PW / kWgrad64Least);
-    const long long want = std::max((rows_total + 255) / 256, std::max<long long>(1, positions / PW));
+    const long long positions = std::min<long long>(kWgrad64Positions, (rows_total * PW + kWgrad64Least - 1) / kWgrad64Least);
+    const long long want = std::max((rows_total + 255) / 256, (positions + PW - 1) / PW);
     int R = (int)std::min(want, rows_total);
     for (;; --R) {
       const int KP = (R * PW + 31) / 32 * 32, xpos = KP + 2 * PW + 2;
