@@ -330,6 +330,282 @@ hipError_t run_narrow_j(const GatherConvArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// 64 -> 64 channels over many pixels (the first stage of ResNet-18), forward and data gradient
+// ------------------------------------------------------------------------------------------------
+// Such a launch streams: 128 x 64 x 64 pixels are 134 .. 540 MB against 39 GFLOP.  conv_narrow_kernel needed 400 registers for it
+// (filter 144, fragment addresses 36, four pixel blocks of accumulators and output operands at once), so one workgroup sat on a
+// compute unit and every wait for memory and every burst of output arithmetic stood still for the others.  Here two workgroups
+// fit (two waves per SIMD) and one computes while the other waits:
+//   * a tile is R whole rows of one image (R W <= 128 pixels), so everything about it but its base address is the same for every
+//     tile of the launch: load offsets and fragment addresses are worked out once;
+//   * the patch is stored PADDED, a zero column before every row and zero rows where the image ends (those lanes load the zero
+//     word), at 144 bytes per position: a tap is then an immediate offset of the LDS read, and 16 consecutive positions fall into
+//     16 different bank groups;
+//   * pixel blocks are taken one after the other: 8 accumulator registers, and the output operands of one block, requested
+//     before its MFMAs;
+//   * the loads of the next tile's patch go out in three parts behind those requests, which therefore need not wait for them;
+//   * the filter rows are dealt to the MFMA rows so that a lane ends with 8 consecutive channels: one 16-byte access per bf16
+//     operand, two per fp32 one.
+// NR rounds of 256 16-byte loads fill a patch (the last one only by the waves it concerns).
+// 128 x 64 x 64, conv_narrow_kernel -> here: forward with sums 104.7 -> 58.0 us (134 MB, 667 TFLOP/s), gated data gradient
+// 138 -> 68, with addend, mask, gate and sums 181 -> 114 (540 MB, 4.7 TB/s); 128 x 32 x 32 forward 39.9 -> 28.3.
+// Not waiting for the last stores of a tile before the next one's barrier gained nothing: the other workgroup runs meanwhile.
+struct Narrow64Launch {
+  int R, PW;                   // rows of a tile; positions of a padded row, W + 1
+  int tiles, tiles_per_image;
+  int units;                   // 16-byte units of a patch, 9 per position
+  int buffer;                  // bytes of a patch buffer
+  int flipped;                 // the taps run from (1, 1) to (-1, -1): a data gradient
+  unsigned long long magic_w, magic_pw, magic_tiles;   // narrow_div by W, PW and tiles_per_image
+};
+constexpr int kNarrow64Pixels = 128, kNarrow64Pitch = 144;
+
+// ADD: the output stage has an fp32 addend (with or without a mask); GATE: a gate, and bnx in the place of the squares
+template <int NR, bool ADD, bool GATE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_narrow64_kernel(GatherConvArgs a, Narrow64Launch L) {
+  constexpr int C = 64, J = 4, PB = kNarrow64Pitch;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // two patch buffers
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;       // 64 pixels, 32 output channels
+  const int W = a.Wi, H = a.Hi, g = lane >> 4, l16 = lane & 15;
+  const unsigned image_bytes = (unsigned)H * W * (C * 2);
+  const int first_tile = narrow_xcd_consecutive(blockIdx.x, gridDim.x);
+
+  // ---- this lane's loads of a patch: byte offset from the tile's first pixel, or far outside for what is padding ----
+  constexpr unsigned OUTSIDE = 0x40000000u;
+  unsigned off[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int i = r * 256 + tid, pos = i / 9, u = i - 9 * pos;
+    const int lr = narrow_div(pos, L.magic_pw), cc = pos - lr * L.PW;
+    off[r] = (u < 8 && cc >= 1 && lr < L.R + 2) ? (unsigned)(((lr - 1) * W + cc - 1) * (C * 2) + u * 16) : OUTSIDE;
+  }
+  const uint64_t zaddr = (uint64_t)g_narrow_zero;
+  auto tile_at = [&](int tile, int& n, int& h0) {
+    n = narrow_div(tile, L.magic_tiles);
+    h0 = (tile - n * L.tiles_per_image) * L.R;
+  };
+  auto issue = [&](int r, const char* image, unsigned tile_off, int buf) {
+    const unsigned o = tile_off + off[r];
+    const uint64_t p = o < image_bytes ? (uint64_t)image + o : zaddr;
+    narrow_dma16(reinterpret_cast<const void*>(p), smem + (size_t)buf * L.buffer + (size_t)(r * 256 + wave * 64) * 16);
+  };
+  auto issue_part = [&](int part, const char* image, unsigned tile_off, int buf) {   // three parts of a patch's loads
+    constexpr int PER = (NR + 2) / 3;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int r = part * PER + k;
+      if (r < NR - 1 || (r == NR - 1 && r * 256 + wave * 64 < L.units)) issue(r, image, tile_off, buf);
+    }
+  };
+  int n = 0, h0 = 0;
+  tile_at(first_tile, n, h0);
+  const char* in = reinterpret_cast<const char*>(a.in);
+  if (first_tile < L.tiles)
+#pragma unroll
+    for (int part = 0; part < 3; ++part) issue_part(part, in + (size_t)n * image_bytes, (unsigned)h0 * W * (C * 2), 0);
+
+  // ---- the filter: MFMA row l16 of channel block nb is output channel 32 wn + 8 (l16 / 4) + 4 nb + l16 % 4; shift t reads the
+  //      weights of tap t, or of tap 8 - t where the taps are flipped ----
+  bf16x8 wf[18][2];
+#pragma unroll
+  for (int s = 0; s < 18; ++s)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const int co = wn * 32 + 8 * (l16 >> 2) + 4 * nb + (l16 & 3);
+      const int slot = L.flipped ? 8 - (s >> 1) : (s >> 1);
+      wf[s][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(a.w + (size_t)co * a.Kw + slot * C + (s & 1) * 32 + 8 * g));
+    }
+
+  // ---- LDS address of this lane's pixel of every block: the position up and left of it, k-unit g ----
+  unsigned paddr[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int pl = (wm * J + j) * 16 + l16;
+    const int q = pl < L.R * W ? pl : 0;
+    const int rl = narrow_div(q, L.magic_w);
+    paddr[j] = (unsigned)((rl * L.PW + q - rl * W) * PB + g * 16);
+  }
+  const unsigned row_step = (unsigned)L.PW * PB;
+  const int c0 = wn * 32 + 8 * g;                // this lane's first output channel
+  float s1[8], s2[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s1[e] = s2[e] = 0.f;
+
+  int cur = 0;
+  for (int tile = first_tile; tile < L.tiles; tile += gridDim.x) {
+    const int rows = H - h0 < L.R ? H - h0 : L.R;
+    const int live = rows * W;                                   // pixels of this tile
+    const size_t base = ((size_t)n * H + h0) * W * C + c0;       // this lane's output element of pixel 0
+    int next_n = 0, next_h0 = 0;
+    const bool more = tile + (int)gridDim.x < L.tiles;
+    tile_at(tile + (int)gridDim.x, next_n, next_h0);
+    const char* next_image = in + (size_t)(more ? next_n : 0) * image_bytes;
+    const unsigned next_off = (unsigned)next_h0 * W * (C * 2);
+
+    __builtin_amdgcn_s_waitcnt(0);   // this tile's patch (and, before the first tile, the filter) has landed
+    __syncthreads();                 // ... for every wave; and every wave is done reading the other buffer
+
+    const unsigned char* patch = smem + (size_t)cur * L.buffer;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int pl = (wm * J + j) * 16 + l16;
+      const bool ok = pl < live;
+      const size_t o = base + (size_t)(ok ? pl : 0) * C;
+      float4 ad[2];
+      uint4 mk, gt, bx;
+      if constexpr (ADD) {
+        ad[0] = *reinterpret_cast<const float4*>(a.addend + o);
+        ad[1] = *reinterpret_cast<const float4*>(a.addend + o + 4);
+        if (a.addmask) mk = *reinterpret_cast<const uint4*>(a.addmask + o);
+      }
+      if constexpr (GATE) {
+        gt = *reinterpret_cast<const uint4*>(a.gate + o);
+        bx = *reinterpret_cast<const uint4*>(a.bnx + o);
+      }
+      if (j < 3 && more) issue_part(j, next_image, next_off, cur ^ 1);
+
+      f32x4 acc[2];
+      acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const unsigned char* at = patch + paddr[j] + (t / 3) * row_step;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const bf16x8 b = *reinterpret_cast<const bf16x8*>(at + (t % 3) * PB + half * 64);
+          acc[0] = mfma16(wf[2 * t + half][0], b, acc[0]);
+          acc[1] = mfma16(wf[2 * t + half][1], b, acc[1]);
+        }
+      }
+
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = acc[e >> 2][e & 3];
+      if constexpr (ADD) {
+        float d[8] = {ad[0].x, ad[0].y, ad[0].z, ad[0].w, ad[1].x, ad[1].y, ad[1].z, ad[1].w};
+        if (a.addmask) {
+          const uint32_t m[4] = {mk.x, mk.y, mk.z, mk.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (!((e & 1 ? bf16_hi(m[e >> 1]) : bf16_lo(m[e >> 1])) > 0.f)) d[e] = 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += d[e];
+      }
+      if constexpr (GATE) {
+        const uint32_t m[4] = {gt.x, gt.y, gt.z, gt.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!((e & 1 ? bf16_hi(m[e >> 1]) : bf16_lo(m[e >> 1])) > 0.f)) v[e] = 0.f;
+      }
+      uint32_t packed[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) packed[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
+      if (ok) {
+        if (a.out_f32) {
+          *reinterpret_cast<float4*>(a.out_f32 + o) = make_float4(v[0], v[1], v[2], v[3]);
+          *reinterpret_cast<float4*>(a.out_f32 + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        }
+        if (a.out_b16) *reinterpret_cast<uint4*>(a.out_b16 + o) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        if (a.stats) {
+          const uint32_t x[4] = {bx.x, bx.y, bx.z, bx.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float rounded = e & 1 ? bf16_hi(packed[e >> 1]) : bf16_lo(packed[e >> 1]);
+            const float r = a.stats_f32 ? v[e] : rounded;
+            s1[e] += r;
+            s2[e] += r * (GATE ? (e & 1 ? bf16_hi(x[e >> 1]) : bf16_lo(x[e >> 1])) : r);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // one block's operands and sums at a time
+    }
+    cur ^= 1;
+    n = next_n; h0 = next_h0;
+  }
+
+  // per-channel sums: over the 16 lanes that hold the same channels, then the two waves of a channel half through LDS (a fixed
+  // order), then one exact add per channel and value
+  if (a.stats) {
+    __shared__ float red[4][2][32];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float x1 = s1[e], x2 = s2[e];
+#pragma unroll
+      for (int d = 8; d > 0; d >>= 1) {
+        x1 += __shfl_xor(x1, d, 16);
+        x2 += __shfl_xor(x2, d, 16);
+      }
+      if (l16 == 0) {
+        red[wave][0][8 * g + e] = x1;
+        red[wave][1][8 * g + e] = x2;
+      }
+    }
+    __syncthreads();
+    if (tid < 2 * C) {
+      const int which = tid / C, c = tid % C, half = c >> 5, cl = c & 31;
+      stat_add(a.stats + (size_t)(blockIdx.x % kStatReplicas) * a.stats_rep_stride, C, which, c,
+               red[2 * half][which][cl] + red[2 * half + 1][which][cl]);
+    }
+  }
+}
+
+template <int NR, bool ADD, bool GATE>
+hipError_t run_narrow64_as(const GatherConvArgs& a, const Narrow64Launch& L, hipStream_t s) {
+  const size_t lds = 2 * (size_t)L.buffer;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_narrow64_kernel<NR, ADD, GATE>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 2 * NR * 4096);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  note_kernel("conv_narrow64_kernel");
+  const int grid = L.tiles < 512 ? L.tiles : 512;   // two workgroups to a compute unit, each takes every grid-th tile
+  hipLaunchKernelGGL((conv_narrow64_kernel<NR, ADD, GATE>), dim3(grid), dim3(256), lds, s, a, L);
+  return hipGetLastError();
+}
+template <int NR>
+hipError_t run_narrow64(const GatherConvArgs& a, const Narrow64Launch& L, hipStream_t s) {
+  if (a.addend) return a.gate ? run_narrow64_as<NR, true, true>(a, L, s) : run_narrow64_as<NR, true, false>(a, L, s);
+  return a.gate ? run_narrow64_as<NR, false, true>(a, L, s) : run_narrow64_as<NR, false, false>(a, L, s);
+}
+
+int narrow64_rounds(int units) { return units <= 8 * 256 ? 8 : 10; }   // the NR that is launched
+
+// Where the kernel above runs: 64 -> 64 channels, enough pixels for four tiles of 128 to each of 512 workgroups (below, the
+// filter is most of what a workgroup loads and the batch-norm pass on the patch is worth more), rows that fill at least half a
+// tile and whose patch fits ten rounds of loads, taps in one of the two orders, gate and bnx together with the sums, and bf16 operands of the output stage at 16-byte addresses.
+bool plan_narrow64(const GatherConvArgs& a, Narrow64Launch& L) {
+  if (a.Ci != 64 || a.Co != 64 || a.N * a.OH * a.OW < 512 * 128 || (!a.gate) != (!a.bnx) || (a.gate && !a.stats)) return false;
+  if (((uintptr_t)a.addmask | (uintptr_t)a.gate | (uintptr_t)a.bnx | (uintptr_t)a.out_b16) % 16 != 0) return false;
+  const int W = a.Wi, H = a.Hi;
+  if (W < 1 || W > kNarrow64Pixels) return false;
+  L.R = std::min(kNarrow64Pixels / W, H);
+  if (2 * L.R * W < kNarrow64Pixels) return false;
+  L.PW = W + 1;
+  L.units = ((L.R + 2) * L.PW + 1) * 9;
+  if (L.units > 10 * 256) return false;
+  const int rounds = narrow64_rounds(L.units);
+  L.buffer = std::max((L.units + 63) / 64 * 1024, (rounds - 1) * 4096);   // all rounds but the last are whole
+  L.tiles_per_image = (H + L.R - 1) / L.R;
+  if ((long long)a.N * L.tiles_per_image + 512 >= (1ll << 30) || L.tiles_per_image > 1024) return false;
+  L.tiles = a.N * L.tiles_per_image;
+  bool plain = true, flipped = true;
+  for (int t = 0; t < 9; ++t) {
+    plain = plain && a.tap[t] == pack_tap(t / 3 - 1, t % 3 - 1, t);
+    flipped = flipped && a.tap[t] == pack_tap(1 - t / 3, 1 - t % 3, t);
+  }
+  if (!plain && !flipped) return false;
+  L.flipped = flipped ? 1 : 0;
+  L.magic_w = ((1ull << 40) + W - 1) / W;
+  L.magic_pw = ((1ull << 40) + L.PW - 1) / L.PW;
+  L.magic_tiles = ((1ull << 40) + L.tiles_per_image - 1) / L.tiles_per_image;
+  return true;
+}
+
+// ------------------------------------------------------------------------------------------------
 // The same with an input transform (GatherConvArgs::tr_mode): the batch-norm pass that would precede the
 // convolution -- forward batch norm + ReLU, or the apply half of a batch-norm backward -- runs on the patch in LDS.
 // ------------------------------------------------------------------------------------------------
@@ -1240,6 +1516,8 @@ hipError_t launch_conv_narrow(const GatherConvArgs& a, hipStream_t s) {
     return a.N * a.OH * a.OW >= 512 * 32 * 2 ? run_narrow<16, 5, 2, 2>(a, s) : run_narrow<16, 5, 2, 1>(a, s);
   if (a.Ci == 16) return run_narrow_j<16, 1, 1>(a, s);
   if (a.Ci == 32) return run_narrow_j<32, 2, 1>(a, s);
+  Narrow64Launch L;
+  if (plan_narrow64(a, L)) return narrow64_rounds(L.units) == 8 ? run_narrow64<8>(a, L, s) : run_narrow64<10>(a, L, s);
   return run_narrow_j<64, 2, 2>(a, s);
 }
 
