@@ -620,8 +620,10 @@ bool plan_narrow64(const GatherConvArgs& a, Narrow64Launch& L) {
 // output stage) is conv_narrow_kernel's.
 // VAR: 0 forward batch norm + ReLU of p (bf16);  1 / 2 batch-norm backward of p (bf16 / fp32) with q;  3 forward batch
 // norm of p (bf16) + fp32 residual r (tr_q) + ReLU.  The forward forms also write y in fp32 where tr_out_f32 is given.
+// Two waves per SIMD are asked for up to two pixel blocks of 64 channels: with accumulators in registers of their own the backward
+// forms took 258, one wave (ResNet-56, batch 128: 2430 -> 2391 us a step).  Four blocks would spill; they keep one wave.
 template <int CI, int NB, int WN, int J, int VAR>
-__global__ __launch_bounds__(256) void conv_narrow_tr_kernel(GatherConvArgs a, NarrowLaunch L) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CI == 64 && J == 4 ? 1 : 2))) void conv_narrow_tr_kernel(GatherConvArgs a, NarrowLaunch L) {
   constexpr bool PF32 = VAR == 2, WQ = VAR == 1 || VAR == 2, WR = VAR == 3;
   constexpr int WM = 4 / WN, TP = 16 * J * WM, CO = 16 * NB * WN;
   constexpr int U = CI / 8, ROWB = CI * 2;
