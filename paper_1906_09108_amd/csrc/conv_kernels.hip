@@ -464,8 +464,10 @@ static GatherConvArgs forward_args(const ConvShape& c, const bf16_t* x, const bf
 }
 
 hipError_t conv_forward(const ConvShape& c, const bf16_t* x, const bf16_t* w, const float* addend, float* out_f32,
-                        bf16_t* out_b16, stat_t* stats, hipStream_t s, int stats_rep_stride) {
-  return launch_conv_gather(forward_args(c, x, w, addend, out_f32, out_b16, stats, stats_rep_stride), s);
+                        bf16_t* out_b16, stat_t* stats, hipStream_t s, int stats_rep_stride, const ConvScratch& scratch) {
+  GatherConvArgs a = forward_args(c, x, w, addend, out_f32, out_b16, stats, stats_rep_stride);
+  a.scratch = scratch;
+  return launch_conv_gather(a, s);
 }
 
 bool conv_forward_bn_applies(const ConvShape& c, bool with_residual) {
@@ -487,11 +489,13 @@ hipError_t conv_forward_bn(const ConvShape& c, const ConvInputBn& bn, const bf16
 static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                   const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                   bf16_t* out_b16, hipStream_t s, bool stats_f32 = false, int rep_stride = 0,
-                                  const bf16_t* dy2 = nullptr, const bf16_t* wt2 = nullptr, const ConvInputBnBwd* bn = nullptr);
+                                  const bf16_t* dy2 = nullptr, const bf16_t* wt2 = nullptr, const ConvInputBnBwd* bn = nullptr,
+                                  const ConvScratch& scratch = {});
 
 hipError_t conv_dgrad(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
-                      const bf16_t* addmask, float* out_f32, bf16_t* out_b16, hipStream_t s) {
-  return conv_dgrad_impl(c, dy, wt, addend, addmask, nullptr, nullptr, nullptr, out_f32, out_b16, s);
+                      const bf16_t* addmask, float* out_f32, bf16_t* out_b16, hipStream_t s, const ConvScratch& scratch) {
+  return conv_dgrad_impl(c, dy, wt, addend, addmask, nullptr, nullptr, nullptr, out_f32, out_b16, s, false, 0, nullptr, nullptr, nullptr,
+                         scratch);
 }
 
 // the narrow kernel, or the two-workgroup form of the wide gather kernel (1x1 layers), runs the whole data gradient of
@@ -527,9 +531,10 @@ bool conv_dgrad_gates(const ConvShape& c) {
 
 hipError_t conv_dgrad_gated(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
                             const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
-                            int gsums_rep_stride) {
+                            int gsums_rep_stride, const ConvScratch& scratch) {
   if (!gate || !bnx || !gsums || !conv_dgrad_gates(c)) return hipErrorInvalidValue;
-  return conv_dgrad_impl(c, dy, wt, addend, nullptr, gate, bnx, gsums, out_f32, out_b16, s, false, gsums_rep_stride);
+  return conv_dgrad_impl(c, dy, wt, addend, nullptr, gate, bnx, gsums, out_f32, out_b16, s, false, gsums_rep_stride, nullptr, nullptr,
+                         nullptr, scratch);
 }
 
 bool conv_dgrad_bn_applies(const ConvShape& c, bool g_is_f32) {
@@ -565,17 +570,19 @@ bool conv_dgrad_pair_applies(const ConvShape& c, const ConvShape& cp) {
 
 hipError_t conv_dgrad_gated_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
                                  const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
-                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride) {
+                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride, const ConvScratch& scratch) {
   const bool gated = gate || bnx || gsums;
   if (!dy2 || !wt2 || (gated && (!gate || !bnx || !gsums)) || !conv_dgrad_pair_applies(c, cp)) return hipErrorInvalidValue;
-  return conv_dgrad_impl(c, dy, wt, nullptr, nullptr, gate, bnx, gsums, out_f32, out_b16, s, false, gsums_rep_stride, dy2, wt2);
+  return conv_dgrad_impl(c, dy, wt, nullptr, nullptr, gate, bnx, gsums, out_f32, out_b16, s, false, gsums_rep_stride, dy2, wt2, nullptr,
+                         scratch);
 }
 
 static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                   const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                   bf16_t* out_b16, hipStream_t s, bool stats_f32, int rep_stride, const bf16_t* dy2,
-                                  const bf16_t* wt2, const ConvInputBnBwd* bn) {
+                                  const bf16_t* wt2, const ConvInputBnBwd* bn, const ConvScratch& scratch) {
   GatherConvArgs a{};
+  a.scratch = scratch;
   a.stats_rep_stride = rep_stride;
   a.in = dy; a.w = wt; a.addend = addend; a.addmask = addmask; a.out_f32 = out_f32; a.out_b16 = out_b16;
   a.gate = gate; a.bnx = bnx; a.stats = gsums; a.stats_f32 = stats_f32 ? 1 : 0;
@@ -671,6 +678,17 @@ static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf
   for (int t = 0; t < a.ntaps; ++t) a.tap[t] = a.ctap[0][t];
   if (a.nclass == 1) a.nclass = 0;   // a single class is the plain form
   return launch_conv_gather(a, s);
+}
+
+size_t conv_scratch_bytes(const ConvShape& c) {
+  const GatherConvArgs f = forward_args(c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
+  const size_t forward = conv_gather_wide_applies(f) ? conv_gather_wide_scratch_bytes(f) : 0;
+  if (c.stride != 1) return forward;
+  GatherConvArgs a{};   // the data gradient
+  a.N = c.N; a.Hi = a.OHf = c.Ho(); a.Wi = a.OWf = c.Wo(); a.Ci = c.Co; a.Co = a.w_rows = c.Cip; a.Kw = c.T * c.Co;
+  a.OH = c.Hi; a.OW = c.Wi; a.in_stride = a.out_stride = 1; a.ntaps = c.T;
+  for (int t = 0; t < c.T; ++t) a.tap[t] = c.T == 9 ? pack_tap(1 - t / 3, 1 - t % 3, t) : pack_tap(0, 0, 0);
+  return std::max(forward, conv_gather_wide_applies(a) ? conv_gather_wide_scratch_bytes(a) : 0);
 }
 
 // A 1x1 convolution with unit stride does not see the image: its pixels are one long list, and the weight-gradient

@@ -16,6 +16,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <type_traits>
+#include <algorithm>
 #include <utility>
 
 namespace fdg {
@@ -33,6 +34,94 @@ __device__ __forceinline__ void dma16(const void* gsrc, void* lds_wave_base) {
 __device__ __forceinline__ int xcd_consecutive(int block, int total) {
   const int base = total >> 3, rem = total & 7, x = block & 7, q = block >> 3;
   return x * base + (x < rem ? x : rem) + q;
+}
+
+// A contraction dealt to several workgroups where whole tiles would leave much of the chip idle: workgroup part * tiles + t takes
+// the channel blocks part * blocks / parts .. (part + 1) * blocks / parts - 1 of tile t and writes its sum, [128 pixels][BN
+// channels] in fp32, to a slot of its own; conv_split_finish_kernel adds a tile's slots in the order of the contraction and does
+// the output stage.  A launch of its own because the chip's L2 caches do not see each other's lines: with the last workgroup of a
+// tile adding the slots, behind fences or with device-scope accesses, a launch took 58 or 20 us more instead of 7.  Equal ranges
+// over the tiles laid end to end (no workgroup idle, but some with the ends of two tiles) were slower too: a second beginning and
+// output stage is 9 us, two channel blocks.
+struct SplitParts {
+  int parts;       // 1: a workgroup takes a whole tile
+  float* partial;
+};
+
+// ROWS pixels x BN channels of a tile, a float4 of a pixel to a thread.  Bound by memory: the slots are read once, and what the
+// output stage reads is requested with them.
+template <int BN>
+__global__ __launch_bounds__(8 * BN / 4) void conv_split_finish_kernel(GatherConvArgs a, SplitParts split, int n_tiles) {
+  constexpr int ROWS = 16, UNITS = BN / 4, THREADS = 8 * UNITS, R = ROWS / 8;
+  const int t = blockIdx.x / (128 / ROWS), row0 = blockIdx.x % (128 / ROWS) * ROWS, tiles = gridDim.x / (128 / ROWS);
+  const int m0 = (t / n_tiles) * 128 + row0, c0 = (t % n_tiles) * BN, Mtot = a.N * a.OH * a.OW;
+  if (m0 >= Mtot) return;
+  const int un = threadIdx.x % UNITS, c = c0 + un * 4;
+  bool ok[R];
+  size_t o[R];
+  f32x4 v[R], ad[R];
+  uint2 mk[R], gt[R], bx[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int m = m0 + r * 8 + threadIdx.x / UNITS;
+    ok[r] = m < Mtot && c < a.Co;
+    o[r] = ok[r] ? (size_t)m * a.Co + c : 0;   // unit strides: the output grid is the input grid
+    v[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (a.addend) ad[r] = *reinterpret_cast<const f32x4*>(a.addend + o[r]);
+    if (a.addend && a.addmask) mk[r] = *reinterpret_cast<const uint2*>(a.addmask + o[r]);
+    if (a.gate) gt[r] = *reinterpret_cast<const uint2*>(a.gate + o[r]);
+    if (a.bnx) bx[r] = *reinterpret_cast<const uint2*>(a.bnx + o[r]);
+  }
+  const f32x4* slot = reinterpret_cast<const f32x4*>(split.partial) + (size_t)t * (128 * UNITS) + (size_t)row0 * UNITS + threadIdx.x;
+#pragma unroll 4
+  for (int k = 0; k < split.parts; ++k)
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] += slot[(size_t)k * tiles * (128 * UNITS) + r * THREADS];
+  f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (!ok[r]) continue;
+    if (a.addend) {
+      if (a.addmask) {
+        if (!(bf16_lo(mk[r].x) > 0.f)) ad[r][0] = 0.f;
+        if (!(bf16_hi(mk[r].x) > 0.f)) ad[r][1] = 0.f;
+        if (!(bf16_lo(mk[r].y) > 0.f)) ad[r][2] = 0.f;
+        if (!(bf16_hi(mk[r].y) > 0.f)) ad[r][3] = 0.f;
+      }
+      v[r] += ad[r];
+    }
+    if (a.gate) {
+      if (!(bf16_lo(gt[r].x) > 0.f)) v[r][0] = 0.f;
+      if (!(bf16_hi(gt[r].x) > 0.f)) v[r][1] = 0.f;
+      if (!(bf16_lo(gt[r].y) > 0.f)) v[r][2] = 0.f;
+      if (!(bf16_hi(gt[r].y) > 0.f)) v[r][3] = 0.f;
+    }
+    const uint2 packed = make_uint2(pack_bf16x2(v[r][0], v[r][1]), pack_bf16x2(v[r][2], v[r][3]));
+    if (a.out_f32) *reinterpret_cast<f32x4*>(a.out_f32 + o[r]) = v[r];
+    if (a.out_b16) *reinterpret_cast<uint2*>(a.out_b16 + o[r]) = packed;
+    if (a.stats) {   // of the bf16 values, as in store_rows32
+      const f32x4 q = {bf16_lo(packed.x), bf16_hi(packed.x), bf16_lo(packed.y), bf16_hi(packed.y)};
+      s1 += q;
+      s2 += q * (a.bnx ? f32x4{bf16_lo(bx[r].x), bf16_hi(bx[r].x), bf16_lo(bx[r].y), bf16_hi(bx[r].y)} : q);
+    }
+  }
+  if (a.stats) {
+    __shared__ f32x4 red[2][THREADS];
+    red[0][threadIdx.x] = s1;
+    red[1][threadIdx.x] = s2;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * BN; i += THREADS) {
+      const int which = i / BN, cl = i % BN;
+      if (c0 + cl >= a.Co) continue;
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) sum += red[which][k * UNITS + (cl >> 2)][cl & 3];
+      stat_add(a.stats + (size_t)(blockIdx.x % kStatReplicas) * a.stats_rep_stride, a.Co, which, c0 + cl, sum);
+    }
+  }
 }
 
 // s_waitcnt vmcnt(n) only (expcnt and lgkmcnt left at "no wait")
@@ -498,7 +587,7 @@ __global__ __launch_bounds__(256) void conv_gather_pipe_kernel(GatherConvArgs a,
 // tensor: its 16-byte units past the last channel are loaded from the zero word, for the patch and the weights alike,
 // which costs every load of such a layer a per-lane address select (the other layers keep the uniform-base form).
 template <int BN, int PR, int WS, bool KTAIL>
-__global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m_tiles, int n_tiles) {
+__global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m_tiles, int n_tiles, SplitParts split) {
   constexpr int BM = 128, ROWB = 128;
   static_assert(BN % 32 == 0 && PR % 32 == 0, "whole DMA instructions and 32x32 blocks");
   constexpr int JX = PR / 32, JW = BN / 32;
@@ -516,9 +605,17 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
   const int Mtot = a.N * a.OH * a.OW;
   const int W = a.Wi, H = a.Hi;
 
-  int t = blockIdx.x;
-  const int total = m_tiles * n_tiles;
-  if ((total & 7) == 0) t = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  const int total = m_tiles * n_tiles, blocks = (a.Ci + 63) >> 6;   // channel blocks of the whole contraction
+  int t = blockIdx.x, c_lo = 0, cpc = blocks;                       // those contracted here: cpc from c_lo on
+  if (split.parts > 1) {
+    t = xcd_consecutive(blockIdx.x, gridDim.x);
+    const int part = t / total;
+    t -= part * total;
+    c_lo = part * blocks / split.parts;
+    cpc = (part + 1) * blocks / split.parts - c_lo;
+  } else if ((total & 7) == 0) {
+    t = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  }
   const int m0 = (t / n_tiles) * BM, c0 = (t % n_tiles) * BN;
 
   if (tid < 32)   // the zero rows of both patch buffers; visible after the first barrier
@@ -547,7 +644,7 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
   int tko[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) tko[i] = (a.tap[i] >> 16) * a.Ci * 2;   // byte offset of the tap's k block in a weight row
-  const int cpc = (a.Ci + 63) >> 6;   // channel blocks
+  const int tail = blocks - 1 - c_lo;   // where the last channel block of the contraction comes among those here
   // KTAIL: bit j (patch loads) / bit 16 + j (weight loads): this lane's unit exists in the last channel block
   unsigned tail_ok = 0;
   uint32_t zero_lo = 0, zero_hi = 0;
@@ -556,13 +653,13 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
     for (int j = 0; j < JX; ++j) {
       const int p = 8 * (4 * j + wave) + (lane >> 3);
       const int u = (lane & 7) ^ ((p >> 1) & 7);
-      if ((cpc - 1) * 64 + u * 8 < a.Ci) tail_ok |= 1u << j;
+      if ((blocks - 1) * 64 + u * 8 < a.Ci) tail_ok |= 1u << j;
     }
 #pragma unroll
     for (int j = 0; j < JW; ++j) {
       const int row = 8 * (4 * j + wave) + (lane >> 3);
       const int u = (lane & 7) ^ ((row >> 1) & 7);
-      if ((cpc - 1) * 64 + u * 8 < a.Ci) tail_ok |= 1u << (16 + j);
+      if ((blocks - 1) * 64 + u * 8 < a.Ci) tail_ok |= 1u << (16 + j);
     }
     const uint64_t z = (uint64_t)g_zero_word;
     zero_lo = (uint32_t)z; zero_hi = (uint32_t)(z >> 32);
@@ -571,10 +668,10 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
   static_assert(JX <= 16 && JW <= 16, "bits of tail_ok");
 
   auto issue_x_one = [&](int j, int c) {
-    const char* base = reinterpret_cast<const char*>(a.in) + (size_t)c * 128;
+    const char* base = reinterpret_cast<const char*>(a.in) + (size_t)(c_lo + c) * 128;
     unsigned char* dst = smem + (c & 1) * XBYTES + (8 * (4 * j + wave)) * ROWB;
     if (KTAIL) {
-      const bool ok = c != cpc - 1 || ((tail_ok >> j) & 1u);
+      const bool ok = c != tail || ((tail_ok >> j) & 1u);
       const uint64_t pa = (uint64_t)(base + (size_t)xoff[j]);
       const uint32_t lo = ok ? (uint32_t)pa : zero_lo, hi = ok ? (uint32_t)(pa >> 32) : zero_hi;
       dma16((const char*)(((uint64_t)hi << 32) | lo), dst);
@@ -584,10 +681,10 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
   };
   // cblock: the channel block the weights belong to
   auto issue_w_one = [&](int j, int slot, int kbyte, int cblock) {
-    const char* base = reinterpret_cast<const char*>(a.w) + (size_t)kbyte;
+    const char* base = reinterpret_cast<const char*>(a.w) + (size_t)(kbyte + c_lo * 128);
     unsigned char* dst = smem + 2 * XBYTES + slot * WBYTES + (8 * (4 * j + wave)) * ROWB;
     if (KTAIL) {
-      const bool ok = cblock != cpc - 1 || ((tail_ok >> (16 + j)) & 1u);
+      const bool ok = cblock != tail || ((tail_ok >> (16 + j)) & 1u);
       const uint64_t pa = (uint64_t)(base + (size_t)woff[j]);
       const uint32_t lo = ok ? (uint32_t)pa : zero_lo, hi = ok ? (uint32_t)(pa >> 32) : zero_hi;
       dma16((const char*)(((uint64_t)hi << 32) | lo), dst);
@@ -797,7 +894,15 @@ __global__ __launch_bounds__(256) void conv_patch_kernel(GatherConvArgs a, int m
   chunk_body(cpc - 1, std::true_type{});
 
   wait_vmcnt<0>();
-  combine_and_store32<FN, BN>(a, acc, m0, c0, wave_m, wk, lane, smem);
+  GatherConvArgs b = a;
+  int m_out = m0, c_out = c0;
+  if (split.parts > 1) {   // the slot as an image of one row of 128 pixels
+    b.N = b.OH = b.OHf = 1; b.OW = b.OWf = BM; b.Co = BN;
+    b.addend = nullptr; b.addmask = b.gate = b.bnx = nullptr; b.stats = nullptr; b.out_b16 = nullptr;
+    b.out_f32 = split.partial + (size_t)((c_lo * split.parts + blocks - 1) / blocks * total + t) * (BM * BN);
+    m_out = c_out = 0;
+  }
+  combine_and_store32<FN, BN>(b, acc, m_out, c_out, wave_m, wk, lane, smem);
 }
 
 // The patch form on tiles of 256 pixels with EIGHT waves, two per SIMD, for layers whose 128-pixel tiles would need
@@ -1093,6 +1198,25 @@ static bool conv_patch_applies(const GatherConvArgs& a) {
   return true;
 }
 
+// Parts of the contraction of a patch launch: as many as fill one round of workgroups, where that shortens the longest workgroup
+// by 896 = 7 x 128 (channel block, output channel) units.  A block of 160 channels is 3.9 us of a workgroup, the slots and the
+// second launch cost 11 us, and what the tiles leave idle is not all lost: the weight gradients of the other stream run there.
+// WRN-28-10 top module, batch 8: 1511 -> 1168 us a step, 37: 1603 -> 1488 (76 tiles of 640 -> 640 at 8 x 8 in three parts: 48.8 ->
+// 28.4 + 8.8 us); beyond the line, batch 64 (128 tiles in two parts): 1821 -> 1917; ResNet-18 top module, batch 32 (64 tiles of 512
+// -> 512, 8 blocks in four parts): 861 -> 883, batch 8 (within): 768 -> 721; bottleneck blocks of 4 blocks, batch 20: 765 -> 812.
+static int patch_parts(const GatherConvArgs& a, int BN) {
+  const int tiles = (a.N * a.OH * a.OW + 127) / 128 * ((a.Co + BN - 1) / BN), blocks = (a.Ci + 63) / 64;
+  int parts = std::min(256 / tiles, blocks);
+  if (parts <= 1) return 1;
+  const int longest = (blocks + parts - 1) / parts;
+  parts = (blocks + longest - 1) / longest;
+  return (blocks - longest) * BN >= 7 * 128 ? parts : 1;
+}
+static size_t patch_parts_bytes(const GatherConvArgs& a, int BN) {
+  const int parts = patch_parts(a, BN), tiles = (a.N * a.OH * a.OW + 127) / 128 * ((a.Co + BN - 1) / BN);
+  return parts > 1 ? (size_t)parts * tiles * 128 * BN * sizeof(float) : 0;
+}
+
 template <int BN, int PR, bool KTAIL>
 static hipError_t run_patch_k(const GatherConvArgs& a, hipStream_t s) {
   constexpr int WS = 5;
@@ -1105,12 +1229,17 @@ static hipError_t run_patch_k(const GatherConvArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured = true;
   }
-  const int Mtot = a.N * a.OH * a.OW;
-  const int m_tiles = (Mtot + 127) / 128, n_tiles = (a.Co + BN - 1) / BN;
-  static char name[64];
-  if (!name[0]) snprintf(name, sizeof(name), KTAIL ? "conv_patch_kernel<%d, %d, %d, true>" : "conv_patch_kernel<%d, %d, %d>", BN, PR, WS);
+  const int m_tiles = (a.N * a.OH * a.OW + 127) / 128, n_tiles = (a.Co + BN - 1) / BN, tiles = m_tiles * n_tiles;
+  SplitParts split{patch_parts(a, BN), a.scratch.partial};
+  if (!split.partial || a.scratch.bytes < patch_parts_bytes(a, BN)) split.parts = 1;
+  static char names[2][64];
+  char* name = names[split.parts > 1];
+  if (!name[0]) snprintf(name, sizeof(names[0]), "conv_patch_kernel<%d, %d, %d%s>%s", BN, PR, WS, KTAIL ? ", true" : "", split.parts > 1 ? " in parts" : "");
   note_kernel(name);
-  hipLaunchKernelGGL((conv_patch_kernel<BN, PR, WS, KTAIL>), dim3(m_tiles * n_tiles), dim3(256), lds, s, a, m_tiles, n_tiles);
+  hipLaunchKernelGGL((conv_patch_kernel<BN, PR, WS, KTAIL>), dim3(tiles * split.parts), dim3(256), lds, s, a, m_tiles, n_tiles, split);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || split.parts == 1) return e;
+  hipLaunchKernelGGL(conv_split_finish_kernel<BN>, dim3(tiles * 8), dim3(8 * BN / 4), 0, s, a, split, n_tiles);
   return hipGetLastError();
 }
 
@@ -1155,6 +1284,10 @@ static hipError_t run_patch_rows(const GatherConvArgs& a, hipStream_t s) {
   if (rows <= 160) return run_patch<BN, 160>(a, s);
   if (rows <= 192) return run_patch<BN, 192>(a, s);
   return run_patch<BN, 224>(a, s);
+}
+
+size_t conv_gather_wide_scratch_bytes(const GatherConvArgs& a) {
+  return conv_patch_applies(a) ? patch_parts_bytes(a, a.Co % 160 == 0 ? 160 : 128) : 0;
 }
 
 bool conv_gather_wide_applies(const GatherConvArgs& a) {

@@ -56,6 +56,12 @@ __device__ __forceinline__ double stat_value(long long hi, long long lo, long lo
 }
 #endif
 
+// Device memory with which a wide convolution of few tiles may deal the contraction of a tile to several workgroups: room for
+// their partial sums.  Launches on one stream may share it.
+struct ConvScratch {
+  float* partial;        // nullptr: none
+  size_t bytes;
+};
 struct GatherConvArgs {
   const bf16_t* in;      // [N, Hi, Wi, Ci] bf16, Ci % 8 == 0
   const bf16_t* w;       // [w_rows, Kw] bf16, k contiguous
@@ -118,6 +124,7 @@ struct GatherConvArgs {
   float* tr_run_var;
   float* tr_dgamma;
   float* tr_dbeta;
+  ConvScratch scratch;   // optional, wide kernels only
   float tr_eps, tr_momentum;
   int tr_rep_stride;     // stat_t elements between the copies of tr_sums and tr_bsums (0: one copy)
 };
@@ -183,7 +190,7 @@ struct ConvShape {
 // stats (optional, [2*Co], pre-zeroed): += per-channel sum and sum of squares of the bf16-rounded result,
 // i.e. the batch-norm statistics of the tensor just produced
 hipError_t conv_forward(const ConvShape& c, const bf16_t* x, const bf16_t* w, const float* addend, float* out_f32,
-                        bf16_t* out_b16, stat_t* stats, hipStream_t s, int stats_rep_stride = 0);
+                        bf16_t* out_b16, stat_t* stats, hipStream_t s, int stats_rep_stride = 0, const ConvScratch& scratch = {});
 // The same convolution of relu(batchnorm(x_raw)) with the batch-norm pass done on the patch in LDS (narrow layers, see
 // GatherConvArgs::tr_mode = 1): act_out receives relu(batchnorm(x_raw)) in bf16 as a pass of its own would have written
 // it; run_mean / run_var (optional) take one running-statistics step.  conv_forward_bn_applies says where.
@@ -230,7 +237,7 @@ hipError_t conv_dgrad_after_bn(const ConvShape& c, const ConvInputBnBwd& bn, con
                                float* out_f32, bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
 // dx[N,Hi,Wi,Cip] = conv^T(dy[N,Ho,Wo,Co], wt[Cip][T][Co]) (+ addend, optionally only where addmask > 0)
 hipError_t conv_dgrad(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
-                      const bf16_t* addmask, float* out_f32, bf16_t* out_b16, hipStream_t s);
+                      const bf16_t* addmask, float* out_f32, bf16_t* out_b16, hipStream_t s, const ConvScratch& scratch = {});
 // The same, ending in the gate of the ReLU below and the two sums of the batch norm below it:
 //   dx = gate > 0 ? dgrad + addend : 0;  gsums[c] += sum bf16(dx[.., c]);  gsums[Cip + c] += sum bf16(dx[.., c]) * bnx[.., c].
 // Only where conv_dgrad_gates(c) (the wide kernels); hipErrorInvalidValue otherwise.
@@ -249,10 +256,12 @@ bool conv_dgrad_gates(const ConvShape& c);
 bool conv_dgrad_pair_applies(const ConvShape& c, const ConvShape& cp);
 hipError_t conv_dgrad_gated_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
                                  const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
-                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
+                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0, const ConvScratch& scratch = {});
 hipError_t conv_dgrad_gated(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
                             const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
-                            int gsums_rep_stride = 0);
+                            int gsums_rep_stride = 0, const ConvScratch& scratch = {});
+// bytes of scratch that the calls above can use for this layer, forward and data gradient (0: none)
+size_t conv_scratch_bytes(const ConvShape& c);
 // dw[Co][T][Ci] (+)= sum over pixels of dy * x.  overwrite = false: accumulated into dw (fp32 atomics where the
 // pixel dimension is split), dw zeroed by the caller;  overwrite = true: dw is written, whatever it held.
 // scratch (optional): device memory for the partial sums of the pixel splits; without it they are added

@@ -83,6 +83,7 @@ struct Plan {
   size_t o_wscratch = 0, wscratch_bytes = 0;   // partial sums of the split weight gradient
   int wscratch_buffers = 1;
   size_t o_dwscratch = 0, dwscratch_bytes = 0; // the same for depthwise convolutions (they run on the caller's stream)
+  size_t o_split[2] = {0, 0}, split_bytes = 0; // partial sums of the wide convolutions that split their tiles: the forward's and the backward's
   size_t o_col = 0, o_colb = 0, col_bytes = 0; // operand rows of a 7x7 stem (launch_im2col7): the forward's and the backward's copy
   size_t total = 0;
   // layout of a caller-provided trace buffer (parity accessors): per layer the fp32 output of the forward and the fp32
@@ -396,6 +397,10 @@ bool build_plan(const fdg_module_desc* desc, int save_mode, Plan& p, fdg_status*
   p.o_dwscratch = take(p.dwscratch_bytes);
   p.o_col = take(p.col_bytes);
   p.o_colb = (desc->delay >= 1 && !p.replay) ? take(p.col_bytes) : p.o_col;   // as o_TPB: the two may run on two streams
+  for (const ConvInfo& ci : p.convs)
+    if (!ci.depthwise) p.split_bytes = std::max(p.split_bytes, conv_scratch_bytes(ci.sh));
+  p.o_split[0] = take(p.split_bytes);
+  p.o_split[1] = (desc->delay >= 1 && !p.replay) ? take(p.split_bytes) : p.o_split[0];   // as o_TPB
   p.total = o;
   {
     size_t to = 0;
@@ -495,6 +500,9 @@ struct fdg_module {
   bf16_t* T(int i) const { return reinterpret_cast<bf16_t*>(ws + p.o_T[i]); }
   float* TP() const { return reinterpret_cast<float*>(ws + p.o_TP); }
   // projection-shortcut temporary of the backward: its own where forward and backward may overlap
+  ConvScratch split(int backward) const {
+    return p.split_bytes ? ConvScratch{reinterpret_cast<float*>(ws + p.o_split[backward]), p.split_bytes} : ConvScratch{};
+  }
   float* TPB() const { return reinterpret_cast<float*>(ws + ((p.d.delay >= 1 && !p.replay) ? p.o_TPB : p.o_TP)); }
 };
 
@@ -587,7 +595,7 @@ hipError_t mconv_forward(const fdg_module* m, const ConvInfo& c, const bf16_t* x
   const double bytes = 2 * conv_in_elems(c.sh) + 2 * conv_w_elems(c.sh) +
                        conv_out_elems(c.sh) * ((addend ? 4 : 0) + (out_f32 ? 4 : 0) + (out_b16 ? 2 : 0));
   ProfScope ps(m, PC_CONV_FWD, conv_flops(c.sh), bytes, s);
-  const hipError_t e = conv_forward(c.sh, x, w, addend, out_f32, out_b16, stats, s, m->p.stat_rep);
+  const hipError_t e = conv_forward(c.sh, x, w, addend, out_f32, out_b16, stats, s, m->p.stat_rep, m->split(0));
   ps.label(c.sh);
   return e;
 }
@@ -650,7 +658,7 @@ hipError_t mconv_dgrad(const fdg_module* m, const ConvInfo& c, const bf16_t* dy,
   const double bytes = 2 * conv_out_elems(c.sh) + 2 * conv_w_elems(c.sh) +
                        conv_in_elems(c.sh) * ((addend ? 4 : 0) + (addmask ? 2 : 0) + (out_f32 ? 4 : 0) + (out_b16 ? 2 : 0));
   ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c.sh), bytes, s);
-  const hipError_t e = conv_dgrad(c.sh, dy, wt, addend, addmask, out_f32, out_b16, s);
+  const hipError_t e = conv_dgrad(c.sh, dy, wt, addend, addmask, out_f32, out_b16, s, m->split(1));
   ps.label(c.sh);
   return e;
 }
@@ -809,7 +817,7 @@ hipError_t gated_dgrad(const fdg_module* m, const ConvInfo& c, const bf16_t* dy,
   if (hipError_t e = side_wait_readers(m, g, s); e != hipSuccess) return e;
   const double bytes = 2 * conv_out_elems(c.sh) + 2 * conv_w_elems(c.sh) + conv_in_elems(c.sh) * ((dgrad_addend ? 4 : 0) + 2 + 2 + 2);
   ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c.sh), bytes, s);
-  const hipError_t e = conv_dgrad_gated(c.sh, dy, wt, dgrad_addend, gate, x, m->bsums(b), nullptr, g, s, m->p.stat_rep);
+  const hipError_t e = conv_dgrad_gated(c.sh, dy, wt, dgrad_addend, gate, x, m->bsums(b), nullptr, g, s, m->p.stat_rep, m->split(1));
   ps.label(c.sh);
   return e;
 }

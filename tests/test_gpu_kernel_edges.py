@@ -2,7 +2,10 @@
 checks of tests/test_gpu_kernels.py (same oracle, same bars), with the kernel that ran named."""
 import pytest
 
+import fdg_workloads as W
+from fdg_workloads import Layer, ModuleSpec
 from tests import test_gpu_kernels as TK
+from tests import test_gpu_step_dispatch as TD
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +28,28 @@ def test_64_channels_over_many_pixels(case, kernel):
     for check in (TK.test_conv_fwd, TK.test_conv_dgrad, TK.test_data_gradient_that_feeds_the_layer_below):
         check(case)
         assert K.fdgk_last_kernel() == kernel
+
+
+# Wide 3x3 convolutions of few tiles: the contraction in parts, added up by a launch of its own that does the output stage.  Whole
+# parts and parts of two lengths, ragged pixel and channel tiles, a partly filled last channel block, both tile widths; forward, and
+# the data gradients with gate and sums, with an addend, and plain, as a step of a module makes them
+@pytest.mark.parametrize("kind, c_in, c_out, n, h, w, kernel", [
+    (W.BASIC_PREACT, 640, 640, 5, 7, 9, "conv_patch_kernel<160, 160, 5> in parts"),
+    (W.BASIC_PREACT, 584, 640, 3, 9, 17, "conv_patch_kernel<160, 192, 5> in parts"),
+    (W.BASIC_POSTACT, 640, 640, 9, 16, 8, "conv_patch_kernel<160, 160, 5> in parts"),
+    (W.BASIC_PREACT, 568, 584, 2, 5, 30, "conv_patch_kernel<128, 192, 5, true> in parts"),
+    (W.BASIC_PREACT, 512, 512, 4, 8, 8, "conv_patch_kernel<128, 160, 5> in parts"),
+    (W.BASIC_PREACT, 512, 512, 17, 8, 8, "conv_patch_kernel<128, 160, 5>"),   # 36 tiles: eight blocks in fewer than eight parts
+])
+def test_contraction_in_parts(kind, c_in, c_out, n, h, w, kernel):
+    from paper_1906_09108_amd import FdgModule, kernels as K
+    import torch as t
+    spec = ModuleSpec(n, c_in, h, w, [Layer(kind, c_in, c_out, 1)], delay=1, is_bottom=False, beta=0.5, name="parts", **TD.H)
+    TD.check(f"parts {c_in}>{c_out} {n}x{h}x{w}", spec)
+    m = FdgModule(spec)
+    m.set_params(W.make_params(spec, 0))
+    x = t.zeros((n, c_in, h, w), device="cuda")
+    m.forward(x, None, m.new_output())
+    t.cuda.synchronize()
+    assert K.fdgk_last_kernel() == kernel
+    m.close()
