@@ -172,6 +172,7 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
   uint64_t p_gate = (uint64_t)a.gate, p_bnx = (uint64_t)a.bnx;
   int Co = a.Co;
   int want_stats = a.stats != nullptr;
+  const float gate_hi = a.gate_hi > 0.f ? a.gate_hi : __builtin_nanf("");   // nothing is >= NaN
   asm volatile("" : "+v"(p_addend), "+v"(p_mask), "+v"(p_f32), "+v"(p_b16), "+v"(Co), "+v"(want_stats), "+v"(p_gate), "+v"(p_bnx));
   float s1[PERIOD][4], s2[PERIOD][4];
 #pragma unroll
@@ -257,6 +258,12 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
         if (!(bf16_hi(gt[k][0]) > 0.f)) v[k][1] = 0.f;
         if (!(bf16_lo(gt[k][1]) > 0.f)) v[k][2] = 0.f;
         if (!(bf16_hi(gt[k][1]) > 0.f)) v[k][3] = 0.f;
+        if (F32S) {   // the upper end of a ReLU6
+          if (bf16_lo(gt[k][0]) >= gate_hi) v[k][0] = 0.f;
+          if (bf16_hi(gt[k][0]) >= gate_hi) v[k][1] = 0.f;
+          if (bf16_lo(gt[k][1]) >= gate_hi) v[k][2] = 0.f;
+          if (bf16_hi(gt[k][1]) >= gate_hi) v[k][3] = 0.f;
+        }
       }
     }
 #pragma unroll
@@ -405,6 +412,9 @@ size_t conv_gather_wide_scratch_bytes(const GatherConvArgs& a);   // what that l
 // into at least 128 (conv_wide_kernels.hip).  No gate, no bnx.
 bool conv_gather_thin_applies(const GatherConvArgs& a);
 hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s);
+// 1x1 layers whose output stage takes a gate with an upper end and the sums of the fp32 values (conv_dgrad_with_sums)
+bool conv_gather_feeding_applies(const GatherConvArgs& a);
+hipError_t launch_conv_gather_feeding(const GatherConvArgs& a, hipStream_t s);
 // The wide-channel weight gradient: output and input channels multiples of 160, output width dividing 64.
 bool conv_wgrad_wide_applies(const WgradArgs& a);
 hipError_t launch_conv_wgrad_wide(const WgradArgs& a, hipStream_t s);

@@ -521,6 +521,24 @@ hipError_t conv_dgrad_feeding_next(const ConvShape& c, const bf16_t* dy, const b
   return conv_dgrad_impl(c, dy, wt, addend, addmask, gate, bnx, gsums, out_f32, out_b16, s, /*stats_f32=*/true, gsums_rep_stride);
 }
 
+static GatherConvArgs dgrad1x1_args(const ConvShape& c) {
+  GatherConvArgs a{};
+  a.N = c.N; a.Hi = a.OH = a.OHf = c.Hi; a.Wi = a.OW = a.OWf = c.Wi; a.in_stride = a.out_stride = 1;
+  a.Ci = a.Kw = c.Co; a.Co = a.w_rows = c.Cip;
+  a.ntaps = 1; a.tap[0] = pack_tap(0, 0, 0);
+  return a;
+}
+bool conv_dgrad_sums_applies(const ConvShape& c) { return c.T == 1 && c.stride == 1 && conv_gather_feeding_applies(dgrad1x1_args(c)); }
+hipError_t conv_dgrad_with_sums(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
+                                float gate_hi, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
+                                int gsums_rep_stride) {
+  if (!bnx || !gsums || !out_f32 || !conv_dgrad_sums_applies(c)) return hipErrorInvalidValue;
+  GatherConvArgs a = dgrad1x1_args(c);
+  a.in = dy; a.w = wt; a.addend = addend; a.gate = gate; a.gate_hi = gate_hi; a.bnx = bnx;
+  a.stats = gsums; a.stats_f32 = 1; a.stats_rep_stride = gsums_rep_stride; a.out_f32 = out_f32; a.out_b16 = out_b16;
+  return launch_conv_gather_feeding(a, s);
+}
+
 // The gate and the sums are taken where the wide kernels or the narrow kernel run the whole data gradient.
 bool conv_dgrad_gates(const ConvShape& c) {
   GatherConvArgs a{};

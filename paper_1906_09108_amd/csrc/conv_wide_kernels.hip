@@ -1380,22 +1380,22 @@ bool conv_gather_thin_applies(const GatherConvArgs& a) {
   return a.Ci % 64 == 0 && a.Ci >= 128 && a.Co >= 40 && a.Co <= 96 && tiles >= 128;
 }
 
-template <int BN, int STAGES, bool KTAIL>
+template <int BN, int STAGES, bool KTAIL, bool F32S = false>
 static hipError_t run_thin(const GatherConvArgs& a, hipStream_t s) {
   constexpr size_t lds = gather_dma_lds_bytes(BN, STAGES);
   static_assert(lds <= 160 * 1024, "LDS of one compute unit");
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, false>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, F32S>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     configured = true;
   }
   static char name[64];
-  if (!name[0]) snprintf(name, sizeof(name), "conv_gather_dma_pair_kernel<%d, %d>", BN, STAGES);
+  if (!name[0]) snprintf(name, sizeof(name), F32S ? "conv_gather_dma_pair_kernel<%d, %d, feeding>" : "conv_gather_dma_pair_kernel<%d, %d>", BN, STAGES);
   note_kernel(name);
   const int m_tiles = (a.N * a.OH * a.OW + 127) / 128, n_tiles = (a.Co + BN - 1) / BN;
-  hipLaunchKernelGGL((conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, false>), dim3(m_tiles * n_tiles), dim3(256), lds, s, a, m_tiles, n_tiles);
+  hipLaunchKernelGGL((conv_gather_dma_pair_kernel<BN, STAGES, KTAIL, F32S>), dim3(m_tiles * n_tiles), dim3(256), lds, s, a, m_tiles, n_tiles);
   return hipGetLastError();
 }
 
@@ -1404,6 +1404,22 @@ hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s) {
   if (a.Co >= 128) return run_thin<128, 2, true>(a, s);   // two workgroups to a compute unit: most of the time is output
   if (a.Co <= 64) return run_thin<64, 3, false>(a, s);
   return run_thin<96, 4, false>(a, s);
+}
+
+// The data gradients of inverted residual blocks end in a gate and the sums of a batch-norm backward: the same instantiations with
+// the output stage that sums fp32 values, for any number of pixels (a few tiles leave the chip as idle either way, and the pass
+// over the fp32 result that is saved is a launch at least).  128 x 16 x 16, 64 -> 384: 22 + 19.4 for the pass -> 32.8 us.
+bool conv_gather_feeding_applies(const GatherConvArgs& a) {
+  if (a.nclass > 1 || a.ntaps != 1 || a.in_stride != 1 || a.w_rows != a.Co || a.Kw % 8 != 0) return false;
+  if (a.Hi >= 32768 || a.Wi >= 32768 || (long long)a.N * a.OH * a.OW >= (1ll << 30)) return false;
+  if (a.Co >= 128) return (a.Ci % 64 == 0 && a.Ci <= 1024) || (a.Ci % 8 == 0 && a.Ci > 64 && a.Ci < 128);
+  return a.Ci % 64 == 0 && a.Ci >= 128 && a.Co >= 40 && a.Co <= 96;
+}
+hipError_t launch_conv_gather_feeding(const GatherConvArgs& a, hipStream_t s) {
+  if (!conv_gather_feeding_applies(a) || !a.stats || !a.stats_f32 || !a.bnx || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
+  if (a.Co >= 128) return a.Ci % 64 == 0 ? run_thin<128, 2, false, true>(a, s) : run_thin<128, 2, true, true>(a, s);
+  if (a.Co <= 64) return run_thin<64, 3, false, true>(a, s);
+  return run_thin<96, 4, false, true>(a, s);
 }
 
 hipError_t launch_conv_gather_wide(const GatherConvArgs& a, hipStream_t s) {

@@ -76,6 +76,7 @@ struct GatherConvArgs {
                          // the squares -- with stats[c] the two sums the batch-norm backward needs
   int stats_rep_stride;  // stat_t elements between the copies of stats (0: one copy)
   int stats_f32;         // with bnx, narrow / generic output stage: the sums are of the fp32 values, not of the bf16 output
+  float gate_hi;         // > 0: the gate is closed where gate >= gate_hi, too (launch_conv_gather_feeding only)
   int N, Hi, Wi, Ci;
   int OH, OW, in_stride;
   int OHf, OWf, out_stride, ooh, oow;
@@ -247,6 +248,12 @@ bool conv_dgrad_feeds_next(const ConvShape& c);
 hipError_t conv_dgrad_feeding_next(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                    const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                    bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
+// Data gradient of a 1x1 layer in fp32 that ends in the two sums, of the fp32 values, of the batch-norm backward that follows, with
+// or without a gate in between: dx = addend + dgrad, zero unless 0 < gate (< gate_hi, if that is > 0).  conv_dgrad_sums_applies says where.
+bool conv_dgrad_sums_applies(const ConvShape& c);
+hipError_t conv_dgrad_with_sums(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
+                                float gate_hi, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
+                                int gsums_rep_stride);
 bool conv_dgrad_gates(const ConvShape& c);
 // conv_dgrad_gated of c (3x3, stride 2) with the data gradient of the 1x1 stride-2 projection cp beside it (same input
 // tensor, same output grid) added before the gate, in one launch:
@@ -378,6 +385,14 @@ hipError_t launch_dwconv3_fwd(const bf16_t* x, const bf16_t* wt, bf16_t* y, int 
 // dx (bf16) and / or dx_f32 (fp32), at least one
 hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int N, int H, int W, int C, int stride, hipStream_t s,
                                 float* dx_f32 = nullptr);
+// where the two below are the faster ones (H, W: of the convolution's input)
+bool dwconv3_sums_applies(int N, int H, int W, int C);
+// the forward with the batch-norm sums of its bf16 result
+hipError_t launch_dwconv3_fwd_sums(const bf16_t* x, const bf16_t* wt, bf16_t* y, stat_t* sums, int rep_stride, int N, int H, int W, int C,
+                                   int stride, hipStream_t s);
+// the data gradient in fp32 behind a gate (zero unless 0 < gate < gate_hi), with the sums of dx and dx * bnx
+hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const bf16_t* gate, float gate_hi, const bf16_t* bnx, float* dx,
+                                     stat_t* sums, int rep_stride, int N, int H, int W, int C, int stride, hipStream_t s);
 size_t dwconv3_wgrad_scratch_bytes(int N, int H, int W, int C, int stride);
 hipError_t launch_dwconv3_wgrad(const bf16_t* x, const bf16_t* dy, float* dw, float* scratch, size_t scratch_bytes, int N, int H, int W,
                                 int C, int stride, hipStream_t s);

@@ -985,8 +985,12 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
              *t_c3 = v.act(L.act[5]);
       FDG_TRY(mconv_forward(m, c1, cur_b, v.W(c1), nullptr, nullptr, t_c1, v.sums(b1), s));
       FDG_TRY(bn_apply(m, v, b1, t_c1, nullptr, nullptr, nullptr, nullptr, t_a1, replayed, s, /*relu6*/ 2));
-      FDG_TRY(launch_dwconv3_fwd(t_a1, v.Wt(c2), t_c2, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-      FDG_TRY(bn_stats(v, b2, t_c2, s));
+      if (dwconv3_sums_applies(N, L.Hi, L.Wi, c2.sh.Co)) {
+        FDG_TRY(launch_dwconv3_fwd_sums(t_a1, v.Wt(c2), t_c2, v.sums(b2), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
+      } else {
+        FDG_TRY(launch_dwconv3_fwd(t_a1, v.Wt(c2), t_c2, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
+        FDG_TRY(bn_stats(v, b2, t_c2, s));
+      }
       FDG_TRY(bn_apply(m, v, b2, t_c2, nullptr, nullptr, nullptr, nullptr, t_a2, replayed, s, /*relu6*/ 2));
       FDG_TRY(mconv_forward(m, c3, t_a2, v.W(c3), nullptr, nullptr, t_c3, v.sums(b3), s));
       const bool adds = L.stride == 1 && L.c_in == L.c_out;
@@ -1375,19 +1379,48 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
                    *t_c3 = v.act(L.act[5]);
       const bool adds = L.stride == 1 && L.c_in == L.c_out;
       // the block ends in a batch norm: nothing gates the incoming gradient
-      FDG_TRY(bn_backward(m, v, b3, m->G(cur), true, nullptr, t_c3, nullptr, nullptr, m->T(0), s));
+      if (fed_here) FDG_TRY(bn_backward_fed_from_above(m, v, b3, m->G(cur), t_c3, m->T(0), s));
+      else FDG_TRY(bn_backward(m, v, b3, m->G(cur), true, nullptr, t_c3, nullptr, nullptr, m->T(0), s));
       FDG_TRY(mconv_wgrad(m, c3, t_a2, m->T(0), s));
       // the gradients that go into a gate and a batch-norm backward stay in fp32 (a bf16 one, rounded again after that
       // backward, is rounded with a bias that the per-channel sums of this block's many pixels add up)
       float* gf = m->TPB();
-      FDG_TRY(mconv_dgrad(m, c3, m->T(0), v.Wt(c3), nullptr, nullptr, gf, nullptr, s));
-      FDG_TRY(bn_backward(m, v, b2, gf, true, t_a2, t_c2, nullptr, nullptr, m->T(0), s, 6.f));
+      if (conv_dgrad_sums_applies(c3.sh)) {
+        {
+          ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c3.sh), 2 * conv_out_elems(c3.sh) + 2 * conv_w_elems(c3.sh) + conv_in_elems(c3.sh) * (4 + 2 + 2), s);
+          const hipError_t e = conv_dgrad_with_sums(c3.sh, m->T(0), v.Wt(c3), nullptr, t_a2, 6.f, t_c2, m->bsums(b2), gf, nullptr, s, p.stat_rep);
+          ps.label(c3.sh);
+          FDG_TRY(e);
+        }
+        FDG_TRY(bn_backward_fed_from_above(m, v, b2, gf, t_c2, m->T(0), s));
+      } else {
+        FDG_TRY(mconv_dgrad(m, c3, m->T(0), v.Wt(c3), nullptr, nullptr, gf, nullptr, s));
+        FDG_TRY(bn_backward(m, v, b2, gf, true, t_a2, t_c2, nullptr, nullptr, m->T(0), s, 6.f));
+      }
       FDG_TRY(launch_dwconv3_wgrad(t_a1, m->T(0), m->grads() + c2.p_off, reinterpret_cast<float*>(m->ws + p.o_dwscratch),
                                    p.dwscratch_bytes, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-      FDG_TRY(launch_dwconv3_dgrad(m->T(0), v.Wt(c2), nullptr, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s, gf));
-      FDG_TRY(bn_backward(m, v, b1, gf, true, t_a1, t_c1, nullptr, nullptr, m->T(0), s, 6.f));
+      if (dwconv3_sums_applies(N, L.Hi, L.Wi, c2.sh.Co)) {
+        FDG_TRY(launch_dwconv3_dgrad_sums(m->T(0), v.Wt(c2), t_a1, 6.f, t_c1, gf, m->bsums(b1), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
+        FDG_TRY(bn_backward_fed_from_above(m, v, b1, gf, t_c1, m->T(0), s));
+      } else {
+        FDG_TRY(launch_dwconv3_dgrad(m->T(0), v.Wt(c2), nullptr, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s, gf));
+        FDG_TRY(bn_backward(m, v, b1, gf, true, t_a1, t_c1, nullptr, nullptr, m->T(0), s, 6.f));
+      }
       FDG_TRY(mconv_wgrad(m, c1, in_b, m->T(0), s));
-      if (need_dx) FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, G_out, GB_out, s));
+      // the layer below, if it is another such block, begins its backward with the batch norm it ends in: its sums come from here
+      if (need_dx && li > 0 && p.L[li - 1].kind == FDG_INVERTED_RESIDUAL && conv_dgrad_sums_applies(c1.sh)) {
+        const LayerPlan& B = p.L[li - 1];
+        ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh), 2 * conv_out_elems(c1.sh) + 2 * conv_w_elems(c1.sh) +
+                     conv_in_elems(c1.sh) * ((adds ? 4 : 0) + 2 + 4 + (GB_out ? 2 : 0)), s);
+        if (GB_out) FDG_TRY(side_wait_readers(m, GB_out, s));
+        const hipError_t e = conv_dgrad_with_sums(c1.sh, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, 0.f, v.act(B.act[5]),
+                                                  m->bsums(p.bns[B.bn[3]]), m->G(nxt), GB_out, s, p.stat_rep);
+        ps.label(c1.sh);
+        FDG_TRY(e);
+        fed = true;
+      } else if (need_dx) {
+        FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, G_out, GB_out, s));
+      }
     } else {  // pre-activation block: y = conv2(o2) + shortcut
       const ConvInfo &c1 = p.convs[L.conv[0]], &c2 = p.convs[L.conv[1]];
       const BnInfo &b1 = p.bns[L.bn[0]], &b2 = p.bns[L.bn[1]];
@@ -1425,7 +1458,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
     if (m->trace && need_dx) {
       FDG_TRY(hipMemcpyAsync(m->trace + p.tr_bwd[li], m->G(nxt), (size_t)N * L.Hi * L.Wi * round8(L.c_in) * 4,
                              hipMemcpyDeviceToDevice, s));
-      m->tr_gated[li] = fed ? 1 : 0;
+      m->tr_gated[li] = fed && p.L[li - 1].kind != FDG_INVERTED_RESIDUAL ? 1 : 0;   // an inverted block has no gate at its end
     }
     cur = nxt;
   }

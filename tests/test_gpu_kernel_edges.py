@@ -5,6 +5,7 @@ import pytest
 import fdg_workloads as W
 from fdg_workloads import Layer, ModuleSpec
 from tests import test_gpu_kernels as TK
+from tests import test_gpu_layerwise as LT
 from tests import test_gpu_step_dispatch as TD
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +54,19 @@ def test_contraction_in_parts(kind, c_in, c_out, n, h, w, kernel):
     t.cuda.synchronize()
     assert K.fdgk_last_kernel() == kernel
     m.close()
+
+
+# Inverted residual blocks: data gradients of the 1x1 layers that end in a gate and sums (every instantiation: 64 channels and a partly
+# filled block of 72 into the expanded tensor; 384, 576 and 432 channels down to 64, 96 and 72), the depthwise kernels with sums (a
+# partly filled block of channels, odd images, both strides, more and fewer cells than a round takes), blocks that feed the one below
+@pytest.mark.parametrize("channels, n, h, w", [
+    ([(64, 64, 1), (64, 96, 1), (96, 96, 1)], 3, 13, 11),
+    ([(64, 72, 2), (72, 72, 1), (72, 64, 2)], 2, 19, 23),
+    ([(24, 40, 1), (40, 64, 2), (64, 64, 1)], 5, 9, 12),
+    ([(96, 96, 1)], 1, 6, 6),
+])
+def test_inverted_blocks_with_sums(channels, n, h, w):
+    layers = [Layer(W.INVERTED_RESIDUAL, ci, co, s) for ci, co, s in channels]
+    spec = ModuleSpec(n, channels[0][0], h, w, layers, delay=1, is_bottom=False, beta=0.5, name="inverted", **TD.H)
+    print(f"case inverted {channels} {n}x{h}x{w}", flush=True)
+    LT._judge(LT._run(spec, seed=1, steps_after_warmup=2), f"inverted {channels[0][0]}-{channels[-1][1]} {n}x{h}x{w}")
