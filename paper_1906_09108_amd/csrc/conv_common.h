@@ -412,6 +412,9 @@ size_t conv_gather_wide_scratch_bytes(const GatherConvArgs& a);   // what that l
 // into at least 128 (conv_wide_kernels.hip).  No gate, no bnx.
 bool conv_gather_thin_applies(const GatherConvArgs& a);
 hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s);
+// the parity classes of a stride-2 data gradient into 40 .. 96 channels, with a second source
+bool conv_gather_thin_classes_applies(const GatherConvArgs& a);
+hipError_t launch_conv_gather_thin_classes(const GatherConvArgs& a, hipStream_t s);
 // 1x1 layers whose output stage takes a gate with an upper end and the sums of the fp32 values (conv_dgrad_with_sums)
 bool conv_gather_feeding_applies(const GatherConvArgs& a);
 hipError_t launch_conv_gather_feeding(const GatherConvArgs& a, hipStream_t s);
@@ -420,6 +423,7 @@ bool conv_wgrad_wide_applies(const WgradArgs& a);
 hipError_t launch_conv_wgrad_wide(const WgradArgs& a, hipStream_t s);
 // The same for channel counts that are multiples of 128: 128 x 128 blocks, contraction split over the waves.
 bool conv_wgrad128_applies(const WgradArgs& a);
+int conv_wgrad128_splits(const WgradArgs& a);   // slots of scratch it can use
 hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s);
 // Output channels a multiple of 320, input channels a multiple of 64: 320 x 64 blocks.
 bool conv_wgrad_tall_applies(const WgradArgs& a);

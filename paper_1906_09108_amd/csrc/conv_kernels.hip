@@ -595,6 +595,23 @@ hipError_t conv_dgrad_gated_pair(const ConvShape& c, const bf16_t* dy, const bf1
                          scratch);
 }
 
+bool conv_dgrad_thin_pair_applies(const ConvShape& c, const ConvShape& cp) {
+  if (c.stride != 2 || cp.stride != 2 || c.T != 9 || cp.T != 1 || c.N != cp.N || c.Hi != cp.Hi || c.Wi != cp.Wi ||
+      c.Ci != cp.Ci || c.Cip != cp.Cip || c.Co != cp.Co || c.Hi < 2 || c.Wi < 2)
+    return false;
+  GatherConvArgs probe{};
+  probe.N = c.N; probe.Hi = c.Ho(); probe.Wi = c.Wo(); probe.OHf = c.Hi; probe.OWf = c.Wi;
+  probe.Ci = c.Co; probe.Co = c.Cip; probe.w_rows = c.Cip; probe.Kw = c.T * c.Co;
+  return conv_gather_thin_classes_applies(probe);
+}
+hipError_t conv_dgrad_thin_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
+                                const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16,
+                                hipStream_t s, int gsums_rep_stride) {
+  const bool gated = gate || bnx || gsums;
+  if (!dy2 || !wt2 || !out_f32 || (gated && (!gate || !bnx || !gsums)) || !conv_dgrad_thin_pair_applies(c, cp)) return hipErrorInvalidValue;
+  return conv_dgrad_impl(c, dy, wt, nullptr, nullptr, gate, bnx, gsums, out_f32, out_b16, s, gated, gsums_rep_stride, dy2, wt2);
+}
+
 static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                   const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                   bf16_t* out_b16, hipStream_t s, bool stats_f32, int rep_stride, const bf16_t* dy2,
@@ -638,7 +655,8 @@ static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf
     // wide layers: all four classes in one launch, heaviest first (4, 2, 2, 1 taps of a 3x3 filter)
     GatherConvArgs probe = a;
     probe.OH = (c.Hi + 1) / 2; probe.OW = (c.Wi + 1) / 2; probe.ntaps = 1; probe.tap[0] = pack_tap(0, 0, 0);
-    if (conv_gather_wide_applies(probe) && c.Hi >= 2 && c.Wi >= 2) {
+    const bool wide = conv_gather_wide_applies(probe);
+    if ((wide || conv_gather_thin_classes_applies(probe)) && c.Hi >= 2 && c.Wi >= 2) {
       static const int order[4][2] = {{1, 1}, {0, 1}, {1, 0}, {0, 0}};
       a.nclass = 4;
       a.out_stride = 2;
@@ -664,7 +682,7 @@ static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf
         }
       }
       a.OH = a.cOH[0]; a.OW = a.cOW[0]; a.ooh = 1; a.oow = 1; a.ntaps = 0;
-      return launch_conv_gather_wide(a, s);
+      return wide ? launch_conv_gather_wide(a, s) : launch_conv_gather_thin_classes(a, s);
     }
   }
   if (dy2) return hipErrorInvalidValue;   // only the launch above adds a second data gradient
@@ -733,7 +751,9 @@ size_t conv_wgrad_scratch_bytes(const ConvShape& c_in) {
   // room for the partial sums of the pixel splits: 8 of them, or as many as it takes the 160 x 160 kernel to fill
   // the chip when a layer has few blocks (160 -> 160: 9 blocks per filter)
   size_t splits = 8;
-  if (!conv_wgrad128_applies(a) && !conv_wgrad_tall_applies(a)) {
+  if (conv_wgrad128_applies(a)) {
+    if (a.Ci == 64) splits = std::max<size_t>(splits, conv_wgrad128_splits(a));   // five blocks for all nine taps
+  } else if (!conv_wgrad_tall_applies(a)) {
     const size_t tiles = (size_t)(c.Co / 160) * (c.Ci / 160) * c.T;
     splits = std::min<size_t>(32, std::max<size_t>(8, (256 + tiles - 1) / tiles));
   }

@@ -152,7 +152,9 @@ constexpr size_t gather_dma_lds_bytes(int BN, int STAGES) {
   return need;
 }
 
-template <int BN, int STAGES, bool KTAIL, bool F32S = false>
+// CLASSES: several output geometries, and a second source in one of them (GatherConvArgs::nclass, in2): one more tap with pointers
+// of its own, as in the pipelined kernel below.
+template <int BN, int STAGES, bool KTAIL, bool F32S, bool CLASSES>
 __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_tiles, int n_tiles) {
   constexpr int BM = 128;
   static_assert(BN % 32 == 0, "whole 32x32 blocks");
@@ -171,7 +173,7 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
   // workgroup -> tile, XCD aware: hardware deals workgroup ids round robin over 8 XCDs
   GatherConvArgs b = a;      // the geometry this workgroup works on
   int t = blockIdx.x, cls = 0;
-  if (a.nclass > 1) {
+  if (CLASSES) {
     // classes are ordered by decreasing work, so the plain order lets the dispatcher balance them
     while (cls + 1 < a.nclass && t >= a.cls_start[cls + 1]) ++cls;
     t -= a.cls_start[cls];
@@ -210,7 +212,17 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
   }
   const char* zero = reinterpret_cast<const char*>(g_zero_word);
   const int cpc = (a.Ci + 63) >> 6;       // chunks per tap
-  const int nchunks = b.ntaps * cpc;
+  const bool has2 = CLASSES && a.in2 != nullptr && cls == a.cls2;
+  const int nchunks = (b.ntaps + (has2 ? 1 : 0)) * cpc;
+  const long delta2 = has2 ? (long)(reinterpret_cast<const char*>(a.in2) - reinterpret_cast<const char*>(a.in)) : 0;
+  const char* src2[JW];   // weight rows of the second source
+  if (CLASSES) {
+#pragma unroll
+    for (int j = 0; j < JW; ++j) {
+      const int row = 8 * (4 * (JX + j) + wave) + (lane >> 3), u = (lane & 7) ^ ((row >> 1) & 7);
+      src2[j] = reinterpret_cast<const char*>(has2 ? a.w2 : a.w) + (size_t)(wok[j] ? c0 + row - BM : 0) * (has2 ? a.Kw2 : a.Kw) * 2 + u * 16;
+    }
+  }
   // the k-unit this lane loads is the same for all its rows: (row >> 1) & 7 = (4 * (wave & 1) + (lane >> 4)) & 7
   const int ku = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
 
@@ -218,9 +230,10 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
     unsigned char* stage = smem + (size_t)(kc % STAGES) * (R * ROWB);
     const int tapi = kc / cpc, cb = (kc - tapi * cpc) * 128;   // byte offset of the 64-channel block
     const bool kv = !KTAIL || (cb >> 1) + ku * 8 < a.Ci;       // this lane's 8 channels exist
-    const int tp = a.nclass > 1 ? a.ctap[cls][tapi] : a.tap[tapi];
+    const bool second = has2 && tapi == b.ntaps;
+    const int tp = CLASSES ? (second ? pack_tap(0, 0, 0) : a.ctap[cls][tapi]) : a.tap[tapi];
     const int dh = (tp & 0xff) - 8, dw = ((tp >> 8) & 0xff) - 8, kofs = tp >> 16;
-    const long xoff = ((long)dh * a.Wi + dw) * a.Ci * 2 + cb;
+    const long xoff = ((long)dh * a.Wi + dw) * a.Ci * 2 + cb + (second ? delta2 : 0);
     const long woff = (long)kofs * a.Ci * 2 + cb;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -229,7 +242,8 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
         const int ih = (hw[j] >> 16) + dh, iw = (hw[j] & 0xffff) + dw;
         g = ((unsigned)ih < (unsigned)a.Hi && (unsigned)iw < (unsigned)a.Wi && kv) ? src[j] + xoff : zero;
       } else {
-        g = (wok[j - JX] && kv) ? src[j] + woff : zero;
+        const char* row = CLASSES && second ? src2[j - JX] + cb : src[j] + woff;
+        g = (wok[j - JX] && kv) ? row : zero;
       }
       dma16(g, stage + (size_t)(8 * (4 * j + wave)) * ROWB);
     }
@@ -287,10 +301,10 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
 // Within 256 registers.  <128, 2> (73 KB of LDS, like <64, 3>) so fits two workgroups on a compute unit, two waves per SIMD;
 // <96, 4> holds 112 KB and one workgroup.
 // F32S: sums of the fp32 values in the output stage (GatherConvArgs::stats_f32), for a data gradient that feeds the layer below.
-template <int BN, int STAGES, bool KTAIL, bool F32S>
+template <int BN, int STAGES, bool KTAIL, bool F32S, bool CLASSES = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_gather_dma_pair_kernel(
     GatherConvArgs a, int m_tiles, int n_tiles) {
-  gather_dma_body<BN, STAGES, KTAIL, F32S>(a, m_tiles, n_tiles);
+  gather_dma_body<BN, STAGES, KTAIL, F32S, CLASSES>(a, m_tiles, n_tiles);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1406,6 +1420,47 @@ hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s) {
   return run_thin<96, 4, false>(a, s);
 }
 
+// Data gradient of a stride-2 layer into 40 .. 96 channels (64 -> 128, the transition out of ResNet-18's first stage): its four
+// parity classes, and the 1x1 projection's data gradient beside it as a second source, on the kernel above.  The generic kernel
+// takes one register-staged 32-channel chunk at a time, the projection's went through memory in fp32, and the layer below summed
+// its batch norm's gradient in a pass of its own.  128 x 64 x 64, 64 -> 128, all three: 227 + 72 -> 104 us (370 MB; a tile of a class
+// is 2 .. 8 steps, most of the time is the output stage).
+bool conv_gather_thin_classes_applies(const GatherConvArgs& a) {
+  return a.Ci % 64 == 0 && a.Co >= 40 && a.Co <= 96 && a.w_rows == a.Co && a.Kw % 8 == 0 && !a.addmask && a.Hi < 32768 && a.Wi < 32768 &&
+         (long long)a.N * a.OHf * a.OWf < (1ll << 30);
+}
+template <int BN, int STAGES, bool F32S>
+static hipError_t run_thin_classes(const GatherConvArgs& a, hipStream_t s) {
+  constexpr size_t lds = gather_dma_lds_bytes(BN, STAGES);
+  static_assert(lds <= 160 * 1024, "LDS of one compute unit");
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_gather_dma_pair_kernel<BN, STAGES, false, F32S, true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  GatherConvArgs m = a;
+  int tiles = 0;
+  for (int i = 0; i < a.nclass; ++i) {
+    m.cls_start[i] = tiles;
+    tiles += (a.N * a.cOH[i] * a.cOW[i] + 127) / 128;
+  }
+  m.cls_start[a.nclass] = tiles;
+  if (tiles <= 0) return hipErrorInvalidValue;
+  static char name[64];
+  if (!name[0]) snprintf(name, sizeof(name), "conv_gather_dma_pair_kernel<%d, %d, classes%s>", BN, STAGES, F32S ? ", feeding" : "");
+  note_kernel(name);
+  hipLaunchKernelGGL((conv_gather_dma_pair_kernel<BN, STAGES, false, F32S, true>), dim3(tiles), dim3(256), lds, s, m, 0, 1);
+  return hipGetLastError();
+}
+hipError_t launch_conv_gather_thin_classes(const GatherConvArgs& a, hipStream_t s) {
+  if (!conv_gather_thin_classes_applies(a) || a.nclass < 1 || a.nclass > 4) return hipErrorInvalidValue;
+  if (a.stats && !a.stats_f32) return hipErrorInvalidValue;   // only sums of the fp32 values are asked for
+  if (a.Co <= 64) return a.stats ? run_thin_classes<64, 3, true>(a, s) : run_thin_classes<64, 3, false>(a, s);
+  return a.stats ? run_thin_classes<96, 4, true>(a, s) : run_thin_classes<96, 4, false>(a, s);
+}
+
 // The data gradients of inverted residual blocks end in a gate and the sums of a batch-norm backward: the same instantiations with
 // the output stage that sums fp32 values, for any number of pixels (a few tiles leave the chip as idle either way, and the pass
 // over the fp32 result that is saved is a launch at least).  128 x 16 x 16, 64 -> 384: 22 + 19.4 for the pass -> 32.8 us.
@@ -1715,7 +1770,10 @@ struct Wgrad128Launch {
 // wherever it exists, so chunks need not start a row: the x pointer advances 64 pixels per chunk, and only the
 // validity of a lane's pixel (does the tap stay inside the image?) depends on where the chunk starts; it repeats
 // every OH OW / gcd(64, OH OW) chunks (49 for 7, 14, 28 and 56 pixels square), one bit of a 64-bit mask each.
-template <int STAGES, bool FLAT>
+// PAIRED: 64 input channels.  The 128 columns of a block are the channels of two taps, 2 tapi and 2 tapi + 1 (nine taps: five
+// blocks, the last one half empty): a lane loads the pixel of its tap.  128 x 64 x 64, 64 -> 128, 3x3, stride 2: the generic kernel,
+// whose blocks are 128 channels of one tap of which 64 exist, 111.5 + 7.2 us for its parts -> 35.9 + 4.8.
+template <int STAGES, bool FLAT, bool PAIRED = false>
 __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad128Launch L) {
   constexpr int BC = 128, BKP = 64, ROWB = BC * 2, PART = BKP * ROWB, STAGE = 2 * PART, NT = 512, NW = NT / 64;
   constexpr int JP = BKP * (BC / 8) / NT, NJ = 2 * JP;   // loads per thread, chunk and operand: 2
@@ -1733,13 +1791,13 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   // tile, input tile, tap): one pixel split (or two), few channel tiles, all their taps.  Dealt round robin,
   // every XCD would fetch both operands in full: 8 x 21 MB per launch.
   int t = xcd_consecutive(blockIdx.x, gridDim.x);
-  const int tapi = t % a.ntaps; t /= a.ntaps;
+  const int blocks = PAIRED ? (a.ntaps + 1) / 2 : a.ntaps;   // of a tap, or of a pair
+  const int tapi = t % blocks; t /= blocks;
   const int ci_t = t % L.ci_tiles; t /= L.ci_tiles;
   const int co_t = t % L.co_tiles;
   const int split = t / L.co_tiles;
   const int co0 = co_t * BC, ci0 = ci_t * BC;
-  const int tp = a.tap[tapi];
-  const int dh = (tp & 0xff) - 8, dw = ((tp >> 8) & 0xff) - 8;
+  const int tp = a.tap[PAIRED ? 2 * tapi : tapi], tp2 = PAIRED && 2 * tapi + 1 < a.ntaps ? a.tap[2 * tapi + 1] : tp;
   const int total_chunks = (a.N * a.OH * a.OW) / BKP;
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
@@ -1763,9 +1821,12 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     const int r = P >> 4, up = P & 15;
     const int u = 2 * ((up >> 1) ^ (2 * (r & 3))) + (up & 1);           // 256-byte rows: slot ^ 2 * (pixel & 3)
     aoff32[j] = (unsigned)((r * a.Co + co0 + u * 8) * 2);
+    const bool second = PAIRED && u >= 8;                               // this lane's unit belongs to the second tap of the pair
+    const int my = second ? tp2 : tp, dh = (my & 0xff) - 8, dw = ((my >> 8) & 0xff) - 8;
+    const int chan = PAIRED ? (u & 7) * 8 : ci0 + u * 8;
     mask_t mask = 0;
     if constexpr (FLAT) {
-      boff32[j] = (unsigned)(margin + ((r + dh * a.Wi + dw) * a.Cx + ci0 + u * 8) * 2);
+      boff32[j] = (unsigned)(margin + ((r + dh * a.Wi + dw) * a.Cx + chan) * 2);
       int ow = (m0 + r) % a.OW, oh = ((m0 + r) / a.OW) % a.OH;
       for (int q = 0; q < L.period; ++q) {
         if ((unsigned)(ow + dw) < (unsigned)a.Wi && (unsigned)(oh + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
@@ -1779,7 +1840,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
       const int ow = r % a.OW, orow = r / a.OW;
       const int iw = ow * a.stride + dw;
       const bool colok = (unsigned)iw < (unsigned)a.Wi;
-      boff32[j] = (unsigned)(margin + (((orow * a.stride + dh) * a.Wi + iw) * a.Cx + ci0 + u * 8) * 2);
+      boff32[j] = (unsigned)(margin + (((orow * a.stride + dh) * a.Wi + iw) * a.Cx + chan) * 2);
       int ohq = (oh0 + orow) % a.OH;
       for (int q = 0; q < L.period; ++q) {
         if (colok && (unsigned)(ohq * a.stride + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
@@ -1787,7 +1848,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
         if (ohq >= a.OH) ohq -= a.OH;
       }
     }
-    bmask[j] = mask;
+    bmask[j] = second && 2 * tapi + 1 >= a.ntaps ? (mask_t)0 : mask;
   }
   const uint64_t zero_addr = (uint64_t)g_zero_word;
   uint32_t zero_lo = (uint32_t)zero_addr, zero_hi = (uint32_t)(zero_addr >> 32);
@@ -1964,11 +2025,13 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   const int co_base = co0 + 64 * wm + 32 * wk + 4 * (lane >> 5);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int ci = ci0 + 64 * wn + 32 * j + (lane & 31);
+    const int ci = PAIRED ? 32 * j + (lane & 31) : ci0 + 64 * wn + 32 * j + (lane & 31);
+    const int tap = PAIRED ? 2 * tapi + wn : tapi;
+    if (PAIRED && tap >= ntaps) continue;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int co = co_base + 8 * (v >> 2) + (v & 3);
-      float* o = dst + ((size_t)co * ntaps + tapi) * Ci + ci;
+      float* o = dst + ((size_t)co * ntaps + tap) * Ci + ci;
       const float val = keep[j][v];
       if (mode == 0) *o = val;
       else if (mode == 1) atomicAdd(o, val);
@@ -1987,11 +2050,18 @@ static int wgrad128_flat_period(const WgradArgs& a) {
   return period <= 64 ? (int)period : 0;
 }
 
+bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 9; }
 bool conv_wgrad128_applies(const WgradArgs& a) {
-  if (a.Co % 128 != 0 || a.Ci % 128 != 0 || a.Cx != a.Ci || a.ntaps < 1) return false;
+  const bool paired = conv_wgrad128_paired(a);
+  if (a.Co % 128 != 0 || (a.Ci % 128 != 0 && !paired) || a.Cx != a.Ci || a.ntaps < 1) return false;
   if (a.OW < 1 || (a.N * a.OH * a.OW) % 64 != 0) return false;
-  if (64 % a.OW != 0 || a.OH > 32) return wgrad128_flat_period(a) > 0;
+  if (64 % a.OW != 0 || a.OH > 32) return !paired && wgrad128_flat_period(a) > 0;
   return a.Hi == a.stride * a.OH;
+}
+// pixel splits that leave a workgroup to every compute unit (with fewer than 8 chunks each they would be mostly beginnings and ends)
+int conv_wgrad128_splits(const WgradArgs& a) {
+  const int blocks = conv_wgrad128_paired(a) ? (a.ntaps + 1) / 2 : a.Ci / 128 * a.ntaps, tiles = a.Co / 128 * blocks;
+  return tiles <= 128 ? std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 64 / 8)) : 1;
 }
 
 hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
@@ -2005,18 +2075,13 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   const int total_chunks = a.N * a.OH * a.OW / 64;
   Wgrad128Launch L;
   L.co_tiles = a.Co / 128;
-  L.ci_tiles = a.Ci / 128;
-  const int tiles = L.co_tiles * L.ci_tiles * a.ntaps;
+  const bool paired = conv_wgrad128_paired(a);
+  L.ci_tiles = paired ? 1 : a.Ci / 128;
+  const int tiles = L.co_tiles * L.ci_tiles * (paired ? (a.ntaps + 1) / 2 : a.ntaps);
   const size_t elems = (size_t)a.Co * a.ntaps * a.Ci;
   // pixel splits only when the blocks alone leave most compute units idle, and only through scratch
   const int max_by_scratch = a.scratch ? (int)(a.scratch_bytes / (elems * 4)) : 0;
-  int S = 1;
-  if (tiles <= 128 && max_by_scratch >= 2) {
-    S = 256 / tiles;
-    if (S > max_by_scratch) S = max_by_scratch;
-    if (S > total_chunks / 8) S = total_chunks / 8;
-    if (S < 1) S = 1;
-  }
+  const int S = max_by_scratch >= 2 ? std::min(conv_wgrad128_splits(a), max_by_scratch) : 1;
   L.chunks_per_split = (total_chunks + S - 1) / S;
   L.splits = (total_chunks + L.chunks_per_split - 1) / L.chunks_per_split;
   L.partial = L.splits > 1 ? a.scratch : nullptr;
@@ -2045,6 +2110,16 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
     }
     note_kernel("conv_wgrad128w8_kernel<5, flat>");
     hipLaunchKernelGGL((conv_wgrad128w8_kernel<STAGES, true>), dim3(tiles * L.splits), dim3(512), lds, s, a, L);
+  } else if (paired) {
+    static bool configured_paired = false;
+    if (!configured_paired) {
+      hipError_t e8 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad128w8_kernel<STAGES, false, true>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e8 != hipSuccess) return e8;
+      configured_paired = true;
+    }
+    note_kernel("conv_wgrad128w8_kernel<5, paired>");
+    hipLaunchKernelGGL((conv_wgrad128w8_kernel<STAGES, false, true>), dim3(tiles * L.splits), dim3(512), lds, s, a, L);
   } else {
     static bool configured8 = false;
     if (!configured8) {
@@ -2056,14 +2131,9 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
     note_kernel("conv_wgrad128w8_kernel<5>");
     hipLaunchKernelGGL((conv_wgrad128w8_kernel<STAGES, false>), dim3(tiles * L.splits), dim3(512), lds, s, a, L);
   }
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
-  const size_t n4 = elems / 4;
-  size_t blocks = (n4 + 255) / 256;
-  if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<float4*>(a.dw),
-                     reinterpret_cast<const float4*>(a.scratch), n4, L.splits, elems / 4, a.overwrite);
-  return hipGetLastError();
+  return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1281,6 +1281,20 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
                                                      G_out, GB_out, s);
           ps.label(c1.sh);
           FDG_TRY(e);
+        } else if (need_dx && G_out && conv_dgrad_thin_pair_applies(c1.sh, cp.sh)) {
+          // the same into few channels, where the output stage can also do the first half of the backward of the layer below
+          const bf16_t* bnx = nullptr;
+          const BnInfo* bb = li > 0 ? closing_bn(p, v, p.L[li - 1], &bnx) : nullptr;
+          const bool feeds = bb && bb->C == c1.sh.Cip;
+          FDG_TRY(side_wait_readers(m, GB_out, s));
+          const double bytes = 2 * (conv_out_elems(c1.sh) + conv_out_elems(cp.sh)) + 2 * (conv_w_elems(c1.sh) + conv_w_elems(cp.sh)) +
+                               conv_in_elems(c1.sh) * (write_bytes + (feeds ? 2 + 2 : 0));
+          ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh) + conv_flops(cp.sh), bytes, s);
+          const hipError_t e = conv_dgrad_thin_pair(c1.sh, m->T(0), v.Wt(c1), cp.sh, m->T(1), v.Wt(cp), feeds ? in_b : nullptr, feeds ? bnx : nullptr,
+                                                    feeds ? m->bsums(*bb) : nullptr, G_out, GB_out, s, p.stat_rep);
+          ps.label(c1.sh);
+          FDG_TRY(e);
+          fed = feeds;
         } else if (need_dx) {
           FDG_TRY(mconv_dgrad(m, cp, m->T(1), v.Wt(cp), nullptr, nullptr, m->TPB(), nullptr, s));
           FDG_TRY(mconv_dgrad(m, c1, m->T(0), v.Wt(c1), m->TPB(), nullptr, G_out, GB_out, s));

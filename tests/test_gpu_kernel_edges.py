@@ -70,3 +70,33 @@ def test_inverted_blocks_with_sums(channels, n, h, w):
     spec = ModuleSpec(n, channels[0][0], h, w, layers, delay=1, is_bottom=False, beta=0.5, name="inverted", **TD.H)
     print(f"case inverted {channels} {n}x{h}x{w}", flush=True)
     LT._judge(LT._run(spec, seed=1, steps_after_warmup=2), f"inverted {channels[0][0]}-{channels[-1][1]} {n}x{h}x{w}")
+
+
+# 64 -> 128 channels at stride 2: the data gradient's parity classes on the 1x1 kernels' loop (even and odd images, a last class
+# of a single column, 72 and 96 channels), the weight gradient with two taps to a block (widths that divide 64; others: the
+# generic kernel), and in a module the projection beside them and the sums of the layer below
+@pytest.mark.parametrize("case, dgrad, wgrad", [
+    ((3, 16, 16, 64, 128, 3, 2), "conv_gather_dma_pair_kernel<64, 3, classes>", "conv_wgrad128w8_kernel<5, paired>"),
+    ((2, 64, 64, 64, 256, 3, 2), "conv_gather_dma_pair_kernel<64, 3, classes>", "conv_wgrad128w8_kernel<5, paired>"),
+    ((5, 9, 14, 64, 128, 3, 2), "conv_gather_dma_pair_kernel<64, 3, classes>", "conv_wgrad_kernel<128, 128, 2, 2, 1>"),
+    ((4, 7, 2, 72, 128, 3, 2), "conv_gather_dma_pair_kernel<96, 4, classes>", "conv_wgrad_kernel<128, 128, 2, 2, 1>"),
+    ((2, 10, 6, 96, 192, 1, 2), "conv_gather_dma_pair_kernel<96, 4, classes>", "conv_wgrad_kernel<128, 128, two sums>"),
+    ((4, 8, 8, 64, 128, 3, 1), None, "conv_wgrad128w8_kernel<5, paired>"),
+])
+def test_stride_2_into_few_channels(case, dgrad, wgrad):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co, k, s = case
+    if dgrad:
+        TK.test_conv_dgrad(case)
+        z = [t.zeros(c, device="cuda", dtype=t.bfloat16) for c in (n * h * w * co, ci * k * k * co)]
+        K.fdgk_conv_dgrad(z[0], z[1], None, None, t.empty(n * h * w * ci, device="cuda"), None, n, h, w, ci, co, k, s)
+        assert K.fdgk_last_kernel() == dgrad
+    TK.test_conv_wgrad(case)
+    assert K.fdgk_last_kernel() == wgrad
+
+
+@pytest.mark.parametrize("c, n, h, w", [(64, 4, 14, 16), (64, 3, 9, 11), (96, 2, 6, 7)])
+def test_projecting_block_that_feeds_the_one_below(c, n, h, w):
+    layers = [Layer(W.BASIC_POSTACT, c, c, 1), Layer(W.BASIC_POSTACT, c, 2 * c, 2), Layer(W.BASIC_POSTACT, 2 * c, 2 * c, 1)]
+    TD.check(f"projecting {c} {n}x{h}x{w}", ModuleSpec(n, c, h, w, layers, delay=1, is_bottom=False, beta=0.5, name="projecting", **TD.H))
