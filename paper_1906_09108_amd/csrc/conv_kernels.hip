@@ -752,7 +752,9 @@ size_t conv_wgrad_scratch_bytes(const ConvShape& c_in) {
   // the chip when a layer has few blocks (160 -> 160: 9 blocks per filter)
   size_t splits = 8;
   if (conv_wgrad128_applies(a)) {
-    if (a.Ci == 64) splits = std::max<size_t>(splits, conv_wgrad128_splits(a));   // five blocks for all nine taps
+    // five blocks for all nine taps of 64 channels; layers that the ragged form takes from the generic kernel, whose sums are not
+    // to become longer than they have to
+    if (a.Ci == 64 || conv_wgrad128_ragged(a)) splits = std::max<size_t>(splits, conv_wgrad128_splits(a));
   } else if (!conv_wgrad_tall_applies(a)) {
     const size_t tiles = (size_t)(c.Co / 160) * (c.Ci / 160) * c.T;
     splits = std::min<size_t>(32, std::max<size_t>(8, (256 + tiles - 1) / tiles));

@@ -1725,7 +1725,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_lanes_kernel(float4* __restr
 hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s) {
   if (elems % 4 != 0 || parts < 1) return hipErrorInvalidValue;
   const size_t n4 = elems / 4;
-  if (parts >= 32) {
+  if (parts >= 12) {   // also the smaller error: sixteen short sums instead of a long one
     hipLaunchKernelGGL(wgrad_reduce_lanes_kernel, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, reinterpret_cast<float4*>(dw),
                        reinterpret_cast<const float4*>(partial), n4, parts, n4, overwrite);
     return hipGetLastError();
@@ -1773,7 +1773,9 @@ struct Wgrad128Launch {
 // PAIRED: 64 input channels.  The 128 columns of a block are the channels of two taps, 2 tapi and 2 tapi + 1 (nine taps: five
 // blocks, the last one half empty): a lane loads the pixel of its tap.  128 x 64 x 64, 64 -> 128, 3x3, stride 2: the generic kernel,
 // whose blocks are 128 channels of one tap of which 64 exist, 111.5 + 7.2 us for its parts -> 35.9 + 4.8.
-template <int STAGES, bool FLAT, bool PAIRED = false>
+// RAGGED (with FLAT): any number of pixels, and channel counts that are no multiple of 128.  The rows of the last chunk past the last
+// pixel, and the units past the last channel, are loaded from the zero word, for dy and x alike.
+template <int STAGES, bool FLAT, bool PAIRED = false, bool RAGGED = false>
 __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad128Launch L) {
   constexpr int BC = 128, BKP = 64, ROWB = BC * 2, PART = BKP * ROWB, STAGE = 2 * PART, NT = 512, NW = NT / 64;
   constexpr int JP = BKP * (BC / 8) / NT, NJ = 2 * JP;   // loads per thread, chunk and operand: 2
@@ -1798,7 +1800,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   const int split = t / L.co_tiles;
   const int co0 = co_t * BC, ci0 = ci_t * BC;
   const int tp = a.tap[PAIRED ? 2 * tapi : tapi], tp2 = PAIRED && 2 * tapi + 1 < a.ntaps ? a.tap[2 * tapi + 1] : tp;
-  const int total_chunks = (a.N * a.OH * a.OW) / BKP;
+  const int total_chunks = (a.N * a.OH * a.OW + (RAGGED ? BKP - 1 : 0)) / BKP;
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
   if (n <= 0) return;
@@ -1814,6 +1816,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   const char* b_next = reinterpret_cast<const char*>(a.x) + (FLAT ? (long long)m0 : xrow0 * a.Wi) * a.Cx * 2 - margin;
   typedef typename std::conditional<FLAT, unsigned long long, unsigned>::type mask_t;
   unsigned aoff32[JP], boff32[JP];
+  int arows[JP], brows[JP];                // RAGGED: the lane's unit exists in chunks that hold more rows than this
   mask_t bmask[JP];
 #pragma unroll
   for (int j = 0; j < JP; ++j) {
@@ -1849,6 +1852,8 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
       }
     }
     bmask[j] = second && 2 * tapi + 1 >= a.ntaps ? (mask_t)0 : mask;
+    arows[j] = co0 + u * 8 < a.Co ? r : BKP;
+    brows[j] = chan < a.Cx ? r : BKP;
   }
   const uint64_t zero_addr = (uint64_t)g_zero_word;
   uint32_t zero_lo = (uint32_t)zero_addr, zero_hi = (uint32_t)(zero_addr >> 32);
@@ -1858,13 +1863,21 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   mask_t phase_bit = 1;                    // 1 << ((chunk being issued) mod period)
   const mask_t last_phase_bit = (mask_t)1 << (L.period - 1);
   unsigned issue_stage = 0;                // LDS byte offset of the stage being filled
+  int rows_left = a.N * a.OH * a.OW - m0;  // RAGGED: from the chunk being issued on
   auto issue_one = [&](int d) {
     unsigned char* stage = smem + issue_stage;
     if (d < JP) {
-      dma16(a_next + aoff32[d], stage + (64 * (NW * d + wave)) * 16);
+      if constexpr (RAGGED) {
+        const bool ok = arows[d] < min(rows_left, BKP);
+        const uint64_t pa = (uint64_t)(a_next + aoff32[d]);
+        const uint32_t lo = ok ? (uint32_t)pa : zero_lo, hi = ok ? (uint32_t)(pa >> 32) : zero_hi;
+        dma16((const char*)(((uint64_t)hi << 32) | lo), stage + (64 * (NW * d + wave)) * 16);
+      } else {
+        dma16(a_next + aoff32[d], stage + (64 * (NW * d + wave)) * 16);
+      }
     } else {
       const int j = d - JP;
-      const bool ok = (bmask[j] & phase_bit) != 0;
+      const bool ok = (bmask[j] & phase_bit) != 0 && (!RAGGED || brows[j] < min(rows_left, BKP));
       const uint64_t pa = (uint64_t)(b_next + boff32[j]);
       const uint32_t lo = ok ? (uint32_t)pa : zero_lo, hi = ok ? (uint32_t)(pa >> 32) : zero_hi;
       dma16((const char*)(((uint64_t)hi << 32) | lo), stage + PART + (64 * (NW * j + wave)) * 16);
@@ -1875,6 +1888,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     issue_stage = issue_stage == (STAGES - 1) * STAGE ? 0u : issue_stage + STAGE;
     a_next += L.a_step;
     b_next += L.b_step;
+    if (RAGGED) rows_left -= BKP;
   };
 
   f32x16 acc[2][2];
@@ -1987,13 +2001,51 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     if constexpr (decltype(issue_tag)::value) issue_done();
     rd_stage = next_stage;
   };
+  // RAGGED and PAIRED: the sums of every 4 chunks (128 pixels a wave) are added to totals: the generic kernel, which ran these layers, split them
+  // further, and no sum is to lose digits to that.  Error against 64 bits, generic -> one sum -> totals: 127 x 14 x 14 320 -> 320
+  // 2.05e-7 -> 3.07e-7 -> 1.0e-7, 13 x 28 x 28 128 -> 128 1.00e-7 -> 1.10e-7 -> 0.9e-7 (about 2 % of the time).  The next step's reads are waited for first: between steps nothing
+  // else keeps the compiler from moving their registers.
+  constexpr bool FOLDS = RAGGED || PAIRED;
+  f32x16 total[2][2];
+  if constexpr (FOLDS) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) total[i][j] = acc[i][j];
+  }
+  auto fold = [&]() {
+    if constexpr (FOLDS) {
+      static_for<4>([&](auto f) { wait_frag(I0{}, f, I0{}); });
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            total[i][j][v] += acc[i][j][v];
+            acc[i][j][v] = 0.f;
+          }
+    }
+  };
   {
     using yes = std::true_type;
     using no = std::false_type;
     int c = 0;
-    for (; c + STAGES - 1 < n; ++c) chunk(yes{}, yes{});
-    for (; c + 1 < n; ++c) chunk(yes{}, no{});
+    for (; c + STAGES - 1 < n; ++c) {
+      chunk(yes{}, yes{});
+      if (FOLDS && (c & 3) == 3) fold();
+    }
+    for (; c + 1 < n; ++c) {
+      chunk(yes{}, no{});
+      if (FOLDS && (c & 3) == 3) fold();
+    }
     if (c < n) chunk(no{}, no{});
+  }
+  if constexpr (FOLDS) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] += total[i][j];
   }
 
   // ---- add the two pixel halves: wave (wm, wn, wk) keeps block row wk of its two and receives its partner's ----
@@ -2027,10 +2079,11 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   for (int j = 0; j < 2; ++j) {
     const int ci = PAIRED ? 32 * j + (lane & 31) : ci0 + 64 * wn + 32 * j + (lane & 31);
     const int tap = PAIRED ? 2 * tapi + wn : tapi;
-    if (PAIRED && tap >= ntaps) continue;
+    if ((PAIRED && tap >= ntaps) || (RAGGED && ci >= Ci)) continue;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int co = co_base + 8 * (v >> 2) + (v & 3);
+      if (RAGGED && co >= a.Co) continue;
       float* o = dst + ((size_t)co * ntaps + tap) * Ci + ci;
       const float val = keep[j][v];
       if (mode == 0) *o = val;
@@ -2051,17 +2104,26 @@ static int wgrad128_flat_period(const WgradArgs& a) {
 }
 
 bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 9; }
+// The ragged form: layers that would otherwise go to the generic kernel (odd batches of 7 x 7 or 14 x 14 images; 320 channels at such
+// widths, which the kernels for multiples of 160 do not take).
+bool conv_wgrad128_ragged(const WgradArgs& a) {
+  if (a.Co < 128 || a.Ci < 128 || a.Co % 8 != 0 || a.Ci % 8 != 0 || a.Cx != a.Ci || a.ntaps < 1 || a.N * a.OH * a.OW < 64) return false;
+  if (wgrad128_flat_period(a) <= 0) return false;
+  return (a.Co % 128 != 0 || a.Ci % 128 != 0 || (a.N * a.OH * a.OW) % 64 != 0) && !conv_wgrad_tall_applies(a) && !conv_wgrad_wide_applies(a);
+}
 bool conv_wgrad128_applies(const WgradArgs& a) {
+  if (conv_wgrad128_ragged(a)) return true;
   const bool paired = conv_wgrad128_paired(a);
   if (a.Co % 128 != 0 || (a.Ci % 128 != 0 && !paired) || a.Cx != a.Ci || a.ntaps < 1) return false;
   if (a.OW < 1 || (a.N * a.OH * a.OW) % 64 != 0) return false;
   if (64 % a.OW != 0 || a.OH > 32) return !paired && wgrad128_flat_period(a) > 0;
   return a.Hi == a.stride * a.OH;
 }
-// pixel splits that leave a workgroup to every compute unit (with fewer than 8 chunks each they would be mostly beginnings and ends)
+// pixel splits that leave a workgroup to every compute unit (with fewer than 8 chunks each they would be mostly beginnings and ends;
+// the ragged form goes down to 4, as its layers' sums were that short before)
 int conv_wgrad128_splits(const WgradArgs& a) {
-  const int blocks = conv_wgrad128_paired(a) ? (a.ntaps + 1) / 2 : a.Ci / 128 * a.ntaps, tiles = a.Co / 128 * blocks;
-  return tiles <= 128 ? std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 64 / 8)) : 1;
+  const int blocks = conv_wgrad128_paired(a) ? (a.ntaps + 1) / 2 : (a.Ci + 127) / 128 * a.ntaps, tiles = (a.Co + 127) / 128 * blocks;
+  return tiles <= 128 ? std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 64 / (conv_wgrad128_ragged(a) ? 4 : 8))) : 1;
 }
 
 hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
@@ -2072,11 +2134,12 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   if (!configured) {
     configured = true;   // (the two forms of the kernel are configured where they are launched)
   }
-  const int total_chunks = a.N * a.OH * a.OW / 64;
+  const bool ragged = conv_wgrad128_ragged(a);
+  const int total_chunks = (a.N * a.OH * a.OW + 63) / 64;
   Wgrad128Launch L;
-  L.co_tiles = a.Co / 128;
+  L.co_tiles = (a.Co + 127) / 128;
   const bool paired = conv_wgrad128_paired(a);
-  L.ci_tiles = paired ? 1 : a.Ci / 128;
+  L.ci_tiles = paired ? 1 : (a.Ci + 127) / 128;
   const int tiles = L.co_tiles * L.ci_tiles * (paired ? (a.ntaps + 1) / 2 : a.ntaps);
   const size_t elems = (size_t)a.Co * a.ntaps * a.Ci;
   // pixel splits only when the blocks alone leave most compute units idle, and only through scratch
@@ -2094,13 +2157,27 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   L.a_step = (long long)64 * a.Co * 2;
   L.b_step = (long long)d_oh_full * a.stride * a.Wi * a.Cx * 2;
   L.step_w = 0;
-  const bool flat = 64 % a.OW != 0 || a.OH > 32;   // conv_wgrad128_applies has checked that the flat form applies then
+  const bool flat = ragged || 64 % a.OW != 0 || a.OH > 32;   // conv_wgrad128_applies has checked that the flat form applies then
   if (flat) {
     L.period = wgrad128_flat_period(a);
     if (L.period <= 0) return hipErrorInvalidValue;
     L.d_oh = d_oh_full % a.OH;
     L.step_w = 64 % a.OW;
     L.b_step = (long long)64 * a.Cx * 2;
+    if (ragged) {
+      static bool configured_ragged = false;
+      if (!configured_ragged) {
+        hipError_t e8 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad128w8_kernel<STAGES, true, false, true>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e8 != hipSuccess) return e8;
+        configured_ragged = true;
+      }
+      note_kernel("conv_wgrad128w8_kernel<5, flat, ragged>");
+      hipLaunchKernelGGL((conv_wgrad128w8_kernel<STAGES, true, false, true>), dim3(tiles * L.splits), dim3(512), lds, s, a, L);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess || !L.partial) return e;
+      return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
+    }
     static bool configured_flat = false;
     if (!configured_flat) {
       hipError_t e8 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad128w8_kernel<STAGES, true>),

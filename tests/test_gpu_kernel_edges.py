@@ -100,3 +100,24 @@ def test_stride_2_into_few_channels(case, dgrad, wgrad):
 def test_projecting_block_that_feeds_the_one_below(c, n, h, w):
     layers = [Layer(W.BASIC_POSTACT, c, c, 1), Layer(W.BASIC_POSTACT, c, 2 * c, 2), Layer(W.BASIC_POSTACT, 2 * c, 2 * c, 1)]
     TD.check(f"projecting {c} {n}x{h}x{w}", ModuleSpec(n, c, h, w, layers, delay=1, is_bottom=False, beta=0.5, name="projecting", **TD.H))
+
+
+# Weight gradients of unit stride whose pixels fill no whole chunk of 64 or whose channels no whole tile of 128: one chunk and a pixel,
+# a last chunk of one row, more chunks than stages, sums folded more than once, both tiles ragged, 1x1, images of one row; scratch and
+# none (test_conv_wgrad runs both); shapes just outside keep their kernels
+@pytest.mark.parametrize("case, kernel", [
+    ((5, 1, 13, 136, 128, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((3, 7, 7, 128, 256, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((9, 14, 14, 320, 200, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((37, 14, 14, 256, 136, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((50, 8, 9, 128, 128, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((7, 28, 28, 160, 320, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((3, 15, 15, 128, 256, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),     # the validity of a pixel repeats too late
+    ((4, 4, 4, 128, 120, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),       # fewer than 128 channels
+    ((1, 7, 9, 128, 128, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),       # less than a chunk
+    ((16, 14, 14, 128, 256, 3, 1), "conv_wgrad128w8_kernel<5, flat>"),
+])
+def test_ragged_weight_gradients(case, kernel):
+    from paper_1906_09108_amd import kernels as K
+    TK.test_conv_wgrad(case)
+    assert K.fdgk_last_kernel() == kernel
