@@ -1285,11 +1285,13 @@ static hipError_t run_patch256(const GatherConvArgs& a, hipStream_t s) {
 
 template <int BN>
 static hipError_t run_patch_rows(const GatherConvArgs& a, hipStream_t s) {
-  // 256-pixel tiles where 128-pixel tiles need more than one round of workgroups and the larger ones still fill the chip
+  // 256-pixel tiles where 128-pixel tiles need more than one round of workgroups: one of twice as large ones is shorter than two, also
+  // where it leaves part of the chip idle (tiles of 128 pixels -> of 256): 84 x 14 x 14 256 -> 256 (258 tiles) 40.8 -> 31.4 us, 128 x 14 x
+  // 14 (392) 45.4 -> 37.3, 40 x 32 x 32 160 -> 160 (320) 51.5 -> 35.7; of three rounds against two: 66 x 32 x 32 160 -> 160 (528) 75.5 ->
+  // 71.6, 70 x 32 x 32 128 -> 128 (560) 49.4 -> 45.8.  One round of the smaller ones stays (640 -> 640 at 8 x 8, 256 tiles).
   {
     const int Mtot = a.N * a.OH * a.OW, n_tiles = (a.Co + BN - 1) / BN;
-    const int t128 = (Mtot + 127) / 128 * n_tiles, t256 = (Mtot + 255) / 256 * n_tiles;
-    if (t128 > 256 && t256 >= 224) {
+    if ((Mtot + 127) / 128 * n_tiles > 256) {
       if (a.Ci % 64 != 0) return run_patch256<BN, 384, 3, true>(a, s);
       return 256 + 2 * a.Wi + 2 <= 320 ? run_patch256<BN, 320, 3, false>(a, s) : run_patch256<BN, 384, 3, false>(a, s);
     }

@@ -121,3 +121,16 @@ def test_ragged_weight_gradients(case, kernel):
     from paper_1906_09108_amd import kernels as K
     TK.test_conv_wgrad(case)
     assert K.fdgk_last_kernel() == kernel
+
+
+# One round of 128-pixel tiles, and one more tile than that: tiles of 256 pixels, which leave half the chip idle
+@pytest.mark.parametrize("case, kernel", [
+    ((128, 8, 8, 128, 512, 3, 1), "conv_patch_kernel<128, 160, 5>"),
+    ((257, 8, 8, 64, 256, 3, 1), "conv_patch256_kernel<128, 320, 3>"),
+    ((33, 31, 32, 136, 136, 3, 1), "conv_patch256_kernel<128, 384, 3, true>"),
+])
+def test_tiles_of_256_pixels(case, kernel):
+    from paper_1906_09108_amd import kernels as K
+    TK.test_conv_fwd(case)
+    assert K.fdgk_last_kernel() == kernel
+    TK.test_conv_dgrad(case)
