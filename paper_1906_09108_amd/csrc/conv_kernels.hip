@@ -716,11 +716,13 @@ static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf
   return launch_conv_gather(a, s);
 }
 
-size_t conv_scratch_bytes(const ConvShape& c) {
-  const GatherConvArgs f = forward_args(c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
+size_t conv_scratch_bytes(const ConvShape& c, int workgroups) {
+  GatherConvArgs f = forward_args(c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
+  f.scratch.workgroups = workgroups;
   const size_t forward = conv_gather_wide_applies(f) ? conv_gather_wide_scratch_bytes(f) : 0;
   if (c.stride != 1) return forward;
   GatherConvArgs a{};   // the data gradient
+  a.scratch.workgroups = workgroups;
   a.N = c.N; a.Hi = a.OHf = c.Ho(); a.Wi = a.OWf = c.Wo(); a.Ci = c.Co; a.Co = a.w_rows = c.Cip; a.Kw = c.T * c.Co;
   a.OH = c.Hi; a.OW = c.Wi; a.in_stride = a.out_stride = 1; a.ntaps = c.T;
   for (int t = 0; t < c.T; ++t) a.tap[t] = c.T == 9 ? pack_tap(1 - t / 3, 1 - t % 3, t) : pack_tap(0, 0, 0);

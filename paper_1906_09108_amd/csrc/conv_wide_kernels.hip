@@ -1212,15 +1212,18 @@ static bool conv_patch_applies(const GatherConvArgs& a) {
   return true;
 }
 
-// Parts of the contraction of a patch launch: as many as fill one round of workgroups, where that shortens the longest workgroup
-// by 896 = 7 x 128 (channel block, output channel) units.  A block of 160 channels is 3.9 us of a workgroup, the slots and the
+// Parts of the contraction of a patch launch: as many as fill one round of workgroups (half a round where the caller says that
+// launches of another stream run beside these: see ConvScratch), where that shortens the longest workgroup by 896 = 7 x 128 (channel block, output channel) units.  A block of 160 channels is 3.9 us of a workgroup, the slots and the
 // second launch cost 11 us, and what the tiles leave idle is not all lost: the weight gradients of the other stream run there.
 // WRN-28-10 top module, batch 8: 1511 -> 1168 us a step, 37: 1603 -> 1488 (76 tiles of 640 -> 640 at 8 x 8 in three parts: 48.8 ->
 // 28.4 + 8.8 us); beyond the line, batch 64 (128 tiles in two parts): 1821 -> 1917; ResNet-18 top module, batch 32 (64 tiles of 512
 // -> 512, 8 blocks in four parts): 861 -> 883, batch 8 (within): 768 -> 721; bottleneck blocks of 4 blocks, batch 20: 765 -> 812.
+// Forward and backward on two streams, whole tiles / a full round / half a round: WRN-28-10 blocks 7 - 9, batch 32 at 16 x 16 (64
+// tiles of 640 -> 640) 530 / 542 / 530, blocks 9 - 11 at 8 x 8, batch 20 and 40: 526 / 389 / 390 and 545 / 454 / 419; one stream,
+// the same blocks, batch 16 (32 tiles): 841 / 600 / 616.
 static int patch_parts(const GatherConvArgs& a, int BN) {
   const int tiles = (a.N * a.OH * a.OW + 127) / 128 * ((a.Co + BN - 1) / BN), blocks = (a.Ci + 63) / 64;
-  int parts = std::min(256 / tiles, blocks);
+  int parts = std::min(a.scratch.workgroups / tiles, blocks);
   if (parts <= 1) return 1;
   const int longest = (blocks + parts - 1) / parts;
   parts = (blocks + longest - 1) / longest;

@@ -57,11 +57,13 @@ __device__ __forceinline__ double stat_value(long long hi, long long lo, long lo
 #endif
 
 // Device memory with which a wide convolution of few tiles may deal the contraction of a tile to several workgroups: room for
-// their partial sums.  Launches on one stream may share it.
+// their partial sums, and how many workgroups the launch may fill with them.  Launches on one stream may share it.
 struct ConvScratch {
   float* partial;        // nullptr: none
   size_t bytes;
+  int workgroups;        // kSplitRound, or half of it where the forward and the backward of a module run on two streams
 };
+constexpr int kSplitRound = 256;   // one workgroup to a compute unit
 struct GatherConvArgs {
   const bf16_t* in;      // [N, Hi, Wi, Ci] bf16, Ci % 8 == 0
   const bf16_t* w;       // [w_rows, Kw] bf16, k contiguous
@@ -273,7 +275,7 @@ hipError_t conv_dgrad_gated(const ConvShape& c, const bf16_t* dy, const bf16_t* 
                             const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
                             int gsums_rep_stride = 0, const ConvScratch& scratch = {});
 // bytes of scratch that the calls above can use for this layer, forward and data gradient (0: none)
-size_t conv_scratch_bytes(const ConvShape& c);
+size_t conv_scratch_bytes(const ConvShape& c, int workgroups);
 // dw[Co][T][Ci] (+)= sum over pixels of dy * x.  overwrite = false: accumulated into dw (fp32 atomics where the
 // pixel dimension is split), dw zeroed by the caller;  overwrite = true: dw is written, whatever it held.
 // scratch (optional): device memory for the partial sums of the pixel splits; without it they are added

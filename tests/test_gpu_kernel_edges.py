@@ -34,18 +34,20 @@ def test_64_channels_over_many_pixels(case, kernel):
 # Wide 3x3 convolutions of few tiles: the contraction in parts, added up by a launch of its own that does the output stage.  Whole
 # parts and parts of two lengths, ragged pixel and channel tiles, a partly filled last channel block, both tile widths; forward, and
 # the data gradients with gate and sums, with an addend, and plain, as a step of a module makes them
-@pytest.mark.parametrize("kind, c_in, c_out, n, h, w, kernel", [
-    (W.BASIC_PREACT, 640, 640, 5, 7, 9, "conv_patch_kernel<160, 160, 5> in parts"),
-    (W.BASIC_PREACT, 584, 640, 3, 9, 17, "conv_patch_kernel<160, 192, 5> in parts"),
-    (W.BASIC_POSTACT, 640, 640, 9, 16, 8, "conv_patch_kernel<160, 160, 5> in parts"),
-    (W.BASIC_PREACT, 568, 584, 2, 5, 30, "conv_patch_kernel<128, 192, 5, true> in parts"),
-    (W.BASIC_PREACT, 512, 512, 4, 8, 8, "conv_patch_kernel<128, 160, 5> in parts"),
-    (W.BASIC_PREACT, 512, 512, 17, 8, 8, "conv_patch_kernel<128, 160, 5>"),   # 36 tiles: eight blocks in fewer than eight parts
+@pytest.mark.parametrize("kind, c_in, c_out, n, h, w, delay, kernel", [
+    (W.BASIC_PREACT, 640, 640, 5, 7, 9, 1, "conv_patch_kernel<160, 160, 5> in parts"),
+    (W.BASIC_PREACT, 584, 640, 3, 9, 17, 1, "conv_patch_kernel<160, 192, 5> in parts"),
+    (W.BASIC_POSTACT, 640, 640, 9, 16, 8, 1, "conv_patch_kernel<160, 160, 5> in parts"),
+    (W.BASIC_PREACT, 568, 584, 2, 5, 30, 1, "conv_patch_kernel<128, 192, 5, true> in parts"),
+    (W.BASIC_PREACT, 512, 512, 4, 8, 8, 1, "conv_patch_kernel<128, 160, 5> in parts"),
+    (W.BASIC_PREACT, 512, 512, 17, 8, 8, 1, "conv_patch_kernel<128, 160, 5>"),   # 36 tiles: eight blocks in fewer than eight parts
+    (W.BASIC_PREACT, 640, 640, 17, 12, 12, 0, "conv_patch_kernel<160, 160, 5> in parts"),   # 80 tiles: three parts fill a round,
+    (W.BASIC_PREACT, 640, 640, 17, 12, 12, 1, "conv_patch_kernel<160, 160, 5>"),   # and half a round, where two streams run, is full
 ])
-def test_contraction_in_parts(kind, c_in, c_out, n, h, w, kernel):
+def test_contraction_in_parts(kind, c_in, c_out, n, h, w, delay, kernel):
     from paper_1906_09108_amd import FdgModule, kernels as K
     import torch as t
-    spec = ModuleSpec(n, c_in, h, w, [Layer(kind, c_in, c_out, 1)], delay=1, is_bottom=False, beta=0.5, name="parts", **TD.H)
+    spec = ModuleSpec(n, c_in, h, w, [Layer(kind, c_in, c_out, 1)], delay=delay, is_bottom=False, beta=0.5, name="parts", **TD.H)
     TD.check(f"parts {c_in}>{c_out} {n}x{h}x{w}", spec)
     m = FdgModule(spec)
     m.set_params(W.make_params(spec, 0))
