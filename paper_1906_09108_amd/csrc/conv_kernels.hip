@@ -431,7 +431,9 @@ static size_t generic_wgrad_scratch_bytes(const WgradArgs& a) {
 hipError_t launch_conv_wgrad(const WgradArgs& a, hipStream_t s) {
   if (a.Co % 8 != 0 || a.Cx % 8 != 0 || a.Ci > a.Cx || a.ntaps < 1 || a.ntaps > 9 || a.N * a.OH * a.OW <= 0)
     return hipErrorInvalidValue;
-  if (conv_wgrad128_applies(a)) return launch_conv_wgrad128(a, s);
+  // (a thin layer is one to six tiles: without room for its splits the generic kernel, which can add them with atomics, runs it)
+  if (conv_wgrad128_applies(a) && (!conv_wgrad128_thin(a) || (a.scratch && a.scratch_bytes >= (size_t)conv_wgrad128_splits(a) * a.Co * a.Ci * sizeof(float))))
+    return launch_conv_wgrad128(a, s);
   if (conv_wgrad_tall_applies(a)) return launch_conv_wgrad_tall(a, s);
   if (conv_wgrad_wide_applies(a)) return launch_conv_wgrad_wide(a, s);
   if (conv_wgrad_narrow_applies(a) && a.scratch && a.scratch_bytes >= conv_wgrad_narrow_scratch_bytes(a))

@@ -1761,6 +1761,7 @@ struct Wgrad128Launch {
   int d_oh;              // output rows per chunk (64 / OW), reduced mod OH
   int step_w;            // flat form (any width, unit stride): a chunk moves a pixel by 64 = d_oh rows and step_w columns
   long long a_step, b_step;   // bytes from one chunk to the next in dy and in x
+  int fold_mask;         // sums are folded into totals after every fold_mask + 1 chunks (forms that fold)
 };
 
 // EIGHT waves, two per SIMD.  Four waves would issue the direct-to-LDS loads, the LDS reads
@@ -2006,7 +2007,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     if constexpr (decltype(issue_tag)::value) issue_done();
     rd_stage = next_stage;
   };
-  // RAGGED and PAIRED: the sums of every 4 chunks (128 pixels a wave) are added to totals: the generic kernel, which ran these layers, split them
+  // RAGGED and PAIRED: the sums of every 4 chunks (128 pixels a wave; thin 1x1 layers: 2) are added to totals: the generic kernel, which ran these layers, split them
   // further, and no sum is to lose digits to that.  Error against 64 bits, generic -> one sum -> totals: 127 x 14 x 14 320 -> 320
   // 2.05e-7 -> 3.07e-7 -> 1.0e-7, 13 x 28 x 28 128 -> 128 1.00e-7 -> 1.10e-7 -> 0.9e-7 (about 2 % of the time).  The next step's reads are waited for first: between steps nothing
   // else keeps the compiler from moving their registers.
@@ -2038,11 +2039,11 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     int c = 0;
     for (; c + STAGES - 1 < n; ++c) {
       chunk(yes{}, yes{});
-      if (FOLDS && (c & 3) == 3) fold();
+      if (FOLDS && (c & L.fold_mask) == L.fold_mask) fold();
     }
     for (; c + 1 < n; ++c) {
       chunk(yes{}, no{});
-      if (FOLDS && (c & 3) == 3) fold();
+      if (FOLDS && (c & L.fold_mask) == L.fold_mask) fold();
     }
     if (c < n) chunk(no{}, no{});
   }
@@ -2101,6 +2102,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
 // Chunks per repetition of the flat form's validity pattern (0: the flat form does not apply): unit stride, any width.
 static int wgrad128_flat_period(const WgradArgs& a) {
   if (a.stride != 1 || a.Hi != a.OH || a.Wi != a.OW || a.OW < 1 || a.OH < 1) return 0;
+  if (a.ntaps == 1) return 1;   // 1x1: every pixel is valid
   const long long img = (long long)a.OH * a.OW;
   long long g = img, h = 64;
   while (h) { const long long r = g % h; g = h; h = r; }
@@ -2110,9 +2112,18 @@ static int wgrad128_flat_period(const WgradArgs& a) {
 
 bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 9; }
 // The ragged form: layers that would otherwise go to the generic kernel (odd batches of 7 x 7 or 14 x 14 images; 320 channels at such
-// widths, which the kernels for multiples of 160 do not take).
+// widths, which the kernels for multiples of 160 do not take), and the 1x1 layers of fewer than 128 channels on a side, down to 32
+// (inverted residual blocks).  Those are bound by memory, and that a block of 64 x 128 leaves half the matrix instructions unused costs
+// nothing; the generic kernel, which loads a chunk into registers, transposes it and has one chunk in flight, waits.  Both launches,
+// generic -> here: 128 x 16 x 16 64 -> 384 29.4 -> 17.2 us (29 MB), 96 -> 576 33.9 -> 19.8, 128 x 32 x 32 32 -> 192 23.7 -> 19.9, 128 x
+// 56 x 56 64 -> 256 77 -> 55 (257 MB, 4.7 TB/s); the smallest, 8 x 16 x 16 64 -> 384 12.7 -> 11.2, 16 x 12 x 12 32 -> 192 11.0 -> 10.9.
+// Their splits go down to two chunks and their sums are folded every two: error against 64 bits 1.18e-7 -> 1.11e-7, 37 x 14 x 14 1.04e-7
+// -> 1.02e-7 (every four: 1.10e-7, and 3 % of the time).  Images of one column, plain lists of pixels that no network has, stay on the
+// generic kernel: what its sums lose over long lists is pinned by a test.
+bool conv_wgrad128_thin(const WgradArgs& a) { return a.ntaps == 1 && (a.Co < 128 || a.Ci < 128); }
 bool conv_wgrad128_ragged(const WgradArgs& a) {
-  if (a.Co < 128 || a.Ci < 128 || a.Co % 8 != 0 || a.Ci % 8 != 0 || a.Cx != a.Ci || a.ntaps < 1 || a.N * a.OH * a.OW < 64) return false;
+  if (conv_wgrad128_thin(a) ? (a.Co < 32 || a.Ci < 32 || a.OW < 2) : (a.Co < 128 || a.Ci < 128)) return false;
+  if (a.Co % 8 != 0 || a.Ci % 8 != 0 || a.Cx != a.Ci || a.ntaps < 1 || a.N * a.OH * a.OW < 64) return false;
   if (wgrad128_flat_period(a) <= 0) return false;
   return (a.Co % 128 != 0 || a.Ci % 128 != 0 || (a.N * a.OH * a.OW) % 64 != 0) && !conv_wgrad_tall_applies(a) && !conv_wgrad_wide_applies(a);
 }
@@ -2125,10 +2136,10 @@ bool conv_wgrad128_applies(const WgradArgs& a) {
   return a.Hi == a.stride * a.OH;
 }
 // pixel splits that leave a workgroup to every compute unit (with fewer than 8 chunks each they would be mostly beginnings and ends;
-// the ragged form goes down to 4, as its layers' sums were that short before)
+// the ragged form goes down to 4, thin 1x1 layers to 2, as their sums were that short before)
 int conv_wgrad128_splits(const WgradArgs& a) {
   const int blocks = conv_wgrad128_paired(a) ? (a.ntaps + 1) / 2 : (a.Ci + 127) / 128 * a.ntaps, tiles = (a.Co + 127) / 128 * blocks;
-  return tiles <= 128 ? std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 64 / (conv_wgrad128_ragged(a) ? 4 : 8))) : 1;
+  return tiles <= 128 ? std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 64 / (conv_wgrad128_thin(a) ? 2 : conv_wgrad128_ragged(a) ? 4 : 8))) : 1;
 }
 
 hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
@@ -2142,6 +2153,7 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   const bool ragged = conv_wgrad128_ragged(a);
   const int total_chunks = (a.N * a.OH * a.OW + 63) / 64;
   Wgrad128Launch L;
+  L.fold_mask = conv_wgrad128_thin(a) ? 1 : 3;
   L.co_tiles = (a.Co + 127) / 128;
   const bool paired = conv_wgrad128_paired(a);
   L.ci_tiles = paired ? 1 : (a.Ci + 127) / 128;

@@ -118,6 +118,15 @@ def test_projecting_block_that_feeds_the_one_below(c, n, h, w):
     ((4, 4, 4, 128, 120, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),       # fewer than 128 channels
     ((1, 7, 9, 128, 128, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),       # less than a chunk
     ((16, 14, 14, 128, 256, 3, 1), "conv_wgrad128w8_kernel<5, flat>"),
+    # 1x1 of fewer than 128 channels on a side: one chunk and a pixel, any image width, a partly filled tile on either side or both,
+    # 32 channels and just below, folds in the middle and at the end of a split; without scratch and at stride 2 the generic kernel
+    ((5, 1, 13, 32, 40, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((2, 31, 31, 32, 192, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((19, 15, 15, 576, 96, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((64, 16, 16, 64, 384, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((5, 64, 1, 64, 96, 1, 1), "conv_wgrad_kernel<128, 128, two sums>"),       # one column
+    ((4, 16, 16, 24, 144, 1, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),
+    ((8, 16, 16, 64, 384, 1, 2), "conv_wgrad_kernel<128, 128, two sums>"),
 ])
 def test_ragged_weight_gradients(case, kernel):
     from paper_1906_09108_amd import kernels as K
