@@ -430,5 +430,9 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s);
 // Output channels a multiple of 320, input channels a multiple of 64: 320 x 64 blocks.
 bool conv_wgrad_tall_applies(const WgradArgs& a);
 hipError_t launch_conv_wgrad_tall(const WgradArgs& a, hipStream_t s);
+// Output channels a multiple of 160, input channels of 8: 160 x 128 blocks, columns over taps and channels.  Needs scratch for its splits.
+bool conv_wgrad_columns_applies(const WgradArgs& a);
+int conv_wgrad_columns_splits(const WgradArgs& a);
+hipError_t launch_conv_wgrad_columns(const WgradArgs& a, hipStream_t s);
 
 }  // namespace fdg

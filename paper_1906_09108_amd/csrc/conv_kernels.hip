@@ -428,6 +428,13 @@ static size_t generic_wgrad_scratch_bytes(const WgradArgs& a) {
   return elems % 4 == 0 ? (size_t)parts * elems * sizeof(float) : 0;
 }
 
+// (without room for the splits the kernels that can add them with atomics run these layers)
+static bool wgrad_runs_columns(const WgradArgs& a) {
+  if (!conv_wgrad_columns_applies(a)) return false;
+  const int S = conv_wgrad_columns_splits(a);
+  return S == 1 || (a.scratch && a.scratch_bytes >= (size_t)S * a.Co * a.ntaps * a.Ci * sizeof(float));
+}
+
 hipError_t launch_conv_wgrad(const WgradArgs& a, hipStream_t s) {
   if (a.Co % 8 != 0 || a.Cx % 8 != 0 || a.Ci > a.Cx || a.ntaps < 1 || a.ntaps > 9 || a.N * a.OH * a.OW <= 0)
     return hipErrorInvalidValue;
@@ -435,6 +442,7 @@ hipError_t launch_conv_wgrad(const WgradArgs& a, hipStream_t s) {
   if (conv_wgrad128_applies(a) && (!conv_wgrad128_thin(a) || (a.scratch && a.scratch_bytes >= (size_t)conv_wgrad128_splits(a) * a.Co * a.Ci * sizeof(float))))
     return launch_conv_wgrad128(a, s);
   if (conv_wgrad_tall_applies(a)) return launch_conv_wgrad_tall(a, s);
+  if (wgrad_runs_columns(a)) return launch_conv_wgrad_columns(a, s);
   if (conv_wgrad_wide_applies(a)) return launch_conv_wgrad_wide(a, s);
   if (conv_wgrad_narrow_applies(a) && a.scratch && a.scratch_bytes >= conv_wgrad_narrow_scratch_bytes(a))
     return launch_conv_wgrad_narrow(a, s);
@@ -751,6 +759,7 @@ size_t conv_wgrad_scratch_bytes(const ConvShape& c_in) {
     for (int q = 0; q < 3; ++q) a.tap[r * 3 + q] = pack_tap(r - 1, q - 1, 0);
   a.Cx = c.Cip;
   if (conv_wgrad_narrow_applies(a)) return conv_wgrad_narrow_scratch_bytes(a);
+  if (!conv_wgrad128_applies(a) && conv_wgrad_columns_applies(a)) return (size_t)conv_wgrad_columns_splits(a) * c.Co * c.T * c.Ci * 4;
   if (!(conv_wgrad_wide_applies(a) || conv_wgrad128_applies(a) || conv_wgrad_tall_applies(a))) return generic_wgrad_scratch_bytes(a);
   // room for the partial sums of the pixel splits: 8 of them, or as many as it takes the 160 x 160 kernel to fill
   // the chip when a layer has few blocks (160 -> 160: 9 blocks per filter)

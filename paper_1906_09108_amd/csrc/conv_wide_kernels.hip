@@ -2240,31 +2240,38 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
 // wave >> 1) takes ONE 16-pixel step of it; the fragments of chunk c+1 are read during the MFMAs of chunk c.
 // Rows are 640 bytes (dy) and 128 bytes (x): the row pitch is 4 mod 8 slots of 32 bytes, so pixels p and p+2
 // start in the same banks and the slot is XORed with 2 * ((pixel >> 1) & 1).
-template <int STAGES>
+// CW = 2: 160 output channels x 128 columns of the flattened (tap, input channel) axis, which is the order of dw: a wave owns all 160
+// channels and one half of the columns, the unit a lane loads belongs to one tap (input channels are a multiple of 8), units past the
+// last column come from the zero word.  160 channels have no other tiling on 32x32x16 MFMAs that wastes as little (160 x 1440: 6 %); a
+// chunk is 18 KB for 71 flop a byte (54.6 with 320 x 64).  For layers of 160 channels, which ran conv_wgrad_dma_kernel (16x16x32 MFMAs,
+// loads, reads and MFMAs of a chunk one after the other), and for 16 -> 160, which ran the generic kernel a tap at a time:
+// 128 x 32 x 32, both launches: 160 -> 160 124 -> 88 us (685 TFLOP/s), 160 -> 320 at stride 2 72 -> 50, its 1x1 projection 42 -> 20,
+// 16 -> 160 163 -> 28; batch 8: 31.9 -> 27.3, 26.3 -> 21.6, 18.6 -> 14.7.
+template <int STAGES, int CW = 1>
 __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad128Launch L) {
-  constexpr int TA = 320, TB = 64, BKP = 32;
+  constexpr int TA = CW == 1 ? 320 : 160, TB = 64 * CW, BKP = 32;
   constexpr int ROWA = TA * 2, ROWBB = TB * 2, PARTA = BKP * ROWA, PARTB = BKP * ROWBB, STAGE = PARTA + PARTB;
   constexpr int UA = TA / 8, UB = TB / 8;                  // 16-byte units per row
-  constexpr int JA = BKP * UA / 256, JB = BKP * UB / 256, NJ = JA + JB;
+  constexpr int JA = (BKP * UA + 255) / 256, JB = BKP * UB / 256, NJ = JA + JB;
   constexpr int FA = 5, FB = 2, NF = FA + FB, NM = FA * FB;
-  static_assert(BKP * UA % 256 == 0 && BKP * UB % 256 == 0, "whole load instructions");
+  static_assert(BKP * UA % 128 == 0 && BKP * UB % 256 == 0, "whole load instructions");
+  constexpr bool DUMP = BKP * UA % 256 != 0;               // the last dy load of waves 2 and 3 goes to 1 KB behind the stages
   static_assert(STAGES >= 4 && (STAGES - 2) * NJ < 64, "pipeline depth / vmcnt range");
-  static_assert(STAGES * STAGE >= 4 * FA * 16 * 256, "room for the exchange of the partial blocks");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // STAGES * STAGE
+  static_assert(CW == 2 || STAGES * STAGE >= 4 * FA * 16 * 256, "room for the exchange of the partial blocks");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // wgrad_tall_lds<STAGES, CW>()
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave_m = wave & 1, wk = wave >> 1;
+  const int wave_m = CW == 1 ? wave & 1 : 0, wave_n = CW == 1 ? 0 : wave & 1, wk = wave >> 1;
 
   // blocks of one XCD: consecutive in the order (split, output tile, input tile, tap), see the 128 x 128 kernel
   int t = xcd_consecutive(blockIdx.x, gridDim.x);
-  const int tapi = t % a.ntaps; t /= a.ntaps;
-  const int ci_t = t % L.ci_tiles; t /= L.ci_tiles;
+  const int tapi = CW == 1 ? t % a.ntaps : 0;
+  if (CW == 1) t /= a.ntaps;
+  const int ci_t = t % L.ci_tiles; t /= L.ci_tiles;       // CW = 2: the columns' tile
   const int co_t = t % L.co_tiles;
   const int split = t / L.co_tiles;
   const int co0 = co_t * TA, ci0 = ci_t * TB;
-  const int tp = a.tap[tapi];
-  const int dh = (tp & 0xff) - 8, dw = ((tp >> 8) & 0xff) - 8;
   const int total_chunks = (a.N * a.OH * a.OW) / BKP;
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
@@ -2278,20 +2285,24 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   for (int j = 0; j < JA; ++j) {
     const int P = 64 * (4 * j + wave) + lane;
     const int r = P / UA, up = P % UA;
-    const int u = 2 * ((up >> 1) ^ (2 * ((r >> 1) & 1))) + (up & 1);
+    const int u = CW == 1 ? 2 * ((up >> 1) ^ (2 * ((r >> 1) & 1))) + (up & 1) : up;   // 320 bytes: 4 pixels are in 4 different 64-byte windows
     aptr[j] = reinterpret_cast<const char*>(a.dy) + ((size_t)(chunk_lo * BKP + r) * a.Co + co0 + u * 8) * 2;
+    if (DUMP && r >= BKP) aptr[j] = reinterpret_cast<const char*>(g_zero_word);
   }
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
     const int P = 64 * (4 * j + wave) + lane;
     const int r = P / UB, up = P % UB;
-    const int u = 2 * ((up >> 1) ^ (2 * ((r >> 1) & 1))) + (up & 1);
+    const int u = 2 * ((up >> 1) ^ (CW == 1 ? 2 * ((r >> 1) & 1) : 2 * (r & 3))) + (up & 1);
+    const int col = ci0 + u * 8, my_tap = CW == 1 ? tapi : col / a.Ci, ci = CW == 1 ? col : col % a.Ci;
+    const int tp = a.tap[CW == 1 || my_tap < a.ntaps ? my_tap : 0];
+    const int dh = (tp & 0xff) - 8, dw = ((tp >> 8) & 0xff) - 8;
     const int m = chunk_lo * BKP + r;
     const int ow = m % a.OW, t2 = m / a.OW, oh = t2 % a.OH, nimg = t2 / a.OH;
     const int iw = ow * a.stride + dw;
     const bool colok = (unsigned)iw < (unsigned)a.Wi;
     bptr[j] = reinterpret_cast<const char*>(a.x) +
-              ((((long long)nimg * a.Hi + oh * a.stride + dh) * a.Wi + iw) * a.Cx + ci0 + u * 8) * 2;
+              ((((long long)nimg * a.Hi + oh * a.stride + dh) * a.Wi + iw) * a.Cx + ci) * 2;
     unsigned mask = 0;
     int ohq = oh;
     for (int q = 0; q < L.period; ++q) {
@@ -2299,7 +2310,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
       ohq += L.d_oh;
       if (ohq >= a.OH) ohq -= a.OH;
     }
-    bmask[j] = mask;
+    bmask[j] = my_tap < a.ntaps ? mask : 0u;
   }
   const char* zero = reinterpret_cast<const char*>(g_zero_word);
 
@@ -2307,7 +2318,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   auto issue_one = [&](int d, int c) {   // piece d of chunk c (relative to chunk_lo)
     unsigned char* stage = smem + (size_t)(c % STAGES) * STAGE;
     if (d < JA) {
-      dma16(aptr[d] + (long long)c * L.a_step, stage + (64 * (4 * d + wave)) * 16);
+      const bool dump = DUMP && d == JA - 1 && wave >= 2;
+      dma16(aptr[d] + (dump ? 0ll : (long long)c * L.a_step), dump ? smem + STAGES * STAGE : stage + (64 * (4 * d + wave)) * 16);
     } else {
       const int j = d - JA;
       const bool ok = (bmask[j] >> issue_phase) & 1u;
@@ -2332,12 +2344,12 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   {
     const int g = lane >> 4, i16 = lane & 15;
     const int prow = 16 * wk + 8 * (g >> 1) + (i16 >> 2);
-    const int x = 2 * (((i16 >> 2) >> 1) & 1);
+    const int xa = CW == 1 ? 2 * (((i16 >> 2) >> 1) & 1) : 0, xb = CW == 1 ? xa : 2 * ((i16 >> 2) & 3);
 #pragma unroll
     for (int f = 0; f < FA; ++f)
-      aoff[f] = prow * ROWA + (i16 & 3) * 8 + (((2 * (FA * wave_m + f) + (g & 1)) ^ x) * 32);
+      aoff[f] = prow * ROWA + (i16 & 3) * 8 + (((2 * (FA * wave_m + f) + (g & 1)) ^ xa) * 32);
 #pragma unroll
-    for (int f = 0; f < FB; ++f) boff[f] = PARTA + prow * ROWBB + (i16 & 3) * 8 + (((2 * f + (g & 1)) ^ x) * 32);
+    for (int f = 0; f < FB; ++f) boff[f] = PARTA + prow * ROWBB + (i16 & 3) * 8 + (((2 * (FB * wave_n + f) + (g & 1)) ^ xb) * 32);
   }
   const unsigned lds0 = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)smem);
   // fragment position in issue order = the order the MFMAs (K = FB i + j) need them: A0, B0, B1, A1, ..., A4
@@ -2503,15 +2515,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   // D block i: lane holds column ci = 32 wk + (lane & 31), rows co = 32 i + 8 (v >> 2) + 4 (lane >> 5) + (v & 3)
   float* dst = L.partial ? L.partial + (size_t)split * L.split_stride : a.dw;
   const int mode = (L.partial || (L.splits == 1 && a.overwrite)) ? 0 : (L.splits > 1 ? 1 : 2);
-  const int ntaps = a.ntaps, Ci = a.Ci;
-  const int ci = ci0 + 32 * wk + (lane & 31);
+  const int row = a.ntaps * a.Ci, col = (CW == 1 ? tapi * a.Ci : 0) + ci0 + 64 * wave_n + 32 * wk + (lane & 31);
+  if (CW == 2 && col >= row) return;
   const int co_base = co0 + 160 * wave_m + 4 * (lane >> 5);
 #pragma unroll
   for (int i = 0; i < FA; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int co = co_base + 32 * i + 8 * (v >> 2) + (v & 3);
-      float* o = dst + ((size_t)co * ntaps + tapi) * Ci + ci;
+      float* o = dst + (size_t)co * row + col;
       const float val = keep[i][v];
       if (mode == 0) *o = val;
       else if (mode == 1) atomicAdd(o, val);
@@ -2524,32 +2536,43 @@ bool conv_wgrad_tall_applies(const WgradArgs& a) {
   if (a.OW < 1 || 32 % a.OW != 0 || (a.N * a.OH * a.OW) % 32 != 0 || a.OH > 32) return false;
   return a.Hi == a.stride * a.OH;
 }
+bool conv_wgrad_columns_applies(const WgradArgs& a) {
+  // (8 x 32 x 32 16 -> 160 on the generic kernel 17.0 us, here 18.2; 37 x 32 x 32 48 and 24)
+  if (a.Ci < 128 && a.N * a.OH * a.OW < 16384) return false;
+  if (a.Co % 160 != 0 || a.Ci % 8 != 0 || a.Ci < 16 || a.Cx != a.Ci || a.ntaps < 1 || conv_wgrad_tall_applies(a)) return false;
+  if (a.OW < 1 || 32 % a.OW != 0 || (a.N * a.OH * a.OW) % 32 != 0 || a.OH > 32) return false;
+  return a.Hi == a.stride * a.OH;
+}
+// One round of workgroups; splits of at least eight chunks (of four: 16 x 16 x 16 160 -> 160 21.1 -> 22.5 us).  Error against 64 bits, before -> here: 128 x 32 x 32 160 -> 160 3.58e-7 ->
+// 2.85e-7, 16 -> 160 2.38e-7 -> 1.34e-7, batch 8 1.19e-7 -> 1.04e-7.
+int conv_wgrad_columns_splits(const WgradArgs& a) {
+  const int tiles = a.Co / 160 * ((a.ntaps * a.Ci + 127) / 128);
+  return std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 32 / 8));
+}
 
-hipError_t launch_conv_wgrad_tall(const WgradArgs& a, hipStream_t s) {
-  if (!conv_wgrad_tall_applies(a) || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
+template <int STAGES, int CW>
+static constexpr size_t wgrad_tall_lds() {   // the stages, or the exchange of the partial blocks
+  return std::max((size_t)STAGES * 32 * (CW == 1 ? 640 + 128 : 320 + 256) + (CW == 1 ? 0 : 1024), (size_t)4 * 5 * 16 * 256);
+}
+
+// S pixel splits, through scratch where there are several
+template <int CW>
+static hipError_t run_wgrad_tall(const WgradArgs& a, int S, const char* name, hipStream_t s) {
   constexpr int STAGES = 4;   // 4 x 24 KB (deeper rings measured slower)
-  constexpr size_t lds = (size_t)STAGES * 32 * (640 + 128);
+  constexpr size_t lds = wgrad_tall_lds<STAGES, CW>();
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_tall_kernel<STAGES>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_tall_kernel<STAGES, CW>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     configured = true;
   }
   const int total_chunks = a.N * a.OH * a.OW / 32;
   Wgrad128Launch L;
-  L.co_tiles = a.Co / 320;
-  L.ci_tiles = a.Ci / 64;
-  const int tiles = L.co_tiles * L.ci_tiles * a.ntaps;
+  L.co_tiles = a.Co / (CW == 1 ? 320 : 160);
+  L.ci_tiles = CW == 1 ? a.Ci / 64 : (a.ntaps * a.Ci + 127) / 128;
+  const int tiles = L.co_tiles * L.ci_tiles * (CW == 1 ? a.ntaps : 1);
   const size_t elems = (size_t)a.Co * a.ntaps * a.Ci;
-  const int max_by_scratch = a.scratch ? (int)(a.scratch_bytes / (elems * 4)) : 0;
-  int S = 1;
-  if (tiles <= 128 && max_by_scratch >= 2) {
-    S = 256 / tiles;
-    if (S > max_by_scratch) S = max_by_scratch;
-    if (S > total_chunks / 16) S = total_chunks / 16;
-    if (S < 1) S = 1;
-  }
   L.chunks_per_split = (total_chunks + S - 1) / S;
   L.splits = (total_chunks + L.chunks_per_split - 1) / L.chunks_per_split;
   L.partial = L.splits > 1 ? a.scratch : nullptr;
@@ -2561,16 +2584,38 @@ hipError_t launch_conv_wgrad_tall(const WgradArgs& a, hipStream_t s) {
   L.period = a.OH / g;
   L.a_step = (long long)32 * a.Co * 2;
   L.b_step = (long long)d_oh_full * a.stride * a.Wi * a.Cx * 2;
-  note_kernel("conv_wgrad_tall_kernel<4>");
-  hipLaunchKernelGGL((conv_wgrad_tall_kernel<STAGES>), dim3(tiles * L.splits), dim3(256), lds, s, a, L);
+  note_kernel(name);
+  hipLaunchKernelGGL((conv_wgrad_tall_kernel<STAGES, CW>), dim3(tiles * L.splits), dim3(256), lds, s, a, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
+  if (CW == 2) return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
   const size_t n4 = elems / 4;
   size_t blocks = (n4 + 255) / 256;
   if (blocks > 2048) blocks = 2048;
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<float4*>(a.dw),
                      reinterpret_cast<const float4*>(a.scratch), n4, L.splits, elems / 4, a.overwrite);
   return hipGetLastError();
+}
+
+hipError_t launch_conv_wgrad_tall(const WgradArgs& a, hipStream_t s) {
+  if (!conv_wgrad_tall_applies(a) || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
+  const int tiles = a.Co / 320 * (a.Ci / 64) * a.ntaps, total_chunks = a.N * a.OH * a.OW / 32;
+  const int max_by_scratch = a.scratch ? (int)(a.scratch_bytes / ((size_t)a.Co * a.ntaps * a.Ci * 4)) : 0;
+  int S = 1;
+  if (tiles <= 128 && max_by_scratch >= 2) {
+    S = 256 / tiles;
+    if (S > max_by_scratch) S = max_by_scratch;
+    if (S > total_chunks / 16) S = total_chunks / 16;
+    if (S < 1) S = 1;
+  }
+  return run_wgrad_tall<1>(a, S, "conv_wgrad_tall_kernel<4>", s);
+}
+
+hipError_t launch_conv_wgrad_columns(const WgradArgs& a, hipStream_t s) {
+  const int S = conv_wgrad_columns_applies(a) ? conv_wgrad_columns_splits(a) : 0;
+  if (S < 1 || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
+  if (S > 1 && (!a.scratch || a.scratch_bytes < (size_t)S * a.Co * a.ntaps * a.Ci * 4)) return hipErrorInvalidValue;
+  return run_wgrad_tall<2>(a, S, "conv_wgrad_tall_kernel<4, columns>", s);
 }
 
 bool conv_wgrad_wide_applies(const WgradArgs& a) {

@@ -145,3 +145,29 @@ def test_tiles_of_256_pixels(case, kernel):
     TK.test_conv_fwd(case)
     assert K.fdgk_last_kernel() == kernel
     TK.test_conv_dgrad(case)
+
+
+# Weight gradients of 160 output channels on blocks of 128 columns of the (tap, channel) axis: columns that fill whole tiles and not, a
+# unit's tap changing within a tile, strides, 1x1, images narrower than a chunk, fewer chunks than stages, chunks in odd and even
+# number; without scratch (test_conv_wgrad runs both) and outside the rule the kernels that ran before
+@pytest.mark.parametrize("case, kernel", [
+    ((1, 8, 8, 160, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
+    ((7, 16, 16, 160, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
+    ((5, 32, 32, 160, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
+    ((64, 16, 16, 24, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
+    ((4, 32, 32, 160, 320, 3, 2), "conv_wgrad_tall_kernel<4, columns>"),
+    ((8, 16, 16, 160, 320, 1, 2), "conv_wgrad_tall_kernel<4, columns>"),
+    ((512, 4, 8, 16, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
+    ((511, 4, 8, 16, 160, 3, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),      # 16 channels over fewer than 16384 pixels
+    ((2, 64, 64, 160, 160, 3, 1), "conv_wgrad_dma_kernel<3>"),               # rows longer than a chunk
+    ((4, 32, 32, 8, 160, 3, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),      # fewer than 16 channels
+])
+def test_weight_gradients_over_columns(case, kernel):
+    from paper_1906_09108_amd import kernels as K
+    n, h, w, ci, co, k, s = case
+    TK.test_conv_wgrad(case)
+    import torch as t
+    z = [t.zeros(c, device="cuda", dtype=t.bfloat16) for c in (n * h * w * ci, n * ((h - 1) // s + 1) * ((w - 1) // s + 1) * co)]
+    dw, scratch = t.empty(co * k * k * ci, device="cuda"), t.empty(K.fdgk_conv_wgrad_scratch_bytes(n, h, w, ci, co, k, s) // 4, device="cuda")
+    K.fdgk_conv_wgrad(*z, dw, scratch, n, h, w, ci, co, k, s, overwrite=True)
+    assert K.fdgk_last_kernel() == kernel
