@@ -2247,7 +2247,12 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
 // loads, reads and MFMAs of a chunk one after the other), and for 16 -> 160, which ran the generic kernel a tap at a time:
 // 128 x 32 x 32, both launches: 160 -> 160 124 -> 88 us (685 TFLOP/s), 160 -> 320 at stride 2 72 -> 50, its 1x1 projection 42 -> 20,
 // 16 -> 160 163 -> 28; batch 8: 31.9 -> 27.3, 26.3 -> 21.6, 18.6 -> 14.7.
-template <int STAGES, int CW = 1>
+// FLAT (with CW = 2): unit stride, any image width and number of pixels, as the flat and ragged forms of the 128 x 128 kernel: the x
+// pointer advances 32 pixels a chunk, whether a pixel is valid repeats every OH OW / gcd(32, OH OW) chunks, rows past the last pixel
+// come from the zero word.  For 16 -> 160 at other widths: 37 x 28 x 28 45.5 -> 26.6 us, 128 x 24 x 24 84 -> 25.6 (error against 64 bits
+// 1.29e-7 -> 1.08e-7 and 1.80e-7 -> 1.18e-7).  160 -> 160 would gain as well (128 x 28 x 28 147 -> 77), but with sums that are not
+// folded its error is 2.42e-7 and not 1.55e-7.
+template <int STAGES, int CW = 1, bool FLAT = false>
 __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad128Launch L) {
   constexpr int TA = CW == 1 ? 320 : 160, TB = 64 * CW, BKP = 32;
   constexpr int ROWA = TA * 2, ROWBB = TB * 2, PARTA = BKP * ROWA, PARTB = BKP * ROWBB, STAGE = PARTA + PARTB;
@@ -2272,7 +2277,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   const int co_t = t % L.co_tiles;
   const int split = t / L.co_tiles;
   const int co0 = co_t * TA, ci0 = ci_t * TB;
-  const int total_chunks = (a.N * a.OH * a.OW) / BKP;
+  const int Mtot = a.N * a.OH * a.OW, total_chunks = (Mtot + (FLAT ? BKP - 1 : 0)) / BKP;
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
   if (n <= 0) return;
@@ -2280,13 +2285,16 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   // ---- per-thread DMA sources: instruction j of this wave covers the 64 units 64*(4j+wave) .. of a tile ----
   const char* aptr[JA];
   const char* bptr[JB];
-  unsigned bmask[JB];
+  typedef typename std::conditional<FLAT, unsigned long long, unsigned>::type mask_t;
+  mask_t bmask[JB];
+  int arow[JA], brow[JB];   // FLAT: rows of the chunk
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
     const int P = 64 * (4 * j + wave) + lane;
     const int r = P / UA, up = P % UA;
     const int u = CW == 1 ? 2 * ((up >> 1) ^ (2 * ((r >> 1) & 1))) + (up & 1) : up;   // 320 bytes: 4 pixels are in 4 different 64-byte windows
     aptr[j] = reinterpret_cast<const char*>(a.dy) + ((size_t)(chunk_lo * BKP + r) * a.Co + co0 + u * 8) * 2;
+    arow[j] = r;
     if (DUMP && r >= BKP) aptr[j] = reinterpret_cast<const char*>(g_zero_word);
   }
 #pragma unroll
@@ -2301,16 +2309,30 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
     const int ow = m % a.OW, t2 = m / a.OW, oh = t2 % a.OH, nimg = t2 / a.OH;
     const int iw = ow * a.stride + dw;
     const bool colok = (unsigned)iw < (unsigned)a.Wi;
-    bptr[j] = reinterpret_cast<const char*>(a.x) +
-              ((((long long)nimg * a.Hi + oh * a.stride + dh) * a.Wi + iw) * a.Cx + ci) * 2;
-    unsigned mask = 0;
-    int ohq = oh;
-    for (int q = 0; q < L.period; ++q) {
-      if (colok && (unsigned)(ohq * a.stride + dh) < (unsigned)a.Hi) mask |= 1u << q;
-      ohq += L.d_oh;
-      if (ohq >= a.OH) ohq -= a.OH;
+    brow[j] = r;
+    mask_t mask = 0;
+    if constexpr (FLAT) {
+      bptr[j] = reinterpret_cast<const char*>(a.x) + (((long long)m + dh * a.Wi + dw) * a.Cx + ci) * 2;
+      int owq = ow, ohq = oh;
+      for (int q = 0; q < L.period; ++q) {
+        if ((unsigned)(owq + dw) < (unsigned)a.Wi && (unsigned)(ohq + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
+        owq += L.step_w;
+        const int carry = owq >= a.OW ? 1 : 0;
+        owq -= carry * a.OW;
+        ohq += L.d_oh + carry;          // d_oh < OH: below 2 OH
+        if (ohq >= a.OH) ohq -= a.OH;
+      }
+    } else {
+      bptr[j] = reinterpret_cast<const char*>(a.x) +
+                ((((long long)nimg * a.Hi + oh * a.stride + dh) * a.Wi + iw) * a.Cx + ci) * 2;
+      int ohq = oh;
+      for (int q = 0; q < L.period; ++q) {
+        if (colok && (unsigned)(ohq * a.stride + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
+        ohq += L.d_oh;
+        if (ohq >= a.OH) ohq -= a.OH;
+      }
     }
-    bmask[j] = my_tap < a.ntaps ? mask : 0u;
+    bmask[j] = my_tap < a.ntaps ? mask : (mask_t)0;
   }
   const char* zero = reinterpret_cast<const char*>(g_zero_word);
 
@@ -2319,10 +2341,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
     unsigned char* stage = smem + (size_t)(c % STAGES) * STAGE;
     if (d < JA) {
       const bool dump = DUMP && d == JA - 1 && wave >= 2;
-      dma16(aptr[d] + (dump ? 0ll : (long long)c * L.a_step), dump ? smem + STAGES * STAGE : stage + (64 * (4 * d + wave)) * 16);
+      if constexpr (FLAT) {
+        const bool ok = arow[d] < Mtot - (chunk_lo + c) * BKP;   // (a dumped load's own source is the zero word)
+        const uint64_t pa = (uint64_t)(aptr[d] + (dump ? 0ll : (long long)c * L.a_step)), pz = (uint64_t)zero;
+        const uint32_t lo = ok ? (uint32_t)pa : (uint32_t)pz, hi = ok ? (uint32_t)(pa >> 32) : (uint32_t)(pz >> 32);
+        dma16((const char*)(((uint64_t)hi << 32) | lo), dump ? smem + STAGES * STAGE : stage + (64 * (4 * d + wave)) * 16);
+      } else dma16(aptr[d] + (dump ? 0ll : (long long)c * L.a_step), dump ? smem + STAGES * STAGE : stage + (64 * (4 * d + wave)) * 16);
     } else {
       const int j = d - JA;
-      const bool ok = (bmask[j] >> issue_phase) & 1u;
+      const bool ok = ((bmask[j] >> issue_phase) & 1u) && (!FLAT || brow[j] < Mtot - (chunk_lo + c) * BKP);
       const uint64_t pa = (uint64_t)(bptr[j] + (long long)c * L.b_step), pz = (uint64_t)zero;
       const uint32_t lo = ok ? (uint32_t)pa : (uint32_t)pz, hi = ok ? (uint32_t)(pa >> 32) : (uint32_t)(pz >> 32);
       dma16((const char*)(((uint64_t)hi << 32) | lo), stage + PARTA + (64 * (4 * j + wave)) * 16);
@@ -2536,12 +2563,23 @@ bool conv_wgrad_tall_applies(const WgradArgs& a) {
   if (a.OW < 1 || 32 % a.OW != 0 || (a.N * a.OH * a.OW) % 32 != 0 || a.OH > 32) return false;
   return a.Hi == a.stride * a.OH;
 }
+// chunks of 32 pixels per repetition of the flat form's validity pattern (0: it does not apply)
+static int wgrad_columns_flat_period(const WgradArgs& a) {
+  if (a.stride != 1 || a.Hi != a.OH || a.Wi != a.OW || a.OW < 1 || a.OH < 1) return 0;
+  if (a.ntaps == 1 || a.Ci >= 128) return 0;   // those run the 128 x 128 kernel, whose folded sums are closer to 64 bits
+  const long long img = (long long)a.OH * a.OW;
+  long long g = 1;
+  while (g < 32 && img % (2 * g) == 0) g *= 2;
+  return img / g <= 64 ? (int)(img / g) : 0;
+}
+static bool wgrad_columns_by_rows(const WgradArgs& a) {   // chunks of whole rows
+  return a.OW >= 1 && 32 % a.OW == 0 && (a.N * a.OH * a.OW) % 32 == 0 && a.OH <= 32 && a.Hi == a.stride * a.OH;
+}
 bool conv_wgrad_columns_applies(const WgradArgs& a) {
   // (8 x 32 x 32 16 -> 160 on the generic kernel 17.0 us, here 18.2; 37 x 32 x 32 48 and 24)
   if (a.Ci < 128 && a.N * a.OH * a.OW < 16384) return false;
   if (a.Co % 160 != 0 || a.Ci % 8 != 0 || a.Ci < 16 || a.Cx != a.Ci || a.ntaps < 1 || conv_wgrad_tall_applies(a)) return false;
-  if (a.OW < 1 || 32 % a.OW != 0 || (a.N * a.OH * a.OW) % 32 != 0 || a.OH > 32) return false;
-  return a.Hi == a.stride * a.OH;
+  return wgrad_columns_by_rows(a) || wgrad_columns_flat_period(a) > 0;
 }
 // One round of workgroups; splits of at least eight chunks (of four: 16 x 16 x 16 160 -> 160 21.1 -> 22.5 us).  Error against 64 bits, before -> here: 128 x 32 x 32 160 -> 160 3.58e-7 ->
 // 2.85e-7, 16 -> 160 2.38e-7 -> 1.34e-7, batch 8 1.19e-7 -> 1.04e-7.
@@ -2556,18 +2594,18 @@ static constexpr size_t wgrad_tall_lds() {   // the stages, or the exchange of t
 }
 
 // S pixel splits, through scratch where there are several
-template <int CW>
+template <int CW, bool FLAT = false>
 static hipError_t run_wgrad_tall(const WgradArgs& a, int S, const char* name, hipStream_t s) {
   constexpr int STAGES = 4;   // 4 x 24 KB (deeper rings measured slower)
   constexpr size_t lds = wgrad_tall_lds<STAGES, CW>();
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_tall_kernel<STAGES, CW>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_tall_kernel<STAGES, CW, FLAT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  const int total_chunks = a.N * a.OH * a.OW / 32;
+  const int total_chunks = (a.N * a.OH * a.OW + 31) / 32;
   Wgrad128Launch L;
   L.co_tiles = a.Co / (CW == 1 ? 320 : 160);
   L.ci_tiles = CW == 1 ? a.Ci / 64 : (a.ntaps * a.Ci + 127) / 128;
@@ -2584,8 +2622,14 @@ static hipError_t run_wgrad_tall(const WgradArgs& a, int S, const char* name, hi
   L.period = a.OH / g;
   L.a_step = (long long)32 * a.Co * 2;
   L.b_step = (long long)d_oh_full * a.stride * a.Wi * a.Cx * 2;
+  if (FLAT) {
+    L.period = wgrad_columns_flat_period(a);
+    if (L.period <= 0) return hipErrorInvalidValue;
+    L.step_w = 32 % a.OW;
+    L.b_step = (long long)32 * a.Cx * 2;
+  }
   note_kernel(name);
-  hipLaunchKernelGGL((conv_wgrad_tall_kernel<STAGES, CW>), dim3(tiles * L.splits), dim3(256), lds, s, a, L);
+  hipLaunchKernelGGL((conv_wgrad_tall_kernel<STAGES, CW, FLAT>), dim3(tiles * L.splits), dim3(256), lds, s, a, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
   if (CW == 2) return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
@@ -2615,6 +2659,7 @@ hipError_t launch_conv_wgrad_columns(const WgradArgs& a, hipStream_t s) {
   const int S = conv_wgrad_columns_applies(a) ? conv_wgrad_columns_splits(a) : 0;
   if (S < 1 || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
   if (S > 1 && (!a.scratch || a.scratch_bytes < (size_t)S * a.Co * a.ntaps * a.Ci * 4)) return hipErrorInvalidValue;
+  if (!wgrad_columns_by_rows(a)) return run_wgrad_tall<2, true>(a, S, "conv_wgrad_tall_kernel<4, columns, flat>", s);
   return run_wgrad_tall<2>(a, S, "conv_wgrad_tall_kernel<4, columns>", s);
 }
 

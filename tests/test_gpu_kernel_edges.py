@@ -159,6 +159,10 @@ def test_tiles_of_256_pixels(case, kernel):
     ((8, 16, 16, 160, 320, 1, 2), "conv_wgrad_tall_kernel<4, columns>"),
     ((512, 4, 8, 16, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns>"),
     ((511, 4, 8, 16, 160, 3, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),      # 16 channels over fewer than 16384 pixels
+    ((21, 28, 28, 16, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns, flat>"),   # pixels that fill no whole chunk
+    ((60, 15, 22, 40, 160, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>"),       # the validity of a pixel repeats too late
+    ((301, 7, 9, 40, 320, 3, 1), "conv_wgrad_tall_kernel<4, columns, flat>"),
+    ((342, 48, 1, 16, 160, 3, 1), "conv_wgrad_tall_kernel<4, columns, flat>"),   # rows of one pixel
     ((2, 64, 64, 160, 160, 3, 1), "conv_wgrad_dma_kernel<3>"),               # rows longer than a chunk
     ((4, 32, 32, 8, 160, 3, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),      # fewer than 16 channels
 ])
