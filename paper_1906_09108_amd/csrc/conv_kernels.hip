@@ -447,7 +447,7 @@ hipError_t launch_conv_wgrad(const WgradArgs& a, hipStream_t s) {
   if (conv_wgrad_narrow_applies(a) && a.scratch && a.scratch_bytes >= conv_wgrad_narrow_scratch_bytes(a))
     return launch_conv_wgrad_narrow(a, s);
   if (a.Co <= 64 && a.Cx <= 64) return run_wgrad<32, 32, 1, 1, 4>(a, s);
-  if (a.Cx <= 32) return run_wgrad<128, 32, 4, 1, 1>(a, s);   // many output channels from few inputs (WRN's 16 -> 160)
+  if (a.Cx <= 32) return run_wgrad<128, 32, 4, 1, 1>(a, s);   // many output channels from few inputs (WRN's 16 -> 160 at small batches)
   return run_wgrad<128, 128, 2, 2, 1>(a, s);
 }
 
