@@ -424,6 +424,7 @@ hipError_t launch_conv_wgrad_wide(const WgradArgs& a, hipStream_t s);
 // The same for channel counts that are multiples of 128: 128 x 128 blocks, contraction split over the waves.
 bool conv_wgrad128_applies(const WgradArgs& a);
 bool conv_wgrad128_ragged(const WgradArgs& a);
+bool conv_wgrad128_paired(const WgradArgs& a);
 bool conv_wgrad128_thin(const WgradArgs& a);   // 1x1 with fewer than 128 channels on a side
 int conv_wgrad128_splits(const WgradArgs& a);   // slots of scratch it can use
 hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s);

@@ -428,19 +428,25 @@ static size_t generic_wgrad_scratch_bytes(const WgradArgs& a) {
   return elems % 4 == 0 ? (size_t)parts * elems * sizeof(float) : 0;
 }
 
-// (without room for the splits the kernels that can add them with atomics run these layers)
+// Where the kernels below took layers over from the generic kernel, they run them with room for their splits in scratch: they do not
+// split without it, and the generic kernel, which can add its splits with atomics, is then the faster and the more exact one.
+// Without scratch, generic / one workgroup a tile: 128 x 64 x 64 64 -> 128 3x3 at stride 2 106 / 920 us (error 2.5e-7 / 4.1e-7),
+// 128 x 32 x 32 192 -> 160 1x1 52 / 1032 us (2.3e-7 / 4.1e-7).
+static bool wgrad_has_room(const WgradArgs& a, int splits) {
+  return splits == 1 || (a.scratch && a.scratch_bytes >= (size_t)splits * a.Co * a.ntaps * a.Ci * sizeof(float));
+}
+static bool wgrad_runs_128(const WgradArgs& a) {
+  if (!conv_wgrad128_applies(a)) return false;
+  return !(conv_wgrad128_ragged(a) || conv_wgrad128_paired(a)) || wgrad_has_room(a, conv_wgrad128_splits(a));
+}
 static bool wgrad_runs_columns(const WgradArgs& a) {
-  if (!conv_wgrad_columns_applies(a)) return false;
-  const int S = conv_wgrad_columns_splits(a);
-  return S == 1 || (a.scratch && a.scratch_bytes >= (size_t)S * a.Co * a.ntaps * a.Ci * sizeof(float));
+  return conv_wgrad_columns_applies(a) && wgrad_has_room(a, conv_wgrad_columns_splits(a));
 }
 
 hipError_t launch_conv_wgrad(const WgradArgs& a, hipStream_t s) {
   if (a.Co % 8 != 0 || a.Cx % 8 != 0 || a.Ci > a.Cx || a.ntaps < 1 || a.ntaps > 9 || a.N * a.OH * a.OW <= 0)
     return hipErrorInvalidValue;
-  // (a thin layer is one to six tiles: without room for its splits the generic kernel, which can add them with atomics, runs it)
-  if (conv_wgrad128_applies(a) && (!conv_wgrad128_thin(a) || (a.scratch && a.scratch_bytes >= (size_t)conv_wgrad128_splits(a) * a.Co * a.Ci * sizeof(float))))
-    return launch_conv_wgrad128(a, s);
+  if (wgrad_runs_128(a)) return launch_conv_wgrad128(a, s);
   if (conv_wgrad_tall_applies(a)) return launch_conv_wgrad_tall(a, s);
   if (wgrad_runs_columns(a)) return launch_conv_wgrad_columns(a, s);
   if (conv_wgrad_wide_applies(a)) return launch_conv_wgrad_wide(a, s);

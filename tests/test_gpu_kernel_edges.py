@@ -175,3 +175,26 @@ def test_weight_gradients_over_columns(case, kernel):
     dw, scratch = t.empty(co * k * k * ci, device="cuda"), t.empty(K.fdgk_conv_wgrad_scratch_bytes(n, h, w, ci, co, k, s) // 4, device="cuda")
     K.fdgk_conv_wgrad(*z, dw, scratch, n, h, w, ci, co, k, s, overwrite=True)
     assert K.fdgk_last_kernel() == kernel
+
+
+# Scratch for the splits of a weight gradient is optional.  The kernels that took layers over from the generic one run them only with
+# room for their splits (one tile after the other took up to twenty times as long, in sums as many times longer); a byte too few
+# counts as none, a layer of one split needs none
+@pytest.mark.parametrize("case, without, within", [
+    ((8, 32, 32, 64, 128, 3, 2), "conv_wgrad_kernel<128, 128, 2, 2, 1>", "conv_wgrad128w8_kernel<5, paired>"),
+    ((8, 16, 16, 64, 256, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>", "conv_wgrad128w8_kernel<5, paired>"),
+    ((21, 14, 14, 136, 160, 3, 1), "conv_wgrad_kernel<128, 128, 2, 2, 1>", "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((8, 28, 28, 192, 160, 1, 1), "conv_wgrad_kernel<128, 128, two sums>", "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((8, 16, 16, 64, 384, 1, 1), "conv_wgrad_kernel<128, 128, two sums>", "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((3, 7, 7, 128, 256, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>", "conv_wgrad128w8_kernel<5, flat, ragged>"),
+])
+def test_weight_gradients_without_room_for_their_splits(case, without, within):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co, k, s = case
+    TK.test_conv_wgrad(case)
+    z = [t.zeros(c, device="cuda", dtype=t.bfloat16) for c in (n * h * w * ci, n * ((h - 1) // s + 1) * ((w - 1) // s + 1) * co)]
+    dw, room = t.empty(co * k * k * ci, device="cuda"), K.fdgk_conv_wgrad_scratch_bytes(n, h, w, ci, co, k, s) // 4
+    for scratch, kernel in ((None, without), (t.empty(co * k * k * ci - 1, device="cuda"), without), (t.empty(room, device="cuda"), within)):
+        K.fdgk_conv_wgrad(*z, dw, scratch, n, h, w, ci, co, k, s, overwrite=True)
+        assert K.fdgk_last_kernel() == kernel
