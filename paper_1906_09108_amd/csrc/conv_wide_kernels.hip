@@ -1775,7 +1775,9 @@ struct Wgrad128Launch {
 // FLAT: unit stride and any image width.  The input pixel of output pixel P under tap (dh, dw) is P + dh W + dw
 // wherever it exists, so chunks need not start a row: the x pointer advances 64 pixels per chunk, and only the
 // validity of a lane's pixel (does the tap stay inside the image?) depends on where the chunk starts; it repeats
-// every OH OW / gcd(64, OH OW) chunks (49 for 7, 14, 28 and 56 pixels square), one bit of a 64-bit mask each.
+// every OH OW / gcd(64, OH OW) chunks (49 for 7, 14, 28 and 56 pixels square), one bit of a 64-bit mask each.  Only
+// the bits of chunks that the workgroup has are worked out: all 49 took 8 us, longer than the whole of a small layer (2 x 7 x 7
+// 128 -> 128, generic kernel / all bits / these bits: 12.5 / 15.8 / 7.8 us; 5 x 14 x 14: 19.3 / 20.7 / 13.5; 37 x 14 x 14 42 / 28 / 21).
 // PAIRED: 64 input channels.  The 128 columns of a block are the channels of two taps, 2 tapi and 2 tapi + 1 (nine taps: five
 // blocks, the last one half empty): a lane loads the pixel of its tap.  128 x 64 x 64, 64 -> 128, 3x3, stride 2: the generic kernel,
 // whose blocks are 128 channels of one tap of which 64 exist, 111.5 + 7.2 us for its parts -> 35.9 + 4.8.
@@ -1810,6 +1812,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
   if (n <= 0) return;
+  const int phases = min(L.period, n);   // of the validity pattern that this workgroup meets
 
   // ---- per-thread DMA sources: 32-bit byte offsets from two uniform pointers that advance with the chunk.  The x
   //      pointer starts one input row and one pixel before the chunk's first pixel, so that the offsets of taps
@@ -1837,7 +1840,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     if constexpr (FLAT) {
       boff32[j] = (unsigned)(margin + ((r + dh * a.Wi + dw) * a.Cx + chan) * 2);
       int ow = (m0 + r) % a.OW, oh = ((m0 + r) / a.OW) % a.OH;
-      for (int q = 0; q < L.period; ++q) {
+      for (int q = 0; q < phases; ++q) {
         if ((unsigned)(ow + dw) < (unsigned)a.Wi && (unsigned)(oh + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
         ow += L.step_w;
         const int carry = ow >= a.OW ? 1 : 0;
@@ -1851,7 +1854,7 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
       const bool colok = (unsigned)iw < (unsigned)a.Wi;
       boff32[j] = (unsigned)(margin + (((orow * a.stride + dh) * a.Wi + iw) * a.Cx + chan) * 2);
       int ohq = (oh0 + orow) % a.OH;
-      for (int q = 0; q < L.period; ++q) {
+      for (int q = 0; q < phases; ++q) {
         if (colok && (unsigned)(ohq * a.stride + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
         ohq += L.d_oh;
         if (ohq >= a.OH) ohq -= a.OH;
@@ -2281,6 +2284,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
   const int chunk_lo = split * L.chunks_per_split;
   const int n = min(total_chunks, chunk_lo + L.chunks_per_split) - chunk_lo;
   if (n <= 0) return;
+  const int phases = min(L.period, n);
 
   // ---- per-thread DMA sources: instruction j of this wave covers the 64 units 64*(4j+wave) .. of a tile ----
   const char* aptr[JA];
@@ -2314,7 +2318,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
     if constexpr (FLAT) {
       bptr[j] = reinterpret_cast<const char*>(a.x) + (((long long)m + dh * a.Wi + dw) * a.Cx + ci) * 2;
       int owq = ow, ohq = oh;
-      for (int q = 0; q < L.period; ++q) {
+      for (int q = 0; q < phases; ++q) {
         if ((unsigned)(owq + dw) < (unsigned)a.Wi && (unsigned)(ohq + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
         owq += L.step_w;
         const int carry = owq >= a.OW ? 1 : 0;
@@ -2326,7 +2330,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
       bptr[j] = reinterpret_cast<const char*>(a.x) +
                 ((((long long)nimg * a.Hi + oh * a.stride + dh) * a.Wi + iw) * a.Cx + ci) * 2;
       int ohq = oh;
-      for (int q = 0; q < L.period; ++q) {
+      for (int q = 0; q < phases; ++q) {
         if (colok && (unsigned)(ohq * a.stride + dh) < (unsigned)a.Hi) mask |= (mask_t)1 << q;
         ohq += L.d_oh;
         if (ohq >= a.OH) ohq -= a.OH;

@@ -198,3 +198,12 @@ def test_weight_gradients_without_room_for_their_splits(case, without, within):
     for scratch, kernel in ((None, without), (t.empty(co * k * k * ci - 1, device="cuda"), without), (t.empty(room, device="cuda"), within)):
         K.fdgk_conv_wgrad(*z, dw, scratch, n, h, w, ci, co, k, s, overwrite=True)
         assert K.fdgk_last_kernel() == kernel
+
+
+# The validity of a pixel under a tap repeats after a number of chunks: workgroups with fewer chunks than that, with exactly as many
+# and with several times as many
+@pytest.mark.parametrize("case", [(9, 6, 6, 512, 512, 3, 1), (16, 6, 6, 512, 512, 3, 1), (37, 6, 6, 512, 512, 3, 1), (24, 6, 12, 640, 512, 3, 1)])
+def test_weight_gradients_whose_pixels_repeat(case):
+    from paper_1906_09108_amd import kernels as K
+    TK.test_conv_wgrad(case)
+    assert K.fdgk_last_kernel().startswith("conv_wgrad128w8_kernel<5, flat")
