@@ -386,7 +386,7 @@ static void wgrad_plan(const WgradArgs& a, int& splits, int& chunks_per_split, i
   splits = (total_chunks + chunks_per_split - 1) / chunks_per_split;   // every split has at least one chunk
   parts = splits * WK;
 }
-hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s);
+hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s, bool pairs = false);
 
 template <int BM, int BN, int WM, int WN, int WK>
 static hipError_t run_wgrad(const WgradArgs& a, hipStream_t s) {

@@ -1703,7 +1703,9 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(float4* __restrict__ 
 }
 
 // The same for many parts of a small array: 16 lanes share a float4 of dw, lane q adds the parts q, q + 16, ... and the
-// sixteen partial sums are added through LDS in lane order (a fixed order).
+// sixteen partial sums are added through LDS in a fixed order: lane after lane, or (PAIRS) pairs of neighbours, then pairs of those,
+// which rounds four times on the way of a value and not up to sixteen times.
+template <bool PAIRS>
 __global__ __launch_bounds__(256) void wgrad_reduce_lanes_kernel(float4* __restrict__ dw, const float4* __restrict__ partial,
                                                                  size_t n4, int parts, size_t stride4, int overwrite) {
   __shared__ float4 sh[16][16];
@@ -1721,17 +1723,30 @@ __global__ __launch_bounds__(256) void wgrad_reduce_lanes_kernel(float4* __restr
   __syncthreads();
   if (q == 0 && i < n4) {
     float4 t = overwrite ? make_float4(0.f, 0.f, 0.f, 0.f) : dw[i];
+    if constexpr (PAIRS) {
+      float4 v[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) { t.x += sh[j][e].x; t.y += sh[j][e].y; t.z += sh[j][e].z; t.w += sh[j][e].w; }
+      for (int j = 0; j < 16; ++j) v[j] = sh[j][e];
+#pragma unroll
+      for (int d = 1; d < 16; d *= 2)
+#pragma unroll
+        for (int j = 0; j < 16; j += 2 * d) { v[j].x += v[j + d].x; v[j].y += v[j + d].y; v[j].z += v[j + d].z; v[j].w += v[j + d].w; }
+      t.x += v[0].x; t.y += v[0].y; t.z += v[0].z; t.w += v[0].w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) { t.x += sh[j][e].x; t.y += sh[j][e].y; t.z += sh[j][e].z; t.w += sh[j][e].w; }
+    }
     dw[i] = t;
   }
 }
 
-hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s) {
+// pairs: for the kernels that take fewer splits than the one that ran their layers before, so that no digits are lost to that
+hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s, bool pairs) {
   if (elems % 4 != 0 || parts < 1) return hipErrorInvalidValue;
   const size_t n4 = elems / 4;
   if (parts >= 12) {   // also the smaller error: sixteen short sums instead of a long one
-    hipLaunchKernelGGL(wgrad_reduce_lanes_kernel, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, reinterpret_cast<float4*>(dw),
+    auto kernel = pairs ? &wgrad_reduce_lanes_kernel<true> : &wgrad_reduce_lanes_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, reinterpret_cast<float4*>(dw),
                        reinterpret_cast<const float4*>(partial), n4, parts, n4, overwrite);
     return hipGetLastError();
   }
@@ -2010,10 +2025,12 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     if constexpr (decltype(issue_tag)::value) issue_done();
     rd_stage = next_stage;
   };
-  // RAGGED and PAIRED: the sums of every 4 chunks (128 pixels a wave; thin 1x1 layers: 2) are added to totals: the generic kernel, which ran these layers, split them
-  // further, and no sum is to lose digits to that.  Error against 64 bits, generic -> one sum -> totals: 127 x 14 x 14 320 -> 320
-  // 2.05e-7 -> 3.07e-7 -> 1.0e-7, 13 x 28 x 28 128 -> 128 1.00e-7 -> 1.10e-7 -> 0.9e-7 (about 2 % of the time).  The next step's reads are waited for first: between steps nothing
-  // else keeps the compiler from moving their registers.
+  // RAGGED and PAIRED: the sums of a few chunks are added to totals, since the generic kernel, which ran these layers, split them
+  // further and no sum is to lose digits to that.  After every chunk where a workgroup has up to 3, every 2nd up to 10, every 4th
+  // beyond: a sum of sums loses least where both are short.  Error against 64 bits over the generic kernel's, folds every 1 / 2 / 4
+  // chunks: 5 x 7 x 7 512 -> 512 (4 chunks) 0.97 / 0.96 / 1.03, 16 x 7 x 7 (13) 1.02 / 0.93 / 0.93, 37 x 14 x 14 (114) 1.39 / 1.05 /
+  // 0.83; 1x1: 5 x 7 x 7 256 -> 1024 (4) 0.96 / 0.96 / 1.04, 128 x 32 x 32 96 -> 480 (32) 1.00 / 0.90 / -.  About 2 % of the time for
+  // every 4.  The next step's reads are waited for first: between steps nothing else keeps the compiler from moving their registers.
   constexpr bool FOLDS = RAGGED || PAIRED;
   f32x16 total[2][2];
   if constexpr (FOLDS) {
@@ -2120,8 +2137,7 @@ bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 
 // nothing; the generic kernel, which loads a chunk into registers, transposes it and has one chunk in flight, waits.  Both launches,
 // generic -> here: 128 x 16 x 16 64 -> 384 29.4 -> 17.2 us (29 MB), 96 -> 576 33.9 -> 19.8, 128 x 32 x 32 32 -> 192 23.7 -> 19.9, 128 x
 // 56 x 56 64 -> 256 77 -> 55 (257 MB, 4.7 TB/s); the smallest, 8 x 16 x 16 64 -> 384 12.7 -> 11.2, 16 x 12 x 12 32 -> 192 11.0 -> 10.9.
-// Their splits go down to two chunks and their sums are folded every two: error against 64 bits 1.18e-7 -> 1.11e-7, 37 x 14 x 14 1.04e-7
-// -> 1.02e-7 (every four: 1.10e-7, and 3 % of the time).  Images of one column, plain lists of pixels that no network has, stay on the
+// Their splits go down to two chunks.  Images of one column, plain lists of pixels that no network has, stay on the
 // generic kernel: what its sums lose over long lists is pinned by a test.
 bool conv_wgrad128_thin(const WgradArgs& a) { return a.ntaps == 1 && (a.Co < 128 || a.Ci < 128); }
 bool conv_wgrad128_ragged(const WgradArgs& a) {
@@ -2156,7 +2172,6 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   const bool ragged = conv_wgrad128_ragged(a);
   const int total_chunks = (a.N * a.OH * a.OW + 63) / 64;
   Wgrad128Launch L;
-  L.fold_mask = conv_wgrad128_thin(a) ? 1 : 3;
   L.co_tiles = (a.Co + 127) / 128;
   const bool paired = conv_wgrad128_paired(a);
   L.ci_tiles = paired ? 1 : (a.Ci + 127) / 128;
@@ -2166,6 +2181,7 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   const int max_by_scratch = a.scratch ? (int)(a.scratch_bytes / (elems * 4)) : 0;
   const int S = max_by_scratch >= 2 ? std::min(conv_wgrad128_splits(a), max_by_scratch) : 1;
   L.chunks_per_split = (total_chunks + S - 1) / S;
+  L.fold_mask = L.chunks_per_split <= 3 ? 0 : L.chunks_per_split <= 10 ? 1 : 3;
   L.splits = (total_chunks + L.chunks_per_split - 1) / L.chunks_per_split;
   L.partial = L.splits > 1 ? a.scratch : nullptr;
   L.split_stride = elems;
@@ -2196,7 +2212,7 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
       hipLaunchKernelGGL((conv_wgrad128w8_kernel<STAGES, true, false, true>), dim3(tiles * L.splits), dim3(512), lds, s, a, L);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess || !L.partial) return e;
-      return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
+      return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s, true);
     }
     static bool configured_flat = false;
     if (!configured_flat) {
@@ -2230,7 +2246,7 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
-  return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
+  return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s, true);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2636,7 +2652,7 @@ static hipError_t run_wgrad_tall(const WgradArgs& a, int S, const char* name, hi
   hipLaunchKernelGGL((conv_wgrad_tall_kernel<STAGES, CW, FLAT>), dim3(tiles * L.splits), dim3(256), lds, s, a, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
-  if (CW == 2) return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s);
+  if (CW == 2) return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s, true);
   const size_t n4 = elems / 4;
   size_t blocks = (n4 + 255) / 256;
   if (blocks > 2048) blocks = 2048;

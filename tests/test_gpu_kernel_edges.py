@@ -207,3 +207,44 @@ def test_weight_gradients_whose_pixels_repeat(case):
     from paper_1906_09108_amd import kernels as K
     TK.test_conv_wgrad(case)
     assert K.fdgk_last_kernel().startswith("conv_wgrad128w8_kernel<5, flat")
+
+
+# Kernels that took layers over from the generic one split their pixels less, and no sum is to lose digits to that: the error against
+# 64 bits is no larger than the generic kernel's on the same operands.  Those were measured once and are the bounds: workgroups of
+# two to five chunks, of more than a fold each, parts added up one after the other and in pairs; the ragged, thin and paired forms
+def check_weight_gradient_against_64_bits(case, bound, kernel):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co, k, s = case
+    ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+    g = t.Generator(device="cuda")
+    g.manual_seed(11)
+    x = t.randn(n, h, w, ci, generator=g, device="cuda").relu().bfloat16()
+    dy = t.randn(n * ho * wo, co, generator=g, device="cuda").bfloat16()
+    scratch = t.empty(K.fdgk_conv_wgrad_scratch_bytes(*case) // 4, device="cuda")
+    dw = t.empty(co, k, k, ci, device="cuda")
+    K.fdgk_conv_wgrad(x, dy, dw, scratch, *case, overwrite=True)
+    ran = K.fdgk_last_kernel()
+    xp, dyt = t.nn.functional.pad(x, (0, 0, k // 2, k // 2, k // 2, k // 2)).double(), dy.double().t().contiguous()
+    num = den = 0.0
+    for r in range(k):
+        for q in range(k):
+            ref = dyt @ xp[:, r:r + (ho - 1) * s + 1:s, q:q + (wo - 1) * s + 1:s].reshape(n * ho * wo, ci)
+            num, den = num + float((dw[:, r, q].double() - ref).square().sum()), den + float(ref.square().sum())
+    err = (num / den) ** 0.5
+    print(f"weight gradient {case}: {err:.3e} (bound {bound:.3e}) {ran}", flush=True)
+    assert ran == kernel and err <= bound
+
+
+@pytest.mark.parametrize("case, bound", [
+    ((2, 7, 7, 512, 512, 3, 1), 3.45e-8), ((5, 7, 7, 320, 320, 3, 1), 4.77e-8), ((5, 7, 7, 256, 1024, 1, 1), 5.07e-8), ((37, 14, 14, 128, 512, 1, 1), 9.88e-8),
+    ((19, 14, 14, 512, 512, 3, 1), 1.063e-7), ((128, 8, 8, 96, 576, 1, 1), 9.57e-8), ((5, 26, 37, 64, 320, 1, 1), 9.52e-8), ((16, 14, 14, 384, 64, 1, 1), 9.43e-8),
+    ((128, 32, 32, 96, 480, 1, 1), 1.382e-7),
+])
+def test_ragged_weight_gradients_against_64_bits(case, bound):
+    check_weight_gradient_against_64_bits(case, bound, "conv_wgrad128w8_kernel<5, flat, ragged>")
+
+
+@pytest.mark.parametrize("case, bound", [((4, 16, 16, 64, 256, 3, 2), 4.97e-8), ((9, 64, 64, 64, 128, 3, 2), 1.034e-7), ((64, 16, 16, 64, 128, 3, 1), 1.072e-7)])
+def test_paired_weight_gradients_against_64_bits(case, bound):
+    check_weight_gradient_against_64_bits(case, bound, "conv_wgrad128w8_kernel<5, paired>")
