@@ -1741,11 +1741,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_lanes_kernel(float4* __restr
 }
 
 // pairs: for the kernels that take fewer splits than the one that ran their layers before, so that no digits are lost to that
+// (up to 31 parts always: lane after lane 18 parts are further off than as one sum, 2 x 48 x 48 64 -> 128 at stride 2 8.83e-8 to 8.75e-8)
 hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s, bool pairs) {
   if (elems % 4 != 0 || parts < 1) return hipErrorInvalidValue;
   const size_t n4 = elems / 4;
-  if (parts >= 12) {   // also the smaller error: sixteen short sums instead of a long one
-    auto kernel = pairs ? &wgrad_reduce_lanes_kernel<true> : &wgrad_reduce_lanes_kernel<false>;
+  if (parts >= 12) {
+    auto kernel = pairs || parts < 32 ? &wgrad_reduce_lanes_kernel<true> : &wgrad_reduce_lanes_kernel<false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, reinterpret_cast<float4*>(dw),
                        reinterpret_cast<const float4*>(partial), n4, parts, n4, overwrite);
     return hipGetLastError();
@@ -2601,11 +2602,18 @@ bool conv_wgrad_columns_applies(const WgradArgs& a) {
   if (a.Co % 160 != 0 || a.Ci % 8 != 0 || a.Ci < 16 || a.Cx != a.Ci || a.ntaps < 1 || conv_wgrad_tall_applies(a)) return false;
   return wgrad_columns_by_rows(a) || wgrad_columns_flat_period(a) > 0;
 }
-// One round of workgroups; splits of at least eight chunks (of four: 16 x 16 x 16 160 -> 160 21.1 -> 22.5 us).  Error against 64 bits, before -> here: 128 x 32 x 32 160 -> 160 3.58e-7 ->
-// 2.85e-7, 16 -> 160 2.38e-7 -> 1.34e-7, batch 8 1.19e-7 -> 1.04e-7.
+// One round of workgroups, splits of at least eight chunks (of four: 16 x 16 x 16 160 -> 160 21.1 -> 22.5 us).  Error against 64 bits,
+// before -> here: 128 x 32 x 32 160 -> 160 3.58e-7 -> 2.77e-7, 16 -> 160 2.38e-7 -> 1.34e-7, batch 8 1.19e-7 -> 1.04e-7.
+// This form does not fold its sums (they and their totals would take more than the 512 registers of a lane), and layers of other
+// channels come from the generic kernel, which has more splits: splits of four chunks for them, and a second round of workgroups
+// where one would have less than half of its splits.  Generic / one round / this rule: 64 x 32 x 32 96 -> 640 2.73 / 3.04 / 2.06 e-7,
+// 28 x 28 104 -> 320 1.82 / 1.95 / 1.36 e-7, 4 x 16 x 16 136 -> 160 at stride 2 5.03 / 5.31 / 4.88 e-8; 128 x 32 x 32 96 -> 640 420 / 187 /
+// 201 us.
 int conv_wgrad_columns_splits(const WgradArgs& a) {
-  const int tiles = a.Co / 160 * ((a.ntaps * a.Ci + 127) / 128);
-  return std::max(1, std::min(256 / tiles, a.N * a.OH * a.OW / 32 / 8));
+  const int tiles = a.Co / 160 * ((a.ntaps * a.Ci + 127) / 128), chunks = a.N * a.OH * a.OW / 32;
+  if (a.Ci % 160 == 0) return std::max(1, std::min(256 / tiles, chunks / 8));
+  const int generic = 1024 / ((a.Co + 127) / 128 * ((a.Ci + 127) / 128) * a.ntaps);
+  return std::max(1, std::min(2 * (256 / tiles) <= generic ? 512 / tiles : 256 / tiles, chunks / 4));
 }
 
 template <int STAGES, int CW>

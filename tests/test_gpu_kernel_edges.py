@@ -248,3 +248,13 @@ def test_ragged_weight_gradients_against_64_bits(case, bound):
 @pytest.mark.parametrize("case, bound", [((4, 16, 16, 64, 256, 3, 2), 4.97e-8), ((9, 64, 64, 64, 128, 3, 2), 1.034e-7), ((64, 16, 16, 64, 128, 3, 1), 1.072e-7)])
 def test_paired_weight_gradients_against_64_bits(case, bound):
     check_weight_gradient_against_64_bits(case, bound, "conv_wgrad128w8_kernel<5, paired>")
+
+
+# Blocks of 128 columns hold a sum as long as its split: by rows and flat, splits of four chunks, one round of workgroups and two
+@pytest.mark.parametrize("case, bound, form", [
+    ((4, 16, 16, 136, 160, 3, 2), 5.02e-8, "columns"), ((4, 16, 16, 192, 480, 3, 2), 4.93e-8, "columns"),
+    ((64, 32, 32, 96, 640, 3, 1), 2.73e-7, "columns"), ((64, 32, 32, 120, 160, 3, 1), 1.73e-7, "columns"),
+    ((64, 28, 28, 104, 320, 3, 1), 1.82e-7, "columns, flat"), ((128, 24, 24, 16, 160, 3, 1), 1.83e-7, "columns, flat"),
+])
+def test_weight_gradients_over_columns_against_64_bits(case, bound, form):
+    check_weight_gradient_against_64_bits(case, bound, f"conv_wgrad_tall_kernel<4, {form}>")
