@@ -2138,11 +2138,10 @@ bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 
 // nothing; the generic kernel, which loads a chunk into registers, transposes it and has one chunk in flight, waits.  Both launches,
 // generic -> here: 128 x 16 x 16 64 -> 384 29.4 -> 17.2 us (29 MB), 96 -> 576 33.9 -> 19.8, 128 x 32 x 32 32 -> 192 23.7 -> 19.9, 128 x
 // 56 x 56 64 -> 256 77 -> 55 (257 MB, 4.7 TB/s); the smallest, 8 x 16 x 16 64 -> 384 12.7 -> 11.2, 16 x 12 x 12 32 -> 192 11.0 -> 10.9.
-// Their splits go down to two chunks.  Images of one column, plain lists of pixels that no network has, stay on the
-// generic kernel: what its sums lose over long lists is pinned by a test.
+// Their splits go down to two chunks.
 bool conv_wgrad128_thin(const WgradArgs& a) { return a.ntaps == 1 && (a.Co < 128 || a.Ci < 128); }
 bool conv_wgrad128_ragged(const WgradArgs& a) {
-  if (conv_wgrad128_thin(a) ? (a.Co < 32 || a.Ci < 32 || a.OW < 2) : (a.Co < 128 || a.Ci < 128)) return false;
+  if (conv_wgrad128_thin(a) ? (a.Co < 32 || a.Ci < 32) : (a.Co < 128 || a.Ci < 128)) return false;
   if (a.Co % 8 != 0 || a.Ci % 8 != 0 || a.Cx != a.Ci || a.ntaps < 1 || a.N * a.OH * a.OW < 64) return false;
   if (wgrad128_flat_period(a) <= 0) return false;
   return (a.Co % 128 != 0 || a.Ci % 128 != 0 || (a.N * a.OH * a.OW) % 64 != 0) && !conv_wgrad_tall_applies(a) && !conv_wgrad_wide_applies(a);

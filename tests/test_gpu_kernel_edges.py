@@ -124,7 +124,7 @@ def test_projecting_block_that_feeds_the_one_below(c, n, h, w):
     ((2, 31, 31, 32, 192, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
     ((19, 15, 15, 576, 96, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
     ((64, 16, 16, 64, 384, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
-    ((5, 64, 1, 64, 96, 1, 1), "conv_wgrad_kernel<128, 128, two sums>"),       # one column
+    ((5, 64, 1, 64, 96, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),     # one column
     ((4, 16, 16, 24, 144, 1, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),
     ((8, 16, 16, 64, 384, 1, 2), "conv_wgrad_kernel<128, 128, two sums>"),
 ])

@@ -188,24 +188,36 @@ def test_thin_1x1_layers(case, forward, dgrad):
 
 
 # One round of workgroups means longer sums: the 1x1 weight gradient against 64 bits on long lists of pixels.  The error of fp32
-# sums grows with the pixels of one sum; with 1024 workgroups, one sum each, it is 1.42e-7, 1.53e-7 and 1.79e-7 here, with 512
-# it was 1.59e-7, 1.78e-7 and 2.10e-7.  Bounds: 4 % above the former.
-@pytest.mark.parametrize("case", [(131072, 384, 64, 1.48e-7), (134912, 448, 64, 1.59e-7), (401408, 72, 136, 1.86e-7)])
-def test_weight_gradient_of_1x1_layers_against_64_bits(case):
+# sums grows with the pixels of one sum; on the generic kernel, with 1024 workgroups, one sum each, it is 1.42e-7, 1.53e-7 and 1.79e-7
+# here, with 512 it was 1.59e-7, 1.78e-7 and 2.10e-7.  Bounds: 4 % above the former.  Unit stride, as a list and as images, on the
+# kernel that runs such layers in a network; stride 2 on the generic one
+TWO_SUMS, RAGGED = "conv_wgrad_kernel<128, 128, two sums>", "conv_wgrad128w8_kernel<5, flat, ragged>"
+
+
+@pytest.mark.parametrize("case, bound, kernel", [
+    ((1, 131072, 1, 384, 64, 1, 1), 1.48e-7, RAGGED), ((1, 134912, 1, 448, 64, 1, 1), 1.59e-7, RAGGED),
+    ((1, 401408, 1, 72, 136, 1, 1), 1.86e-7, RAGGED), ((128, 32, 32, 384, 64, 1, 1), 1.48e-7, RAGGED),
+    ((31, 68, 64, 448, 64, 1, 1), 1.59e-7, RAGGED), ((128, 56, 56, 72, 136, 1, 1), 1.86e-7, RAGGED),
+    ((128, 64, 64, 384, 64, 1, 2), 1.48e-7, TWO_SUMS), ((31, 136, 128, 448, 64, 1, 2), 1.59e-7, TWO_SUMS),
+    ((128, 112, 112, 72, 136, 1, 2), 1.86e-7, TWO_SUMS),
+])
+def test_weight_gradient_of_1x1_layers_against_64_bits(case, bound, kernel):
     import torch as t
     from paper_1906_09108_amd import kernels as K
-    pixels, ci, co, bound = case
+    n, h, w, ci, co, k, s = case
+    pixels = n * (h // s) * (w // s)
     g = t.Generator(device="cuda")
     g.manual_seed(3)
-    x = t.randn(pixels, ci, generator=g, device="cuda").relu().bfloat16()
+    x = t.randn(n, h, w, ci, generator=g, device="cuda").relu().bfloat16()
     dy = t.randn(pixels, co, generator=g, device="cuda").bfloat16()
-    scratch = t.empty(K.fdgk_conv_wgrad_scratch_bytes(1, pixels, 1, ci, co, 1, 1) // 4, device="cuda")
+    scratch = t.empty(K.fdgk_conv_wgrad_scratch_bytes(*case) // 4, device="cuda")
     dw = t.empty(co, ci, device="cuda")
-    K.fdgk_conv_wgrad(x, dy, dw, scratch, 1, pixels, 1, ci, co, 1, 1, overwrite=True)
-    ref = dy.cpu().double().T @ x.cpu().double()
+    K.fdgk_conv_wgrad(x, dy, dw, scratch, *case, overwrite=True)
+    ran = K.fdgk_last_kernel()
+    ref = dy.cpu().double().T @ x[:, ::s, ::s].reshape(pixels, ci).cpu().double()
     err = float((dw.cpu().double() - ref).norm() / ref.norm())
     print(f"1x1 weight gradient {case}: {err:.3e}", flush=True)
-    assert K.fdgk_last_kernel() == "conv_wgrad_kernel<128, 128, two sums>"
+    assert ran == kernel
     assert err <= bound
 
 
