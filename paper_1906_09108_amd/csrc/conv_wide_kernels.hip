@@ -1741,11 +1741,13 @@ __global__ __launch_bounds__(256) void wgrad_reduce_lanes_kernel(float4* __restr
 }
 
 // pairs: for the kernels that take fewer splits than the one that ran their layers before, so that no digits are lost to that
-// (up to 31 parts always: lane after lane 18 parts are further off than as one sum, 2 x 48 x 48 64 -> 128 at stride 2 8.83e-8 to 8.75e-8)
+// (up to 31 parts always: lane after lane 18 parts are further off than as one sum, 2 x 48 x 48 64 -> 128 at stride 2 8.83e-8 to 8.75e-8).
+// Those share a float4 of a small array between lanes for any number of parts: a thread that adds eleven parts one after the other
+// waits for memory eleven times (9 x 15 x 15 40 -> 240 1x1, both launches 13.1 -> 11.4 us; the generic kernel's 11.9).
 hipError_t launch_wgrad_reduce(float* dw, const float* partial, size_t elems, int parts, int overwrite, hipStream_t s, bool pairs) {
   if (elems % 4 != 0 || parts < 1) return hipErrorInvalidValue;
   const size_t n4 = elems / 4;
-  if (parts >= 12) {
+  if (parts >= 12 || (pairs && n4 <= 32768)) {
     auto kernel = pairs || parts < 32 ? &wgrad_reduce_lanes_kernel<true> : &wgrad_reduce_lanes_kernel<false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, s, reinterpret_cast<float4*>(dw),
                        reinterpret_cast<const float4*>(partial), n4, parts, n4, overwrite);
@@ -2137,11 +2139,18 @@ bool conv_wgrad128_paired(const WgradArgs& a) { return a.Ci == 64 && a.ntaps == 
 // (inverted residual blocks).  Those are bound by memory, and that a block of 64 x 128 leaves half the matrix instructions unused costs
 // nothing; the generic kernel, which loads a chunk into registers, transposes it and has one chunk in flight, waits.  Both launches,
 // generic -> here: 128 x 16 x 16 64 -> 384 29.4 -> 17.2 us (29 MB), 96 -> 576 33.9 -> 19.8, 128 x 32 x 32 32 -> 192 23.7 -> 19.9, 128 x
-// 56 x 56 64 -> 256 77 -> 55 (257 MB, 4.7 TB/s); the smallest, 8 x 16 x 16 64 -> 384 12.7 -> 11.2, 16 x 12 x 12 32 -> 192 11.0 -> 10.9.
-// Their splits go down to two chunks.
+// 56 x 56 64 -> 256 77 -> 55 (257 MB, 4.7 TB/s); 8 x 16 x 16 64 -> 384 12.7 -> 11.2.  Their splits go down to two chunks.
+// The generic kernel's smaller blocks (up to 64 channels on both sides, or 32 input channels) are the faster ones from 200 to 8192
+// pixels: 64 -> 64, generic / here, 208 pixels 9.0 / 9.0 us, 1024 8.4 / 12.1, 3136 9.1 / 11.0, 8192 10.4 / 10.5, 13357 16.3 / 12.4;
+// 32 -> 192 208 8.5 / 8.6, 1024 8.4 / 11.0, 3136 8.8 / 10.1, 8192 9.3 / 9.8, 10240 10.8 / 10.0.
 bool conv_wgrad128_thin(const WgradArgs& a) { return a.ntaps == 1 && (a.Co < 128 || a.Ci < 128); }
 bool conv_wgrad128_ragged(const WgradArgs& a) {
-  if (conv_wgrad128_thin(a) ? (a.Co < 32 || a.Ci < 32) : (a.Co < 128 || a.Ci < 128)) return false;
+  if (conv_wgrad128_thin(a)) {
+    const bool small_blocks = (a.Co <= 64 && a.Ci <= 64) || a.Ci <= 32;
+    if (a.Co < 32 || a.Ci < 32 || (small_blocks && a.N * a.OH * a.OW >= 200 && a.N * a.OH * a.OW <= 8192)) return false;
+  } else if (a.Co < 128 || a.Ci < 128) {
+    return false;
+  }
   if (a.Co % 8 != 0 || a.Ci % 8 != 0 || a.Cx != a.Ci || a.ntaps < 1 || a.N * a.OH * a.OW < 64) return false;
   if (wgrad128_flat_period(a) <= 0) return false;
   return (a.Co % 128 != 0 || a.Ci % 128 != 0 || (a.N * a.OH * a.OW) % 64 != 0) && !conv_wgrad_tall_applies(a) && !conv_wgrad_wide_applies(a);
@@ -2246,7 +2255,7 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !L.partial) return e;
-  return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s, true);
+  return launch_wgrad_reduce(a.dw, a.scratch, elems, L.splits, a.overwrite, s, paired);
 }
 
 // ------------------------------------------------------------------------------------------------

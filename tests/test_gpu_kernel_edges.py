@@ -121,7 +121,12 @@ def test_projecting_block_that_feeds_the_one_below(c, n, h, w):
     # 1x1 of fewer than 128 channels on a side: one chunk and a pixel, any image width, a partly filled tile on either side or both,
     # 32 channels and just below, folds in the middle and at the end of a split; without scratch and at stride 2 the generic kernel
     ((5, 1, 13, 32, 40, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
-    ((2, 31, 31, 32, 192, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((2, 31, 31, 32, 192, 1, 1), "conv_wgrad_kernel<128, 32, 4, 1, 1>"),       # smaller blocks, from 200 to 8192 pixels
+    ((9, 31, 31, 32, 192, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((1, 1, 199, 64, 40, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((1, 8, 25, 64, 64, 1, 1), "conv_wgrad_kernel<32, 32, 1, 1, 4>"),
+    ((8, 32, 32, 40, 64, 1, 1), "conv_wgrad_kernel<32, 32, 1, 1, 4>"),
+    ((3, 2731, 1, 64, 64, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
     ((19, 15, 15, 576, 96, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
     ((64, 16, 16, 64, 384, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
     ((5, 64, 1, 64, 96, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),     # one column
