@@ -326,11 +326,13 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
 // 32-pixel block (wave wk keeps block j = wk and receives its partner's), then all four run the output stage.
 // smem must hold max(4 * FN * 16 * 256, 4 * out_stage_bytes(BN) + stats_stage_bytes(BN)) bytes and be idle (no loads
 // in flight).
-template <int FN>
-__device__ __forceinline__ void combine32(const f32x16 (&acc)[FN][2], f32x16 (&keep)[FN], int wave_m, int wk, int lane, unsigned char* smem) {
+template <int FN, int BN, bool F32S = false>
+__device__ __forceinline__ void combine_and_store32(const GatherConvArgs& a, f32x16 (&acc)[FN][2], int m_tile, int c_tile,
+                                                    int wave_m, int wk, int lane, unsigned char* smem) {
   __syncthreads();
   f32x4* mine = reinterpret_cast<f32x4*>(smem) + (size_t)(wave_m * 2 + wk) * (FN * 4 * 64);
   const f32x4* theirs = reinterpret_cast<const f32x4*>(smem) + (size_t)(wave_m * 2 + (wk ^ 1)) * (FN * 4 * 64);
+  f32x16 keep[FN];
 #pragma unroll
   for (int i = 0; i < FN; ++i) {
     const f32x16 give = wk == 0 ? acc[i][1] : acc[i][0];
@@ -348,20 +350,9 @@ __device__ __forceinline__ void combine32(const f32x16 (&acc)[FN][2], f32x16 (&k
       keep[i][4 * g] += p[0]; keep[i][4 * g + 1] += p[1]; keep[i][4 * g + 2] += p[2]; keep[i][4 * g + 3] += p[3];
     }
   __syncthreads();
-}
-template <int FN, int BN, bool F32S = false>
-__device__ __forceinline__ void store_combined32(const GatherConvArgs& a, const f32x16 (&keep)[FN], int m_tile, int c_tile, int wave_m,
-                                                 int wk, int lane, unsigned char* smem) {
   const int wave = wave_m * 2 + wk;
   store_rows32<FN, BN, BN == 96 ? 6 : 10, 32, 4, F32S>(a, keep, m_tile + wave_m * 64 + wk * 32, c_tile, lane, smem + (size_t)wave * out_stage_bytes(BN),
                        smem + (size_t)4 * out_stage_bytes(BN));
-}
-template <int FN, int BN, bool F32S = false>
-__device__ __forceinline__ void combine_and_store32(const GatherConvArgs& a, f32x16 (&acc)[FN][2], int m_tile, int c_tile,
-                                                    int wave_m, int wk, int lane, unsigned char* smem) {
-  f32x16 keep[FN];
-  combine32<FN>(acc, keep, wave_m, wk, lane, smem);
-  store_combined32<FN, BN, F32S>(a, keep, m_tile, c_tile, wave_m, wk, lane, smem);
 }
 
 // End of the 256-pixel kernel: eight waves (wave_m, wk), wave_m = wave & 3 owns 64 pixels as two 32-pixel blocks j, wk =

@@ -574,9 +574,10 @@ hipError_t run_narrow64(const GatherConvArgs& a, const Narrow64Launch& L, hipStr
 
 int narrow64_rounds(int units) { return units <= 8 * 256 ? 8 : 10; }   // the NR that is launched
 
-// Where the kernel above runs: 64 -> 64 channels, enough pixels for four tiles of 128 to each of 512 workgroups (below, the
+// Where the kernel above runs: 64 -> 64 channels, enough pixels for a tile of 128 to each of 512 workgroups (below, the
 // filter is most of what a workgroup loads and the batch-norm pass on the patch is worth more), rows that fill at least half a
-// tile and whose patch fits ten rounds of loads, taps in one of the two orders, gate and bnx together with the sums, and bf16 operands of the output stage at 16-byte addresses.
+// tile and whose patch fits ten rounds of loads, taps in one of the two orders, gate and bnx together with the sums, and bf16
+// operands of the output stage at 16-byte addresses.
 bool plan_narrow64(const GatherConvArgs& a, Narrow64Launch& L) {
   if (a.Ci != 64 || a.Co != 64 || a.N * a.OH * a.OW < 512 * 128 || (!a.gate) != (!a.bnx) || (a.gate && !a.stats)) return false;
   if (((uintptr_t)a.addmask | (uintptr_t)a.gate | (uintptr_t)a.bnx | (uintptr_t)a.out_b16) % 16 != 0) return false;

@@ -1213,8 +1213,9 @@ static bool conv_patch_applies(const GatherConvArgs& a) {
 }
 
 // Parts of the contraction of a patch launch: as many as fill one round of workgroups (half a round where the caller says that
-// launches of another stream run beside these: see ConvScratch), where that shortens the longest workgroup by 896 = 7 x 128 (channel block, output channel) units.  A block of 160 channels is 3.9 us of a workgroup, the slots and the
-// second launch cost 11 us, and what the tiles leave idle is not all lost: the weight gradients of the other stream run there.
+// launches of another stream run beside these: see ConvScratch), where that shortens the longest workgroup by 896 = 7 x 128 (channel
+// block, output channel) units.  A block of 160 channels is 3.9 us of a workgroup, the slots and the second launch cost 11 us, and
+// what the tiles leave idle is not all lost: the weight gradients of the other stream run there.
 // WRN-28-10 top module, batch 8: 1511 -> 1168 us a step, 37: 1603 -> 1488 (76 tiles of 640 -> 640 at 8 x 8 in three parts: 48.8 ->
 // 28.4 + 8.8 us); beyond the line, batch 64 (128 tiles in two parts): 1821 -> 1917; ResNet-18 top module, batch 32 (64 tiles of 512
 // -> 512, 8 blocks in four parts): 861 -> 883, batch 8 (within): 768 -> 721; bottleneck blocks of 4 blocks, batch 20: 765 -> 812.
@@ -2174,10 +2175,6 @@ hipError_t launch_conv_wgrad128(const WgradArgs& a, hipStream_t s) {
   if (!conv_wgrad128_applies(a) || a.N * a.OH * a.OW <= 0) return hipErrorInvalidValue;
   constexpr int STAGES = 5;   // 5 x 32 KB: all of the LDS
   constexpr size_t lds = (size_t)STAGES * 2 * 64 * 256;
-  static bool configured = false;
-  if (!configured) {
-    configured = true;   // (the two forms of the kernel are configured where they are launched)
-  }
   const bool ragged = conv_wgrad128_ragged(a);
   const int total_chunks = (a.N * a.OH * a.OW + 63) / 64;
   Wgrad128Launch L;
@@ -2632,7 +2629,7 @@ static constexpr size_t wgrad_tall_lds() {   // the stages, or the exchange of t
 // S pixel splits, through scratch where there are several
 template <int CW, bool FLAT = false>
 static hipError_t run_wgrad_tall(const WgradArgs& a, int S, const char* name, hipStream_t s) {
-  constexpr int STAGES = 4;   // 4 x 24 KB (deeper rings measured slower)
+  constexpr int STAGES = 4;   // 4 x 24 KB, columns 4 x 18 KB and 1 KB (deeper rings measured slower)
   constexpr size_t lds = wgrad_tall_lds<STAGES, CW>();
   static bool configured = false;
   if (!configured) {

@@ -265,7 +265,7 @@ bool conv_dgrad_gates(const ConvShape& c);
 bool conv_dgrad_pair_applies(const ConvShape& c, const ConvShape& cp);
 hipError_t conv_dgrad_gated_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
                                  const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
-                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0, const ConvScratch& scratch = {});
+                                 bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
 // The same for layers of 40 .. 96 input channels, in fp32 (and bf16), with the sums of the fp32 values
 bool conv_dgrad_thin_pair_applies(const ConvShape& c, const ConvShape& cp);
 hipError_t conv_dgrad_thin_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
