@@ -119,6 +119,19 @@ int fdgk_conv_dgrad_gated_pair(const void* dy_b16, const void* wt_b16, const voi
                                const void* gate_b16, const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n,
                                int h, int w, int ci, int co, void* hip_stream);
 
+/* The same sum of two data gradients for layers of 40 .. 96 input channels, in fp32 (dx_f32 is required; dx_b16 may be NULL), with
+ * the sums of the FP32 values; 1 elsewhere.                                                            */
+int fdgk_conv_dgrad_thin_pair(const void* dy_b16, const void* wt_b16, const void* dy2_b16, const void* wt2_b16, const void* gate_b16,
+                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
+                              void* hip_stream);
+/* Data gradient of a 1x1 unit-stride convolution in an inverted residual block, ending in the two sums, of the FP32 values, of the
+ * batch-norm backward that follows, with a gate in between or without one (gate_b16 NULL): dx = data gradient + addend (may be
+ * NULL), zero unless 0 < gate, and zero where gate >= gate_hi if gate_hi > 0 (6: a ReLU6).  dx_f32, bnx_b16 and gsums are required.
+ * Where co % 64 == 0 or 64 < co < 128 and ci >= 128 (co <= 1024), or co % 64 == 0, co >= 128 and 40 <= ci <= 96; 1 elsewhere.   */
+int fdgk_conv_dgrad_with_sums(const void* dy_b16, const void* wt_b16, const float* addend_f32, const void* gate_b16, float gate_hi,
+                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
+                              void* hip_stream);
+
 /* Weight gradient, the adjoint in w, into dw_f32 [co][ksize*ksize][ci]:
  *   dw[o,r,q,i] (+)= sum_{n,ho,wo} dy[n,ho,wo,o] * x[n, ho*s+r-p, wo*s+q-p, i].
  * overwrite == 0: the sum is ADDED to dw (zero it first for the plain gradient); overwrite != 0: dw is
@@ -214,6 +227,12 @@ int fdgk_maxpool3s2(const void* x_b16, float* y_f32, void* y_b16, int n, int h, 
 int fdgk_maxpool3s2_bwd(const void* x_b16, const float* dy_f32, float* dx_f32, int n, int h, int w, int c, void* hip_stream);
 int fdgk_dwconv3_fwd(const void* x_b16, const void* wt_b16, void* y_b16, int n, int h, int w, int c, int stride, void* hip_stream);
 int fdgk_dwconv3_dgrad(const void* dy_b16, const void* wt_b16, void* dx_b16, int n, int h, int w, int c, int stride, void* hip_stream);
+/* The forward with the batch-norm sums (sum y, sum y^2) of its bf16 result, and the data gradient in fp32 behind a gate (zero unless
+ * 0 < gate < gate_hi) with the sums (sum dx, sum dx * bnx); sums: a sums array of c channels, zero it first.          */
+int fdgk_dwconv3_fwd_sums(const void* x_b16, const void* wt_b16, void* y_b16, void* sums, int n, int h, int w, int c, int stride,
+                          void* hip_stream);
+int fdgk_dwconv3_dgrad_sums(const void* dy_b16, const void* wt_b16, const void* gate_b16, float gate_hi, const void* bnx_b16,
+                            float* dx_f32, void* sums, int n, int h, int w, int c, int stride, void* hip_stream);
 size_t fdgk_dwconv3_wgrad_scratch_bytes(int n, int h, int w, int c, int stride);
 int fdgk_dwconv3_wgrad(const void* x_b16, const void* dy_b16, float* dw_f32, float* scratch_f32, size_t scratch_bytes, int n, int h,
                        int w, int c, int stride, void* hip_stream);

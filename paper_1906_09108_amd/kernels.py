@@ -6,10 +6,11 @@ import ctypes
 
 from .binding import _ptr, _stream_handle, load
 
-KERNEL_EXPORTS = ["fdgk_conv_fwd", "fdgk_conv_fwd_bn_applies", "fdgk_conv_fwd_bn", "fdgk_conv_dgrad_bn_applies", "fdgk_conv_dgrad_bn", "fdgk_conv_dgrad", "fdgk_conv_dgrad_gated", "fdgk_conv_dgrad_feeding_next", "fdgk_conv_dgrad_gates", "fdgk_conv_dgrad_pair_applies", "fdgk_conv_dgrad_gated_pair", "fdgk_bn_bwd_gated", "fdgk_conv_wgrad", "fdgk_conv_wgrad_scratch_bytes", "fdgk_bn_stats", "fdgk_bn_apply",
+KERNEL_EXPORTS = ["fdgk_conv_fwd", "fdgk_conv_fwd_bn_applies", "fdgk_conv_fwd_bn", "fdgk_conv_dgrad_bn_applies", "fdgk_conv_dgrad_bn", "fdgk_conv_dgrad", "fdgk_conv_dgrad_gated", "fdgk_conv_dgrad_feeding_next", "fdgk_conv_dgrad_gates", "fdgk_conv_dgrad_pair_applies", "fdgk_conv_dgrad_gated_pair", "fdgk_conv_dgrad_thin_pair", "fdgk_conv_dgrad_with_sums", "fdgk_bn_bwd_gated", "fdgk_conv_wgrad", "fdgk_conv_wgrad_scratch_bytes", "fdgk_bn_stats", "fdgk_bn_apply",
                   "fdgk_bn_bwd", "fdgk_sgd", "fdgk_bn_bwd_static", "fdgk_bn_bwd_static_max_c", "fdgk_sums_bytes", "fdgk_sums_read",
                   "fdgk_avgpool", "fdgk_fc_fwd", "fdgk_softmax_ce", "fdgk_fc_bwd", "fdgk_pool_bwd", "fdgk_nchw_to_nhwc", "fdgk_nhwc_to_nchw",
                   "fdgk_im2col7", "fdgk_maxpool3s2", "fdgk_maxpool3s2_bwd", "fdgk_dwconv3_fwd", "fdgk_dwconv3_dgrad",
+                  "fdgk_dwconv3_fwd_sums", "fdgk_dwconv3_dgrad_sums",
                   "fdgk_dwconv3_wgrad_scratch_bytes", "fdgk_dwconv3_wgrad", "fdgk_last_kernel"]
 _ready = False
 
@@ -30,6 +31,8 @@ def _lib():
         lib.fdgk_conv_dgrad_gates.argtypes = [i, i, i, i, i, i, i]
         lib.fdgk_conv_dgrad_pair_applies.argtypes = [i, i, i, i, i]
         lib.fdgk_conv_dgrad_gated_pair.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_conv_dgrad_thin_pair.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_conv_dgrad_with_sums.argtypes = [vp, vp, vp, vp, f, vp, vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_bn_bwd_gated.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, f, vp]
         lib.fdgk_conv_wgrad.argtypes = [vp, vp, vp, vp, sz, i, i, i, i, i, i, i, i, vp]
         lib.fdgk_conv_wgrad_scratch_bytes.argtypes = [i, i, i, i, i, i, i]
@@ -53,6 +56,8 @@ def _lib():
         lib.fdgk_maxpool3s2_bwd.argtypes = [vp, vp, vp, i, i, i, i, vp]
         lib.fdgk_dwconv3_fwd.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_dgrad.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_dwconv3_fwd_sums.argtypes = [vp, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_dwconv3_dgrad_sums.argtypes = [vp, vp, vp, f, vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_wgrad_scratch_bytes.argtypes = [i, i, i, i, i]
         lib.fdgk_dwconv3_wgrad.argtypes = [vp, vp, vp, vp, sz, i, i, i, i, i, vp]
         lib.fdgk_last_kernel.argtypes = []
@@ -154,6 +159,20 @@ def fdgk_conv_dgrad_feeding_next(dy_b16, wt_b16, addend_f32, addmask_b16, gate_b
     _ok(_lib().fdgk_conv_dgrad_feeding_next(_ptr(dy_b16), _ptr(wt_b16), _ptr(addend_f32), _ptr(addmask_b16), _ptr(gate_b16),
                                             _ptr(bnx_b16), _ptr(gsums_f32), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, ksize,
                                             stride, _stream_handle(stream)), "fdgk_conv_dgrad_feeding_next")
+
+
+def fdgk_conv_dgrad_thin_pair(dy_b16, wt_b16, dy2_b16, wt2_b16, gate_b16, bnx_b16, gsums, dx_f32, dx_b16, n, h, w, ci, co,
+                              stream=None):
+    _ok(_lib().fdgk_conv_dgrad_thin_pair(_ptr(dy_b16), _ptr(wt_b16), _ptr(dy2_b16), _ptr(wt2_b16), _ptr(gate_b16), _ptr(bnx_b16),
+                                         _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
+        "fdgk_conv_dgrad_thin_pair")
+
+
+def fdgk_conv_dgrad_with_sums(dy_b16, wt_b16, addend_f32, gate_b16, gate_hi, bnx_b16, gsums, dx_f32, dx_b16, n, h, w, ci, co,
+                              stream=None):
+    _ok(_lib().fdgk_conv_dgrad_with_sums(_ptr(dy_b16), _ptr(wt_b16), _ptr(addend_f32), _ptr(gate_b16), gate_hi, _ptr(bnx_b16),
+                                         _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
+        "fdgk_conv_dgrad_with_sums")
 
 
 def fdgk_bn_bwd_gated(g_b16, x_b16, sums_f32, gamma, gsums_f32, addend_f32, dx_f32, dx_b16, dgamma, dbeta, m, c, eps,
@@ -264,6 +283,16 @@ def fdgk_dwconv3_fwd(x_b16, wt_b16, y_b16, n, h, w, c, stride, stream=None):
 def fdgk_dwconv3_dgrad(dy_b16, wt_b16, dx_b16, n, h, w, c, stride, stream=None):
     _ok(_lib().fdgk_dwconv3_dgrad(_ptr(dy_b16), _ptr(wt_b16), _ptr(dx_b16), n, h, w, c, stride, _stream_handle(stream)),
         "fdgk_dwconv3_dgrad")
+
+
+def fdgk_dwconv3_fwd_sums(x_b16, wt_b16, y_b16, sums, n, h, w, c, stride, stream=None):
+    _ok(_lib().fdgk_dwconv3_fwd_sums(_ptr(x_b16), _ptr(wt_b16), _ptr(y_b16), _ptr(sums), n, h, w, c, stride, _stream_handle(stream)),
+        "fdgk_dwconv3_fwd_sums")
+
+
+def fdgk_dwconv3_dgrad_sums(dy_b16, wt_b16, gate_b16, gate_hi, bnx_b16, dx_f32, sums, n, h, w, c, stride, stream=None):
+    _ok(_lib().fdgk_dwconv3_dgrad_sums(_ptr(dy_b16), _ptr(wt_b16), _ptr(gate_b16), gate_hi, _ptr(bnx_b16), _ptr(dx_f32), _ptr(sums),
+                                       n, h, w, c, stride, _stream_handle(stream)), "fdgk_dwconv3_dgrad_sums")
 
 
 def fdgk_dwconv3_wgrad_scratch_bytes(n, h, w, c, stride) -> int:

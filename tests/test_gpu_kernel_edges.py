@@ -1,5 +1,6 @@
 """Kernels chosen by a rule on sizes, at the edges of that rule and at shapes that divide into none of their tiles: the parity
 checks of tests/test_gpu_kernels.py (same oracle, same bars), with the kernel that ran named."""
+import numpy as np
 import pytest
 
 import fdg_workloads as W
@@ -263,3 +264,99 @@ def test_paired_weight_gradients_against_64_bits(case, bound):
 ])
 def test_weight_gradients_over_columns_against_64_bits(case, bound, form):
     check_weight_gradient_against_64_bits(case, bound, f"conv_wgrad_tall_kernel<4, {form}>")
+
+
+# The output stages that gate by a ReLU6 and take the sums of the batch-norm backward behind it, with about a third of the gate shut
+# from below, a third clamped at 6 and values just below 6: the gradient is zero where the activation is clamped, and only there
+def relu6_operands(shape, r):
+    z = r.standard_normal(shape).astype(np.float32) * 7 + 3
+    gate = TK.bf16_round(np.clip(z, 0, 6))
+    gate[gate == 6] = np.where(r.random(int((gate == 6).sum())) < 0.1, np.float32(5.96875), np.float32(6))   # the bf16 below 6
+    bnx = TK.bf16_round(r.standard_normal(shape) * (0.5 + r.random((1, shape[1], 1, 1))) + r.standard_normal((1, shape[1], 1, 1)))
+    shut, clamped = gate == 0, gate == 6
+    assert shut.mean() > 0.2 and clamped.mean() > 0.2 and (gate == 5.96875).any()
+    return gate, bnx, shut | clamped
+
+
+def check_gated_with_sums(dx32, ref, closed, bnx, sums, c):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    got = TK.nhwc_to_nchw(dx32)
+    assert TK.rel(got, ref * ~closed) <= TK.F32_TOL
+    assert np.all(got[closed] == 0) and np.mean(got[~closed] != 0) > 0.99
+    g, x = dx32.to(t.float64).reshape(-1, c).cpu().numpy(), bnx.transpose(0, 2, 3, 1).reshape(-1, c).astype(np.float64)
+    total = K.fdgk_sums_read(sums, c)
+    assert TK.rel(total[:c], g.sum(0)) <= 1e-5 and TK.rel(total[c:], (g * x).sum(0)) <= 1e-5
+
+
+# every instantiation: 64 and a partly filled block of 72 channels into 128 and more, 128 and more into up to 64 and up to 96; ragged
+# pixels, several tiles; with and without an addend
+@pytest.mark.parametrize("case, kernel", [
+    ((3, 7, 9, 200, 64, 1, 1), "conv_gather_dma_pair_kernel<128, 2, feeding>"), ((5, 16, 16, 384, 72, 1, 1), "conv_gather_dma_pair_kernel<128, 2, feeding>"),
+    ((2, 13, 11, 64, 384, 1, 1), "conv_gather_dma_pair_kernel<64, 3, feeding>"), ((4, 9, 12, 40, 128, 1, 1), "conv_gather_dma_pair_kernel<64, 3, feeding>"),
+    ((3, 10, 13, 96, 576, 1, 1), "conv_gather_dma_pair_kernel<96, 4, feeding>"), ((1, 5, 5, 72, 192, 1, 1), "conv_gather_dma_pair_kernel<96, 4, feeding>"),
+])
+def test_data_gradient_behind_a_relu6(case, kernel):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co, k, s = case
+    print("dgrad behind a ReLU6", case, flush=True)
+    x, wt, dy, ho, wo = TK._conv_data(case, 31)
+    r = np.random.default_rng(32)
+    gate, bnx, closed = relu6_operands(x.shape, r)
+    ref = TK.K32.conv_bwd_data(dy, wt, x.shape, 1, 0).astype(np.float64)
+    add = r.standard_normal(ref.shape).astype(np.float32) * 0.5
+    dyd, wtd = TK.to_dev_nhwc_b16(dy), t.from_numpy(wt.transpose(1, 2, 3, 0).copy()).to(t.bfloat16).contiguous().cuda()
+    for addend, gated, hi in ((None, True, 6.0), (add, True, 6.0), (add, True, 0.0), (add, False, 0.0)):
+        sums, dx32 = K.new_sums(ci), t.full((n, h, w, ci), float("nan"), device="cuda")
+        K.fdgk_conv_dgrad_with_sums(dyd, wtd, None if addend is None else TK.to_dev_nhwc_f32(addend), TK.to_dev_nhwc_b16(gate) if gated else None,
+                                    hi, TK.to_dev_nhwc_b16(bnx), sums, dx32, None, n, h, w, ci, co)
+        assert K.fdgk_last_kernel() == kernel
+        shut = closed if hi else (gate <= 0) & gated     # no upper end: only what is not positive
+        check_gated_with_sums(dx32, ref + (0 if addend is None else addend), shut, bnx, sums, ci)
+
+
+@pytest.mark.parametrize("case", [(3, 9, 11, 72, 1), (2, 16, 16, 192, 1), (1, 1, 1, 8, 1), (3, 9, 11, 72, 2), (2, 16, 16, 192, 2), (40, 31, 30, 64, 1)])
+def test_depthwise_kernels_with_sums(case):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, c, s = case
+    print("depthwise with sums", case, flush=True)
+    ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+    r = np.random.default_rng(33)
+    x, dy = (TK.bf16_round(r.standard_normal(sh).astype(np.float32)) for sh in ((n, c, h, w), (n, c, ho, wo)))
+    wgt = TK.bf16_round((r.standard_normal((c, 1, 3, 3)) * np.sqrt(2.0 / 9)).astype(np.float32))
+    wt = t.from_numpy(np.ascontiguousarray(wgt.reshape(c, 9).T)).to(t.bfloat16).cuda()
+    y, plain = (t.empty((n, ho, wo, c), dtype=t.bfloat16, device="cuda") for _ in range(2))
+    sums = K.new_sums(c)
+    K.fdgk_dwconv3_fwd(TK.to_dev_nhwc_b16(x), wt, plain, n, h, w, c, s)
+    K.fdgk_dwconv3_fwd_sums(TK.to_dev_nhwc_b16(x), wt, y, sums, n, h, w, c, s)
+    assert t.equal(y, plain)
+    yd, total = y.to(t.float64).reshape(-1, c).cpu().numpy(), K.fdgk_sums_read(sums, c)
+    assert TK.rel(total[:c], yd.sum(0)) <= 1e-5 and TK.rel(total[c:], (yd * yd).sum(0)) <= 1e-5
+    if x.size < 100:     # too few cells for a share of them to be clamped
+        return
+    gate, bnx, closed = relu6_operands(x.shape, r)
+    dx, sums = t.full((n, h, w, c), float("nan"), device="cuda"), K.new_sums(c)
+    K.fdgk_dwconv3_dgrad_sums(TK.to_dev_nhwc_b16(dy), wt, TK.to_dev_nhwc_b16(gate), 6.0, TK.to_dev_nhwc_b16(bnx), dx, sums, n, h, w, c, s)
+    check_gated_with_sums(dx, TK.K32.dwconv_bwd_data(dy, wgt, x.shape, s, 1).astype(np.float64), closed, bnx, sums, c)
+
+
+def clamped_params(spec, theta):
+    """theta with the batch norms of the expanded tensors at 4 x + 3: about a fifth of the ReLU6 outputs is 0 and a fifth 6."""
+    theta, expanded, at = theta.copy(), {6 * L.c_in for L in spec.layers}, 0
+    for _, shape, role in W.param_shapes(spec):
+        if role in ("gamma", "beta") and shape[0] in expanded:
+            theta[at:at + shape[0]] = 4 if role == "gamma" else 3
+        at += int(np.prod(shape))
+    return theta
+
+
+# Two inverted blocks whose batch norms push a good part of their ReLU6 outputs to the clamp, layer by layer
+@pytest.mark.parametrize("stride", [1, 2])
+def test_inverted_blocks_at_the_clamp(stride, monkeypatch):
+    layers = [Layer(W.INVERTED_RESIDUAL, 64, 64, 1), Layer(W.INVERTED_RESIDUAL, 64, 96, stride)]
+    spec = ModuleSpec(3, 64, 12, 13, layers, delay=1, is_bottom=False, beta=0.5, name="clamped", **TD.H)
+    make = W.make_params
+    monkeypatch.setattr(W, "make_params", lambda sp, seed, **kw: clamped_params(sp, make(sp, seed, **kw)))
+    LT._judge(LT._run(spec, seed=1, steps_after_warmup=2), f"clamped stride {stride}")
