@@ -120,17 +120,18 @@ int fdgk_conv_dgrad_gated_pair(const void* dy_b16, const void* wt_b16, const voi
                                int h, int w, int ci, int co, void* hip_stream);
 
 /* The same sum of two data gradients for layers of 40 .. 96 input channels, in fp32 (dx_f32 is required; dx_b16 may be NULL), with
- * the sums of the FP32 values; 1 elsewhere.                                                            */
+ * the sums of the FP32 values; 1 elsewhere.  Here and below bnx_sums is the complete forward sums array of bnx (may be NULL): the
+ * second sum is then taken around the batch mean, so that a mean that is large against the spread costs it no digits.      */
 int fdgk_conv_dgrad_thin_pair(const void* dy_b16, const void* wt_b16, const void* dy2_b16, const void* wt2_b16, const void* gate_b16,
-                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
-                              void* hip_stream);
+                              const void* bnx_b16, const void* bnx_sums, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w,
+                              int ci, int co, void* hip_stream);
 /* Data gradient of a 1x1 unit-stride convolution in an inverted residual block, ending in the two sums, of the FP32 values, of the
  * batch-norm backward that follows, with a gate in between or without one (gate_b16 NULL): dx = data gradient + addend (may be
  * NULL), zero unless 0 < gate, and zero where gate >= gate_hi if gate_hi > 0 (6: a ReLU6).  dx_f32, bnx_b16 and gsums are required.
  * Where co % 64 == 0 or 64 < co < 128 and ci >= 128 (co <= 1024), or co % 64 == 0, co >= 128 and 40 <= ci <= 96; 1 elsewhere.   */
 int fdgk_conv_dgrad_with_sums(const void* dy_b16, const void* wt_b16, const float* addend_f32, const void* gate_b16, float gate_hi,
-                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
-                              void* hip_stream);
+                              const void* bnx_b16, const void* bnx_sums, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w,
+                              int ci, int co, void* hip_stream);
 
 /* Weight gradient, the adjoint in w, into dw_f32 [co][ksize*ksize][ci]:
  *   dw[o,r,q,i] (+)= sum_{n,ho,wo} dy[n,ho,wo,o] * x[n, ho*s+r-p, wo*s+q-p, i].
@@ -232,7 +233,7 @@ int fdgk_dwconv3_dgrad(const void* dy_b16, const void* wt_b16, void* dx_b16, int
 int fdgk_dwconv3_fwd_sums(const void* x_b16, const void* wt_b16, void* y_b16, void* sums, int n, int h, int w, int c, int stride,
                           void* hip_stream);
 int fdgk_dwconv3_dgrad_sums(const void* dy_b16, const void* wt_b16, const void* gate_b16, float gate_hi, const void* bnx_b16,
-                            float* dx_f32, void* sums, int n, int h, int w, int c, int stride, void* hip_stream);
+                            const void* bnx_sums, float* dx_f32, void* sums, int n, int h, int w, int c, int stride, void* hip_stream);
 size_t fdgk_dwconv3_wgrad_scratch_bytes(int n, int h, int w, int c, int stride);
 int fdgk_dwconv3_wgrad(const void* x_b16, const void* dy_b16, float* dw_f32, float* scratch_f32, size_t scratch_bytes, int n, int h,
                        int w, int c, int stride, void* hip_stream);

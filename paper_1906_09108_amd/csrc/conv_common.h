@@ -147,10 +147,10 @@ constexpr int stats_stage_bytes(int BN) { return 4 * ((BN / 4) % 16 == 0 ? 1 : (
 // loads of GROUP = 5 iterations together (about 14 registers per iteration) and park the statistics of PARKW = 8
 // waves where the regions were (stats_lds may then overlap them: a barrier separates the two uses).
 // F32S: the per-channel sums are of the fp32 values (a data gradient whose fp32 result the batch norm below reads),
-// not of their bf16 roundings.
+// not of their bf16 roundings, and the second one is taken around centre[channel of the tile] (LDS; see StatMean).
 template <int FN, int BN, int GROUP = 10, int ROWS = 32, int PARKW = 4, bool F32S = false>
 __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x16 (&acc)[FN], int m_base, int c_tile,
-                                             int lane, unsigned char* lds, unsigned char* stats_lds) {
+                                             int lane, unsigned char* lds, unsigned char* stats_lds, const float* centre = nullptr) {
   static_assert(FN * 32 == BN, "one wave carries all channels of the tile");
   static_assert(ROWS == 32 || ROWS == 16, "whole or half blocks");
   constexpr int PITCH = out_stage_pitch(BN);
@@ -179,6 +179,11 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
   for (int k = 0; k < PERIOD; ++k)
 #pragma unroll
     for (int e = 0; e < 4; ++e) s1[k][e] = s2[k][e] = 0.f;
+  f32x4 mu[PERIOD];
+  if constexpr (F32S) {
+#pragma unroll
+    for (int k = 0; k < PERIOD; ++k) mu[k] = *reinterpret_cast<const f32x4*>(centre + ((k * 64 + lane) % UNITS) * 4);
+  }
 #pragma unroll
   for (int part = 0; part < 32 / ROWS; ++part) {
   {
@@ -277,7 +282,10 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
           const float r2 = F32S ? v[k][2] : bf16_lo(packed[1]), r3 = F32S ? v[k][3] : bf16_hi(packed[1]);
           const int kk = (it0 + k) % PERIOD;
           s1[kk][0] += r0; s1[kk][1] += r1; s1[kk][2] += r2; s1[kk][3] += r3;
-          if (p_bnx) {
+          if (F32S && p_bnx) {
+            s2[kk][0] += r0 * (bf16_lo(bx[k][0]) - mu[kk][0]); s2[kk][1] += r1 * (bf16_hi(bx[k][0]) - mu[kk][1]);
+            s2[kk][2] += r2 * (bf16_lo(bx[k][1]) - mu[kk][2]); s2[kk][3] += r3 * (bf16_hi(bx[k][1]) - mu[kk][3]);
+          } else if (p_bnx) {
             s2[kk][0] += r0 * bf16_lo(bx[k][0]); s2[kk][1] += r1 * bf16_hi(bx[k][0]);
             s2[kk][2] += r2 * bf16_lo(bx[k][1]); s2[kk][3] += r3 * bf16_hi(bx[k][1]);
           } else {
@@ -308,14 +316,19 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
       const int c = c_tile + cl;
       if (c >= a.Co) continue;
       const int un = cl >> 2, e = cl & 3;
-      float sum = 0.f;
+      auto total = [&](int of) {
+        float sum = 0.f;
 #pragma unroll
-      for (int k = 0; k < PERIOD; ++k) {
-        const int l0 = ((un - k * 64) % UNITS + UNITS) % UNITS;   // lanes with (k*64 + lane) % UNITS == un
-        for (int l = l0; l < 64; l += UNITS)
+        for (int k = 0; k < PERIOD; ++k) {
+          const int l0 = ((un - k * 64) % UNITS + UNITS) % UNITS;   // lanes with (k*64 + lane) % UNITS == un
+          for (int l = l0; l < 64; l += UNITS)
 #pragma unroll
-          for (int w = 0; w < PARKW; ++w) sum += park[(size_t)((w * PERIOD + k) * 64 + l) * 8 + which * 4 + e];
-      }
+            for (int w = 0; w < PARKW; ++w) sum += park[(size_t)((w * PERIOD + k) * 64 + l) * 8 + of * 4 + e];
+        }
+        return sum;
+      };
+      double sum = total(which);
+      if (F32S && which == 1 && a.bnx_sums) sum += (double)centre[cl] * total(0);
       stat_add(a.stats + (size_t)(blockIdx.x % kStatReplicas) * a.stats_rep_stride, a.Co, which, c, sum);
     }
   }
@@ -328,7 +341,7 @@ __device__ __forceinline__ void store_rows32(const GatherConvArgs& a, const f32x
 // in flight).
 template <int FN, int BN, bool F32S = false>
 __device__ __forceinline__ void combine_and_store32(const GatherConvArgs& a, f32x16 (&acc)[FN][2], int m_tile, int c_tile,
-                                                    int wave_m, int wk, int lane, unsigned char* smem) {
+                                                    int wave_m, int wk, int lane, unsigned char* smem, const float* centre = nullptr) {
   __syncthreads();
   f32x4* mine = reinterpret_cast<f32x4*>(smem) + (size_t)(wave_m * 2 + wk) * (FN * 4 * 64);
   const f32x4* theirs = reinterpret_cast<const f32x4*>(smem) + (size_t)(wave_m * 2 + (wk ^ 1)) * (FN * 4 * 64);
@@ -352,7 +365,7 @@ __device__ __forceinline__ void combine_and_store32(const GatherConvArgs& a, f32
   __syncthreads();
   const int wave = wave_m * 2 + wk;
   store_rows32<FN, BN, BN == 96 ? 6 : 10, 32, 4, F32S>(a, keep, m_tile + wave_m * 64 + wk * 32, c_tile, lane, smem + (size_t)wave * out_stage_bytes(BN),
-                       smem + (size_t)4 * out_stage_bytes(BN));
+                       smem + (size_t)4 * out_stage_bytes(BN), centre);
 }
 
 // End of the 256-pixel kernel: eight waves (wave_m, wk), wave_m = wave & 3 owns 64 pixels as two 32-pixel blocks j, wk =

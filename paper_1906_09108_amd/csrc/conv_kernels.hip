@@ -506,7 +506,7 @@ static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf
                                   const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                   bf16_t* out_b16, hipStream_t s, bool stats_f32 = false, int rep_stride = 0,
                                   const bf16_t* dy2 = nullptr, const bf16_t* wt2 = nullptr, const ConvInputBnBwd* bn = nullptr,
-                                  const ConvScratch& scratch = {});
+                                  const ConvScratch& scratch = {}, const stat_t* bnx_sums = nullptr);
 
 hipError_t conv_dgrad(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                       const bf16_t* addmask, float* out_f32, bf16_t* out_b16, hipStream_t s, const ConvScratch& scratch) {
@@ -546,11 +546,12 @@ static GatherConvArgs dgrad1x1_args(const ConvShape& c) {
 }
 bool conv_dgrad_sums_applies(const ConvShape& c) { return c.T == 1 && c.stride == 1 && conv_gather_feeding_applies(dgrad1x1_args(c)); }
 hipError_t conv_dgrad_with_sums(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
-                                float gate_hi, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
-                                int gsums_rep_stride) {
+                                float gate_hi, const bf16_t* bnx, const stat_t* bnx_sums, stat_t* gsums, float* out_f32, bf16_t* out_b16,
+                                hipStream_t s, int gsums_rep_stride) {
   if (!bnx || !gsums || !out_f32 || !conv_dgrad_sums_applies(c)) return hipErrorInvalidValue;
   GatherConvArgs a = dgrad1x1_args(c);
   a.in = dy; a.w = wt; a.addend = addend; a.gate = gate; a.gate_hi = gate_hi; a.bnx = bnx;
+  a.bnx_sums = bnx_sums; a.bnx_inv_m = 1.0 / ((double)c.N * c.Hi * c.Wi);
   a.stats = gsums; a.stats_f32 = 1; a.stats_rep_stride = gsums_rep_stride; a.out_f32 = out_f32; a.out_b16 = out_b16;
   return launch_conv_gather_feeding(a, s);
 }
@@ -620,19 +621,21 @@ bool conv_dgrad_thin_pair_applies(const ConvShape& c, const ConvShape& cp) {
   return conv_gather_thin_classes_applies(probe);
 }
 hipError_t conv_dgrad_thin_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
-                                const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16,
-                                hipStream_t s, int gsums_rep_stride) {
+                                const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, const stat_t* bnx_sums, stat_t* gsums,
+                                float* out_f32, bf16_t* out_b16, hipStream_t s, int gsums_rep_stride) {
   const bool gated = gate || bnx || gsums;
   if (!dy2 || !wt2 || !out_f32 || (gated && (!gate || !bnx || !gsums)) || !conv_dgrad_thin_pair_applies(c, cp)) return hipErrorInvalidValue;
-  return conv_dgrad_impl(c, dy, wt, nullptr, nullptr, gate, bnx, gsums, out_f32, out_b16, s, gated, gsums_rep_stride, dy2, wt2);
+  return conv_dgrad_impl(c, dy, wt, nullptr, nullptr, gate, bnx, gsums, out_f32, out_b16, s, gated, gsums_rep_stride, dy2, wt2, nullptr, {},
+                         bnx_sums);
 }
 
 static hipError_t conv_dgrad_impl(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                   const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                   bf16_t* out_b16, hipStream_t s, bool stats_f32, int rep_stride, const bf16_t* dy2,
-                                  const bf16_t* wt2, const ConvInputBnBwd* bn, const ConvScratch& scratch) {
+                                  const bf16_t* wt2, const ConvInputBnBwd* bn, const ConvScratch& scratch, const stat_t* bnx_sums) {
   GatherConvArgs a{};
   a.scratch = scratch;
+  a.bnx_sums = bnx_sums; a.bnx_inv_m = 1.0 / ((double)c.N * c.Hi * c.Wi);
   a.stats_rep_stride = rep_stride;
   a.in = dy; a.w = wt; a.addend = addend; a.addmask = addmask; a.out_f32 = out_f32; a.out_b16 = out_b16;
   a.gate = gate; a.bnx = bnx; a.stats = gsums; a.stats_f32 = stats_f32 ? 1 : 0;

@@ -211,6 +211,10 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
     }
   }
   const char* zero = reinterpret_cast<const char*>(g_zero_word);
+  __shared__ __attribute__((aligned(16))) float centre[F32S ? BN : 4];
+  const bool centres = F32S && a.bnx_sums && tid < BN && c0 + tid < a.Co;
+  StatMean sm;   // requested here, waited for behind the main loop (copies, whose words have to be added, are requested there)
+  if (centres && a.stats_rep_stride == 0) sm.load(a.bnx_sums, a.Co, c0 + tid, 0);
   const int cpc = (a.Ci + 63) >> 6;       // chunks per tap
   const bool has2 = CLASSES && a.in2 != nullptr && cls == a.cls2;
   const int nchunks = (b.ntaps + (has2 ? 1 : 0)) * cpc;
@@ -295,7 +299,11 @@ __device__ __forceinline__ void gather_dma_body(const GatherConvArgs& a, int m_t
     }
   }
   wait_vmcnt<0>();
-  combine_and_store32<FN, BN, F32S>(b, acc, m0, c0, wave_m, wk, lane, smem);
+  if (F32S) {
+    if (centres && a.stats_rep_stride != 0) sm.load(a.bnx_sums, a.Co, c0 + tid, a.stats_rep_stride);
+    if (tid < BN) centre[tid] = centres ? sm.mean(a.bnx_inv_m) : 0.f;
+  }
+  combine_and_store32<FN, BN, F32S>(b, acc, m0, c0, wave_m, wk, lane, smem, centre);
 }
 
 // Within 256 registers.  <128, 2> (73 KB of LDS, like <64, 3>) so fits two workgroups on a compute unit, two waves per SIMD;

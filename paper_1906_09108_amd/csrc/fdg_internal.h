@@ -38,9 +38,8 @@ constexpr int kStatWords = 3;                                   // stat_t per su
 inline size_t stat_elems(size_t channels) { return 2 * channels * kStatWords; }   // stat_t of a sums array
 
 #if defined(__HIPCC__)
-// total[which][c] += s, for the sums array of C channels starting at `stats`
-__device__ __forceinline__ void stat_add(stat_t* stats, int C, int which, int c, float s) {
-  const double d = (double)s;
+// total[which][c] += d, for the sums array of C channels starting at `stats`
+__device__ __forceinline__ void stat_add(stat_t* stats, int C, int which, int c, double d) {
   stat_t* p = stats + (size_t)which * C + c;
   if (fabs(d) < 0x1p39) {
     const double h = rint(d * 0x1p11);
@@ -54,6 +53,26 @@ __device__ __forceinline__ void stat_add(stat_t* stats, int C, int which, int c,
 __device__ __forceinline__ double stat_value(long long hi, long long lo, long long big) {
   return __builtin_bit_cast(double, big) + ((double)hi * 0x1p-11 + (double)lo * 0x1p-62);
 }
+// The batch mean of channel c from its forward sums over 1 / inv_m rows, for a producer of the backward sums that takes the second
+// one around it: sum g (x - mean) in fp32, to which mean * sum g is added in double when the partial goes into the total.  The total is
+// sum g x as ever, but what cancels when its reader subtracts mean * sum g was never rounded in fp32.
+// load() requests the words, mean() waits for them.
+struct StatMean {
+  long long hi = 0, lo = 0;
+  double big = 0.0;
+  __device__ __forceinline__ void load(const stat_t* sums, int C, int c, int rep_stride) {
+    const stat_t* q = sums + c;
+    hi = q[0]; lo = q[2 * (size_t)C]; big = __builtin_bit_cast(double, q[4 * (size_t)C]);
+    if (rep_stride > 0) {
+#pragma unroll
+      for (int k = 1; k < kStatReplicas; ++k) {
+        q += rep_stride;
+        hi += q[0]; lo += q[2 * (size_t)C]; big += __builtin_bit_cast(double, q[4 * (size_t)C]);
+      }
+    }
+  }
+  __device__ __forceinline__ float mean(double inv_m) const { return (float)(stat_value(hi, lo, __builtin_bit_cast(long long, big)) * inv_m); }
+};
 #endif
 
 // Device memory with which a wide convolution of few tiles may deal the contraction of a tile to several workgroups: room for
@@ -79,6 +98,10 @@ struct GatherConvArgs {
   int stats_rep_stride;  // stat_t elements between the copies of stats (0: one copy)
   int stats_f32;         // with bnx, narrow / generic output stage: the sums are of the fp32 values, not of the bf16 output
   float gate_hi;         // > 0: the gate is closed where gate >= gate_hi, too (launch_conv_gather_feeding only)
+  // optional, with bnx and stats_f32 (the feeding and the classes form of conv_gather_dma_pair_kernel): the forward sums of the batch
+  // norm whose input bnx is, copies stats_rep_stride apart; the second sum is then taken around the mean (StatMean)
+  const stat_t* bnx_sums;
+  double bnx_inv_m;
   int N, Hi, Wi, Ci;
   int OH, OW, in_stride;
   int OHf, OWf, out_stride, ooh, oow;
@@ -250,12 +273,13 @@ bool conv_dgrad_feeds_next(const ConvShape& c);
 hipError_t conv_dgrad_feeding_next(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend,
                                    const bf16_t* addmask, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32,
                                    bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
+// (bnx_sums here and below: the forward sums of that batch norm; the second sum is taken around its mean.  nullptr: around zero)
 // Data gradient of a 1x1 layer in fp32 that ends in the two sums, of the fp32 values, of the batch-norm backward that follows, with
 // or without a gate in between: dx = addend + dgrad, zero unless 0 < gate (< gate_hi, if that is > 0).  conv_dgrad_sums_applies says where.
 bool conv_dgrad_sums_applies(const ConvShape& c);
 hipError_t conv_dgrad_with_sums(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
-                                float gate_hi, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
-                                int gsums_rep_stride);
+                                float gate_hi, const bf16_t* bnx, const stat_t* bnx_sums, stat_t* gsums, float* out_f32, bf16_t* out_b16,
+                                hipStream_t s, int gsums_rep_stride);
 bool conv_dgrad_gates(const ConvShape& c);
 // conv_dgrad_gated of c (3x3, stride 2) with the data gradient of the 1x1 stride-2 projection cp beside it (same input
 // tensor, same output grid) added before the gate, in one launch:
@@ -269,8 +293,8 @@ hipError_t conv_dgrad_gated_pair(const ConvShape& c, const bf16_t* dy, const bf1
 // The same for layers of 40 .. 96 input channels, in fp32 (and bf16), with the sums of the fp32 values
 bool conv_dgrad_thin_pair_applies(const ConvShape& c, const ConvShape& cp);
 hipError_t conv_dgrad_thin_pair(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const ConvShape& cp, const bf16_t* dy2,
-                                const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16,
-                                hipStream_t s, int gsums_rep_stride = 0);
+                                const bf16_t* wt2, const bf16_t* gate, const bf16_t* bnx, const stat_t* bnx_sums, stat_t* gsums,
+                                float* out_f32, bf16_t* out_b16, hipStream_t s, int gsums_rep_stride = 0);
 hipError_t conv_dgrad_gated(const ConvShape& c, const bf16_t* dy, const bf16_t* wt, const float* addend, const bf16_t* gate,
                             const bf16_t* bnx, stat_t* gsums, float* out_f32, bf16_t* out_b16, hipStream_t s,
                             int gsums_rep_stride = 0, const ConvScratch& scratch = {});
@@ -398,8 +422,8 @@ bool dwconv3_sums_applies(int N, int H, int W, int C);
 hipError_t launch_dwconv3_fwd_sums(const bf16_t* x, const bf16_t* wt, bf16_t* y, stat_t* sums, int rep_stride, int N, int H, int W, int C,
                                    int stride, hipStream_t s);
 // the data gradient in fp32 behind a gate (zero unless 0 < gate < gate_hi), with the sums of dx and dx * bnx
-hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const bf16_t* gate, float gate_hi, const bf16_t* bnx, float* dx,
-                                     stat_t* sums, int rep_stride, int N, int H, int W, int C, int stride, hipStream_t s);
+hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const bf16_t* gate, float gate_hi, const bf16_t* bnx,
+                                     const stat_t* bnx_sums, float* dx, stat_t* sums, int rep_stride, int N, int H, int W, int C, int stride, hipStream_t s);
 size_t dwconv3_wgrad_scratch_bytes(int N, int H, int W, int C, int stride);
 hipError_t launch_dwconv3_wgrad(const bf16_t* x, const bf16_t* dy, float* dw, float* scratch, size_t scratch_bytes, int N, int H, int W,
                                 int C, int stride, hipStream_t s);

@@ -1293,7 +1293,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
                                conv_in_elems(c1.sh) * (write_bytes + (feeds ? 2 + 2 : 0));
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c1.sh) + conv_flops(cp.sh), bytes, s);
           const hipError_t e = conv_dgrad_thin_pair(c1.sh, m->T(0), v.Wt(c1), cp.sh, m->T(1), v.Wt(cp), feeds ? in_b : nullptr, feeds ? bnx : nullptr,
-                                                    feeds ? m->bsums(*bb) : nullptr, G_out, GB_out, s, p.stat_rep);
+                                                    feeds ? v.sums(*bb) : nullptr, feeds ? m->bsums(*bb) : nullptr, G_out, GB_out, s, p.stat_rep);
           ps.label(c1.sh);
           FDG_TRY(e);
           fed = feeds;
@@ -1404,7 +1404,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       if (conv_dgrad_sums_applies(c3.sh)) {
         {
           ProfScope ps(m, PC_CONV_DGRAD, conv_flops(c3.sh), 2 * conv_out_elems(c3.sh) + 2 * conv_w_elems(c3.sh) + conv_in_elems(c3.sh) * (4 + 2 + 2), s);
-          const hipError_t e = conv_dgrad_with_sums(c3.sh, m->T(0), v.Wt(c3), nullptr, t_a2, 6.f, t_c2, m->bsums(b2), gf, nullptr, s, p.stat_rep);
+          const hipError_t e = conv_dgrad_with_sums(c3.sh, m->T(0), v.Wt(c3), nullptr, t_a2, 6.f, t_c2, v.sums(b2), m->bsums(b2), gf, nullptr, s, p.stat_rep);
           ps.label(c3.sh);
           FDG_TRY(e);
         }
@@ -1416,7 +1416,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       FDG_TRY(launch_dwconv3_wgrad(t_a1, m->T(0), m->grads() + c2.p_off, reinterpret_cast<float*>(m->ws + p.o_dwscratch),
                                    p.dwscratch_bytes, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
       if (dwconv3_sums_applies(N, L.Hi, L.Wi, c2.sh.Co)) {
-        FDG_TRY(launch_dwconv3_dgrad_sums(m->T(0), v.Wt(c2), t_a1, 6.f, t_c1, gf, m->bsums(b1), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
+        FDG_TRY(launch_dwconv3_dgrad_sums(m->T(0), v.Wt(c2), t_a1, 6.f, t_c1, v.sums(b1), gf, m->bsums(b1), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
         FDG_TRY(bn_backward_fed_from_above(m, v, b1, gf, t_c1, m->T(0), s));
       } else {
         FDG_TRY(launch_dwconv3_dgrad(m->T(0), v.Wt(c2), nullptr, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s, gf));
@@ -1430,7 +1430,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
                      conv_in_elems(c1.sh) * ((adds ? 4 : 0) + 2 + 4 + (GB_out ? 2 : 0)), s);
         if (GB_out) FDG_TRY(side_wait_readers(m, GB_out, s));
         const hipError_t e = conv_dgrad_with_sums(c1.sh, m->T(0), v.Wt(c1), adds ? m->G(cur) : nullptr, nullptr, 0.f, v.act(B.act[5]),
-                                                  m->bsums(p.bns[B.bn[3]]), m->G(nxt), GB_out, s, p.stat_rep);
+                                                  v.sums(p.bns[B.bn[3]]), m->bsums(p.bns[B.bn[3]]), m->G(nxt), GB_out, s, p.stat_rep);
         ps.label(c1.sh);
         FDG_TRY(e);
         fed = true;

@@ -151,25 +151,25 @@ int fdgk_conv_dgrad_feeding_next(const void* dy_b16, const void* wt_b16, const f
 }
 
 int fdgk_conv_dgrad_thin_pair(const void* dy_b16, const void* wt_b16, const void* dy2_b16, const void* wt2_b16, const void* gate_b16,
-                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
-                              void* hip_stream) {
+                              const void* bnx_b16, const void* bnx_sums, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w,
+                              int ci, int co, void* hip_stream) {
   ConvShape c, cp;
   if (!dy_b16 || !wt_b16 || !dy2_b16 || !wt2_b16 || !dx_f32 || !conv_shape(c, n, h, w, ci, co, 3, 2) || !conv_shape(cp, n, h, w, ci, co, 1, 2))
     return (int)hipErrorInvalidValue;
   return (int)conv_dgrad_thin_pair(c, static_cast<const bf16_t*>(dy_b16), static_cast<const bf16_t*>(wt_b16), cp,
                                    static_cast<const bf16_t*>(dy2_b16), static_cast<const bf16_t*>(wt2_b16),
-                                   static_cast<const bf16_t*>(gate_b16), static_cast<const bf16_t*>(bnx_b16), static_cast<stat_t*>(gsums),
-                                   dx_f32, static_cast<bf16_t*>(dx_b16), st(hip_stream));
+                                   static_cast<const bf16_t*>(gate_b16), static_cast<const bf16_t*>(bnx_b16),
+                                   static_cast<const stat_t*>(bnx_sums), static_cast<stat_t*>(gsums), dx_f32, static_cast<bf16_t*>(dx_b16), st(hip_stream));
 }
 
 int fdgk_conv_dgrad_with_sums(const void* dy_b16, const void* wt_b16, const float* addend_f32, const void* gate_b16, float gate_hi,
-                              const void* bnx_b16, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w, int ci, int co,
-                              void* hip_stream) {
+                              const void* bnx_b16, const void* bnx_sums, void* gsums, float* dx_f32, void* dx_b16, int n, int h, int w,
+                              int ci, int co, void* hip_stream) {
   ConvShape c;
   if (!dy_b16 || !wt_b16 || !bnx_b16 || !gsums || !dx_f32 || !conv_shape(c, n, h, w, ci, co, 1, 1)) return (int)hipErrorInvalidValue;
   return (int)conv_dgrad_with_sums(c, static_cast<const bf16_t*>(dy_b16), static_cast<const bf16_t*>(wt_b16), addend_f32,
                                    static_cast<const bf16_t*>(gate_b16), gate_hi, static_cast<const bf16_t*>(bnx_b16),
-                                   static_cast<stat_t*>(gsums), dx_f32, static_cast<bf16_t*>(dx_b16), st(hip_stream), 0);
+                                   static_cast<const stat_t*>(bnx_sums), static_cast<stat_t*>(gsums), dx_f32, static_cast<bf16_t*>(dx_b16), st(hip_stream), 0);
 }
 
 int fdgk_conv_dgrad_gates(int n, int h, int w, int ci, int co, int ksize, int stride) {
@@ -349,10 +349,10 @@ int fdgk_dwconv3_fwd_sums(const void* x_b16, const void* wt_b16, void* y_b16, vo
 }
 
 int fdgk_dwconv3_dgrad_sums(const void* dy_b16, const void* wt_b16, const void* gate_b16, float gate_hi, const void* bnx_b16,
-                            float* dx_f32, void* sums, int n, int h, int w, int c, int stride, void* hip_stream) {
+                            const void* bnx_sums, float* dx_f32, void* sums, int n, int h, int w, int c, int stride, void* hip_stream) {
   return (int)launch_dwconv3_dgrad_sums(static_cast<const bf16_t*>(dy_b16), static_cast<const bf16_t*>(wt_b16),
-                                        static_cast<const bf16_t*>(gate_b16), gate_hi, static_cast<const bf16_t*>(bnx_b16), dx_f32,
-                                        static_cast<stat_t*>(sums), 0, n, h, w, c, stride, st(hip_stream));
+                                        static_cast<const bf16_t*>(gate_b16), gate_hi, static_cast<const bf16_t*>(bnx_b16),
+                                        static_cast<const stat_t*>(bnx_sums), dx_f32, static_cast<stat_t*>(sums), 0, n, h, w, c, stride, st(hip_stream));
 }
 
 size_t fdgk_dwconv3_wgrad_scratch_bytes(int n, int h, int w, int c, int stride) { return dwconv3_wgrad_scratch_bytes(n, h, w, c, stride); }

@@ -275,6 +275,7 @@ struct DwSums {
   float* dx;            // data gradient
   const bf16_t* gate;
   const bf16_t* bnx;
+  const stat_t* bnx_sums;   // forward sums of bnx's batch norm: the second sum is taken around its mean (StatMean); nullptr: around 0
   float gate_hi;
   stat_t* sums;
   int rep_stride;
@@ -284,14 +285,25 @@ struct DwSums {
 template <int S, bool DGRAD>
 __global__ __launch_bounds__(256) void dwconv3_sums_kernel(DwSums a) {
   __shared__ float red[2][32][64];
+  __shared__ float centre[64];
   const int C = a.C, CG = C / 8, WB = (a.Wd + 1) / 2, HB = (a.Hd + 1) / 2;
   const int cgl = threadIdx.x & 7, rl = threadIdx.x >> 3, cg = blockIdx.x * 8 + cgl;
+  const int own = blockIdx.x * 64 + threadIdx.x;
+  const bool centres = DGRAD && threadIdx.x < 64 && a.bnx_sums && own < C;
+  StatMean sm;
+  if (centres) sm.load(a.bnx_sums, C, own, a.rep_stride);
+  float k[9][8], mu[8];
+  if (cg < CG) dw_filter(a.wt, C, cg, k);
+  if (DGRAD) {
+    if (threadIdx.x < 64) centre[threadIdx.x] = centres ? sm.mean(1.0 / ((double)a.N * a.Hd * a.Wd)) : 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mu[j] = centre[cgl * 8 + j];
+  }
   float s1[8], s2[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) s1[j] = s2[j] = 0.f;
   if (cg < CG) {
-    float k[9][8];
-    dw_filter(a.wt, C, cg, k);
     const unsigned per_image = (unsigned)HB * WB, units = (unsigned)a.N * per_image;
     for (int round = 0; round < a.rounds; ++round) {
       const unsigned u = (blockIdx.y * (unsigned)a.rounds + round) * 32u + rl;
@@ -327,7 +339,7 @@ __global__ __launch_bounds__(256) void dwconv3_sums_kernel(DwSums a) {
           for (int j = 0; j < 8; ++j) {
             if (!(g[j] > 0.f) || g[j] >= a.gate_hi) f[j] = 0.f;
             s1[j] += f[j];
-            s2[j] += f[j] * x[j];
+            s2[j] += f[j] * (x[j] - mu[j]);
           }
           store_f32(a.dx + o, f);
         } else {
@@ -351,9 +363,14 @@ __global__ __launch_bounds__(256) void dwconv3_sums_kernel(DwSums a) {
   __syncthreads();
   const int which = threadIdx.x >> 6, c = blockIdx.x * 64 + (threadIdx.x & 63);
   if (which < 2 && c < C) {
-    float t = 0.f;
+    auto total = [&](int w) {
+      float t = 0.f;
 #pragma unroll
-    for (int r = 0; r < 32; ++r) t += red[which][r][threadIdx.x & 63];
+      for (int r = 0; r < 32; ++r) t += red[w][r][threadIdx.x & 63];
+      return t;
+    };
+    double t = total(which);
+    if (DGRAD && which == 1 && a.bnx_sums) t += (double)centre[threadIdx.x & 63] * total(0);
     stat_add(a.sums + (size_t)((blockIdx.x + blockIdx.y) % kStatReplicas) * a.rep_stride, C, which, c, t);
   }
 }
@@ -588,12 +605,12 @@ hipError_t launch_dwconv3_fwd_sums(const bf16_t* x, const bf16_t* wt, bf16_t* y,
   return launch_dw_sums(a, stride, false, s);
 }
 
-hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const bf16_t* gate, float gate_hi, const bf16_t* bnx, float* dx,
-                                     stat_t* sums, int rep_stride, int N, int H, int W, int C, int stride, hipStream_t s) {
+hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const bf16_t* gate, float gate_hi, const bf16_t* bnx,
+                                     const stat_t* bnx_sums, float* dx, stat_t* sums, int rep_stride, int N, int H, int W, int C, int stride, hipStream_t s) {
   if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || C % 8 != 0 || (stride != 1 && stride != 2) || !dy || !wt || !gate || !bnx || !dx || !sums)
     return hipErrorInvalidValue;
   DwSums a{};
-  a.src = dy; a.wt = wt; a.dx = dx; a.gate = gate; a.gate_hi = gate_hi; a.bnx = bnx; a.sums = sums; a.rep_stride = rep_stride;
+  a.src = dy; a.wt = wt; a.dx = dx; a.gate = gate; a.gate_hi = gate_hi; a.bnx = bnx; a.bnx_sums = bnx_sums; a.sums = sums; a.rep_stride = rep_stride;
   a.N = N; a.Hs = (H - 1) / stride + 1; a.Ws = (W - 1) / stride + 1; a.C = C; a.Hd = H; a.Wd = W;
   return launch_dw_sums(a, stride, true, s);
 }

@@ -31,8 +31,8 @@ def _lib():
         lib.fdgk_conv_dgrad_gates.argtypes = [i, i, i, i, i, i, i]
         lib.fdgk_conv_dgrad_pair_applies.argtypes = [i, i, i, i, i]
         lib.fdgk_conv_dgrad_gated_pair.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
-        lib.fdgk_conv_dgrad_thin_pair.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
-        lib.fdgk_conv_dgrad_with_sums.argtypes = [vp, vp, vp, vp, f, vp, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_conv_dgrad_thin_pair.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_conv_dgrad_with_sums.argtypes = [vp, vp, vp, vp, f, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_bn_bwd_gated.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i, i, f, vp]
         lib.fdgk_conv_wgrad.argtypes = [vp, vp, vp, vp, sz, i, i, i, i, i, i, i, i, vp]
         lib.fdgk_conv_wgrad_scratch_bytes.argtypes = [i, i, i, i, i, i, i]
@@ -57,7 +57,7 @@ def _lib():
         lib.fdgk_dwconv3_fwd.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_dgrad.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_fwd_sums.argtypes = [vp, vp, vp, vp, i, i, i, i, i, vp]
-        lib.fdgk_dwconv3_dgrad_sums.argtypes = [vp, vp, vp, f, vp, vp, vp, i, i, i, i, i, vp]
+        lib.fdgk_dwconv3_dgrad_sums.argtypes = [vp, vp, vp, f, vp, vp, vp, vp, i, i, i, i, i, vp]
         lib.fdgk_dwconv3_wgrad_scratch_bytes.argtypes = [i, i, i, i, i]
         lib.fdgk_dwconv3_wgrad.argtypes = [vp, vp, vp, vp, sz, i, i, i, i, i, vp]
         lib.fdgk_last_kernel.argtypes = []
@@ -162,16 +162,16 @@ def fdgk_conv_dgrad_feeding_next(dy_b16, wt_b16, addend_f32, addmask_b16, gate_b
 
 
 def fdgk_conv_dgrad_thin_pair(dy_b16, wt_b16, dy2_b16, wt2_b16, gate_b16, bnx_b16, gsums, dx_f32, dx_b16, n, h, w, ci, co,
-                              stream=None):
+                              bnx_sums=None, stream=None):
     _ok(_lib().fdgk_conv_dgrad_thin_pair(_ptr(dy_b16), _ptr(wt_b16), _ptr(dy2_b16), _ptr(wt2_b16), _ptr(gate_b16), _ptr(bnx_b16),
-                                         _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
+                                         _ptr(bnx_sums), _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
         "fdgk_conv_dgrad_thin_pair")
 
 
 def fdgk_conv_dgrad_with_sums(dy_b16, wt_b16, addend_f32, gate_b16, gate_hi, bnx_b16, gsums, dx_f32, dx_b16, n, h, w, ci, co,
-                              stream=None):
+                              bnx_sums=None, stream=None):
     _ok(_lib().fdgk_conv_dgrad_with_sums(_ptr(dy_b16), _ptr(wt_b16), _ptr(addend_f32), _ptr(gate_b16), gate_hi, _ptr(bnx_b16),
-                                         _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
+                                         _ptr(bnx_sums), _ptr(gsums), _ptr(dx_f32), _ptr(dx_b16), n, h, w, ci, co, _stream_handle(stream)),
         "fdgk_conv_dgrad_with_sums")
 
 
@@ -290,8 +290,8 @@ def fdgk_dwconv3_fwd_sums(x_b16, wt_b16, y_b16, sums, n, h, w, c, stride, stream
         "fdgk_dwconv3_fwd_sums")
 
 
-def fdgk_dwconv3_dgrad_sums(dy_b16, wt_b16, gate_b16, gate_hi, bnx_b16, dx_f32, sums, n, h, w, c, stride, stream=None):
-    _ok(_lib().fdgk_dwconv3_dgrad_sums(_ptr(dy_b16), _ptr(wt_b16), _ptr(gate_b16), gate_hi, _ptr(bnx_b16), _ptr(dx_f32), _ptr(sums),
+def fdgk_dwconv3_dgrad_sums(dy_b16, wt_b16, gate_b16, gate_hi, bnx_b16, dx_f32, sums, n, h, w, c, stride, bnx_sums=None, stream=None):
+    _ok(_lib().fdgk_dwconv3_dgrad_sums(_ptr(dy_b16), _ptr(wt_b16), _ptr(gate_b16), gate_hi, _ptr(bnx_b16), _ptr(bnx_sums), _ptr(dx_f32), _ptr(sums),
                                        n, h, w, c, stride, _stream_handle(stream)), "fdgk_dwconv3_dgrad_sums")
 
 

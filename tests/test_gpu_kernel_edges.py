@@ -5,6 +5,7 @@ import pytest
 
 import fdg_workloads as W
 from fdg_workloads import Layer, ModuleSpec
+from tests import layerwise as LW
 from tests import test_gpu_kernels as TK
 from tests import test_gpu_layerwise as LT
 from tests import test_gpu_step_dispatch as TD
@@ -360,3 +361,77 @@ def test_inverted_blocks_at_the_clamp(stride, monkeypatch):
     make = W.make_params
     monkeypatch.setattr(W, "make_params", lambda sp, seed, **kw: clamped_params(sp, make(sp, seed, **kw)))
     LT._judge(LT._run(spec, seed=1, steps_after_warmup=2), f"clamped stride {stride}")
+
+
+# The second sum of a batch-norm backward, sum g (x - mean), against 64 bits, with batch means of up to 64 standard deviations: from the
+# launches that take it where the gradient is made, given the forward sums.  The pass of its own that they replace is off by 1.2e-7 ..
+# 1.6e-7 at these sizes, whatever the mean; sums of g x from which mean * sum g is subtracted later by 1.5e-7, 5e-7, 2e-6 and 1e-5 at means
+# of 1, 4, 16 and 64
+BIASED = {
+    "depthwise": ((32, 16, 16, 192), lambda K, r, x, gt, st, dx, b: K.fdgk_dwconv3_dgrad_sums(
+        r(32, 16, 16, 192), r(9, 192), gt, 6.0, x, dx, st, 32, 16, 16, 192, 1, bnx_sums=b)),
+    "depthwise stride 2": ((32, 16, 16, 72), lambda K, r, x, gt, st, dx, b: K.fdgk_dwconv3_dgrad_sums(
+        r(32, 8, 8, 72), r(9, 72), gt, 6.0, x, dx, st, 32, 16, 16, 72, 2, bnx_sums=b)),
+    "1x1 up": ((32, 16, 16, 384), lambda K, r, x, gt, st, dx, b: K.fdgk_conv_dgrad_with_sums(
+        r(32, 16, 16, 64), r(384, 64), None, gt, 6.0, x, st, dx, None, 32, 16, 16, 384, 64, bnx_sums=b)),
+    "1x1 to 64": ((32, 16, 16, 64), lambda K, r, x, gt, st, dx, b: K.fdgk_conv_dgrad_with_sums(
+        r(32, 16, 16, 384), r(64, 384), None, None, 0.0, x, st, dx, None, 32, 16, 16, 64, 384, bnx_sums=b)),
+    "1x1 to 96": ((32, 16, 16, 96), lambda K, r, x, gt, st, dx, b: K.fdgk_conv_dgrad_with_sums(
+        r(32, 16, 16, 576), r(96, 576), None, None, 0.0, x, st, dx, None, 32, 16, 16, 96, 576, bnx_sums=b)),
+    "pair": ((32, 32, 32, 64), lambda K, r, x, gt, st, dx, b: K.fdgk_conv_dgrad_thin_pair(
+        r(32, 16, 16, 128), r(64, 9, 128), r(32, 16, 16, 128), r(64, 128), gt, x, st, dx, None, 32, 32, 32, 64, 128, bnx_sums=b)),
+    "pair to 96": ((32, 16, 16, 96), lambda K, r, x, gt, st, dx, b: K.fdgk_conv_dgrad_thin_pair(
+        r(32, 8, 8, 192), r(96, 9, 192), r(32, 8, 8, 192), r(96, 192), gt, x, st, dx, None, 32, 16, 16, 96, 192, bnx_sums=b)),
+}
+
+
+@pytest.mark.parametrize("mean", [0.0, 4.0, 64.0])
+@pytest.mark.parametrize("name", sorted(BIASED))
+def test_batch_norm_sums_around_the_mean(name, mean):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    shape, launch = BIASED[name]
+    c, m = shape[3], shape[0] * shape[1] * shape[2]
+    g = t.Generator(device="cuda")
+    g.manual_seed(5)
+    r = lambda *sh: t.randn(*sh, generator=g, device="cuda").bfloat16()
+    x = (t.randn(*shape, generator=g, device="cuda") + mean).bfloat16()
+    gate = (t.randn(*shape, generator=g, device="cuda") * 3 + 2).clamp(0, 6).bfloat16()
+    forward, sums, dx = K.new_sums(c), K.new_sums(c), t.empty(*shape, device="cuda")
+    K.fdgk_bn_stats(x, forward, m, c)
+    launch(K, r, x, gate, sums, dx, forward)
+    batch_mean = t.from_numpy(K.fdgk_sums_read(forward, c)[:c] / m).cuda()
+    ref = (dx.double().reshape(m, c) * (x.double().reshape(m, c) - batch_mean)).sum(0)
+    total = t.from_numpy(K.fdgk_sums_read(sums, c)).cuda()
+    err = float((total[c:] - batch_mean * total[:c] - ref).norm() / ref.norm())
+    print(f"{name}, mean {mean}: {err:.2e}", flush=True)
+    assert err <= 1.6e-7
+
+
+# The same through a module: the lower block's last batch norm, whose sums the block above takes.  Its input has means of up to a hundred
+# standard deviations (the depthwise convolution's batch norm at 0.05 x + 3); what is left is fp32 rounding of the gradient itself
+def test_scale_gradient_of_a_biased_batch_norm():
+    from paper_1906_09108_amd import FdgModule
+    import torch as t
+    spec = ModuleSpec(8, 64, 16, 16, [Layer(W.INVERTED_RESIDUAL, 64, 64, 1)] * 2, delay=0, is_bottom=False, beta=0.5, name="biased", **TD.H)
+    theta, at, where, seen = W.make_params(spec, 0), 0, {}, 0
+    for name, shape, role in W.param_shapes(spec):
+        if role == "gamma":
+            where[seen], seen = at, seen + 1
+        if role in ("gamma", "beta") and seen == 2:
+            theta[at:at + shape[0]] = 0.05 if role == "gamma" else 3
+        at += int(np.prod(shape))
+    m = FdgModule(spec)
+    m.set_params(theta)
+    m.trace_attach()
+    m.forward(t.from_numpy(W.make_input(spec, 0, 0)).cuda())
+    m.backward_delayed(t.from_numpy(W.make_grad_out(spec, 0, 0)).cuda(), t.empty(spec.input_shape(), device="cuda"))
+    g, x = m.trace_read(1, 1)[0].astype(np.float64), m.saved_read(0, 0, LW.BN_INPUT[W.INVERTED_RESIDUAL]["bn3"]).astype(np.float64)
+    got = m.get_grads()[where[2]:where[2] + 64]
+    m.close()
+    mean, std = x.mean((0, 2, 3), keepdims=True), np.sqrt(x.var((0, 2, 3), keepdims=True) + TD.H["bn_eps"])
+    assert np.median(np.abs(mean) / std) > 10
+    ref = (g * (x - mean) / std).sum((0, 2, 3))
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"scale gradient: {err:.2e}", flush=True)
+    assert err <= 1e-6
