@@ -837,6 +837,15 @@ bool bwd_bn_fuses(const ConvInfo& c, const BnInfo& b, bool g_f32) {
   return b.C == c.sh.Co && (long long)b.M == (long long)c.sh.N * c.sh.Ho() * c.sh.Wo() && conv_dgrad_bn_applies(c.sh, g_f32);
 }
 
+// A basic block that is fed from above does the backward of its last batch norm on the patch of its second convolution's data
+// gradient (fuse2 below).  That suits blocks that are fed by another of their own width; over the few pixels for which it is done
+// it is longer than the passes of their own (64 channels, 8 x 63 x 63: 66 us against 13 + 6 + 22), so the transition above does not feed it.
+bool fuses_when_fed(const Plan& p, const LayerPlan& L) {
+  if (L.kind != FDG_BASIC_POSTACT) return false;
+  const ConvInfo& c2 = p.convs[L.conv[1]];
+  return dgrad_gates_for(c2, p.bns[L.bn[0]]) && bwd_bn_fuses(c2, p.bns[L.bn[1]], /*g_f32=*/true);
+}
+
 hipError_t dgrad_relu_bn_backward(const fdg_module* m, const SlotView& v, const ConvInfo& c, const bf16_t* dy, const bf16_t* wt,
                                   const float* dgrad_addend, const BnInfo& b, const bf16_t* gate, const bf16_t* x, bf16_t* g,
                                   const float* bn_addend, float* out_f32, bf16_t* out_b16, hipStream_t s) {
@@ -1287,7 +1296,7 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
           // the same into few channels, where the output stage can also do the first half of the backward of the layer below
           const bf16_t* bnx = nullptr;
           const BnInfo* bb = li > 0 ? closing_bn(p, v, p.L[li - 1], &bnx) : nullptr;
-          const bool feeds = bb && bb->C == c1.sh.Cip;
+          const bool feeds = bb && bb->C == c1.sh.Cip && !fuses_when_fed(p, p.L[li - 1]);
           FDG_TRY(side_wait_readers(m, GB_out, s));
           const double bytes = 2 * (conv_out_elems(c1.sh) + conv_out_elems(cp.sh)) + 2 * (conv_w_elems(c1.sh) + conv_w_elems(cp.sh)) +
                                conv_in_elems(c1.sh) * (write_bytes + (feeds ? 2 + 2 : 0));

@@ -435,3 +435,52 @@ def test_scale_gradient_of_a_biased_batch_norm():
     err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     print(f"scale gradient: {err:.2e}", flush=True)
     assert err <= 1e-6
+
+
+# The two data gradients of a projecting block of 40 .. 96 channels in one launch: gated, with the sums of the fp32 values, and plain
+@pytest.mark.parametrize("case", [(3, 9, 11, 64, 128), (4, 16, 14, 64, 64), (2, 7, 2, 72, 128), (5, 8, 8, 96, 192), (2, 5, 6, 40, 192)])
+def test_data_gradients_of_a_thin_projecting_block(case):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co = case
+    print("thin pair", case, flush=True)
+    x, wt, dy, ho, wo = TK._conv_data((n, h, w, ci, co, 3, 2), 41)
+    _, wt2, dy2, _, _ = TK._conv_data((n, h, w, ci, co, 1, 2), 42)
+    r = np.random.default_rng(43)
+    ref = (TK.K32.conv_bwd_data(dy, wt, x.shape, 2, 1).astype(np.float64) + TK.K32.conv_bwd_data(dy2, wt2, x.shape, 2, 0).astype(np.float64))
+    gate = TK.bf16_round(np.maximum(r.standard_normal(ref.shape), 0))
+    bnx = TK.bf16_round(r.standard_normal(ref.shape) + 3 * r.standard_normal((1, ci, 1, 1)))
+    w1, w2 = (t.from_numpy(a.transpose(1, 2, 3, 0).copy()).to(t.bfloat16).contiguous().cuda() for a in (wt, wt2))
+    xd, forward = TK.to_dev_nhwc_b16(bnx), K.new_sums(ci)
+    K.fdgk_bn_stats(xd, forward, n * h * w, ci)
+    for bnx_sums in (None, forward):
+        sums, dx32, dx16 = K.new_sums(ci), t.full((n, h, w, ci), float("nan"), device="cuda"), t.zeros((n, h, w, ci), device="cuda", dtype=t.bfloat16)
+        K.fdgk_conv_dgrad_thin_pair(TK.to_dev_nhwc_b16(dy), w1, TK.to_dev_nhwc_b16(dy2), w2, TK.to_dev_nhwc_b16(gate), xd, sums, dx32, dx16,
+                                    n, h, w, ci, co, bnx_sums=bnx_sums)
+        check_gated_with_sums(dx32, ref, gate <= 0, bnx, sums, ci)
+        assert TK.rel(TK.nhwc_to_nchw(dx16), ref * (gate > 0)) <= TK.B16_TOL
+    K.fdgk_conv_dgrad_thin_pair(TK.to_dev_nhwc_b16(dy), w1, TK.to_dev_nhwc_b16(dy2), w2, None, None, None, dx32, None, n, h, w, ci, co)
+    assert TK.rel(TK.nhwc_to_nchw(dx32), ref) <= TK.F32_TOL
+
+
+# A projecting block takes the sums of the layer below where that layer reads them in a pass of its own: a stem, a block of channels
+# that the narrow kernels do not run, 64 channels over many pixels; not where they would send it to a slower kernel
+@pytest.mark.parametrize("below, c, n, h, w, feeds", [
+    ([], 64, 2, 10, 12, True), ([Layer(W.BASIC_POSTACT, 96, 96, 1)], 96, 2, 6, 7, True), ([Layer(W.BASIC_POSTACT, 64, 64, 1)], 64, 3, 9, 11, False),
+    ([Layer(W.BASIC_POSTACT, 64, 64, 1)], 64, 33, 64, 64, True),
+])
+def test_what_a_projecting_block_feeds(below, c, n, h, w, feeds):
+    from paper_1906_09108_amd import FdgModule
+    import torch as t
+    layers = ([] if below else [Layer(W.STEM, 3, c, 1)]) + below + [Layer(W.BASIC_POSTACT, c, 2 * c, 2)]
+    spec = ModuleSpec(n, layers[0].c_in, h, w, layers, delay=0, is_bottom=not below, beta=0.5, name="feeds", **TD.H)
+    if n * h * w < 1000:
+        TD.check(f"projecting above {len(below)} {c}", spec)
+    m = FdgModule(spec)
+    m.set_params(W.make_params(spec, 0))
+    m.trace_attach()
+    m.forward(t.randn(*spec.input_shape(), device="cuda"))
+    m.backward_delayed(t.randn(*spec.output_shape(), device="cuda"), None if spec.is_bottom else t.empty(spec.input_shape(), device="cuda"))
+    t.cuda.synchronize()
+    assert m.trace_read(1, 1)[1] == feeds
+    m.close()
