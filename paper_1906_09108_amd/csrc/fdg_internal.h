@@ -413,11 +413,7 @@ hipError_t launch_maxpool3s2(const bf16_t* x, float* y_f32, bf16_t* y_b16, int N
 hipError_t launch_maxpool3s2_bwd(const bf16_t* x, const float* dy, float* dx, int N, int H, int W, int C, hipStream_t s);
 // depthwise 3x3 convolution, padding 1, stride 1 or 2; wt bf16 [9][C] (tap-major), dw fp32 [C][9]
 hipError_t launch_dwconv3_fwd(const bf16_t* x, const bf16_t* wt, bf16_t* y, int N, int H, int W, int C, int stride, hipStream_t s);
-// dx (bf16) and / or dx_f32 (fp32), at least one
-hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int N, int H, int W, int C, int stride, hipStream_t s,
-                                float* dx_f32 = nullptr);
-// where the two below are the faster ones (H, W: of the convolution's input)
-bool dwconv3_sums_applies(int N, int H, int W, int C);
+hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int N, int H, int W, int C, int stride, hipStream_t s);
 // the forward with the batch-norm sums of its bf16 result
 hipError_t launch_dwconv3_fwd_sums(const bf16_t* x, const bf16_t* wt, bf16_t* y, stat_t* sums, int rep_stride, int N, int H, int W, int C,
                                    int stride, hipStream_t s);

@@ -996,12 +996,7 @@ fdg_status forward_pass(fdg_module* m, const SlotView& v, const float* x_dev, fl
              *t_c3 = v.act(L.act[5]);
       FDG_TRY(mconv_forward(m, c1, cur_b, v.W(c1), nullptr, nullptr, t_c1, v.sums(b1), s));
       FDG_TRY(bn_apply(m, v, b1, t_c1, nullptr, nullptr, nullptr, nullptr, t_a1, replayed, s, /*relu6*/ 2));
-      if (dwconv3_sums_applies(N, L.Hi, L.Wi, c2.sh.Co)) {
-        FDG_TRY(launch_dwconv3_fwd_sums(t_a1, v.Wt(c2), t_c2, v.sums(b2), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-      } else {
-        FDG_TRY(launch_dwconv3_fwd(t_a1, v.Wt(c2), t_c2, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-        FDG_TRY(bn_stats(v, b2, t_c2, s));
-      }
+      FDG_TRY(launch_dwconv3_fwd_sums(t_a1, v.Wt(c2), t_c2, v.sums(b2), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
       FDG_TRY(bn_apply(m, v, b2, t_c2, nullptr, nullptr, nullptr, nullptr, t_a2, replayed, s, /*relu6*/ 2));
       FDG_TRY(mconv_forward(m, c3, t_a2, v.W(c3), nullptr, nullptr, t_c3, v.sums(b3), s));
       const bool adds = L.stride == 1 && L.c_in == L.c_out;
@@ -1424,13 +1419,9 @@ fdg_status fdg_backward_delayed(fdg_module* m, const float* grad_out_dev, float*
       }
       FDG_TRY(launch_dwconv3_wgrad(t_a1, m->T(0), m->grads() + c2.p_off, reinterpret_cast<float*>(m->ws + p.o_dwscratch),
                                    p.dwscratch_bytes, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-      if (dwconv3_sums_applies(N, L.Hi, L.Wi, c2.sh.Co)) {
-        FDG_TRY(launch_dwconv3_dgrad_sums(m->T(0), v.Wt(c2), t_a1, 6.f, t_c1, v.sums(b1), gf, m->bsums(b1), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s));
-        FDG_TRY(bn_backward_fed_from_above(m, v, b1, gf, t_c1, m->T(0), s));
-      } else {
-        FDG_TRY(launch_dwconv3_dgrad(m->T(0), v.Wt(c2), nullptr, N, L.Hi, L.Wi, c2.sh.Co, L.stride, s, gf));
-        FDG_TRY(bn_backward(m, v, b1, gf, true, t_a1, t_c1, nullptr, nullptr, m->T(0), s, 6.f));
-      }
+      FDG_TRY(launch_dwconv3_dgrad_sums(m->T(0), v.Wt(c2), t_a1, 6.f, t_c1, v.sums(b1), gf, m->bsums(b1), p.stat_rep, N, L.Hi, L.Wi, c2.sh.Co,
+                                        L.stride, s));
+      FDG_TRY(bn_backward_fed_from_above(m, v, b1, gf, t_c1, m->T(0), s));
       FDG_TRY(mconv_wgrad(m, c1, in_b, m->T(0), s));
       // the layer below, if it is another such block, begins its backward with the batch norm it ends in: its sums come from here
       if (need_dx && li > 0 && p.L[li - 1].kind == FDG_INVERTED_RESIDUAL && conv_dgrad_sums_applies(c1.sh)) {

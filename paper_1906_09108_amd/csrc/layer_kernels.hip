@@ -181,8 +181,8 @@ __device__ __forceinline__ void dw_filter(const bf16_t* wt, int C, int cg, float
 }
 template <int S, bool FLIP>
 __global__ __launch_bounds__(256) void dwconv3_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wt,
-                                                      bf16_t* __restrict__ y, float* __restrict__ y_f32, int H, int W, int C, int Ho,
-                                                      int Wo, int blocks_per_image) {
+                                                      bf16_t* __restrict__ y, int H, int W, int C, int Ho, int Wo,
+                                                      int blocks_per_image) {
   static_assert(!FLIP || S == 1, "a stride-2 data gradient has a kernel of its own");
   const int CG = C / 8, WB = (Wo + 1) / 2, HB = (Ho + 1) / 2;
   const int n = blockIdx.x / blocks_per_image;
@@ -199,8 +199,7 @@ __global__ __launch_bounds__(256) void dwconv3_kernel(const bf16_t* __restrict__
       const int ho = 2 * hb + a, wo = 2 * wb + b;
       if (ho >= Ho || wo >= Wo) continue;
       const size_t o = (((size_t)n * Ho + ho) * Wo + wo) * C + cg * 8;
-      if (y) *reinterpret_cast<uint4*>(y + o) = pack(acc[a][b]);
-      if (y_f32) store_f32(y_f32 + o, acc[a][b]);
+      *reinterpret_cast<uint4*>(y + o) = pack(acc[a][b]);
     }
 }
 
@@ -240,8 +239,8 @@ __device__ __forceinline__ void dw_dgrad2_cells(const bf16_t* img, const float (
   }
 }
 __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ wt,
-                                                             bf16_t* __restrict__ dx, float* __restrict__ dx_f32, int H, int W, int C,
-                                                             int Ho, int Wo, int blocks_per_image) {
+                                                             bf16_t* __restrict__ dx, int H, int W, int C, int Ho, int Wo,
+                                                             int blocks_per_image) {
   const int CG = C / 8, WB = (W + 1) / 2, HB = (H + 1) / 2;   // Ho = HB, Wo = WB
   const int n = blockIdx.x / blocks_per_image;
   const unsigned i = (unsigned)(blockIdx.x % blocks_per_image) * 256u + threadIdx.x;
@@ -257,8 +256,7 @@ __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __res
       const int h = 2 * hb + a, w = 2 * wb + b;
       if (h >= H || w >= W) continue;
       const size_t o = (((size_t)n * H + h) * W + w) * C + cg * 8;
-      if (dx) *reinterpret_cast<uint4*>(dx + o) = pack(acc[a][b]);
-      if (dx_f32) store_f32(dx_f32 + o, acc[a][b]);
+      *reinterpret_cast<uint4*>(dx + o) = pack(acc[a][b]);
     }
 }
 
@@ -557,29 +555,24 @@ hipError_t launch_dwconv3_fwd(const bf16_t* x, const bf16_t* wt, bf16_t* y, int 
   const unsigned bpi = dw_blocks_per_image(N, Ho, Wo, C);
   if (!bpi) return hipErrorInvalidValue;
   if (stride == 1)
-    hipLaunchKernelGGL((dwconv3_kernel<1, false>), dim3(bpi * N), dim3(256), 0, s, x, wt, y, (float*)nullptr, H, W, C, Ho, Wo, (int)bpi);
+    hipLaunchKernelGGL((dwconv3_kernel<1, false>), dim3(bpi * N), dim3(256), 0, s, x, wt, y, H, W, C, Ho, Wo, (int)bpi);
   else
-    hipLaunchKernelGGL((dwconv3_kernel<2, false>), dim3(bpi * N), dim3(256), 0, s, x, wt, y, (float*)nullptr, H, W, C, Ho, Wo, (int)bpi);
+    hipLaunchKernelGGL((dwconv3_kernel<2, false>), dim3(bpi * N), dim3(256), 0, s, x, wt, y, H, W, C, Ho, Wo, (int)bpi);
   return hipGetLastError();
 }
 
-hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int N, int H, int W, int C, int stride, hipStream_t s,
-                                float* dx_f32) {
-  if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || C % 8 != 0 || (stride != 1 && stride != 2) || (!dx && !dx_f32)) return hipErrorInvalidValue;
+hipError_t launch_dwconv3_dgrad(const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int N, int H, int W, int C, int stride, hipStream_t s) {
+  if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || C % 8 != 0 || (stride != 1 && stride != 2) || !dx) return hipErrorInvalidValue;
   const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
   const unsigned bpi = dw_blocks_per_image(N, H, W, C);
   if (!bpi) return hipErrorInvalidValue;
   if (stride == 1)
-    hipLaunchKernelGGL((dwconv3_kernel<1, true>), dim3(bpi * N), dim3(256), 0, s, dy, wt, dx, dx_f32, Ho, Wo, C, H, W, (int)bpi);
+    hipLaunchKernelGGL((dwconv3_kernel<1, true>), dim3(bpi * N), dim3(256), 0, s, dy, wt, dx, Ho, Wo, C, H, W, (int)bpi);
   else
-    hipLaunchKernelGGL(dwconv3_dgrad2_kernel, dim3(bpi * N), dim3(256), 0, s, dy, wt, dx, dx_f32, H, W, C, Ho, Wo, (int)bpi);
+    hipLaunchKernelGGL(dwconv3_dgrad2_kernel, dim3(bpi * N), dim3(256), 0, s, dy, wt, dx, H, W, C, Ho, Wo, (int)bpi);
   return hipGetLastError();
 }
 
-// Everywhere but on tensors of a few workgroups, where all that is at stake is a launch in a step of a hundred (two blocks over one
-// 8 x 8 image 426 -> 394 us, 1 x 8 x 8 x 192) and the separate passes are kept as the form whose timing records are counted by hand.
-// Two blocks each of 64 and 96 channels: 2 x 16 x 16 441 -> 406 us, 32 x 31 x 31 832 -> 787; seven blocks, 128 x 32 x 32 2340 -> 2186.
-bool dwconv3_sums_applies(int N, int H, int W, int C) { return (long long)N * H * W * C > (1 << 14); }
 // rounds so that about 1024 workgroups are left, and the sums of a channel get at most as many partials as one array holds
 static hipError_t launch_dw_sums(DwSums a, int stride, bool dgrad, hipStream_t s) {
   const size_t units = (size_t)a.N * ((a.Hd + 1) / 2) * ((a.Wd + 1) / 2), cblocks = (a.C / 8 + 7) / 8, blocks = (units + 31) / 32;

@@ -223,7 +223,7 @@ def test_weight_gradient_of_1x1_layers_against_64_bits(case, bound, kernel):
 
 # The bytes that timing records charge are those of the tensors a launch is given: a gradient that arrives gated needs no gate, the
 # forms of the stream that nobody reads are not written, a batch norm without an activation behind it reads no gate
-@pytest.mark.parametrize("name", ["basic", "projecting", "inverted"])
+@pytest.mark.parametrize("name", ["basic", "projecting", "inverted", "inverted with sums"])
 def test_bytes_of_the_timing_records(name):
     import torch as t
     from paper_1906_09108_amd import FdgModule
@@ -238,10 +238,19 @@ def test_bytes_of_the_timing_records(name):
         e, o, w, wp = 2 * 64 * 128, 2 * 16 * 128, 128 * 9 * 128, 128 * 128
         # conv2 (bf16 in, gate and batch-norm input, bf16 out), then conv1 and the projection in one launch (fp32 out)
         expected = {"conv_dgrad": 2 * o + 2 * w + o * (2 + 2 + 2) + 2 * (o + o) + 2 * (w + wp) + 4 * e}
-    else:
+    elif name == "inverted":
         spec = ModuleSpec(2, 16, 8, 8, [Layer(W.INVERTED_RESIDUAL, 16, 16, 1)], delay=0, beta=0.5, name=name, **H)
         m = 2 * 8 * 8
-        expected = {"bn_bwd": m * 16 * (6 + 6 + 2) + 2 * m * 96 * (8 + 8 + 2)}
+        # the closing batch norm and the one after the depthwise convolution in two passes; the first one's sums come out of the
+        # depthwise data gradient, so only its apply pass runs
+        expected = {"bn_bwd": m * 16 * (6 + 6 + 2) + m * 96 * (8 + 8 + 2) + m * 96 * (4 + 2 + 2)}
+    else:
+        spec = ModuleSpec(2, 64, 8, 8, [Layer(W.INVERTED_RESIDUAL, 64, 64, 1)], delay=0, beta=0.5, name=name, **H)
+        m, w = 2 * 8 * 8, 64 * 384
+        # projecting convolution (bf16 in; gate and batch-norm input, fp32 out), expanding one (bf16 in, fp32 shortcut, fp32 out);
+        # both batch norms of 384 channels have their sums already
+        expected = {"conv_dgrad": 2 * m * 64 + 2 * w + m * 384 * (2 + 2 + 4) + 2 * m * 384 + 2 * w + m * 64 * (4 + 4),
+                    "bn_bwd": m * 64 * (6 + 6 + 2) + 2 * m * 384 * (4 + 2 + 2)}
     mod = FdgModule(spec)
     mod.set_params(W.make_params(spec, 0))
     mod.profile_enable(True)
