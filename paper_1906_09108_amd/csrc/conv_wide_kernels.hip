@@ -1228,8 +1228,13 @@ static bool conv_patch_applies(const GatherConvArgs& a) {
 // 28.4 + 8.8 us); beyond the line, batch 64 (128 tiles in two parts): 1821 -> 1917; ResNet-18 top module, batch 32 (64 tiles of 512
 // -> 512, 8 blocks in four parts): 861 -> 883, batch 8 (within): 768 -> 721; bottleneck blocks of 4 blocks, batch 20: 765 -> 812.
 // Forward and backward on two streams, whole tiles / a full round / half a round: WRN-28-10 blocks 7 - 9, batch 32 at 16 x 16 (64
-// tiles of 640 -> 640) 530 / 542 / 530, blocks 9 - 11 at 8 x 8, batch 20 and 40: 526 / 389 / 390 and 545 / 454 / 419; one stream,
-// the same blocks, batch 16 (32 tiles): 841 / 600 / 616.
+// tiles of 640 -> 640) 539 / 560 / 539, blocks 9 - 11 at 8 x 8, batch 16, 40 and 64: 529 / 382 / 384, 541 / 455 / 417 and 568 / 476 /
+// 459, at 16 x 16, batch 40: 632 / 701 / 632.  The same modules on one stream: 723 / 726 / 724, 828 / 550 / 551, 825 / 608 / 592, 852 /
+// 625 / 645, 895 / 851 / 894; they stay at half a round, as the results of a module are the same on one stream and on two.
+// All of WRN-28-10 as a chain, whole tiles / its top module, which has no history, at a full round / every module at half a round:
+// K = 3, batch 20 and 40 1969 / 1984 / 1938 and 2639 / 2763 / 2639, K = 4, batch 24 2510 / 2576 / 2510, so a module with two and more
+// beside it stays at half a round; K = 2, batch 8, 12, 16 and 24 2387 / 1996 / 2013, 2433 / 2204 / 2086, 2500 / 2150 / 2196, 2660 /
+// 2550 / 2671 (another card 2403 / 2473 at 24): there the top module has its full round.
 static int patch_parts(const GatherConvArgs& a, int BN) {
   const int tiles = (a.N * a.OH * a.OW + 127) / 128 * ((a.Co + BN - 1) / BN), blocks = (a.Ci + 63) / 64;
   int parts = std::min(a.scratch.workgroups / tiles, blocks);

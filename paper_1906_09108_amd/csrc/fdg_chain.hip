@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/fdg_chain.h"
+#include "fdg_internal.h"
 
 namespace {
 
@@ -151,6 +152,7 @@ extern "C" fdg_status fdg_chain_step(fdg_chain* c, const float* x_dev, const int
   for (int32_t k = 0; k < K; ++k) {
     fdg_module* m = c->mods[k];
     hipStream_t s = c->streams[k];
+    const fdg::SharingGpu beside(m, K > 2);
     CHAIN_HIP(hipStreamWaitEvent(s, c->start, 0));
     c->fwd_batch[k] = c->bwd_batch[k] = 0;
     const int32_t in_batch = k == 0 ? (int32_t)t : c->act_batch[r][k - 1];

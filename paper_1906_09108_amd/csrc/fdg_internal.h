@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+struct fdg_module;
+
 namespace fdg {
 
 typedef __bf16 bf16_t;
@@ -80,7 +82,7 @@ struct StatMean {
 struct ConvScratch {
   float* partial;        // nullptr: none
   size_t bytes;
-  int workgroups;        // kSplitRound, or half of it where the forward and the backward of a module run on two streams
+  int workgroups;        // kSplitRound, or half of it where launches of another stream run beside these
 };
 constexpr int kSplitRound = 256;   // one workgroup to a compute unit
 struct GatherConvArgs {
@@ -423,6 +425,14 @@ hipError_t launch_dwconv3_dgrad_sums(const bf16_t* dy, const bf16_t* wt, const b
 size_t dwconv3_wgrad_scratch_bytes(int N, int H, int W, int C, int stride);
 hipError_t launch_dwconv3_wgrad(const bf16_t* x, const bf16_t* dy, float* dw, float* scratch, size_t scratch_bytes, int N, int H, int W,
                                 int C, int stride, hipStream_t s);
+
+// While it lives the calls of module m are enqueued beside those of several others (a chain of three and more): its wide convolutions
+// leave them half of the chip, see ConvScratch.
+struct SharingGpu {
+  fdg_module* m;
+  SharingGpu(fdg_module* m, bool shares);
+  ~SharingGpu();
+};
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);  // bytes % 16 == 0
 

@@ -83,7 +83,7 @@ struct Plan {
   size_t o_wscratch = 0, wscratch_bytes = 0;   // partial sums of the split weight gradient
   int wscratch_buffers = 1;
   size_t o_dwscratch = 0, dwscratch_bytes = 0; // the same for depthwise convolutions (they run on the caller's stream)
-  int split_workgroups = 0;                    // workgroups that a wide convolution may split its tiles into
+  int split_workgroups = 0;                    // workgroups that a wide convolution may split its tiles into, with the GPU to itself
   size_t o_split[2] = {0, 0}, split_bytes = 0; // partial sums of the wide convolutions that split their tiles: the forward's and the backward's
   size_t o_col = 0, o_colb = 0, col_bytes = 0; // operand rows of a 7x7 stem (launch_im2col7): the forward's and the backward's copy
   size_t total = 0;
@@ -398,6 +398,7 @@ bool build_plan(const fdg_module_desc* desc, int save_mode, Plan& p, fdg_status*
   p.o_dwscratch = take(p.dwscratch_bytes);
   p.o_col = take(p.col_bytes);
   p.o_colb = (desc->delay >= 1 && !p.replay) ? take(p.col_bytes) : p.o_col;   // as o_TPB: the two may run on two streams
+  // by what the module can do, not by the streams of a call: its results are the same on one stream and on two
   p.split_workgroups = (desc->delay >= 1 && !p.replay) ? kSplitRound / 2 : kSplitRound;
   for (const ConvInfo& ci : p.convs)
     if (!ci.depthwise) p.split_bytes = std::max(p.split_bytes, conv_scratch_bytes(ci.sh, p.split_workgroups));
@@ -489,6 +490,7 @@ struct fdg_module {
   char* trace = nullptr;              // attached trace buffer (parity accessors), or nullptr
   std::vector<char> tr_gated;         // per layer: the traced input gradient is already gated by the layer below
   bool tr_fwd_valid = false, tr_bwd_valid = false;
+  bool shares_gpu = false;            // a chain enqueues several other modules beside this one
 
   float* params() const { return reinterpret_cast<float*>(ws + p.o_params); }
   float* mom() const { return reinterpret_cast<float*>(ws + p.o_mom); }
@@ -503,10 +505,14 @@ struct fdg_module {
   float* TP() const { return reinterpret_cast<float*>(ws + p.o_TP); }
   // projection-shortcut temporary of the backward: its own where forward and backward may overlap
   ConvScratch split(int backward) const {
-    return p.split_bytes ? ConvScratch{reinterpret_cast<float*>(ws + p.o_split[backward]), p.split_bytes, p.split_workgroups} : ConvScratch{};
+    if (!p.split_bytes) return {};
+    return {reinterpret_cast<float*>(ws + p.o_split[backward]), p.split_bytes, shares_gpu ? kSplitRound / 2 : p.split_workgroups};
   }
   float* TPB() const { return reinterpret_cast<float*>(ws + ((p.d.delay >= 1 && !p.replay) ? p.o_TPB : p.o_TP)); }
 };
+
+fdg::SharingGpu::SharingGpu(fdg_module* m, bool shares) : m(m) { m->shares_gpu = shares; }
+fdg::SharingGpu::~SharingGpu() { m->shares_gpu = false; }
 
 namespace {
 

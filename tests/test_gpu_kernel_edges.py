@@ -60,6 +60,40 @@ def test_contraction_in_parts(kind, c_in, c_out, n, h, w, delay, kernel):
     m.close()
 
 
+# A chain's top module keeps no history, but where two and more modules run beside it, it fills half a round as they do (64 tiles: two
+# parts would not pay), and a whole one again once the chain is gone
+@pytest.mark.parametrize("modules", [2, 3])
+def test_contraction_in_parts_of_a_chain(modules):
+    from paper_1906_09108_amd import FdgChain, binding
+    import torch as t
+    common = dict(n=32, h_in=8, w_in=8, num_classes=10, **TD.H)
+    wide = Layer(W.BASIC_PREACT, 640, 640, 1)
+    layers = [[Layer(W.STEM, 3, 16, 1), Layer(W.BASIC_PREACT, 16, 640, 1)], [wide], [wide, Layer(W.HEAD_PREACT, 640)]]
+    if modules == 2:
+        del layers[1]
+    specs = [ModuleSpec(c_in=ls[0].c_in, layers=ls, delay=2 * (modules - 1 - k), is_bottom=k == 0, beta=0.5 if k < modules - 1 else 1.0,
+                        name=f"module {k}", **common) for k, ls in enumerate(layers)]
+    chain = FdgChain(specs)
+    for m, sp in zip(chain.modules, specs):
+        m.set_params(W.make_params(sp, 0))
+    top = chain.modules[-1]
+    x, labels = t.randn((32, 3, 8, 8), device="cuda"), t.zeros(32, device="cuda", dtype=t.int32)
+
+    def parts(step):
+        top.profile_enable(True)
+        step()
+        t.cuda.synchronize()
+        kernels = [r["kernel"] for r in top.profile_read() if r["name"] in ("conv_fwd", "conv_dgrad") and "conv_patch_kernel" in r["kernel"]]
+        assert kernels
+        return ["in parts" in k for k in kernels]
+
+    assert set(parts(lambda: [chain.step(x, labels, 0.01) for _ in range(modules + 1)])) == {modules == 2}
+    binding.load().fdg_chain_destroy(chain.handle)
+    chain.handle = None
+    assert all(parts(lambda: top.forward(t.randn((32, 640, 8, 8), device="cuda"), labels, top.new_output())))
+    chain.close()
+
+
 # Inverted residual blocks: data gradients of the 1x1 layers that end in a gate and sums (every instantiation: 64 channels and a partly
 # filled block of 72 into the expanded tensor; 384, 576 and 432 channels down to 64, 96 and 72), the depthwise kernels with sums (a
 # partly filled block of channels, odd images, both strides, more and fewer cells than a round takes), blocks that feed the one below
