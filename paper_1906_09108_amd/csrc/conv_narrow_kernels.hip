@@ -176,7 +176,9 @@ __global__ __launch_bounds__(256) void conv_narrow_kernel(GatherConvArgs a, Narr
   constexpr int WM = 4 / WN, TP = 16 * J * WM, CO = 16 * NB * WN;
   constexpr int U = CI / 8, ROWB = CI * 2;          // 16-byte units and bytes of one pixel
   constexpr int S = (9 * CI + 31) / 32;             // 32-wide steps of the contraction (taps x channels)
-  constexpr int SWZ_SHIFT = U == 2 ? 2 : (U == 4 ? 1 : 0);   // (U == 1, the 8-channel stem input: nothing to swizzle)   // unit index ^= (row >> SWZ_SHIFT) & (U - 1): b128 reads of 8 consecutive rows hit 8 bank groups
+  // unit index ^= (row >> SWZ_SHIFT) & (U - 1): b128 reads of 8 consecutive rows hit 8 bank groups (U == 1, the 8-channel stem input:
+  // nothing to swizzle)
+  constexpr int SWZ_SHIFT = U == 2 ? 2 : (U == 4 ? 1 : 0);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;

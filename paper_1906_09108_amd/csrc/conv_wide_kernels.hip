@@ -1442,8 +1442,8 @@ hipError_t launch_conv_gather_thin(const GatherConvArgs& a, hipStream_t s) {
 // Data gradient of a stride-2 layer into 40 .. 96 channels (64 -> 128, the transition out of ResNet-18's first stage): its four
 // parity classes, and the 1x1 projection's data gradient beside it as a second source, on the kernel above.  The generic kernel
 // takes one register-staged 32-channel chunk at a time, the projection's went through memory in fp32, and the layer below summed
-// its batch norm's gradient in a pass of its own.  128 x 64 x 64, 64 -> 128, all three: 227 + 72 -> 104 us (370 MB; a tile of a class
-// is 2 .. 8 steps, most of the time is the output stage).
+// its batch norm's gradient in a pass of its own.  128 x 64 x 64, 64 -> 128, all three: 227 + 72 -> 111 us (370 MB; a tile of a class
+// is 2 .. 8 steps, most of the time is the output stage; 104 with the second sum taken around zero).
 bool conv_gather_thin_classes_applies(const GatherConvArgs& a) {
   return a.Ci % 64 == 0 && a.Co >= 40 && a.Co <= 96 && a.w_rows == a.Co && a.Kw % 8 == 0 && !a.addmask && a.Hi < 32768 && a.Wi < 32768 &&
          (long long)a.N * a.OHf * a.OWf < (1ll << 30);

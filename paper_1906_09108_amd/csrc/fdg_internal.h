@@ -26,7 +26,8 @@ __host__ __device__ static inline int pack_tap(int dh, int dw, int kofs) { retur
 // lo = rint((s - hi * 2^-11) * 2^62) (exact for 2^-39 <= |s| < 2^39; smaller partials are rounded to 2^-62) and both
 // words are added with integer atomics.  Integer addition is associative, so the total does not depend on the order in
 // which workgroups arrive: two runs on the same input give the same bits, which no fp32 atomic sum does.  Either word of a
-// partial is at most 2^50, so kStatMaxPartials = 2^13 - 1 of them fit (a module whose batch norms take more keeps copies).  A partial of 2^39 (5.5e11) or more -- a network that is blowing up -- goes to a third word, a double
+// partial is at most 2^50, so kStatMaxPartials = 2^13 - 1 of them fit (a module whose batch norms take more keeps copies).  A partial
+// of 2^39 (5.5e11) or more -- a network that is blowing up -- goes to a third word, a double
 // added with a floating-point atomic: still a sum, no longer order independent.
 // A sums array for C channels is stat_t[3][2][C] (word, which of the two sums, channel), zero before the producers run;
 // value = big + hi * 2^-11 + lo * 2^-62.

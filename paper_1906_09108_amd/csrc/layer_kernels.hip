@@ -262,10 +262,12 @@ __global__ __launch_bounds__(256) void dwconv3_dgrad2_kernel(const bf16_t* __res
 
 // The same cells with the per-channel sums of the batch norm beside them, which saves that batch norm a pass over the result: of the
 // forward (bf16) the sum and the sum of squares; of a data gradient (fp32, zeroed where the gate is not strictly between 0 and
-// gate_hi) the sum and the sum of its products with bnx.  A workgroup owns 64 channels, eight to a thread, and takes 32 blocks of
-// 2 x 2 cells a round, so that its sums stay in registers and end in one exact add per channel and value (2 x 2 cells of all
-// channels, as above, would add for every block).  Orders are fixed.  128 x 16 x 16 x 384, the passes it replaces -> here: forward
-// 17.4 + 8.7 -> 20.7 us, data gradient 21.9 + 19.4 (and 3.4 of the pass that follows, which reads no gate) -> 33.6 us (126 MB).
+// gate_hi) the sum and the sum of its products with bnx, taken around the mean of bnx.  A workgroup owns 64 channels, eight to a
+// thread, and takes 32 blocks of 2 x 2 cells a round, so that its sums stay in registers and end in one exact add per channel and
+// value (2 x 2 cells of all channels, as above, would add for every block).  Orders are fixed.  128 x 16 x 16 x 384, the passes it
+// replaces -> here: forward 17.4 + 8.7 -> 20.7 us, data gradient 21.9 + 19.4 (and 3.4 of the pass that follows, which reads no gate)
+// -> 34.7 us (126 MB).  At every size: what is saved on the smallest tensors is the launches (two blocks over one 8 x 8 image, 1 x 8 x
+// 8 x 192, 317 .. 322 -> 311 us a step; 2 x 16 x 16 441 -> 406; seven blocks, 128 x 32 x 32 2340 -> 2186).
 struct DwSums {
   const bf16_t* src;    // [N, Hs, Ws, C]
   const bf16_t* wt;
