@@ -1,6 +1,7 @@
 // K module workers on one GPU run as Algorithm I of arXiv 1906.09108: per module backward + update, forward,
 // exchange at the end of the iteration (Section III-A).  Host code only: it sequences the entry points of
-// fdg.h on one stream per module and keeps the double-buffered mailboxes; it holds no arithmetic.
+// fdg.h on one stream per module, tells a module that several others run beside it, and keeps the double-buffered mailboxes; it holds
+// no arithmetic.
 #include <hip/hip_runtime.h>
 
 #include <new>
