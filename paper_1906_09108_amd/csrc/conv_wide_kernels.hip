@@ -2115,7 +2115,10 @@ __global__ __launch_bounds__(512) void conv_wgrad128w8_kernel(WgradArgs a, Wgrad
     }
   // D block: lane holds column ci = 32 j + (lane & 31), rows co = 8 (v >> 2) + 4 (lane >> 5) + (v & 3) of the block row
   float* dst = L.partial ? L.partial + (size_t)split * L.split_stride : a.dw;
-  const int mode = (L.partial || (L.splits == 1 && a.overwrite)) ? 0 : (L.splits > 1 ? 1 : 2);
+  // One split that is added to what dw held: layers that came from the generic kernel add with an atomic, which does not wait for dw to
+  // arrive (8 x 7 x 7 160 -> 160 1x1 14.4 -> 10.6 us, 128 -> 192 3x3 16.3 -> 12.0; the generic kernel, in splits, 10.2 and 10.6).  dw
+  // has one writer an element, so the bits are those of the plain sum.
+  const int mode = (L.partial || (L.splits == 1 && a.overwrite)) ? 0 : (L.splits > 1 || RAGGED || PAIRED ? 1 : 2);
   const int ntaps = a.ntaps, Ci = a.Ci;
   const int co_base = co0 + 64 * wm + 32 * wk + 4 * (lane >> 5);
 #pragma unroll
@@ -2580,7 +2583,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_tall_kernel(WgradArgs a, Wgrad
     }
   // D block i: lane holds column ci = 32 wk + (lane & 31), rows co = 32 i + 8 (v >> 2) + 4 (lane >> 5) + (v & 3)
   float* dst = L.partial ? L.partial + (size_t)split * L.split_stride : a.dw;
-  const int mode = (L.partial || (L.splits == 1 && a.overwrite)) ? 0 : (L.splits > 1 ? 1 : 2);
+  const int mode = (L.partial || (L.splits == 1 && a.overwrite)) ? 0 : (L.splits > 1 || CW == 2 ? 1 : 2);   // as there
   const int row = a.ntaps * a.Ci, col = (CW == 1 ? tapi * a.Ci : 0) + ci0 + 64 * wave_n + 32 * wk + (lane & 31);
   if (CW == 2 && col >= row) return;
   const int co_base = co0 + 160 * wave_m + 4 * (lane >> 5);

@@ -60,6 +60,30 @@ def test_contraction_in_parts(kind, c_in, c_out, n, h, w, delay, kernel):
     m.close()
 
 
+# One split added to what dw held, without scratch: the sum that the same launch writes over dw, plus dw, rounded once
+@pytest.mark.parametrize("case, kernel", [
+    ((8, 7, 7, 160, 160, 1, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((5, 7, 9, 136, 152, 3, 1), "conv_wgrad128w8_kernel<5, flat, ragged>"),
+    ((1, 16, 16, 64, 128, 3, 1), "conv_wgrad128w8_kernel<5, paired>"),
+    ((1, 16, 16, 256, 160, 3, 2), "conv_wgrad_tall_kernel<4, columns>"),
+])
+def test_one_split_added_to_the_weight_gradient(case, kernel):
+    from paper_1906_09108_amd import kernels as K
+    import torch as t
+    n, h, w, ci, co, k, s = case
+    gen = t.Generator(device="cuda")
+    gen.manual_seed(0)
+    ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+    x, dy = (t.randn(m, generator=gen, device="cuda").to(t.bfloat16) for m in (n * h * w * ci, n * ho * wo * co))
+    held = t.randn(co * k * k * ci, generator=gen, device="cuda")
+    written, added = t.empty_like(held), held.clone()
+    K.fdgk_conv_wgrad(x, dy, written, None, n, h, w, ci, co, k, s, overwrite=True)
+    assert K.fdgk_last_kernel() == kernel
+    K.fdgk_conv_wgrad(x, dy, added, None, n, h, w, ci, co, k, s)
+    assert K.fdgk_last_kernel() == kernel
+    assert t.equal(added, held + written)
+
+
 # A chain's top module keeps no history, but where two and more modules run beside it, it fills half a round as they do (64 tiles: two
 # parts would not pay), and a whole one again once the chain is gone
 @pytest.mark.parametrize("modules", [2, 3])
